@@ -76,7 +76,9 @@ enum { DMI_POLICY_BLOCK = 0, DMI_POLICY_DROP_NEWEST = 1 };
 
 /* ring flags */
 enum {
-    DMI_DRAIN_COPY_ENGINE = 1,  /* drain with hipMemcpyAsync on a side stream (default) */
+    DMI_DRAIN_COPY_ENGINE = 1,  /* drain with hipMemcpyAsync on a side stream (the default, except that without
+                                   this flag and without a drain thread a flush moves up to 6 MiB by a copy
+                                   kernel behind the captures, on the stream last passed to dmi_observe) */
     DMI_DRAIN_KERNEL = 2,       /* drain with a copy kernel writing pinned host memory */
     DMI_BG_THREAD = 4           /* the library runs its own drain thread (section 4.3) */
 };

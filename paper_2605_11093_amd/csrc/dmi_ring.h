@@ -138,7 +138,11 @@ struct Probe {
     uint64_t launches;      // how many capture launches that is
     bool fetched;           // the commit slot of launch covers-1 was copied to the host mirror
     Delta delta;            // else: what the launches since the previous probe added
+    uint64_t no;            // how many probes the ring has made, this one included
 };
+
+// Largest span a flush moves with the drain kernel behind the captures (flush_behind_captures()).
+constexpr uint64_t kFlushKernelBytes = 6u << 20;
 
 }  // namespace host
 }  // namespace dmi
@@ -201,6 +205,8 @@ struct dmi_ring {
     uint64_t probed_upto = 0;                              // launches with seq < this have a probe behind them
     std::atomic<uint64_t> confirmed{0};                    // launches with seq < this have finished
     std::atomic<uint64_t> committed{0};                    // device head after launch confirmed-1
+    uint64_t probes_made = 0;                              // under pmu
+    std::atomic<uint64_t> probes_done{0};                  // probes whose event has been seen to be over
     uint64_t snap[6] = {0, 0, 0, 0, 0, 0};                 // counters of the last confirmed slot
 
     // drain / host ring state
@@ -216,6 +222,9 @@ struct dmi_ring {
     // pinned host word that they read themselves.
     volatile uint64_t *htail = nullptr;                    // pinned, coherent
     const uint64_t *htail_dev = nullptr;                   // its device address
+    // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over
+    // once probe number `direct_probe` is.  0: none; no other copy is issued while there is one.
+    uint64_t direct_probe = 0;
     uint64_t poll_cursor = 0, released = 0;
     std::deque<std::pair<uint64_t, uint64_t>> polled;      // (seq, end offset)
 
@@ -284,7 +293,7 @@ namespace dmi {
 namespace host {
 
 // dmi_host.hip
-dmi_status_t record_probe(dmi_ring *r);
+dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub);
