@@ -426,7 +426,9 @@ uint32_t plan_grid(const CaptureArgs &a, uint32_t nb)
     };
     uint64_t groups;
     if (a.summary_mask) {
-        groups = balanced((listed + a.rows_per_wg - 1u) / a.rows_per_wg);
+        // rows a workgroup takes in one step: see the two row-wise paths of capture_kernel
+        const uint64_t rows = a.lanes_per_row ? 4u * (64u / a.lanes_per_row) : a.rows_per_wg;
+        groups = balanced((listed + rows - 1u) / rows);
     } else if (upr >= kThreads && upr < 4u * kThreads && (4u * kThreads) % upr == 0) {
         groups = balanced((listed + 4u * kThreads / upr - 1u) / (4u * kThreads / upr));      // 2 or 4 rows per work item
     } else if (upr >= kThreads) {
@@ -546,9 +548,12 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
                   (index_mode ? DMI_REC_INDEXED : 0u);
     a.row_elems = geo.row_elems;
     a.units_per_row = (uint32_t)upr;
-    // a wavefront per row when rows are short, or of moderate length and plentiful (no block-level
-    // reduction, four rows in flight per workgroup); otherwise a workgroup per row
-    a.rows_per_wg = (upr <= 128u || (upr <= 1024u && listed >= 2048u)) ? 4u : 1u;
+    // a wavefront per row when rows are of moderate length and plentiful (no block-level reduction, four rows
+    // in flight per workgroup); otherwise a workgroup per row
+    a.lanes_per_row = 0;
+    if (xf->summary_mask && upr <= 256u)        // short rows: as few lanes to a row as four loads each allow
+        for (a.lanes_per_row = 4u; 4u * a.lanes_per_row < upr;) a.lanes_per_row *= 2u;
+    a.rows_per_wg = upr <= 1024u && listed >= 2048u ? 4u : 1u;
     a.point_id = point_id;
     a.rank_tag = env.rank_tag;
     a.ring = env.ring;

@@ -43,9 +43,11 @@ struct DevCtrl {
     uint64_t captured_records, captured_rows, captured_bytes;
     uint64_t dropped_records, dropped_rows, dropped_bytes;
     uint64_t bad_rows;              // rows whose device-side index left the tensor (stored as zeros)
+    uint64_t zeros[2];              // always zero, 16-byte aligned: what a lane with nothing to load reads
     uint32_t point_drops[4096];
     CommitSlot slots[kCommitSlots];
 };
+static_assert(__builtin_offsetof(DevCtrl, zeros) % 16u == 0, "read as one 16-byte unit");
 
 // Per-step values of a replayable step (device memory, one block per step object).
 // Kernels launched as part of such a step take from here what an ordinary launch gets as
@@ -95,6 +97,8 @@ struct CaptureKernelArgs {
     uint32_t row_elems;
     uint32_t units_per_row;
     uint32_t rows_per_wg;           // summary kernels: 1 (a workgroup per row) or 4 (a wavefront per row)
+    uint32_t lanes_per_row;         // summary kernels, rows of at most 256 units: lanes that share a row, up to four
+                                    // units each (a power of two from 4 to 64); 0: rows_per_wg says
     uint32_t n_batch, rank_tag;     // n_batch = gridDim.y
     uint64_t seq, step_id;          // seq: of the launch's first record
     // ring

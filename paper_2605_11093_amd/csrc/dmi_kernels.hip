@@ -114,6 +114,31 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The same over groups of `width` consecutive lanes (a power of two from 4 to 64, the same in every
+// lane): the last lane of each group ends up with the group's total.  The steps are those above in
+// the same order, so a group's total has the bits that wave_sum gives for the group alone.
+__device__ __forceinline__ float group_sum(float v, uint32_t width)
+{
+    v += __uint_as_float(dpp_u32<0xB1, 0xF>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_u32<0x4E, 0xF>(__float_as_uint(v)));
+    if (width >= 8u) v += __uint_as_float(dpp_u32<0x141, 0xF>(__float_as_uint(v)));
+    if (width >= 16u) v += __uint_as_float(dpp_u32<0x140, 0xF>(__float_as_uint(v)));
+    if (width >= 32u) v += __uint_as_float(dpp_u32<0x142, 0xA>(__float_as_uint(v)));
+    if (width == 64u) v += __uint_as_float(dpp_u32<0x143, 0xC>(__float_as_uint(v)));
+    return v;
+}
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, uint32_t width)
+{
+    uint32_t o;
+    o = dpp_u32<0xB1, 0xF>(v);  v = o > v ? o : v;
+    o = dpp_u32<0x4E, 0xF>(v);  v = o > v ? o : v;
+    if (width >= 8u)  { o = dpp_u32<0x141, 0xF>(v); v = o > v ? o : v; }
+    if (width >= 16u) { o = dpp_u32<0x140, 0xF>(v); v = o > v ? o : v; }
+    if (width >= 32u) { o = dpp_u32<0x142, 0xA>(v); v = o > v ? o : v; }
+    if (width == 64u) { o = dpp_u32<0x143, 0xC>(v); v = o > v ? o : v; }
+    return v;
+}
+
 // ---------------------------------------------------------------- conversions
 // bf16 -> fp8 E4M3FN (OCP: bias 7, max 448, no inf, S.1111.111 NaN), round to
 // nearest even, saturating.  Integer arithmetic on the bf16 bit pattern; used on the
@@ -330,6 +355,34 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
     }
 }
 
+// Add one step's units (up to four per lane, `have` says which of them are the row's) to the row's partial
+// summaries: every unit summed by itself, the four combined in pairs.  Shorter chains than one running sum,
+// in time and in rounding error.
+template <int ES_IN, int VEC>
+__device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_IN * VEC>::T (&v)[4], uint32_t have,
+                                            uint32_t src_dtype)
+{
+    Accum u[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+        u[k] = Accum{0.f, 0.f, 0u};
+        if (have & (1u << k)) emit_unit<ES_IN, VEC, OUT_NONE, true>(RingW{}, 0, v[k], src_dtype, u[k]);
+    }
+    acc.ss += (u[0].ss + u[1].ss) + (u[2].ss + u[3].ss);
+    acc.s += (u[0].s + u[1].s) + (u[2].s + u[3].s);
+    if constexpr (ES_IN == 2 && VEC == 8) {
+        auto mx = [](uint32_t x, uint32_t y) {
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, x),
+                                                                          __builtin_bit_cast(u16x2_t, y)));
+        };
+        acc.am = mx(acc.am, mx(mx(u[0].am, u[1].am), mx(u[2].am, u[3].am)));
+    } else {
+        const uint32_t a = u[0].am > u[1].am ? u[0].am : u[1].am, b = u[2].am > u[3].am ? u[2].am : u[3].am;
+        const uint32_t m = a > b ? a : b;
+        acc.am = m > acc.am ? m : acc.am;
+    }
+}
+
 template <int ES_IN, int VEC, int OUT>
 __host__ __device__ constexpr uint32_t out_unit_bytes()
 {
@@ -429,10 +482,15 @@ __device__ __forceinline__ void touch_argument_lines(const T &a, const uint8_t *
 }
 
 // ---------------------------------------------------------------- capture kernel
-template <int ES_IN, int VEC, int OUT, bool SUMM>
+// Summaries per row: none; for rows of any length; for rows of at most 256 units (a kernel of its own, or its
+// registers would cost the others a workgroup per compute unit).
+enum SummMode { SUMM_NO = 0, SUMM_ROWS = 1, SUMM_SHORT = 2 };
+
+template <int ES_IN, int VEC, int OUT, int SUMM>
 __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const BatchArgs b)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    __shared__ float short_sums[SUMM == SUMM_SHORT ? 4 * 192 : 1];      // per wavefront: totals of 64 rows
     const uint32_t y = blockIdx.y;                  // which tensor of the batch this workgroup works on
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
@@ -550,7 +608,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     //    now and travel together with the control fetch instead of behind it
     constexpr uint32_t U = 4;                               // loads in flight per lane
     constexpr uint32_t CH = U * kThreads;                   // units per long-row work item
-    const uint32_t rpw = SUMM ? a.rows_per_wg : 1u;
+    const uint32_t rpw = SUMM == SUMM_ROWS ? a.rows_per_wg : 1u;
     const uint32_t gsz = kThreads / rpw;                    // lanes per row (summary passes)
     const uint32_t sub = tid / gsz, l = tid - sub * gsz;
     const uint32_t cpr = (a.units_per_row + CH - 1u) / CH;  // long-row items per row
@@ -561,7 +619,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     // (not in a launch of several records some of which may turn out to be dropped: a dropped
     // record's rows would have been read for nothing)
     const bool may_drop_some = a.n_batch > 1u && (a.drop_newest != 0u || a.step != nullptr);
-    if (simple && !a.paged && !may_drop_some &&
+    if (simple && !a.paged && !may_drop_some && SUMM != SUMM_SHORT &&
         (SUMM || (OUT != OUT_NONE && a.units_per_row >= kThreads && !multi_row_items))) {
         uint32_t g, c_begin, stride;
         if constexpr (SUMM) { g = blockIdx.x * rpw + sub; c_begin = l; stride = gsz; }
@@ -679,30 +737,36 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     // which counts as a global one and makes every wait for it a wait for the row loads too)
     typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const lds_u32 *const L = (const lds_u32 *)lds;
-    auto locate = [&](uint32_t g) -> RowRef {
+    // In two halves: what has to be loaded to find the row (its index, or its block in the cache), and
+    // where that puts it, so that a caller can put other loads in between.
+    struct RowTok {
+        uint32_t at;        // dense: the row; paged: the physical block (signed where it was loaded)
+        uint32_t slot;
+    };
+    // `hint`: a request at or in front of row g's, from a caller that goes through rows in ascending order;
+    // the row's request comes back in it.
+    auto locate_begin = [&](uint32_t g, uint32_t &hint) -> RowTok {
         uint32_t r = g, j = 0;
         if (!simple) {
-            uint32_t lo = 0, hi = n_reqs;
+            uint32_t lo = hint, hi = L[m.pref + hint + 1u] > g ? hint + 1u : n_reqs;
             while (hi - lo > 1u) {
                 const uint32_t mid = (lo + hi) >> 1;
                 if (L[m.pref + mid] <= g) lo = mid; else hi = mid;
             }
             r = lo;
+            hint = r;
             j = g - L[m.pref + r];
         }
-        RowRef ref;
+        RowTok k = {0u, 0u};
         if (!a.paged) {
-            int64_t row;
             if (index_mode) {
-                row = (int64_t)a.row_index[simple ? g : L[m.pref_all + r] + j];
-            } else if (a.table_in_lds) {
-                row = (int64_t)L[m.rb + r] + (int64_t)j * (int64_t)L[m.tab + 4u * r + 2u];
+                k.at = (uint32_t)a.row_index[simple ? g : L[m.pref_all + r] + j];
+            } else if (a.table_in_lds) {        // (the host keeps every listed row below 2^32)
+                k.at = L[m.rb + r] + j * L[m.tab + 4u * r + 2u];
             } else {
-                row = (int64_t)a.row0[r];
-                if (j) row += (int64_t)j * (int64_t)a.req_table[r].z;
+                k.at = a.row0[r];
+                if (j) k.at += j * a.req_table[r].z;
             }
-            ref.ok = row >= 0 && row < a.n_src_rows;
-            ref.base = src + (ref.ok ? row : 0) * a.row_stride_b;
         } else {
             uint32_t tok0, tstep, seq_row;
             if (a.table_in_lds) {
@@ -713,12 +777,22 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             }
             const uint32_t t = tok0 + j * tstep;            // host keeps token positions below 2^31
             const uint32_t lb = a.bs_shift < 32u ? t >> a.bs_shift : t / a.block_size;
-            const uint32_t slot = t - lb * a.block_size;
-            const int64_t blk = (int64_t)a.block_table[(int64_t)seq_row * a.bt_stride + (int64_t)lb];
-            ref.ok = blk >= 0 && blk < a.n_src_rows;
-            ref.base = src + (ref.ok ? blk : 0) * a.block_stride_b + (int64_t)slot * a.slot_stride_b;
+            k.slot = t - lb * a.block_size;
+            k.at = (uint32_t)a.block_table[(int64_t)seq_row * a.bt_stride + (int64_t)lb];
         }
+        return k;
+    };
+    auto locate_end = [&](const RowTok &k) -> RowRef {
+        const int64_t at = a.paged || index_mode ? (int64_t)(int32_t)k.at : (int64_t)k.at;
+        RowRef ref;
+        ref.ok = at >= 0 && at < a.n_src_rows;
+        if (!a.paged) ref.base = src + (ref.ok ? at : 0) * a.row_stride_b;
+        else ref.base = src + (ref.ok ? at : 0) * a.block_stride_b + (int64_t)k.slot * a.slot_stride_b;
         return ref;
+    };
+    auto locate = [&](uint32_t g) -> RowRef {
+        uint32_t first = 0;
+        return locate_end(locate_begin(g, first));
     };
     auto unit_ptr = [&](const RowRef &ref, uint32_t c) -> const uint8_t * {
         if (!a.paged) return ref.base + (uint64_t)c * NB_IN;
@@ -785,7 +859,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             }
         }
 
-        if constexpr (!SUMM) {
+        if constexpr (SUMM == SUMM_NO) {
             if constexpr (OUT != OUT_NONE) {
                 Accum dummy = {0.f, 0.f, 0u};
                 if (a.units_per_row >= kThreads) {
@@ -948,6 +1022,123 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     }
                 }
             }
+        } else if constexpr (SUMM == SUMM_SHORT) {
+            // ---- summaries of short rows (up to 256 units): lanes_per_row lanes share a row, each with up to four
+            //      of its units, so one step of a wavefront is 64 / lanes_per_row whole rows and a row costs one
+            //      reduction over few lanes (a row of 32 units used to take a wavefront of its own, half of its
+            //      lanes and three of its four loads idle, and a reduction over all 64 lanes).  A wavefront works through
+            //      consecutive rows: each starts its search where the row before it was found.  What finding a
+            //      row has to load (its block) is asked for a step before the row's own loads, and totals wait in
+            //      LDS until 64 rows are together: memory operations of a wavefront complete in order, so a row's
+            //      place asked for behind a step's loads, or a store inside the loop, would make every step wait.
+            //      Bound: HBM reads.  8 caches x 72.7 k rows of 32 units, norms and largest magnitudes:
+            //      297 -> 69 us (1.0 -> 4.4 TB/s read).
+            const uint32_t lpr = a.lanes_per_row, lg = 31u - (uint32_t)__builtin_clz(lpr);
+            const uint32_t rpi = 64u >> lg;                             // rows per step, at most 16
+            const uint32_t sub_r = lane >> lg, l_r = lane & (lpr - 1u);
+            const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
+            const uint32_t n_waves = gridDim.x * (kThreads / 64u);
+            const uint64_t per = n_rows ? ((uint64_t)(n_rows - 1u) / n_waves / rpi + 1u) * rpi : 0u;
+            const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
+            const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
+            float *const stash = short_sums + wv * 192u;                // [3][64]
+            // where this lane's units lie in a row does not change from row to row
+            bool in_row[U];
+            int64_t unit_off[U];
+#pragma unroll
+            for (uint32_t k = 0; k < U; k++) {
+                const uint32_t c = l_r + k * lpr;
+                in_row[k] = c < a.units_per_row;
+                const RowRef zero = {nullptr, 1};
+                unit_off[k] = (int64_t)(uintptr_t)unit_ptr(zero, in_row[k] ? c : 0u);
+            }
+            const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
+            uint32_t n_bad = 0, hint = 0;
+            auto begin = [&](uint64_t g) -> RowTok {    // (behind the last row: that one again)
+                const uint64_t x = g + sub_r;
+                return locate_begin((uint32_t)(x < r1 ? x : r1 - 1u), hint);
+            };
+            auto end = [&](const RowTok &k, uint64_t g) -> RowRef {
+                RowRef ref = locate_end(k);
+                const bool live = g + sub_r < r1;
+                n_bad += live && l_r == 0u && !ref.ok ? 1u : 0u;
+                ref.ok = live && ref.ok ? 1u : 0u;
+                return ref;
+            };
+            // a lane with nothing to load (behind the row's end, or the rows', or a bad row) reads zeros
+            auto load = [&](const RowRef &ref, unit_t (&v)[U]) {
+#pragma unroll
+                for (uint32_t k = 0; k < U; k++) {
+                    const uint8_t *ptr = ref.ok && in_row[k] ? ref.base + unit_off[k] : zeros;
+                    typedef __attribute__((address_space(1))) const unit_t global_unit_t;
+                    v[k] = *(global_unit_t *)ptr;
+                }
+            };
+            auto flush = [&](uint64_t from, uint64_t upto) {    // totals of rows [from, upto), at most 64
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (from + lane < upto) {
+                    uint64_t o = off_sum + (from + lane) * 4u;
+                    if (a.summary_mask & 1u) { ring_store<float>(w, o, sqrtf(stash[lane])); o += sum_arr; }
+                    if (a.summary_mask & 2u) { ring_store<float>(w, o, stash[64u + lane] / (float)a.row_elems); o += sum_arr; }
+                    if (a.summary_mask & 4u)
+                        ring_store<float>(w, o, am_value(__float_as_uint(stash[128u + lane]), a.src_dtype));
+                }
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto process = [&](const unit_t (&v)[U], uint64_t g0) {
+                const uint64_t g = g0 + sub_r;
+                if constexpr (OUT != OUT_NONE) {
+                    Accum none = {0.f, 0.f, 0u};
+#pragma unroll
+                    for (uint32_t k = 0; k < U; k++)
+                        if (g < r1 && in_row[k])
+                            emit_unit<ES_IN, VEC, OUT, false>(
+                                w, off_payload + (g * a.units_per_row + l_r + k * lpr) * NB_OUT, v[k], a.src_dtype, none);
+                }
+                Accum acc = {0.f, 0.f, 0u};
+                accum_units<ES_IN, VEC>(acc, v, 15u, a.src_dtype);          // (what is not the row's was read as zeros)
+                const uint32_t at = (uint32_t)(g - r0) & 63u;
+                const bool last = l_r == lpr - 1u;
+                if (a.summary_mask & 1u) {
+                    const float ss = group_sum(acc.ss, lpr);
+                    if (last) stash[at] = ss;
+                }
+                if (a.summary_mask & 2u) {
+                    const float sm = group_sum(acc.s, lpr);
+                    if (last) stash[64u + at] = sm;
+                }
+                if (a.summary_mask & 4u) {
+                    const uint32_t am = group_max_u32(fold_am<ES_IN, VEC>(acc.am), lpr);
+                    if (last) stash[128u + at] = __uint_as_float(am);
+                }
+                const uint64_t done = g0 + rpi - r0;
+                if ((done & 63u) == 0u) flush(r0 + done - 64u, g0 + rpi < r1 ? g0 + rpi : r1);
+                else if (g0 + rpi >= r1) flush(r0 + (done & ~63ull), r1);
+            };
+            if (r0 < r1) {
+                unit_t va[U], vb[U];
+                uint64_t g = r0;
+                const RowTok k0 = begin(g), k1 = begin(g + rpi);
+                RowRef next = end(k0, g);
+                load(next, va);
+                next = end(k1, g + rpi);
+                for (;;) {
+                    RowTok k = begin(g + 2u * rpi);
+                    load(next, vb);
+                    process(va, g);
+                    next = end(k, g + 2u * rpi);
+                    g += rpi;
+                    if (g >= r1) break;
+                    k = begin(g + 2u * rpi);
+                    load(next, va);
+                    process(vb, g);
+                    next = end(k, g + 2u * rpi);
+                    g += rpi;
+                    if (g >= r1) break;
+                }
+                if (n_bad) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
+            }
         } else {
             // ---- row-wise pass with summaries: a workgroup (or a wavefront) per row.  A step is
             //      4 units per lane of one row; rows longer than that take several steps.  Steps
@@ -997,13 +1188,18 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     const bool active = g < n_rows;
                     if (active) {
                         const uint64_t row_off = off_payload + g * a.units_per_row * NB_OUT;
+                        Accum none = {0.f, 0.f, 0u};
+                        uint32_t have = 0;
 #pragma unroll
                         for (uint32_t k = 0; k < U; k++) {
                             const uint32_t c = l + (cur_pass * U + k) * gsz;
-                            if (c < a.units_per_row)
-                                emit_unit<ES_IN, VEC, OUT, true>(w, row_off + (uint64_t)c * NB_OUT,
-                                                                 zero_unless(ref.ok != 0, v[k]), a.src_dtype, acc);
+                            const bool in = c < a.units_per_row;
+                            have |= in && ref.ok != 0 ? 1u << k : 0u;
+                            if (OUT != OUT_NONE && in)
+                                emit_unit<ES_IN, VEC, OUT, false>(w, row_off + (uint64_t)c * NB_OUT,
+                                                                  zero_unless(ref.ok != 0, v[k]), a.src_dtype, none);
                         }
+                        accum_units<ES_IN, VEC>(acc, v, have, a.src_dtype);
                     }
                     if (cur_pass == spr - 1u) {     // the row is complete: reduce and store its summaries
                         acc.ss = wave_sum(acc.ss);
@@ -1082,7 +1278,9 @@ struct DecodeArgs {
     // line 3
     const uint8_t *keep_mask;       // keep vector (MASK variants): request r is captured iff keep_mask[r] != 0
     uint32_t n_wg_rows;             // row workgroups = rows listed (= n_reqs unless requests list several rows)
-    uint32_t spare32;
+    uint32_t unit_stride;           // lane l < unit_stride takes units l, l + unit_stride, ...: all lanes of the
+                                    // workgroup, or as many as the general kernel gives a short row with summaries
+                                    // (the sums are then taken in the same order there and here)
     uint64_t spare[6];
 };
 static_assert(sizeof(DecodeArgs) == 256, "four lines");
@@ -1107,6 +1305,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t par = (a.flags & kDecParIn) ? 1u : 0u;
     const bool meta_wg = blockIdx.x == a.n_wg_rows;
+    const uint32_t ustr = SUMM ? a.unit_stride : kThreads;
     constexpr uint32_t kCtlTid = kThreads - 64u;
 
     // control words first (they depend on nothing but the arguments), then the row
@@ -1138,7 +1337,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
             // ignore it (a load under its own condition makes the compiler wait between loads)
 #pragma unroll
             for (uint32_t k = 0; k < U; k++) {
-                const uint32_t c = tid + k * kThreads;
+                const uint32_t c = tid + k * ustr;
                 v[k] = *reinterpret_cast<const u32x4 *>(base + (uint64_t)(c < a.units_per_row ? c : 0u) * 16u);
             }
         }
@@ -1175,11 +1374,10 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if constexpr (SUMM) {
         Accum acc = {0.f, 0.f, 0u};
         if (!meta_wg) {
+            uint32_t have = 0;
 #pragma unroll
-            for (uint32_t k = 0; k < U; k++) {
-                const uint32_t c = tid + k * kThreads;
-                if (c < a.units_per_row) emit_unit<2, 8, OUT_NONE, true>(RingW{}, 0, v[k], a.hdr7 & 0xFFu, acc);
-            }
+            for (uint32_t k = 0; k < U; k++) have |= tid < ustr && tid + k * ustr < a.units_per_row ? 1u << k : 0u;
+            accum_units<2, 8>(acc, v, have, a.hdr7 & 0xFFu);
             acc.ss = wave_sum(acc.ss);
             acc.s = wave_sum(acc.s);
             const uint32_t am = wave_max_u32(fold_am<2, 8>(acc.am));
@@ -1307,8 +1505,8 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     const uint64_t row_off = a.off_payload + (uint64_t)g * a.units_per_row * NB_OUT;
 #pragma unroll
     for (uint32_t k = 0; k < U; k++) {
-        const uint32_t c = tid + k * kThreads;
-        if (c < a.units_per_row)
+        const uint32_t c = tid + k * ustr;
+        if ((!SUMM || tid < ustr) && c < a.units_per_row)
             emit_unit<2, 8, OUT, false>(w, row_off + (uint64_t)c * NB_OUT, v[k], a.hdr7 & 0xFFu, acc);
     }
     if constexpr (SUMM) {
@@ -1420,11 +1618,14 @@ template <int ES_IN, int VEC, int OUT>
 static hipError_t launch_t(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, hipStream_t s)
 {
     const dim3 g(grid, a.n_batch);
-    if (a.summary_mask)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, true>), g, a.lds_bytes, s,
+    if (a.summary_mask && a.lanes_per_row)
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT>), g, a.lds_bytes, s,
+                           static_cast<const CaptureKernelArgs &>(a), b);
+    else if (a.summary_mask)
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS>), g, a.lds_bytes, s,
                            static_cast<const CaptureKernelArgs &>(a), b);
     else
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, false>), g, a.lds_bytes, s,
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO>), g, a.lds_bytes, s,
                            static_cast<const CaptureKernelArgs &>(a), b);
     return hipGetLastError();
 }
@@ -1478,6 +1679,7 @@ hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipSt
     d.row_stride_b = a.row_stride_b;
     d.rows = a.row_index ? a.row_index : reinterpret_cast<const int32_t *>(a.row_map ? a.row_map : a.row0);
     d.n_wg_rows = a.hdr[9];         // rows listed
+    d.unit_stride = a.lanes_per_row ? a.lanes_per_row : kThreads;
     d.ring = a.ring;
     d.cap = a.cap;
     d.ctrl = a.ctrl;
