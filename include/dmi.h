@@ -268,19 +268,19 @@ dmi_status_t dmi_observe_paged_batch(dmi_ring_t *ring, uint32_t n, const uint32_
 /*
  * dmi_observe for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  It needs no ring object and calls no allocating
- * routine: the device memory a capture needs besides its input and output (control words,
- * counters, the staged request table) is a 128 KiB array that the library's code object holds
- * on every GPU for the life of the process.
- * Runs on the calling thread's current HIP device.  Launches, on hip_stream, two one-workgroup
- * launches that reset the control words and stage the request table, then the capture kernel
- * dmi_observe would launch, and returns.  The record, byte for byte the one dmi_observe would
+ * routine: the device memory a capture needs besides its input and output (above all a long
+ * request table) is a 128 KiB array that the library's code object holds on every GPU for the
+ * life of the process.
+ * Runs on the calling thread's current HIP device.  Launches, on hip_stream, the capture kernel
+ * dmi_observe would launch, with the request table among its arguments (a table of more than 832
+ * words, 5 per request, is staged by small launches in front of it), and returns.  The record, byte for byte the one dmi_observe would
  * produce with sequence number `seq` and this rank_tag, is written at out[0 ..) [device,
  * 64-byte aligned]; its size is in its header (bytes 48..55) and, when the selection has no
  * keep vector, in *record_bytes [host, optional] (with one: an upper bound).  Bytes of `out`
  * behind the record are not touched.  No policy applies: nothing is sampled, dropped or waited for.
  * Limits: at most 1024 requests; the record's upper bound (dmi_record_bytes with every listed
  * row kept) must fit out_bytes (a multiple of 64): otherwise DMI_ERR_TOO_LARGE and nothing is
- * launched.  Every call on a GPU uses that GPU's one array, so calls whose kernels may overlap
+ * launched.  Every call on a GPU may use that GPU's one array, so calls whose kernels may overlap
  * there (different streams with no ordering between them) race; calls on one stream do not.
  * Under a stream capture, call it once outside first: the first call on a device looks the
  * array up and loads the kernels.

@@ -73,8 +73,20 @@ struct BatchArgs {
     uint32_t point[kMaxBatch];      // observation point of each record
 };
 
+// In place of the batch block: a launch that writes one record at the start of the caller's memory
+// (dmi_observe_into).  It has no chain of launches, no control words, no policy and no counters, and its
+// request table (laid out as selection_words() does) travels here if it fits; n_words = 0: the table is in
+// device memory, where the other arguments say.
+constexpr uint32_t kIntoWords = 832;        // 166 requests; both argument blocks stay below 4 KiB
+struct alignas(16) IntoArgs {
+    const uint8_t *src[1];
+    uint32_t point[1];
+    uint32_t n_words;
+    uint32_t words[kIntoWords];
+};
+
 // What the general capture kernel reads (its argument block: five 64-byte lines).
-struct CaptureKernelArgs {
+struct alignas(16) CaptureKernelArgs {
     // source (the data pointer itself is in BatchArgs)
     int64_t row_stride_b;           // dense: bytes between rows
     int64_t n_src_rows;             // dense: rows in the tensor; paged: physical blocks
@@ -149,13 +161,14 @@ hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t gri
 // grid is n_reqs + 1
 bool decode_kernel_applies(const CaptureArgs &a, bool vec16);
 hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s);
+// one record into the caller's memory: either kernel, with no control words behind it
+hipError_t launch_capture_into(const CaptureArgs &a, const IntoArgs &b, bool decode, uint32_t grid, bool vec16,
+                               hipStream_t s);
 hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words, hipStream_t s);
 // start of a replayable step: writes *step and, if par_from != par_to, carries head and
 // tail_for over to the copy the step's first launch reads
 hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint32_t par_from, uint32_t par_to,
                              const uint64_t *host_tail, hipStream_t s);
-// zeroes head / tail copies and the running counters of a control block
-hipError_t launch_ctrl_reset(DevCtrl *ctrl, hipStream_t s);
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s);
 hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap,
                                uint64_t from, uint64_t nbytes, uint32_t grid, hipStream_t s);

@@ -38,7 +38,9 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 
+#include <cstddef>
 #include <cstring>
+#include <type_traits>
 
 namespace dmi {
 
@@ -486,15 +488,38 @@ __device__ __forceinline__ void touch_argument_lines(const T &a, const uint8_t *
 // registers would cost the others a workgroup per compute unit).
 enum SummMode { SUMM_NO = 0, SUMM_ROWS = 1, SUMM_SHORT = 2 };
 
-template <int ES_IN, int VEC, int OUT, int SUMM>
-__global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const BatchArgs b)
+typedef __attribute__((address_space(1))) const uint4 global_uint4;
+typedef __attribute__((address_space(1))) const uint32_t global_u32;
+
+// The request table of a launch into the caller's memory, where the launch carries it: in the second block of
+// the kernel's own arguments (which are plain memory to the lanes that read them), `first` bytes in.
+__device__ __forceinline__ global_uint4 *inline_table(uint32_t first)
 {
+    return (global_uint4 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first + offsetof(IntoArgs, words));
+}
+static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
+
+template <int ES_IN, int VEC, int OUT, int SUMM, typename SRC>
+__global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const SRC b)
+{
+    constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ float short_sums[SUMM == SUMM_SHORT ? 4 * 192 : 1];      // per wavefront: totals of 64 rows
-    const uint32_t y = blockIdx.y;                  // which tensor of the batch this workgroup works on
+    const uint32_t y = INTO ? 0u : blockIdx.y;      // which tensor of the batch this workgroup works on
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
     touch_argument_lines(a, src, point_id);         // all of it in one trip, not one by one
+    global_uint4 *req_table = (global_uint4 *)a.req_table;
+    global_u32 *row0 = (global_u32 *)a.row0;
+    if constexpr (INTO)
+        if (b.n_words) {
+            req_table = inline_table(sizeof(CaptureKernelArgs));
+            row0 = (global_u32 *)(req_table + a.n_reqs);
+        }
+    auto load_entry = [&](uint32_t r) -> uint4 {
+        const u32x4 e = *(__attribute__((address_space(1))) const u32x4 *)(req_table + r);
+        return make_uint4(e.x, e.y, e.z, e.w);
+    };
     constexpr uint32_t NB_IN = ES_IN * VEC;
     constexpr uint32_t NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>();
     typedef typename UnitT<NB_IN>::T unit_t;
@@ -521,7 +546,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     constexpr uint32_t kCtlTid = kThreads - 64u;
     uint64_t cnt_cap[3] = {0, 0, 0}, cnt_drop[3] = {0, 0, 0}, tail_now = 0, seq = a.seq;
     RawControl raw = {};
-    if (tid == kCtlTid)     // issued here, used just before the barrier below
+    if (!INTO && tid == kCtlTid)    // issued here, used just before the barrier below
         raw = fetch_control(a.ctrl, par, a.step);
     auto publish_control = [&]() {
         const Control ct = resolve_control(raw, a.step != nullptr, a.node, a.tail_floor, a.seq, a.step_id,
@@ -549,14 +574,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint32_t r = b * 64u + lane;
             uint32_t cnt = 0, cnt_all = 0;
             if (r < n_reqs) {
-                uint4 e = a.req_table[r];
+                uint4 e = load_entry(r);
                 cnt_all = e.w;
                 const bool keep = a.keep_mask ? a.keep_mask[r] != 0 : true;
                 cnt = keep ? cnt_all : 0u;
                 if (a.table_in_lds) {
                     e.w = cnt;
                     ltab[r] = e;
-                    lrb[r] = a.row0[r];
+                    lrb[r] = row0[r];
                 }
             }
             const uint32_t inc = wave_incl_scan(cnt, lane);
@@ -625,7 +650,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         if constexpr (SUMM) { g = blockIdx.x * rpw + sub; c_begin = l; stride = gsz; }
         else { g = blockIdx.x / cpr; c_begin = (blockIdx.x - g * cpr) * CH + tid; stride = kThreads; }
         if (g < n_reqs) {
-            const int64_t row = index_mode ? (int64_t)a.row_index[g] : (int64_t)a.row0[g];
+            const int64_t row = index_mode ? (int64_t)a.row_index[g] : (int64_t)row0[g];
             pre_ref.ok = row >= 0 && row < a.n_src_rows;
             pre_ref.base = src + (pre_ref.ok ? row : 0) * a.row_stride_b;
 #pragma unroll
@@ -638,7 +663,12 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             pre = true;
         }
     }
-    if (tid == kCtlTid) {
+    if (INTO && tid < 12u) lds[m.bcast + tid] = tid == 8u    ? (uint32_t)a.seq
+                                                : tid == 9u  ? (uint32_t)(a.seq >> 32)
+                                                : tid == 10u ? (uint32_t)a.step_id
+                                                : tid == 11u ? (uint32_t)(a.step_id >> 32)
+                                                             : 0u;      // head, tail, policy: none
+    if (!INTO && tid == kCtlTid) {
         // the drained-up-to mark for the next launch's drop decision: workgroup 0 reads it where
         // the host keeps it (a read across the host link, issued after every other load of this
         // lane so that none of them queues behind it; nothing in this launch waits for it but
@@ -665,8 +695,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     const uint64_t head0 = (uint64_t)lds[m.bcast + 0] | ((uint64_t)lds[m.bcast + 1] << 32);
     const uint64_t head = head0 + (uint64_t)y * record_bytes;
     const uint32_t flags = lds[m.bcast + 6];
-    const bool publisher = blockIdx.x == 0 && y == 0 && tid == kCtlTid;
-    if (flags & kStepSkip) {
+    const bool publisher = !INTO && blockIdx.x == 0 && y == 0 && tid == kCtlTid;
+    if (!INTO && (flags & kStepSkip)) {
         // a sampled-out replay: no record, no sequence number; the chain of head and tail
         // copies still has to reach the next launch
         if (publisher) {
@@ -677,7 +707,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     }
     const uint64_t tail = (uint64_t)lds[m.bcast + 2] | ((uint64_t)lds[m.bcast + 3] << 32);
     const bool drop_newest = (flags & kStepDropNewest) != 0;
-    const bool dropped = a.force_drop != 0u || (drop_newest && head - tail + record_bytes > a.cap);
+    const bool dropped = !INTO && (a.force_drop != 0u || (drop_newest && head - tail + record_bytes > a.cap));
 
     // ---- publish: one lane of the launch leaves head, tail and counters for the next launch and
     //      fills the commit slot of the launch's last record, early, so that it overlaps the copy.
@@ -764,16 +794,16 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             } else if (a.table_in_lds) {        // (the host keeps every listed row below 2^32)
                 k.at = L[m.rb + r] + j * L[m.tab + 4u * r + 2u];
             } else {
-                k.at = a.row0[r];
-                if (j) k.at += j * a.req_table[r].z;
+                k.at = row0[r];
+                if (j) k.at += j * load_entry(r).z;
             }
         } else {
             uint32_t tok0, tstep, seq_row;
             if (a.table_in_lds) {
                 tok0 = L[m.tab + 4u * r + 1u]; tstep = L[m.tab + 4u * r + 2u]; seq_row = L[m.rb + r];
             } else {
-                const uint4 e = a.req_table[r];
-                tok0 = e.y; tstep = e.z; seq_row = a.row0[r];
+                const uint4 e = load_entry(r);
+                tok0 = e.y; tstep = e.z; seq_row = row0[r];
             }
             const uint32_t t = tok0 + j * tstep;            // host keeps token positions below 2^31
             const uint32_t lb = a.bs_shift < 32u ? t >> a.bs_shift : t / a.block_size;
@@ -843,7 +873,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 if (r < n_reqs) {
                     uint4 e;
                     if (a.table_in_lds) e = ltab[r];
-                    else { e = a.req_table[r]; if (!simple) e.w = pref[r + 1] - pref[r]; }
+                    else { e = load_entry(r); if (!simple) e.w = pref[r + 1] - pref[r]; }
                     v.x = e.x; v.y = e.y; v.z = e.z; v.w = e.w;
                 }
                 ring_store<u32x4>(w, 64u + 16ull * r, v);
@@ -1284,22 +1314,32 @@ struct DecodeArgs {
     uint64_t spare[6];
 };
 static_assert(sizeof(DecodeArgs) == 256, "four lines");
-constexpr uint32_t kDecDropNewest = 1u, kDecConsecutive = 2u, kDecIndexed = 4u, kDecParIn = 8u;
+constexpr uint32_t kDecDropNewest = 1u, kDecConsecutive = 2u, kDecIndexed = 4u, kDecParIn = 8u, kDecRowMap = 16u;
 
 // MASK: the paper's best-effort path (section 4.4): a batch-aligned keep vector, read when the
 // kernel runs, decides per request.  Every workgroup reads the whole vector (at most 1024
 // bytes) together with its other loads, the wavefronts ballot it into 16 words of LDS, and
 // each workgroup derives from those the record's row count and its own row's place.  The
 // row itself is loaded before the vector is known and thrown away if the request is out.
-template <int OUT, bool SUMM, bool MASK>
-__global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeArgs a, const BatchArgs b)
+template <int OUT, bool SUMM, bool MASK, typename SRC>
+__global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeArgs a, const SRC b)
 {
+    constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
     __shared__ uint32_t sh[32];
     __shared__ uint64_t kept_bits[16];      // MASK: bit i of word q = request 64 q + i is kept
-    const uint32_t y = blockIdx.y;          // which tensor of the batch
+    const uint32_t y = INTO ? 0u : blockIdx.y;      // which tensor of the batch
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
     touch_argument_lines(a, src, point_id);
+    global_uint4 *req_table = (global_uint4 *)a.req_table;
+    global_u32 *rows = (global_u32 *)a.rows;
+    if constexpr (INTO)
+        if (b.n_words) {
+            req_table = inline_table(sizeof(DecodeArgs));
+            // (the row of every request, or of every listed row behind those, unless the caller gave indexes)
+            if (!(a.flags & kDecIndexed))
+                rows = (global_u32 *)(req_table + a.n_reqs) + (a.flags & kDecRowMap ? a.n_reqs : 0u);
+        }
     constexpr uint32_t U = 4;
     constexpr uint32_t NB_OUT = out_unit_bytes<2, 8, OUT>();
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -1311,7 +1351,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     // control words first (they depend on nothing but the arguments), then the row
     uint64_t cnt_cap[3] = {0, 0, 0}, cnt_drop[3] = {0, 0, 0}, tail_now = 0, seq = a.seq;
     RawControl raw = {};
-    if (tid == kCtlTid) raw = fetch_control(a.ctrl, par, a.step);
+    if (!INTO && tid == kCtlTid) raw = fetch_control(a.ctrl, par, a.step);
     uint32_t kb[4] = {0u, 0u, 0u, 0u};
     if constexpr (MASK) {
 #pragma unroll
@@ -1326,8 +1366,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
         const uint32_t g = blockIdx.x;
         // the usual decode layout (request i in row first + i) saves the dependent trip to the table
         const int64_t row = (a.flags & kDecConsecutive) ? (int64_t)a.row_first + g
-                            : (a.flags & kDecIndexed) ? (int64_t)a.rows[g]
-                                                      : (int64_t)reinterpret_cast<const uint32_t *>(a.rows)[g];
+                            : (a.flags & kDecIndexed) ? (int64_t)(int32_t)rows[g] : (int64_t)rows[g];
         ok = row >= 0 && row < (int64_t)a.n_src_rows;
         const uint8_t *base = src + (ok ? row : 0) * a.row_stride_b;
 #pragma unroll
@@ -1350,7 +1389,13 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
             if (lane == 0) kept_bits[k * 4u + wave] = b;
         }
     }
-    if (tid == kCtlTid) {
+    if (INTO && tid < 28u && (tid < 8u || tid >= 24u))      // head, tail, policy: none
+        sh[tid] = tid == 24u   ? (uint32_t)a.seq
+                  : tid == 25u ? (uint32_t)(a.seq >> 32)
+                  : tid == 26u ? (uint32_t)a.step_id
+                  : tid == 27u ? (uint32_t)(a.step_id >> 32)
+                               : 0u;
+    if (!INTO && tid == kCtlTid) {
         // the drained-up-to mark for the next launch's drop decision, read where the host keeps
         // it by the extra workgroup's lane, after every other load of that lane
         const uint64_t *ts = meta_wg && y == 0 && a.tail_src ? a.tail_src : &a.ctrl->tail;
@@ -1393,8 +1438,8 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     const uint64_t head0 = (uint64_t)sh[0] | ((uint64_t)sh[1] << 32);
     const uint64_t tail = (uint64_t)sh[2] | ((uint64_t)sh[3] << 32);
     const uint32_t flags = sh[6];
-    const bool publisher = meta_wg && y == 0 && tid == kCtlTid;
-    if (flags & kStepSkip) {    // sampled-out replay: pass head and tail on, capture nothing
+    const bool publisher = !INTO && meta_wg && y == 0 && tid == kCtlTid;
+    if (!INTO && (flags & kStepSkip)) {    // sampled-out replay: pass head and tail on, capture nothing
         if (publisher) {
             a.ctrl->head[par ^ 1u] = head0;
             a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
@@ -1429,7 +1474,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     // batch have one size: record y fits iff the y before it did, and then they were kept)
     const bool drop_newest = (flags & kStepDropNewest) != 0;
     const uint64_t head = head0 + (uint64_t)y * record_bytes;
-    const bool dropped = drop_newest && head - tail + record_bytes > a.cap;
+    const bool dropped = !INTO && drop_newest && head - tail + record_bytes > a.cap;
     RingW w;
     w.ring = a.ring;
     w.cap = a.cap;
@@ -1481,8 +1526,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
         for (uint32_t r = tid; r < tab_slots; r += kThreads) {
             u32x4 tv = {0u, 0u, 0u, 0u};
             if (r < a.n_reqs) {
-                const uint4 e = a.req_table[r];
-                tv.x = e.x; tv.y = e.y; tv.z = e.z; tv.w = e.w;
+                tv = *(__attribute__((address_space(1))) const u32x4 *)(req_table + r);
                 if constexpr (MASK) tv.w = (uint32_t)((kept_bits[(r >> 6) & 15u] >> (r & 63u)) & 1ull);
             }
             ring_store<u32x4>(w, 64u + 16ull * r, tv);
@@ -1548,19 +1592,6 @@ __global__ void step_begin_kernel(DevCtrl *ctrl, StepParams *step, const StepPar
     }
 }
 
-// Put a control block back to "empty stream, nothing counted": the chain words and the running
-// counters (a fill kernel, so that a caller under graph capture records a kernel node).
-__global__ void ctrl_reset_kernel(DevCtrl *ctrl)
-{
-    if (threadIdx.x != 0) return;
-    ctrl->head[0] = ctrl->head[1] = 0;
-    ctrl->tail_for[0] = ctrl->tail_for[1] = 0;
-    ctrl->tail = 0;
-    ctrl->captured_records = ctrl->captured_rows = ctrl->captured_bytes = 0;
-    ctrl->dropped_records = ctrl->dropped_rows = ctrl->dropped_bytes = 0;
-    ctrl->bad_rows = 0;
-}
-
 // Fetch one commit slot into pinned host memory: a small launch of its own on the producer's
 // stream, so the capture kernel itself never writes across PCIe (such a store is
 // acknowledged only after some 4-5 microseconds, and a kernel cannot retire before its
@@ -1614,24 +1645,22 @@ extern "C" dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop
         }                                                                                                             \
     } while (0)
 
-template <int ES_IN, int VEC, int OUT>
-static hipError_t launch_t(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, hipStream_t s)
+template <int ES_IN, int VEC, int OUT, typename SRC>
+static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     const dim3 g(grid, a.n_batch);
+    const CaptureKernelArgs &k = a;
     if (a.summary_mask && a.lanes_per_row)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT>), g, a.lds_bytes, s,
-                           static_cast<const CaptureKernelArgs &>(a), b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC>), g, a.lds_bytes, s, k, b);
     else if (a.summary_mask)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS>), g, a.lds_bytes, s,
-                           static_cast<const CaptureKernelArgs &>(a), b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS, SRC>), g, a.lds_bytes, s, k, b);
     else
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO>), g, a.lds_bytes, s,
-                           static_cast<const CaptureKernelArgs &>(a), b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC>), g, a.lds_bytes, s, k, b);
     return hipGetLastError();
 }
 
-template <int ES_IN, int VEC>
-static hipError_t launch_o(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, hipStream_t s)
+template <int ES_IN, int VEC, typename SRC>
+static hipError_t launch_o(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     const bool raw = a.out_dtype == a.src_dtype;
     if (a.out_dtype == 0) return launch_t<ES_IN, VEC, OUT_NONE>(a, b, grid, s);
@@ -1643,7 +1672,8 @@ static hipError_t launch_o(const CaptureArgs &a, const BatchArgs &b, uint32_t gr
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool vec16, hipStream_t s)
+template <typename SRC>
+static hipError_t launch_any(const CaptureArgs &a, const SRC &b, uint32_t grid, bool vec16, hipStream_t s)
 {
     if (grid == 0 || grid > kMaxGrid || a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
     const bool four = a.src_dtype == 3;
@@ -1651,26 +1681,31 @@ hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t gri
     return vec16 ? launch_o<2, 8>(a, b, grid, s) : launch_o<2, 1>(a, b, grid, s);
 }
 
-template <int OUT>
-static hipError_t launch_decode_t(const DecodeArgs &d, const BatchArgs &b, uint32_t n_batch, bool summaries,
-                                  hipStream_t s)
+hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool vec16, hipStream_t s)
+{
+    return launch_any(a, b, grid, vec16, s);
+}
+
+template <int OUT, typename SRC>
+static hipError_t launch_decode_t(const DecodeArgs &d, const SRC &b, uint32_t n_batch, bool summaries, hipStream_t s)
 {
     const dim3 grid(d.n_wg_rows + 1u, n_batch);
     if (d.keep_mask) {
         if (summaries)
-            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, true, true>), grid, 0, s, d, b);
+            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, true, true, SRC>), grid, 0, s, d, b);
         else
-            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, false, true>), grid, 0, s, d, b);
+            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, false, true, SRC>), grid, 0, s, d, b);
     } else {
         if (summaries)
-            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, true, false>), grid, 0, s, d, b);
+            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, true, false, SRC>), grid, 0, s, d, b);
         else
-            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, false, false>), grid, 0, s, d, b);
+            DMI_LAUNCH_CAPTURE(d.step != nullptr, (capture_decode_kernel<OUT, false, false, SRC>), grid, 0, s, d, b);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s)
+template <typename SRC>
+static hipError_t launch_decode_any(const CaptureArgs &a, const SRC &b, hipStream_t s)
 {
     if (a.n_src_rows < 0 || a.n_src_rows > 0xFFFFFFFFll) return hipErrorInvalidValue;
     if (a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
@@ -1694,7 +1729,7 @@ hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipSt
     d.units_per_row = a.units_per_row;
     d.row_first = a.row_first;
     d.flags = (a.drop_newest ? kDecDropNewest : 0u) | (a.rows_consecutive ? kDecConsecutive : 0u) |
-              (a.row_index ? kDecIndexed : 0u) | (a.par_in ? kDecParIn : 0u);
+              (a.row_index ? kDecIndexed : 0u) | (a.par_in ? kDecParIn : 0u) | (a.row_map ? kDecRowMap : 0u);
     d.node = a.node;
     d.summary_mask = a.summary_mask;
     d.row_elems = a.row_elems;
@@ -1718,6 +1753,18 @@ hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipSt
     }
 }
 
+hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s)
+{
+    return launch_decode_any(a, b, s);
+}
+
+hipError_t launch_capture_into(const CaptureArgs &a, const IntoArgs &b, bool decode, uint32_t grid, bool vec16,
+                               hipStream_t s)
+{
+    if (a.n_batch != 1u || a.step) return hipErrorInvalidValue;
+    return decode ? launch_decode_any(a, b, s) : launch_any(a, b, grid, vec16, s);
+}
+
 hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words, hipStream_t s)
 {
     for (uint32_t o = 0; o < n_words; o += 896u) {
@@ -1729,12 +1776,6 @@ hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words,
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-hipError_t launch_ctrl_reset(DevCtrl *ctrl, hipStream_t s)
-{
-    hipLaunchKernelGGL(ctrl_reset_kernel, dim3(1), dim3(64), 0, s, ctrl);
-    return hipGetLastError();
 }
 
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s)

@@ -3,9 +3,11 @@
 //
 // dmi_observe needs device memory beyond the observed tensor and the ring: the control block
 // (head / tail copies, running counters, commit slot) and the request table staged for the
-// kernel.  A ring allocates those when it is created.  Here they live in one file-scope device
-// array, `scratch`, that exists once per GPU for as long as the process does; the record goes
-// straight into memory of the caller's.  The capture kernels are the ones dmi_observe launches.
+// kernel.  A ring allocates those when it is created.  Here the record goes straight into memory of
+// the caller's, so there is no chain of launches to keep, and the table is one of the launch's arguments
+// (IntoArgs); what is left -- tables too long for that, the word that counts bad rows, the zeros idle lanes
+// read -- lives in one file-scope device array, `scratch`, that exists once per GPU for as long as the
+// process does.  The capture kernels are those of dmi_observe, without their control words.
 #include "dmi_ring.h"
 
 using namespace dmi;
@@ -101,15 +103,20 @@ extern "C" dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *
                     words.size(), kIntoTableWords);
 
     hipStream_t s = (hipStream_t)hip_stream;
-    // the array keeps what the last call left: the stream starts at offset 0 with nothing counted
-    HIP_TRY(launch_ctrl_reset(&S->ctrl, s));
-    if (!words.empty()) HIP_TRY(launch_upload(S->table, words.data(), (uint32_t)words.size(), s));
+    // The table travels with the launch if it fits: two launches in front of it, to reset the control words (which
+    // such a launch now does without) and to stage the table, cost a call of a few rows more than the capture itself.
+    IntoArgs b;
+    b.src[0] = a.src;
+    b.point[0] = point_id;
+    b.n_words = words.size() <= kIntoWords ? (uint32_t)words.size() : 0u;
+    if (b.n_words) memcpy(b.words, words.data(), words.size() * 4u);
+    else if (!words.empty()) HIP_TRY(launch_upload(S->table, words.data(), (uint32_t)words.size(), s));
     a.req_table = reinterpret_cast<const uint4 *>(S->table);
     a.row0 = S->table + 4u * (size_t)sel->n_reqs;
     a.row_map = pl.row_map ? a.row0 + sel->n_reqs : nullptr;
     a.seq = seq;
     a.step_id = step_id;
-    a.cslot = &S->ctrl.slots[0];
+    a.cslot = nullptr;
     a.tail_floor = 0;
     a.drop_newest = 0;
     a.tail_src = nullptr;
@@ -117,11 +124,7 @@ extern "C" dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *
     a.step = nullptr;
     a.node = 0;
     a.n_batch = 1;
-    BatchArgs b;
-    memset(&b, 0, sizeof b);
-    b.src[0] = a.src;
-    b.point[0] = point_id;
-    const hipError_t e = pl.decode ? launch_capture_decode(a, b, s) : launch_capture(a, b, pl.grid, geo.vec16, s);
+    const hipError_t e = launch_capture_into(a, b, pl.decode, pl.grid, geo.vec16, s);
     if (e != hipSuccess) return fail(DMI_ERR_HIP, "capture launch failed: %s", hipGetErrorString(e));
     if (record_bytes) *record_bytes = pl.ub;
     return DMI_OK;
