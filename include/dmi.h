@@ -139,8 +139,9 @@ dmi_status_t dmi_ring_destroy(dmi_ring_t *ring);
 
 /* Observed tensor: a row-major matrix [shape[0], shape[1]] of `dtype`
  * (BF16 / FP16 / FP32), stride in elements, stride[1] == 1.  Any 2-byte (4 for
- * FP32) aligned base and any shape are accepted; 16-byte aligned bases and row
- * pitches with shape[1]*sizeof(dtype) % 16 == 0 take the vectorised kernel. */
+ * FP32) aligned base and any shape are accepted; rows of at least 16 bytes are
+ * moved in 16-byte units wherever they lie, fastest where base, row pitch and row
+ * length are multiples of 16 bytes. */
 typedef struct {
     const void *data;           /* [device] */
     uint32_t dtype;

@@ -96,6 +96,7 @@ struct alignas(16) CaptureKernelArgs {
     uint32_t block_size;
     uint32_t n_seg;                 // segments per row (1, or selected heads)
     uint32_t seg_units;             // units per segment
+    uint32_t seg_elems;             // elements per segment
     uint32_t heads_sel[8];
     // selection (device slab)
     const uint4 *req_table;         // {req_id, tok_start, tok_step, tok_count}
@@ -146,6 +147,8 @@ struct CaptureArgs : CaptureKernelArgs {
     const uint32_t *row_map;        // decode-shaped kernel, requests listing several rows: source row of every
                                     // output row, written by the host behind the request table
     uint32_t lds_bytes;
+    uint32_t loose;                 // not on a 16-byte grid, but long enough for 16-byte units
+    uint32_t limit_units;           // units per row by which a record's size is limited
     // record geometry and header words, filled by the host when it knows them exactly (no keep
     // mask: the row count is the listed one); used by the decode-shaped kernel
     uint32_t hdr[16];

@@ -213,8 +213,8 @@ __device__ __forceinline__ float widen16(uint32_t bits, uint32_t src_dtype)
 }
 
 // ---------------------------------------------------------------- units
-// A unit is what one lane moves per access: 16 source bytes on the vector path,
-// one element on the element path.
+// A unit is what one lane moves per access: 16 source bytes, or one element where rows are shorter than that
+// and not 16-byte movable.
 template <int NB> struct UnitT;
 template <> struct UnitT<16> { typedef u32x4 T; };
 template <> struct UnitT<8>  { typedef u32x2 T; };
@@ -238,6 +238,33 @@ __device__ __forceinline__ void ring_store(const RingW &w, uint64_t off, T v)
     // fraction of a line they cost a launch microseconds
     if constexpr (sizeof(T) >= 8) __builtin_nontemporal_store(v, reinterpret_cast<T *>(w.ring + p));
     else *reinterpret_cast<T *>(w.ring + p) = v;
+}
+
+// The same at any address, also across the end of the ring: rows that do not sit on a 16-byte grid are moved in
+// 16-byte units all the same (the memory system takes such accesses; only a unit that wraps is taken apart).
+template <bool LOOSE, typename T>
+__device__ __forceinline__ void unit_store(const RingW &w, uint64_t off, T v)
+{
+    if constexpr (!LOOSE) {
+        ring_store<T>(w, off, v);
+    } else {
+        typedef T __attribute__((aligned(1))) any_t;
+        uint64_t p = w.base + off;
+        if (p >= w.cap) p -= w.cap;
+        if (p + sizeof(T) <= w.cap) {
+            __builtin_nontemporal_store(v, reinterpret_cast<any_t *>(w.ring + p));
+        } else {
+            constexpr uint32_t n = sizeof(T) / 4u;
+            const auto words = __builtin_bit_cast(typename UnitT<sizeof(T)>::T, v);
+            for (uint32_t i = 0; i < sizeof(T); i++) {
+                uint32_t word = words[0];
+                for (uint32_t k = 1; k < n; k++) word = i / 4u == k ? words[k] : word;
+                uint64_t q = p + i;
+                if (q >= w.cap) q -= w.cap;
+                w.ring[q] = (uint8_t)(word >> (8u * (i & 3u)));
+            }
+        }
+    }
 }
 
 // Per-lane partial row summaries.  Sum of squares and sum are fp32; the largest magnitude is
@@ -304,7 +331,7 @@ __device__ __forceinline__ float am_value(uint32_t m, uint32_t src_dtype)
 }
 
 // Convert one source unit and store it; optionally accumulate the row summaries.
-template <int ES_IN, int VEC, int OUT, bool SUMM>
+template <int ES_IN, int VEC, int OUT, bool SUMM, bool LOOSE = false>
 __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
                                           typename UnitT<ES_IN * VEC>::T v, uint32_t src_dtype,
                                           Accum &acc)
@@ -317,7 +344,7 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
             for (int k = 0; k < 4; k++) accum_pair(acc, wd[k], is_bf16);
         }
         if constexpr (OUT == OUT_RAW) {
-            ring_store<u32x4>(w, out_off, v);
+            unit_store<LOOSE, u32x4>(w, out_off, v);
         } else if constexpr (OUT == OUT_FP16) {
             u32x4 o;
             uint32_t ow[4];
@@ -325,7 +352,7 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
             for (int k = 0; k < 4; k++)
                 ow[k] = bf16_to_fp16(wd[k] & 0xFFFFu) | (bf16_to_fp16(wd[k] >> 16) << 16);
             o.x = ow[0]; o.y = ow[1]; o.z = ow[2]; o.w = ow[3];
-            ring_store<u32x4>(w, out_off, o);
+            unit_store<LOOSE, u32x4>(w, out_off, o);
         } else if constexpr (OUT == OUT_FP8) {
             s16x2_t lo = {0, 0}, hi = {0, 0};
             lo = bf16x2_to_fp8x2(wd[0], lo, false);
@@ -335,7 +362,7 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
             u32x2 o;
             o.x = __builtin_bit_cast(uint32_t, lo);
             o.y = __builtin_bit_cast(uint32_t, hi);
-            ring_store<u32x2>(w, out_off, o);
+            unit_store<LOOSE, u32x2>(w, out_off, o);
         }
     } else if constexpr (ES_IN == 4 && VEC == 4) {
         if constexpr (SUMM) {
@@ -344,7 +371,7 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
             accum_f32(acc, v.z);
             accum_f32(acc, v.w);
         }
-        if constexpr (OUT == OUT_RAW) ring_store<u32x4>(w, out_off, v);
+        if constexpr (OUT == OUT_RAW) unit_store<LOOSE, u32x4>(w, out_off, v);
     } else if constexpr (ES_IN == 2) {      // one 2-byte element
         const uint32_t b = v;
         if constexpr (SUMM) accum_16(acc, b, src_dtype);
@@ -499,7 +526,10 @@ __device__ __forceinline__ global_uint4 *inline_table(uint32_t first)
 }
 static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
 
-template <int ES_IN, int VEC, int OUT, int SUMM, typename SRC>
+// LOOSE: rows of at least 16 bytes that do not sit on a 16-byte grid.  They are moved in 16-byte units too,
+// a row's (or head's) last unit ending where the row does and so covering some elements a second time: those
+// are stored twice with the same value and left out of the second unit's sums.
+template <int ES_IN, int VEC, int OUT, int SUMM, typename SRC, bool LOOSE>
 __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const SRC b)
 {
     constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
@@ -522,7 +552,11 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     };
     constexpr uint32_t NB_IN = ES_IN * VEC;
     constexpr uint32_t NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>();
+    constexpr uint32_t ES_OUT = OUT == OUT_NONE ? 0u : OUT == OUT_FP8 ? 1u : (uint32_t)ES_IN;
     typedef typename UnitT<NB_IN>::T unit_t;
+    // a unit as it is loaded: device memory (said explicitly, or a choice between two pointers costs the load its
+    // type), at any address if the rows are
+    typedef __attribute__((address_space(1))) const unit_t __attribute__((aligned(LOOSE ? ES_IN : ES_IN * VEC))) global_unit_t;
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t n_reqs = a.n_reqs;
@@ -631,6 +665,12 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     // -- decode-shaped selections (no mask, one row per request, dense): the first work
     //    item's rows do not depend on anything computed above, so their loads are issued
     //    now and travel together with the control fetch instead of behind it
+    // first element of a segment's unit (a segment is a row, or a head's part of a paged row)
+    auto elem_in_seg = [&](uint32_t c) -> uint64_t {
+        const uint64_t e = (uint64_t)c * VEC;
+        if constexpr (LOOSE) return e + VEC <= a.seg_elems ? e : a.seg_elems - VEC;
+        else return e;
+    };
     constexpr uint32_t U = 4;                               // loads in flight per lane
     constexpr uint32_t CH = U * kThreads;                   // units per long-row work item
     const uint32_t rpw = SUMM == SUMM_ROWS ? a.rows_per_wg : 1u;
@@ -657,8 +697,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             for (uint32_t k = 0; k < U; k++) {
                 const uint32_t c = c_begin + k * stride;
                 const bool want = pre_ref.ok && c < a.units_per_row;
-                const uint8_t *p = want ? pre_ref.base + (uint64_t)c * NB_IN : reinterpret_cast<const uint8_t *>(a.ctrl);
-                pre_v[k] = *reinterpret_cast<const unit_t *>(p);     // zeroed where it is used if not wanted
+                const uint8_t *p = want ? pre_ref.base + elem_in_seg(c) * ES_IN : reinterpret_cast<const uint8_t *>(a.ctrl);
+                pre_v[k] = *(global_unit_t *)p;     // zeroed where it is used if not wanted
             }
             pre = true;
         }
@@ -825,10 +865,32 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         return locate_end(locate_begin(g, first));
     };
     auto unit_ptr = [&](const RowRef &ref, uint32_t c) -> const uint8_t * {
-        if (!a.paged) return ref.base + (uint64_t)c * NB_IN;
+        if (!a.paged) return ref.base + elem_in_seg(c) * ES_IN;
         const uint32_t seg = a.seg_shift < 32u ? c >> a.seg_shift : c / a.seg_units;
         const uint32_t cc = c - seg * a.seg_units;
-        return ref.base + (int64_t)L[m.heads + seg] * a.head_stride_b + (uint64_t)cc * NB_IN;
+        return ref.base + (int64_t)L[m.heads + seg] * a.head_stride_b + elem_in_seg(cc) * ES_IN;
+    };
+    // where unit c of row g goes, in bytes from the record's start
+    auto out_at = [&](uint64_t g, uint32_t c) -> uint64_t {
+        if constexpr (LOOSE) {
+            const uint32_t seg = !a.paged ? 0u : a.seg_shift < 32u ? c >> a.seg_shift : c / a.seg_units;
+            return off_payload + (g * a.row_elems + (uint64_t)seg * a.seg_elems + elem_in_seg(c - seg * a.seg_units)) * ES_OUT;
+        }
+        return off_payload + (g * a.units_per_row + c) * NB_OUT;
+    };
+    // a unit as the row's sums see it: without the elements that the unit in front of it holds as well
+    auto sum_part = [&](unit_t v, uint32_t c) -> unit_t {
+        if constexpr (LOOSE) {
+            const uint32_t cc = !a.paged ? c : a.seg_shift < 32u ? c & ((1u << a.seg_shift) - 1u) : c % a.seg_units;
+            const uint32_t twice = cc + 1u == a.seg_units ? a.seg_units * VEC - a.seg_elems : 0u;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                const uint32_t per = VEC / 4u;      // elements of a 32-bit word
+                const uint32_t gone = twice <= i * per ? 0u : twice - i * per < per ? twice - i * per : per;
+                v[i] &= gone == 0u ? 0xFFFFFFFFu : gone == per ? 0u : 0xFFFF0000u;
+            }
+        }
+        return v;
     };
     // Loads are never put under a condition of their own: the compiler then waits for each
     // one before it issues the next (a register copy where the branches join), and four
@@ -838,8 +900,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     const uint8_t *const safe_src = reinterpret_cast<const uint8_t *>(a.ctrl);
     auto load_unit = [&](const RowRef &ref, uint32_t c, bool want) -> unit_t {
         const uint8_t *p = want ? unit_ptr(ref, want ? c : 0u) : safe_src;
-        // both are device memory; said explicitly, or the choice between two pointers costs the load its type
-        typedef __attribute__((address_space(1))) const unit_t global_unit_t;
         return *(global_unit_t *)p;
     };
     auto zero_unless = [](bool keep, unit_t v) -> unit_t { return keep ? v : unit_t{}; };
@@ -901,7 +961,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                                              ? CH / a.units_per_row : 1u;          // rows per item
                     const uint64_t n_items = rpi > 1u ? ((uint64_t)n_rows + rpi - 1u) / rpi
                                                       : (uint64_t)n_rows * cpr;
-                    // unit k of this lane in item `it`: its flat position in the payload, loaded value
+                    // unit k of this lane in item `it`: where it goes, loaded value
                     auto fetch = [&](uint64_t it, unit_t (&v)[U], uint64_t (&pos)[U], bool (&live)[U], uint32_t &okm) {
                         RowRef ref = {nullptr, 0}, refs[U];
                         uint32_t g_prev = 0xFFFFFFFFu, cs[U];
@@ -921,7 +981,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                                 c = (uint32_t)(it - (uint64_t)g * cpr) * CH + k * kThreads + tid;
                             }
                             live[k] = g < n_rows && c < a.units_per_row;
-                            pos[k] = (uint64_t)g * a.units_per_row + c;
+                            pos[k] = out_at(g, c);
                             if (live[k] && g != g_prev) {
                                 ref = locate(g);
                                 g_prev = g;
@@ -953,7 +1013,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                                 v[k] = pre_v[k];
                                 live[k] = c < a.units_per_row;
                                 okm |= live[k] && pre_ref.ok ? 1u << k : 0u;
-                                pos[k] = (uint64_t)g * a.units_per_row + c;
+                                pos[k] = out_at(g, c);
                             }
                             if (!pre_ref.ok && c0 == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
                         } else {
@@ -970,8 +1030,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                             for (uint32_t k = 0; k < U; k++)
                                 if (live[k])
-                                    emit_unit<ES_IN, VEC, OUT, false>(w, off_payload + pos[k] * NB_OUT,
-                                                                      zero_unless((okm >> k) & 1u, v[k]), a.src_dtype, dummy);
+                                    emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, pos[k], zero_unless((okm >> k) & 1u, v[k]),
+                                                                             a.src_dtype, dummy);
                             if (!more) break;
                             it = nxt;
                             okm = okm_n;
@@ -1045,9 +1105,11 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                         for (uint32_t k = 0; k < U; k++) {
                             const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
+                            const uint32_t g = LOOSE ? row_of((uint32_t)u) : 0u;    // (else a record's units just follow each other)
                             if (live[k])
-                                emit_unit<ES_IN, VEC, OUT, false>(w, off_payload + u * NB_OUT, zero_unless(okk[k], v[k]),
-                                                                  a.src_dtype, dummy);
+                                emit_unit<ES_IN, VEC, OUT, false, LOOSE>(
+                                    w, LOOSE ? out_at(g, (uint32_t)u - g * upr) : off_payload + u * NB_OUT,
+                                    zero_unless(okk[k], v[k]), a.src_dtype, dummy);
                         }
                     }
                 }
@@ -1100,7 +1162,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                 for (uint32_t k = 0; k < U; k++) {
                     const uint8_t *ptr = ref.ok && in_row[k] ? ref.base + unit_off[k] : zeros;
-                    typedef __attribute__((address_space(1))) const unit_t global_unit_t;
                     v[k] = *(global_unit_t *)ptr;
                 }
             };
@@ -1123,11 +1184,13 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++)
                         if (g < r1 && in_row[k])
-                            emit_unit<ES_IN, VEC, OUT, false>(
-                                w, off_payload + (g * a.units_per_row + l_r + k * lpr) * NB_OUT, v[k], a.src_dtype, none);
+                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, l_r + k * lpr), v[k], a.src_dtype, none);
                 }
                 Accum acc = {0.f, 0.f, 0u};
-                accum_units<ES_IN, VEC>(acc, v, 15u, a.src_dtype);          // (what is not the row's was read as zeros)
+                unit_t sv[U];
+#pragma unroll
+                for (uint32_t k = 0; k < U; k++) sv[k] = sum_part(v[k], l_r + k * lpr);
+                accum_units<ES_IN, VEC>(acc, sv, 15u, a.src_dtype);         // (what is not the row's was read as zeros)
                 const uint32_t at = (uint32_t)(g - r0) & 63u;
                 const bool last = l_r == lpr - 1u;
                 if (a.summary_mask & 1u) {
@@ -1217,19 +1280,20 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     const uint64_t g = cur_g0 + sub;
                     const bool active = g < n_rows;
                     if (active) {
-                        const uint64_t row_off = off_payload + g * a.units_per_row * NB_OUT;
                         Accum none = {0.f, 0.f, 0u};
                         uint32_t have = 0;
+                        unit_t sv[U];
 #pragma unroll
                         for (uint32_t k = 0; k < U; k++) {
                             const uint32_t c = l + (cur_pass * U + k) * gsz;
                             const bool in = c < a.units_per_row;
                             have |= in && ref.ok != 0 ? 1u << k : 0u;
                             if (OUT != OUT_NONE && in)
-                                emit_unit<ES_IN, VEC, OUT, false>(w, row_off + (uint64_t)c * NB_OUT,
-                                                                  zero_unless(ref.ok != 0, v[k]), a.src_dtype, none);
+                                emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, c), zero_unless(ref.ok != 0, v[k]),
+                                                                         a.src_dtype, none);
+                            sv[k] = sum_part(v[k], c);
                         }
-                        accum_units<ES_IN, VEC>(acc, v, have, a.src_dtype);
+                        accum_units<ES_IN, VEC>(acc, sv, have, a.src_dtype);
                     }
                     if (cur_pass == spr - 1u) {     // the row is complete: reduce and store its summaries
                         acc.ss = wave_sum(acc.ss);
@@ -1645,29 +1709,29 @@ extern "C" dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop
         }                                                                                                             \
     } while (0)
 
-template <int ES_IN, int VEC, int OUT, typename SRC>
+template <int ES_IN, int VEC, int OUT, bool LOOSE, typename SRC>
 static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     const dim3 g(grid, a.n_batch);
     const CaptureKernelArgs &k = a;
     if (a.summary_mask && a.lanes_per_row)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC>), g, a.lds_bytes, s, k, b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     else if (a.summary_mask)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS, SRC>), g, a.lds_bytes, s, k, b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     else
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC>), g, a.lds_bytes, s, k, b);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     return hipGetLastError();
 }
 
-template <int ES_IN, int VEC, typename SRC>
+template <int ES_IN, int VEC, bool LOOSE, typename SRC>
 static hipError_t launch_o(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     const bool raw = a.out_dtype == a.src_dtype;
-    if (a.out_dtype == 0) return launch_t<ES_IN, VEC, OUT_NONE>(a, b, grid, s);
-    if (raw) return launch_t<ES_IN, VEC, OUT_RAW>(a, b, grid, s);
+    if (a.out_dtype == 0) return launch_t<ES_IN, VEC, OUT_NONE, LOOSE>(a, b, grid, s);
+    if (raw) return launch_t<ES_IN, VEC, OUT_RAW, LOOSE>(a, b, grid, s);
     if constexpr (ES_IN == 2) {
-        if (a.out_dtype == 2) return launch_t<ES_IN, VEC, OUT_FP16>(a, b, grid, s);
-        if (a.out_dtype == 4) return launch_t<ES_IN, VEC, OUT_FP8>(a, b, grid, s);
+        if (a.out_dtype == 2) return launch_t<ES_IN, VEC, OUT_FP16, LOOSE>(a, b, grid, s);
+        if (a.out_dtype == 4) return launch_t<ES_IN, VEC, OUT_FP8, LOOSE>(a, b, grid, s);
     }
     return hipErrorInvalidValue;
 }
@@ -1677,8 +1741,9 @@ static hipError_t launch_any(const CaptureArgs &a, const SRC &b, uint32_t grid, 
 {
     if (grid == 0 || grid > kMaxGrid || a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
     const bool four = a.src_dtype == 3;
-    if (four) return vec16 ? launch_o<4, 4>(a, b, grid, s) : launch_o<4, 1>(a, b, grid, s);
-    return vec16 ? launch_o<2, 8>(a, b, grid, s) : launch_o<2, 1>(a, b, grid, s);
+    if (!vec16 && a.loose) return four ? launch_o<4, 4, true>(a, b, grid, s) : launch_o<2, 8, true>(a, b, grid, s);
+    if (four) return vec16 ? launch_o<4, 4, false>(a, b, grid, s) : launch_o<4, 1, false>(a, b, grid, s);
+    return vec16 ? launch_o<2, 8, false>(a, b, grid, s) : launch_o<2, 1, false>(a, b, grid, s);
 }
 
 hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool vec16, hipStream_t s)

@@ -302,7 +302,7 @@ dmi_status_t dmi_step_update(dmi_step_t *st, uint32_t node, const dmi_req_sel_t 
                 if (reqs[i].row_base + reqs[i].tok_start != a.row_first + i)
                     return fail(DMI_ERR_INVALID_ARG, "captured with request i in row %u + i: capture the step again "
                                                      "to change that", a.row_first);
-        if (listed > 0xFFFFFFFFull || listed * a.units_per_row > 0xFFFFFFFFull)
+        if (listed > 0xFFFFFFFFull || listed * a.limit_units > 0xFFFFFFFFull)
             return fail(DMI_ERR_TOO_LARGE, "selection of %llu rows exceeds one record", (unsigned long long)listed);
         const uint64_t ub = dmi_record_bytes(n_reqs, listed, nd.geo.row_elems, nd.xf.out_dtype, nd.xf.summary_mask);
         if (ub > r->dev_cap)
