@@ -398,7 +398,7 @@ dmi_status_t stage_selection(dmi_ring *r, const dmi_selection_t *sel, bool paged
 // workgroups while the rest idle (up to half the launch for 1 < items/grid < 2).
 // kResident is what stays resident at the register budget of the widest variants.  In a batch
 // (gridDim.y = nb) each workgroup stays with one tensor.
-uint32_t plan_grid(const CaptureArgs &a, uint32_t nb)
+uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
 {
     constexpr uint64_t kResident = 5u * 256u;
     const uint64_t listed = a.listed_rows, upr = a.units_per_row;
@@ -425,10 +425,24 @@ uint32_t plan_grid(const CaptureArgs &a, uint32_t nb)
         return (items + rounds - 1u) / rounds;
     };
     uint64_t groups;
-    if (a.summary_mask) {
-        // rows a workgroup takes in one step: see the two row-wise paths of capture_kernel
-        const uint64_t rows = a.lanes_per_row ? 4u * (64u / a.lanes_per_row) : a.rows_per_wg;
+    if (a.summary_mask && a.row_lanes <= 64u) {
+        const uint64_t rows = 4u * (64u / a.row_lanes);             // what a workgroup takes in one step
         groups = balanced((listed + rows - 1u) / rows);
+    } else if (a.summary_mask) {
+        // Rows of more than 256 units: a workgroup per row, or, where a launch has rows enough, a wavefront per row.
+        // (workgroup / wavefront per row, norm and largest magnitude, us:)
+        //   rows of 288 units, 1.5 k rows 7.5 / 7.5, 3 k 10.0 / 7.4, 6 k 16.6 / 9.9; of 512: 24 k 57.3 / 40.0
+        //   of 640 units, 6 k rows 17.3 / 14.4; 40 x 256 rows of 768, statistics alone 34.7 / 27.7, with the rows 45 / 49
+        //   of 1024 units, 80 x 256 rows, statistics alone 67.6 / 62.5, with the rows 116 / 121; ragged 12 k rows 39.6 / 40.6
+        //   of 1792 units, 12 k rows 66.6 / 69.4
+        // With statistics alone a wavefront takes two rows from 4096 rows on (80 x 256 rows of 512 units: 37.2 with
+        // one, 34.8 with two; 3 k rows 8.7 and 9.0), where the rows are stored too, one (61 and 64 us).
+        const uint64_t rows = listed * nb;
+        const bool alone = a.out_dtype == 0u;
+        a.wave_rows = rows >= 2048u && (upr <= 512u || (alone && upr <= 768u) ||
+                                        (alone && upr <= 1024u && flat && rows >= 16384u));
+        const uint64_t per_wave = alone && rows >= 4096u && upr <= 768u ? 2u : 1u;
+        groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed);
     } else if (upr >= kThreads && upr < 4u * kThreads && (4u * kThreads) % upr == 0) {
         groups = balanced((listed + 4u * kThreads / upr - 1u) / (4u * kThreads / upr));      // 2 or 4 rows per work item
     } else if (upr >= kThreads) {
@@ -553,12 +567,11 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
                   (index_mode ? DMI_REC_INDEXED : 0u);
     a.row_elems = geo.row_elems;
     a.units_per_row = (uint32_t)upr;
-    // a wavefront per row when rows are of moderate length and plentiful (no block-level reduction, four rows
-    // in flight per workgroup); otherwise a workgroup per row
-    a.lanes_per_row = 0;
-    if (xf->summary_mask && upr <= 256u)        // short rows: as few lanes to a row as four loads each allow
-        for (a.lanes_per_row = 4u; 4u * a.lanes_per_row < upr;) a.lanes_per_row *= 2u;
-    a.rows_per_wg = upr <= 1024u && listed >= 2048u ? 4u : 1u;
+    a.row_lanes = 0;
+    if (xf->summary_mask) {                     // as few lanes to a row as four loads each allow
+        a.row_lanes = upr > 1024u ? 256u : upr > 256u ? 64u * (uint32_t)((upr + 255u) / 256u) : 4u;
+        while (upr <= 256u && 4u * a.row_lanes < upr) a.row_lanes *= 2u;
+    }
     a.point_id = point_id;
     a.rank_tag = env.rank_tag;
     a.ring = env.ring;
@@ -664,7 +677,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
 
         // (only the general kernel counts a tail)
         const bool decode = !force_drop && !tail && pl.decode && batch_takes_decode_kernel(a, cnt);
-        const uint32_t grid = force_drop ? 1u : cnt == 1u ? pl.grid : plan_grid(a, cnt);
+        const uint32_t grid = force_drop ? 1u : plan_grid(a, cnt);
         const hipError_t e = decode ? launch_capture_decode(a, b, s) : launch_capture(a, b, grid, geo.vec16, s);
         if (e != hipSuccess) return fail(DMI_ERR_HIP, "capture launch failed: %s", hipGetErrorString(e));
         const uint64_t bytes = force_drop ? 0u : ub * cnt;      // what the launch may add to the ring

@@ -109,9 +109,8 @@ struct alignas(16) CaptureKernelArgs {
     uint32_t src_dtype, out_dtype, summary_mask, rec_flags;
     uint32_t row_elems;
     uint32_t units_per_row;
-    uint32_t rows_per_wg;           // summary kernels: 1 (a workgroup per row) or 4 (a wavefront per row)
-    uint32_t lanes_per_row;         // summary kernels, rows of at most 256 units: lanes that share a row, up to four
-                                    // units each (a power of two from 4 to 64); 0: rows_per_wg says
+    uint32_t row_lanes;             // summary kernels: lanes that share a row, up to four units each (beyond 1024
+                                    // units: four at a time): a power of two from 4 to 64, or 128, 192 or 256
     uint32_t n_batch, rank_tag;     // n_batch = gridDim.y
     uint64_t seq, step_id;          // seq: of the launch's first record
     // ring
@@ -147,6 +146,7 @@ struct CaptureArgs : CaptureKernelArgs {
     const uint32_t *row_map;        // decode-shaped kernel, requests listing several rows: source row of every
                                     // output row, written by the host behind the request table
     uint32_t lds_bytes;
+    uint32_t wave_rows;             // summaries of rows of more than 256 units: a wavefront per row, not a workgroup
     uint32_t loose;                 // not on a 16-byte grid, but long enough for 16-byte units
     uint32_t limit_units;           // units per row by which a record's size is limited
     // record geometry and header words, filled by the host when it knows them exactly (no keep

@@ -384,18 +384,29 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
     }
 }
 
-// Add one step's units (up to four per lane, `have` says which of them are the row's) to the row's partial
-// summaries: every unit summed by itself, the four combined in pairs.  Shorter chains than one running sum,
-// in time and in rounding error.
+// Add one step's units (four per lane; a lane without that unit has zeros) to the row's partial summaries: every unit summed by itself, the four combined in pairs.  Shorter chains
+// than one running sum, in time and in rounding error.
 template <int ES_IN, int VEC>
-__device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_IN * VEC>::T (&v)[4], uint32_t have,
+__device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_IN * VEC>::T (&v)[4],
                                             uint32_t src_dtype)
 {
     Accum u[4];
+    for (uint32_t k = 0; k < 4; k++) u[k] = Accum{0.f, 0.f, 0u};
+    if constexpr (ES_IN == 2 && VEC == 8) {
+        // (the source type is asked for once: a branch per word costs more than the arithmetic it chooses)
+        auto all = [&](auto is_bf16) {
 #pragma unroll
-    for (uint32_t k = 0; k < 4; k++) {
-        u[k] = Accum{0.f, 0.f, 0u};
-        if (have & (1u << k)) emit_unit<ES_IN, VEC, OUT_NONE, true>(RingW{}, 0, v[k], src_dtype, u[k]);
+            for (uint32_t k = 0; k < 4; k++) {
+                accum_pair(u[k], v[k].x, is_bf16.value);
+                accum_pair(u[k], v[k].y, is_bf16.value);
+                accum_pair(u[k], v[k].z, is_bf16.value);
+                accum_pair(u[k], v[k].w, is_bf16.value);
+            }
+        };
+        if (src_dtype == 1u) all(std::true_type()); else all(std::false_type());
+    } else {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) emit_unit<ES_IN, VEC, OUT_NONE, true>(RingW{}, 0, v[k], src_dtype, u[k]);
     }
     acc.ss += (u[0].ss + u[1].ss) + (u[2].ss + u[3].ss);
     acc.s += (u[0].s + u[1].s) + (u[2].s + u[3].s);
@@ -511,18 +522,22 @@ __device__ __forceinline__ void touch_argument_lines(const T &a, const uint8_t *
 }
 
 // ---------------------------------------------------------------- capture kernel
-// Summaries per row: none; for rows of any length; for rows of at most 256 units (a kernel of its own, or its
-// registers would cost the others a workgroup per compute unit).
-enum SummMode { SUMM_NO = 0, SUMM_ROWS = 1, SUMM_SHORT = 2 };
-
-typedef __attribute__((address_space(1))) const uint4 global_uint4;
-typedef __attribute__((address_space(1))) const uint32_t global_u32;
+// Summaries per row: none; a workgroup per row; several rows per wavefront, at most 256 units each; a
+// wavefront per row (kernels of their own, or their registers would cost the others a workgroup per compute unit).
+enum SummMode { SUMM_NO = 0, SUMM_ROWS = 1, SUMM_SHORT = 2, SUMM_WAVE = 3 };
 
 // The request table of a launch into the caller's memory, where the launch carries it: in the second block of
-// the kernel's own arguments (which are plain memory to the lanes that read them), `first` bytes in.
-__device__ __forceinline__ global_uint4 *inline_table(uint32_t first)
+// the kernel's own arguments, `first` bytes in.  Memory like any other to lanes that read entries of their own; and
+// constant, so that what a whole workgroup reads (its row) comes through the scalar cache.
+typedef __attribute__((address_space(1))) const uint32_t global_u32;
+typedef __attribute__((address_space(4))) const uint32_t constant_u32;
+__device__ __forceinline__ global_u32 *inline_table(uint32_t first)
 {
-    return (global_uint4 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first + offsetof(IntoArgs, words));
+    return (global_u32 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first + offsetof(IntoArgs, words));
+}
+__device__ __forceinline__ constant_u32 *inline_table_uniform(uint32_t first)
+{
+    return (constant_u32 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first + offsetof(IntoArgs, words));
 }
 static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
 
@@ -534,21 +549,24 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 {
     constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    __shared__ float short_sums[SUMM == SUMM_SHORT ? 4 * 192 : 1];      // per wavefront: totals of 64 rows
+    __shared__ float row_sums[SUMM == SUMM_SHORT || SUMM == SUMM_WAVE ? 4 * 192 : 1];   // per wavefront: totals of 64 rows
     const uint32_t y = INTO ? 0u : blockIdx.y;      // which tensor of the batch this workgroup works on
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
     touch_argument_lines(a, src, point_id);         // all of it in one trip, not one by one
-    global_uint4 *req_table = (global_uint4 *)a.req_table;
-    global_u32 *row0 = (global_u32 *)a.row0;
-    if constexpr (INTO)
-        if (b.n_words) {
-            req_table = inline_table(sizeof(CaptureKernelArgs));
-            row0 = (global_u32 *)(req_table + a.n_reqs);
-        }
-    auto load_entry = [&](uint32_t r) -> uint4 {
-        const u32x4 e = *(__attribute__((address_space(1))) const u32x4 *)(req_table + r);
-        return make_uint4(e.x, e.y, e.z, e.w);
+    // entry r of the request table; where request r's rows begin (a row, or a row of the block table)
+    auto table_entry = [&](uint32_t r) -> uint4 {
+        if constexpr (INTO)
+            if (b.n_words) {
+                const u32x4 e = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(CaptureKernelArgs)) + 4u * r);
+                return make_uint4(e.x, e.y, e.z, e.w);
+            }
+        return a.req_table[r];
+    };
+    auto row_first = [&](uint32_t r) -> uint32_t {
+        if constexpr (INTO)
+            if (b.n_words) return inline_table(sizeof(CaptureKernelArgs))[4u * a.n_reqs + r];
+        return a.row0[r];
     };
     constexpr uint32_t NB_IN = ES_IN * VEC;
     constexpr uint32_t NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>();
@@ -608,14 +626,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint32_t r = b * 64u + lane;
             uint32_t cnt = 0, cnt_all = 0;
             if (r < n_reqs) {
-                uint4 e = load_entry(r);
+                uint4 e = table_entry(r);
                 cnt_all = e.w;
                 const bool keep = a.keep_mask ? a.keep_mask[r] != 0 : true;
                 cnt = keep ? cnt_all : 0u;
                 if (a.table_in_lds) {
                     e.w = cnt;
                     ltab[r] = e;
-                    lrb[r] = row0[r];
+                    lrb[r] = row_first(r);
                 }
             }
             const uint32_t inc = wave_incl_scan(cnt, lane);
@@ -662,21 +680,22 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         }
         }
     }
-    // -- decode-shaped selections (no mask, one row per request, dense): the first work
-    //    item's rows do not depend on anything computed above, so their loads are issued
-    //    now and travel together with the control fetch instead of behind it
     // first element of a segment's unit (a segment is a row, or a head's part of a paged row)
     auto elem_in_seg = [&](uint32_t c) -> uint64_t {
         const uint64_t e = (uint64_t)c * VEC;
         if constexpr (LOOSE) return e + VEC <= a.seg_elems ? e : a.seg_elems - VEC;
         else return e;
     };
+    // -- decode-shaped selections (no mask, one row per request, dense): the first work
+    //    item's rows do not depend on anything computed above, so their loads are issued
+    //    now and travel together with the control fetch instead of behind it
     constexpr uint32_t U = 4;                               // loads in flight per lane
     constexpr uint32_t CH = U * kThreads;                   // units per long-row work item
-    const uint32_t rpw = SUMM == SUMM_ROWS ? a.rows_per_wg : 1u;
-    const uint32_t gsz = kThreads / rpw;                    // lanes per row (summary passes)
-    const uint32_t sub = tid / gsz, l = tid - sub * gsz;
     const uint32_t cpr = (a.units_per_row + CH - 1u) / CH;  // long-row items per row
+    // summaries: the lanes that share a row; lane l takes units l, l + row_lanes, ..., four at a time
+    const uint32_t row_lanes = SUMM ? a.row_lanes : kThreads;
+    bool first_row_inline = false;
+    if constexpr (INTO) first_row_inline = b.n_words != 0u;
     unit_t pre_v[U];
     RowRef pre_ref = {nullptr, 0};
     bool pre = false;
@@ -686,18 +705,22 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     const bool may_drop_some = a.n_batch > 1u && (a.drop_newest != 0u || a.step != nullptr);
     if (simple && !a.paged && !may_drop_some && SUMM != SUMM_SHORT &&
         (SUMM || (OUT != OUT_NONE && a.units_per_row >= kThreads && !multi_row_items))) {
-        uint32_t g, c_begin, stride;
-        if constexpr (SUMM) { g = blockIdx.x * rpw + sub; c_begin = l; stride = gsz; }
-        else { g = blockIdx.x / cpr; c_begin = (blockIdx.x - g * cpr) * CH + tid; stride = kThreads; }
+        uint32_t g, c_begin = SUMM == SUMM_WAVE ? lane : tid;
+        if constexpr (SUMM == SUMM_WAVE) g = (blockIdx.x * (kThreads / 64u) + wave) * ((n_reqs - 1u) / (gridDim.x * (kThreads / 64u)) + 1u);
+        else if constexpr (SUMM != SUMM_NO) g = blockIdx.x;
+        else { g = blockIdx.x / cpr; c_begin = (blockIdx.x - g * cpr) * CH + tid; }
         if (g < n_reqs) {
-            const int64_t row = index_mode ? (int64_t)a.row_index[g] : (int64_t)row0[g];
+            int64_t row;
+            if (index_mode) row = (int64_t)a.row_index[g];
+            else if (INTO && SUMM != SUMM_WAVE && first_row_inline) row = (int64_t)inline_table_uniform(sizeof(CaptureKernelArgs))[4u * n_reqs + g];
+            else row = (int64_t)row_first(g);
             pre_ref.ok = row >= 0 && row < a.n_src_rows;
             pre_ref.base = src + (pre_ref.ok ? row : 0) * a.row_stride_b;
 #pragma unroll
             for (uint32_t k = 0; k < U; k++) {
-                const uint32_t c = c_begin + k * stride;
-                const bool want = pre_ref.ok && c < a.units_per_row;
-                const uint8_t *p = want ? pre_ref.base + elem_in_seg(c) * ES_IN : reinterpret_cast<const uint8_t *>(a.ctrl);
+                const uint32_t c = c_begin + k * row_lanes;
+                const bool want = pre_ref.ok && c < a.units_per_row && (SUMM != SUMM_ROWS || tid < row_lanes);
+                const uint8_t *p = want ? pre_ref.base + elem_in_seg(c) * ES_IN : reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
                 pre_v[k] = *(global_unit_t *)p;     // zeroed where it is used if not wanted
             }
             pre = true;
@@ -834,16 +857,16 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             } else if (a.table_in_lds) {        // (the host keeps every listed row below 2^32)
                 k.at = L[m.rb + r] + j * L[m.tab + 4u * r + 2u];
             } else {
-                k.at = row0[r];
-                if (j) k.at += j * load_entry(r).z;
+                k.at = row_first(r);
+                if (j) k.at += j * table_entry(r).z;
             }
         } else {
             uint32_t tok0, tstep, seq_row;
             if (a.table_in_lds) {
                 tok0 = L[m.tab + 4u * r + 1u]; tstep = L[m.tab + 4u * r + 2u]; seq_row = L[m.rb + r];
             } else {
-                const uint4 e = load_entry(r);
-                tok0 = e.y; tstep = e.z; seq_row = row0[r];
+                const uint4 e = table_entry(r);
+                tok0 = e.y; tstep = e.z; seq_row = row_first(r);
             }
             const uint32_t t = tok0 + j * tstep;            // host keeps token positions below 2^31
             const uint32_t lb = a.bs_shift < 32u ? t >> a.bs_shift : t / a.block_size;
@@ -895,14 +918,27 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     // Loads are never put under a condition of their own: the compiler then waits for each
     // one before it issues the next (a register copy where the branches join), and four
     // loads in flight become four trips to memory.  A unit that is not wanted (past the
-    // end, or of a row whose index left the source) is read from the control block instead
-    // and replaced by zeros, or skipped, when it is stored.
-    const uint8_t *const safe_src = reinterpret_cast<const uint8_t *>(a.ctrl);
+    // end, or of a row whose index left the source) is read from the control block's zeros.
+    const uint8_t *const safe_src = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
     auto load_unit = [&](const RowRef &ref, uint32_t c, bool want) -> unit_t {
         const uint8_t *p = want ? unit_ptr(ref, want ? c : 0u) : safe_src;
         return *(global_unit_t *)p;
     };
     auto zero_unless = [](bool keep, unit_t v) -> unit_t { return keep ? v : unit_t{}; };
+
+    // Row totals of a wavefront's 64 rows at most, [from, upto), from its part of LDS to the record.
+    float *const stash = row_sums + (SUMM == SUMM_SHORT || SUMM == SUMM_WAVE ? wave * 192u : 0u);       // [3][64]
+    auto flush_totals = [&](uint64_t from, uint64_t upto) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (from + lane < upto) {
+            uint64_t o = off_sum + (from + lane) * 4u;
+            if (a.summary_mask & 1u) { ring_store<float>(w, o, sqrtf(stash[lane])); o += sum_arr; }
+            if (a.summary_mask & 2u) { ring_store<float>(w, o, stash[64u + lane] / (float)a.row_elems); o += sum_arr; }
+            if (a.summary_mask & 4u) ring_store<float>(w, o, am_value(__float_as_uint(stash[128u + lane]), a.src_dtype));
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
 
     if (!dropped) {
         // ---- header, request table and all pad bytes: workgroup 0.  The header is put
@@ -933,7 +969,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 if (r < n_reqs) {
                     uint4 e;
                     if (a.table_in_lds) e = ltab[r];
-                    else { e = load_entry(r); if (!simple) e.w = pref[r + 1] - pref[r]; }
+                    else { e = table_entry(r); if (!simple) e.w = pref[r + 1] - pref[r]; }
                     v.x = e.x; v.y = e.y; v.z = e.z; v.w = e.w;
                 }
                 ring_store<u32x4>(w, 64u + 16ull * r, v);
@@ -952,7 +988,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         if constexpr (SUMM == SUMM_NO) {
             if constexpr (OUT != OUT_NONE) {
                 Accum dummy = {0.f, 0.f, 0u};
-                if (a.units_per_row >= kThreads) {
+                if (VEC > 1 && a.units_per_row >= kThreads) {
                     // ---- long rows: a work item is 1024 consecutive units: a quarter or more of one
                     //      row, or 2 / 4 whole rows of 512 / 256 units; rows are located once per
                     //      item, not per unit.  Software pipelined: the next item's 4 loads per lane
@@ -1115,8 +1151,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 }
             }
         } else if constexpr (SUMM == SUMM_SHORT) {
-            // ---- summaries of short rows (up to 256 units): lanes_per_row lanes share a row, each with up to four
-            //      of its units, so one step of a wavefront is 64 / lanes_per_row whole rows and a row costs one
+            // ---- summaries of short rows (up to 256 units): 4 to 64 lanes share a row, each with up to four
+            //      of its units, so one step of a wavefront is 64 / row_lanes whole rows and a row costs one
             //      reduction over few lanes (a row of 32 units used to take a wavefront of its own, half of its
             //      lanes and three of its four loads idle, and a reduction over all 64 lanes).  A wavefront works through
             //      consecutive rows: each starts its search where the row before it was found.  What finding a
@@ -1125,7 +1161,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             //      place asked for behind a step's loads, or a store inside the loop, would make every step wait.
             //      Bound: HBM reads.  8 caches x 72.7 k rows of 32 units, norms and largest magnitudes:
             //      297 -> 69 us (1.0 -> 4.4 TB/s read).
-            const uint32_t lpr = a.lanes_per_row, lg = 31u - (uint32_t)__builtin_clz(lpr);
+            const uint32_t lpr = row_lanes, lg = 31u - (uint32_t)__builtin_clz(lpr);
             const uint32_t rpi = 64u >> lg;                             // rows per step, at most 16
             const uint32_t sub_r = lane >> lg, l_r = lane & (lpr - 1u);
             const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
@@ -1133,7 +1169,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint64_t per = n_rows ? ((uint64_t)(n_rows - 1u) / n_waves / rpi + 1u) * rpi : 0u;
             const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
-            float *const stash = short_sums + wv * 192u;                // [3][64]
             // where this lane's units lie in a row does not change from row to row
             bool in_row[U];
             int64_t unit_off[U];
@@ -1165,18 +1200,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     v[k] = *(global_unit_t *)ptr;
                 }
             };
-            auto flush = [&](uint64_t from, uint64_t upto) {    // totals of rows [from, upto), at most 64
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                if (from + lane < upto) {
-                    uint64_t o = off_sum + (from + lane) * 4u;
-                    if (a.summary_mask & 1u) { ring_store<float>(w, o, sqrtf(stash[lane])); o += sum_arr; }
-                    if (a.summary_mask & 2u) { ring_store<float>(w, o, stash[64u + lane] / (float)a.row_elems); o += sum_arr; }
-                    if (a.summary_mask & 4u)
-                        ring_store<float>(w, o, am_value(__float_as_uint(stash[128u + lane]), a.src_dtype));
-                }
-                __builtin_amdgcn_wave_barrier();
-            };
             auto process = [&](const unit_t (&v)[U], uint64_t g0) {
                 const uint64_t g = g0 + sub_r;
                 if constexpr (OUT != OUT_NONE) {
@@ -1190,7 +1213,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 unit_t sv[U];
 #pragma unroll
                 for (uint32_t k = 0; k < U; k++) sv[k] = sum_part(v[k], l_r + k * lpr);
-                accum_units<ES_IN, VEC>(acc, sv, 15u, a.src_dtype);         // (what is not the row's was read as zeros)
+                accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);           // (what is not the row's was read as zeros)
                 const uint32_t at = (uint32_t)(g - r0) & 63u;
                 const bool last = l_r == lpr - 1u;
                 if (a.summary_mask & 1u) {
@@ -1206,8 +1229,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     if (last) stash[128u + at] = __uint_as_float(am);
                 }
                 const uint64_t done = g0 + rpi - r0;
-                if ((done & 63u) == 0u) flush(r0 + done - 64u, g0 + rpi < r1 ? g0 + rpi : r1);
-                else if (g0 + rpi >= r1) flush(r0 + (done & ~63ull), r1);
+                if ((done & 63u) == 0u) flush_totals(r0 + done - 64u, g0 + rpi < r1 ? g0 + rpi : r1);
+                else if (g0 + rpi >= r1) flush_totals(r0 + (done & ~63ull), r1);
             };
             if (r0 < r1) {
                 unit_t va[U], vb[U];
@@ -1232,31 +1255,137 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 }
                 if (n_bad) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
             }
+        } else if constexpr (SUMM == SUMM_WAVE) {
+            // ---- summaries, a wavefront per row: where a launch has rows enough to fill the GPU that way, a row costs no
+            //      barrier and a workgroup lives for four rows or more instead of one, so its prologue weighs less.
+            //      The sums are taken in the order in which a workgroup takes them (the decode-shaped kernel, and
+            //      the path below): the row's lanes in parts of 64, each lane's units four at a time, then the lanes
+            //      of a part, then the (at most four) parts.  A step is one part's next four units per lane; its loads
+            //      are issued before the step in front of it is worked on.
+            //      Bound: HBM reads.  80 x 256 rows of 512 units, statistics only: 64 -> 35 us
+            //      (4.8 TB/s); plan_grid() has more figures, and says where the line lies.
+            const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
+            const uint32_t n_waves = gridDim.x * (kThreads / 64u);
+            const uint64_t per = n_rows ? (uint64_t)(n_rows - 1u) / n_waves + 1u : 0u;
+            const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
+            const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
+            const uint32_t parts = row_lanes >> 6, passes = cpr;
+            auto wave_unit = [&](uint32_t part, uint32_t pass, uint32_t t) { return pass * CH + part * 64u + lane + t * row_lanes; };
+            const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
+            struct Step { uint64_t g; uint32_t part, pass; RowRef ref; };
+            uint32_t n_bad = 0, hint = 0;
+            auto begin = [&](uint64_t g) -> RowTok { return locate_begin((uint32_t)(g < r1 ? g : r1 - 1u), hint); };
+            auto end = [&](const RowTok &k, uint64_t g) -> RowRef {
+                RowRef ref = locate_end(k);
+                n_bad += g < r1 && !ref.ok ? 1u : 0u;
+                return ref;
+            };
+            // a lane with nothing to load reads zeros
+            auto load = [&](const Step &s, unit_t (&v)[U]) {
+                const bool ok = s.g < r1 && s.ref.ok;
+#pragma unroll
+                for (uint32_t t = 0; t < U; t++) {
+                    const uint32_t c = wave_unit(s.part, s.pass, t);
+                    const uint8_t *ptr = ok && c < a.units_per_row ? unit_ptr(s.ref, c) : zeros;
+                    v[t] = *(global_unit_t *)ptr;
+                }
+            };
+            Accum acc = {0.f, 0.f, 0u};
+            float ss[2] = {0.f, 0.f}, sm[2] = {0.f, 0.f};      // of parts 0 and 1; of the last part, or of 2 and 3
+            auto process = [&](const Step &s, const unit_t (&v)[U]) {
+                unit_t sv[U];
+#pragma unroll
+                for (uint32_t t = 0; t < U; t++) {
+                    const uint32_t c = wave_unit(s.part, s.pass, t);
+                    if constexpr (OUT != OUT_NONE) {
+                        Accum none = {0.f, 0.f, 0u};
+                        if (c < a.units_per_row)
+                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(s.g, c), v[t], a.src_dtype, none);
+                    }
+                    sv[t] = sum_part(v[t], c);
+                }
+                accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);
+                if (s.pass + 1u < passes) return;
+                if (a.summary_mask & 1u) {
+                    float r = wave_sum(acc.ss);
+                    if (s.part & 1u) r = ss[1] + r;
+                    if (s.part < 2u) ss[0] = r;
+                    ss[1] = r;
+                }
+                if (a.summary_mask & 2u) {
+                    float r = wave_sum(acc.s);
+                    if (s.part & 1u) r = sm[1] + r;
+                    if (s.part < 2u) sm[0] = r;
+                    sm[1] = r;
+                }
+                acc.ss = acc.s = 0.f;
+                if (s.part + 1u < parts) return;
+                const uint32_t at = (uint32_t)(s.g - r0) & 63u;         // the row is complete
+                const uint32_t am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
+                const bool both = parts > 2u;
+                if (lane == 0) {
+                    stash[at] = both ? ss[0] + ss[1] : ss[0];
+                    stash[64u + at] = both ? sm[0] + sm[1] : sm[0];
+                    stash[128u + at] = __uint_as_float(am);
+                }
+                acc = Accum{0.f, 0.f, 0u};
+                if (at == 63u || s.g + 1u >= r1) flush_totals(s.g - at, s.g + 1u);
+            };
+            if (r0 < r1) {
+                unit_t va[U], vb[U];
+                RowTok ask = begin(r0 + 1u);
+                auto next = [&](const Step &s) -> Step {        // (behind the last row: steps that read zeros)
+                    Step n = s;
+                    if (++n.pass < passes) return n;
+                    n.pass = 0;
+                    if (++n.part < parts) return n;
+                    n.part = 0;
+                    n.g++;
+                    n.ref = end(ask, n.g);
+                    ask = begin(n.g + 1u);
+                    return n;
+                };
+                Step s = {r0, 0u, 0u, pre_ref};
+                if (pre) {
+                    n_bad += pre_ref.ok ? 0u : 1u;
+#pragma unroll
+                    for (uint32_t k = 0; k < U; k++) va[k] = pre_v[k];
+                } else {
+                    uint32_t first = 0;
+                    s.ref = end(locate_begin((uint32_t)r0, first), r0);
+                    load(s, va);
+                }
+                for (;;) {
+                    Step n = next(s);
+                    load(n, vb);
+                    process(s, va);
+                    if (n.g >= r1) break;
+                    s = next(n);
+                    load(s, va);
+                    process(n, vb);
+                    if (s.g >= r1) break;
+                }
+                if (n_bad && lane == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
+            }
         } else {
-            // ---- row-wise pass with summaries: a workgroup (or a wavefront) per row.  A step is
-            //      4 units per lane of one row; rows longer than that take several steps.  Steps
-            //      are software pipelined (the next step's loads are issued before this step is
-            //      converted, stored and accumulated), across row boundaries too.
+            // ---- summaries, a workgroup per row: a step is 4 units per lane of one row; rows longer than
+            //      that take several steps.  Steps are software pipelined (the next step's loads are issued before
+            //      this step is converted, stored and accumulated), across row boundaries too.
             float *red = reinterpret_cast<float *>(lds + m.red);
-            const uint32_t spr = (a.units_per_row + gsz * U - 1u) / (gsz * U);     // steps per row
-            const uint64_t row_stride_g = (uint64_t)gridDim.x * rpw;
-            // a step = (g0: first row of the workgroup's current group, pass)
-            auto fetch = [&](uint64_t st_g0, uint32_t st_pass, RowRef &ref, unit_t (&v)[U]) {
-                const uint64_t g = st_g0 + sub;
-                const bool row_live = g < n_rows;
-                if (row_live && st_pass == 0) {
+            auto fetch = [&](uint64_t g, uint32_t pass, RowRef &ref, unit_t (&v)[U]) {
+                if (pass == 0) {
                     ref = locate((uint32_t)g);
-                    if (!ref.ok && l == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
+                    if (!ref.ok && tid == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
                 }
 #pragma unroll
                 for (uint32_t k = 0; k < U; k++) {
-                    const uint32_t c = l + (st_pass * U + k) * gsz;
-                    v[k] = load_unit(ref, c, row_live && ref.ok != 0 && c < a.units_per_row);
+                    const uint32_t c = tid + (pass * U + k) * row_lanes;
+                    v[k] = load_unit(ref, c, ref.ok != 0 && tid < row_lanes && c < a.units_per_row);
                 }
             };
-            uint64_t cur_g0 = (uint64_t)blockIdx.x * rpw;
-            uint32_t cur_pass = 0;
-            if (cur_g0 < n_rows) {
+            uint64_t g = blockIdx.x;
+            uint32_t pass = 0;
+            if (g < n_rows) {
                 RowRef ref = {nullptr, 0};
                 unit_t v[U];
                 if (pre) {
@@ -1264,56 +1393,46 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++) v[k] = pre_v[k];
                     // (fetch() counts the rows it locates; this one was located up front)
-                    if (!ref.ok && l == 0 && cur_g0 + sub < n_rows) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
+                    if (!ref.ok && tid == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
                 } else {
-                    fetch(cur_g0, cur_pass, ref, v);
+                    fetch(g, pass, ref, v);
                 }
                 Accum acc = {0.f, 0.f, 0u};
                 for (;;) {
-                    uint64_t nxt_g0 = cur_g0;
-                    uint32_t nxt_pass = cur_pass + 1u;
-                    if (nxt_pass == spr) { nxt_pass = 0; nxt_g0 += row_stride_g; }
-                    const bool more = nxt_g0 < n_rows;
+                    uint64_t nxt_g = g;
+                    uint32_t nxt_pass = pass + 1u;
+                    if (nxt_pass == cpr) { nxt_pass = 0; nxt_g += gridDim.x; }
+                    const bool more = nxt_g < n_rows;
                     RowRef ref_n = ref;             // a later pass of the same row keeps the row
                     unit_t v_n[U];
-                    if (more) fetch(nxt_g0, nxt_pass, ref_n, v_n);
-                    const uint64_t g = cur_g0 + sub;
-                    const bool active = g < n_rows;
-                    if (active) {
-                        Accum none = {0.f, 0.f, 0u};
-                        uint32_t have = 0;
-                        unit_t sv[U];
+                    if (more) fetch(nxt_g, nxt_pass, ref_n, v_n);
+                    Accum none = {0.f, 0.f, 0u};
+                    unit_t sv[U];
 #pragma unroll
-                        for (uint32_t k = 0; k < U; k++) {
-                            const uint32_t c = l + (cur_pass * U + k) * gsz;
-                            const bool in = c < a.units_per_row;
-                            have |= in && ref.ok != 0 ? 1u << k : 0u;
-                            if (OUT != OUT_NONE && in)
-                                emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, c), zero_unless(ref.ok != 0, v[k]),
-                                                                         a.src_dtype, none);
-                            sv[k] = sum_part(v[k], c);
-                        }
-                        accum_units<ES_IN, VEC>(acc, sv, have, a.src_dtype);
+                    for (uint32_t k = 0; k < U; k++) {
+                        const uint32_t c = tid + (pass * U + k) * row_lanes;
+                        if (OUT != OUT_NONE && tid < row_lanes && c < a.units_per_row)
+                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, c), v[k], a.src_dtype, none);
+                        sv[k] = sum_part(v[k], c);
                     }
-                    if (cur_pass == spr - 1u) {     // the row is complete: reduce and store its summaries
+                    accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);
+                    if (pass == cpr - 1u) {         // the row is complete: reduce and store its summaries
                         acc.ss = wave_sum(acc.ss);
                         acc.s = wave_sum(acc.s);
                         uint32_t am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
-                        if (rpw == 1u) {
-                            lds_barrier();        // the previous row's readers are done with red[]
-                            if (lane == 0) {
-                                red[wave] = acc.ss;
-                                red[4 + wave] = acc.s;
-                                reinterpret_cast<uint32_t *>(red)[8 + wave] = am;
-                            }
-                            lds_barrier();
-                            acc.ss = (red[0] + red[1]) + (red[2] + red[3]);
-                            acc.s = (red[4] + red[5]) + (red[6] + red[7]);
-                            const uint32_t *ra = reinterpret_cast<const uint32_t *>(red) + 8;
-                            const uint32_t m01 = ra[0] > ra[1] ? ra[0] : ra[1], m23 = ra[2] > ra[3] ? ra[2] : ra[3];
-                            am = m01 > m23 ? m01 : m23;
+                        lds_barrier();        // the previous row's readers are done with red[]
+                        if (lane == 0) {
+                            red[wave] = acc.ss;
+                            red[4 + wave] = acc.s;
+                            reinterpret_cast<uint32_t *>(red)[8 + wave] = am;
                         }
-                        if (active && l == 0) {
+                        lds_barrier();
+                        acc.ss = (red[0] + red[1]) + (red[2] + red[3]);
+                        acc.s = (red[4] + red[5]) + (red[6] + red[7]);
+                        const uint32_t *ra = reinterpret_cast<const uint32_t *>(red) + 8;
+                        const uint32_t m01 = ra[0] > ra[1] ? ra[0] : ra[1], m23 = ra[2] > ra[3] ? ra[2] : ra[3];
+                        am = m01 > m23 ? m01 : m23;
+                        if (tid == 0) {
                             uint64_t o = off_sum + g * 4u;
                             if (a.summary_mask & 1u) { ring_store<float>(w, o, sqrtf(acc.ss)); o += sum_arr; }
                             if (a.summary_mask & 2u) { ring_store<float>(w, o, acc.s / (float)a.row_elems); o += sum_arr; }
@@ -1322,8 +1441,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                         acc = Accum{0.f, 0.f, 0u};
                     }
                     if (!more) break;
-                    cur_g0 = nxt_g0;
-                    cur_pass = nxt_pass;
+                    g = nxt_g;
+                    pass = nxt_pass;
                     ref = ref_n;
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++) v[k] = v_n[k];
@@ -1373,8 +1492,8 @@ struct DecodeArgs {
     const uint8_t *keep_mask;       // keep vector (MASK variants): request r is captured iff keep_mask[r] != 0
     uint32_t n_wg_rows;             // row workgroups = rows listed (= n_reqs unless requests list several rows)
     uint32_t unit_stride;           // lane l < unit_stride takes units l, l + unit_stride, ...: all lanes of the
-                                    // workgroup, or as many as the general kernel gives a short row with summaries
-                                    // (the sums are then taken in the same order there and here)
+                                    // workgroup, or with summaries the general kernel's row_lanes (the sums are
+                                    // then taken in the same order there and here)
     uint64_t spare[6];
 };
 static_assert(sizeof(DecodeArgs) == 256, "four lines");
@@ -1395,15 +1514,6 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
     touch_argument_lines(a, src, point_id);
-    global_uint4 *req_table = (global_uint4 *)a.req_table;
-    global_u32 *rows = (global_u32 *)a.rows;
-    if constexpr (INTO)
-        if (b.n_words) {
-            req_table = inline_table(sizeof(DecodeArgs));
-            // (the row of every request, or of every listed row behind those, unless the caller gave indexes)
-            if (!(a.flags & kDecIndexed))
-                rows = (global_u32 *)(req_table + a.n_reqs) + (a.flags & kDecRowMap ? a.n_reqs : 0u);
-        }
     constexpr uint32_t U = 4;
     constexpr uint32_t NB_OUT = out_unit_bytes<2, 8, OUT>();
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -1429,19 +1539,38 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if (!meta_wg) {
         const uint32_t g = blockIdx.x;
         // the usual decode layout (request i in row first + i) saves the dependent trip to the table
-        const int64_t row = (a.flags & kDecConsecutive) ? (int64_t)a.row_first + g
-                            : (a.flags & kDecIndexed) ? (int64_t)(int32_t)rows[g] : (int64_t)rows[g];
+        int64_t row;
+        if (a.flags & kDecConsecutive) {
+            row = (int64_t)a.row_first + g;
+        } else {
+            bool in_args = false;
+            uint32_t at = 0;
+            if constexpr (INTO) {       // the row of every request, or of every listed row behind those
+                in_args = b.n_words && !(a.flags & kDecIndexed);
+                if (in_args) at = inline_table_uniform(sizeof(DecodeArgs))[(a.flags & kDecRowMap ? 5u : 4u) * a.n_reqs + g];
+            }
+            // (the same in every lane, and said so here: the wait for it then stays on this branch, and the common case
+            // above does not wait for the control words before it loads its row)
+            if (!in_args) at = (uint32_t)__builtin_amdgcn_readfirstlane(a.rows[g]);
+            row = a.flags & kDecIndexed ? (int64_t)(int32_t)at : (int64_t)at;
+        }
         ok = row >= 0 && row < (int64_t)a.n_src_rows;
         const uint8_t *base = src + (ok ? row : 0) * a.row_stride_b;
 #pragma unroll
         for (uint32_t k = 0; k < U; k++) v[k] = u32x4{0u, 0u, 0u, 0u};
         if (ok) {
-            // straight-line loads: lanes past the end of the row fetch its first unit again and
-            // ignore it (a load under its own condition makes the compiler wait between loads)
+            // straight-line loads: lanes past the end of the row fetch zeros, or (where nothing is summed) its first
+            // unit again and ignore it (a load under its own condition makes the compiler wait between loads)
 #pragma unroll
             for (uint32_t k = 0; k < U; k++) {
                 const uint32_t c = tid + k * ustr;
-                v[k] = *reinterpret_cast<const u32x4 *>(base + (uint64_t)(c < a.units_per_row ? c : 0u) * 16u);
+                if constexpr (SUMM) {
+                    const uint8_t *p = tid < ustr && c < a.units_per_row ? base + (uint64_t)c * 16u
+                                                                         : reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
+                    v[k] = *(__attribute__((address_space(1))) const u32x4 *)p;
+                } else {
+                    v[k] = *reinterpret_cast<const u32x4 *>(base + (uint64_t)(c < a.units_per_row ? c : 0u) * 16u);
+                }
             }
         }
     }
@@ -1483,10 +1612,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if constexpr (SUMM) {
         Accum acc = {0.f, 0.f, 0u};
         if (!meta_wg) {
-            uint32_t have = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < U; k++) have |= tid < ustr && tid + k * ustr < a.units_per_row ? 1u << k : 0u;
-            accum_units<2, 8>(acc, v, have, a.hdr7 & 0xFFu);
+            accum_units<2, 8>(acc, v, a.hdr7 & 0xFFu);
             acc.ss = wave_sum(acc.ss);
             acc.s = wave_sum(acc.s);
             const uint32_t am = wave_max_u32(fold_am<2, 8>(acc.am));
@@ -1590,7 +1716,16 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
         for (uint32_t r = tid; r < tab_slots; r += kThreads) {
             u32x4 tv = {0u, 0u, 0u, 0u};
             if (r < a.n_reqs) {
-                tv = *(__attribute__((address_space(1))) const u32x4 *)(req_table + r);
+                bool have = false;
+                if constexpr (INTO)
+                    if (b.n_words) {
+                        tv = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(DecodeArgs)) + 4u * r);
+                        have = true;
+                    }
+                if (!have) {
+                    const uint4 e = a.req_table[r];
+                    tv.x = e.x; tv.y = e.y; tv.z = e.z; tv.w = e.w;
+                }
                 if constexpr (MASK) tv.w = (uint32_t)((kept_bits[(r >> 6) & 15u] >> (r & 63u)) & 1ull);
             }
             ring_store<u32x4>(w, 64u + 16ull * r, tv);
@@ -1714,12 +1849,21 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
 {
     const dim3 g(grid, a.n_batch);
     const CaptureKernelArgs &k = a;
-    if (a.summary_mask && a.lanes_per_row)
+    if (VEC == 1 && a.units_per_row >= kThreads) return hipErrorInvalidValue;   // rows go by elements only if they are short
+    if (a.summary_mask && a.row_lanes <= 64u) {
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
-    else if (a.summary_mask)
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
-    else
+    } else if (a.summary_mask) {
+        if constexpr (VEC > 1) {
+            if (a.wave_rows)
+                DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_WAVE, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
+            else
+                DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_ROWS, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
+        } else {
+            return hipErrorInvalidValue;
+        }
+    } else {
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
+    }
     return hipGetLastError();
 }
 
@@ -1779,7 +1923,7 @@ static hipError_t launch_decode_any(const CaptureArgs &a, const SRC &b, hipStrea
     d.row_stride_b = a.row_stride_b;
     d.rows = a.row_index ? a.row_index : reinterpret_cast<const int32_t *>(a.row_map ? a.row_map : a.row0);
     d.n_wg_rows = a.hdr[9];         // rows listed
-    d.unit_stride = a.lanes_per_row ? a.lanes_per_row : kThreads;
+    d.unit_stride = a.row_lanes ? a.row_lanes : kThreads;
     d.ring = a.ring;
     d.cap = a.cap;
     d.ctrl = a.ctrl;
