@@ -1415,11 +1415,15 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                             emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, c), v[k], a.src_dtype, none);
                         sv[k] = sum_part(v[k], c);
                     }
-                    accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);
+                    const bool mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)tid) < row_lanes;
+                    if (mine) accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);
                     if (pass == cpr - 1u) {         // the row is complete: reduce and store its summaries
-                        acc.ss = wave_sum(acc.ss);
-                        acc.s = wave_sum(acc.s);
-                        uint32_t am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
+                        uint32_t am = 0;
+                        if (mine) {
+                            acc.ss = wave_sum(acc.ss);
+                            acc.s = wave_sum(acc.s);
+                            am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
+                        }
                         lds_barrier();        // the previous row's readers are done with red[]
                         if (lane == 0) {
                             red[wave] = acc.ss;
@@ -1612,10 +1616,15 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if constexpr (SUMM) {
         Accum acc = {0.f, 0.f, 0u};
         if (!meta_wg) {
-            accum_units<2, 8>(acc, v, a.hdr7 & 0xFFu);
-            acc.ss = wave_sum(acc.ss);
-            acc.s = wave_sum(acc.s);
-            const uint32_t am = wave_max_u32(fold_am<2, 8>(acc.am));
+            // (wavefronts without a part of the row have nothing to add, and with eight of them on a SIMD their
+            // vector instructions would be the others' time)
+            uint32_t am = 0;
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)tid) < ustr) {
+                accum_units<2, 8>(acc, v, a.hdr7 & 0xFFu);
+                if (a.summary_mask & 1u) acc.ss = wave_sum(acc.ss);
+                if (a.summary_mask & 2u) acc.s = wave_sum(acc.s);
+                if (a.summary_mask & 4u) am = wave_max_u32(fold_am<2, 8>(acc.am));
+            }
             float *red = reinterpret_cast<float *>(sh + 8);
             if (lane == 0) {
                 red[wave] = acc.ss;
