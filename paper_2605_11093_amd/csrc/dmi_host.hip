@@ -38,13 +38,13 @@ void atomic_max(std::atomic<uint64_t> &a, uint64_t v)
 }
 
 // Record an event behind everything launched so far (no-op if that is already covered, unless
-// asked for all the same); *no = the number of the probe that covers it.
+// asked for all the same); *no = the number of the probe that covers it, *on = the stream it is on.
 // If the host cannot tell what those launches added (drop-newest, keep vectors), the
 // newest launch's commit slot is fetched into the pinned mirror in front of the event.
 // Both go onto the producer's own stream: a launch on a second hardware queue that waits
 // for an event of this one slows every dispatch here by a microsecond or so while it
 // waits, far more than a small launch every sixteenth capture costs in line.
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no)
+dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no, hipStream_t *on)
 {
     std::lock_guard<std::mutex> lk(r->pmu);
     const uint64_t launched = r->next_seq.load(std::memory_order_acquire);
@@ -61,6 +61,7 @@ dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no)
     HIP_TRY(hipEventRecord(ev, us));
     r->probes.push_back({ev, launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made});
     if (no) *no = r->probes_made;
+    if (on) *on = us;
     r->window = Delta();
     r->window_exact = true;
     r->probed_upto = launched;
@@ -248,13 +249,22 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     }
     const uint64_t from = r->drain_issued, n = target - from;
     if (n == 0 || n > kFlushKernelBytes || n > r->host_cap - (from - r->released)) return DMI_OK;
+    // The stream, asked for only now: a launch counted above has stored its own there before it was counted.  Not
+    // while that stream is being captured: the copy would end up in the graph.
+    hipStream_t us = (hipStream_t)r->last_stream.load(std::memory_order_acquire);
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (r->quiet.load(std::memory_order_acquire) || hipStreamIsCapturing(us, &cs) != hipSuccess ||
+        cs != hipStreamCaptureStatusNone)
+        return DMI_OK;
     atomic_max(r->dev_high, n);
     const uint64_t groups = (n / 16u + kThreads - 1u) / kThreads;
     HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n,
-                                (uint32_t)(groups < 64u ? groups : 64u),
-                                (hipStream_t)r->last_stream.load(std::memory_order_acquire)));
+                                (uint32_t)(groups < 64u ? groups : 64u), us));
     uint64_t no = 0;
-    if ((st = record_probe(r, true, &no)) != DMI_OK) return st;
+    hipStream_t on = us;
+    if ((st = record_probe(r, true, &no, &on)) != DMI_OK) return st;
+    // a producer that has moved on to another stream in the meantime: the probe there does not stand behind the copy
+    if (on != us) HIP_TRY(hipStreamSynchronize(us));
     r->direct_probe = no;
     r->drain_issued = target;
     r->drain_issued_records = records;

@@ -293,7 +293,7 @@ namespace dmi {
 namespace host {
 
 // dmi_host.hip
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr);
+dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr, hipStream_t *on = nullptr);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub);

@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "dmi.h"
@@ -39,8 +40,8 @@ static void scenario(const char *name, uint32_t policy, uint32_t flags, uint64_t
     CHECK(dmi_ring_create(&cfg, &ring) == DMI_OK);
     dmi_policy_t pol = {policy, 1, 0};
     CHECK(dmi_set_policy(ring, &pol) == DMI_OK);
-    hipStream_t stream;
-    CHECK(hipStreamCreate(&stream) == hipSuccess);
+    hipStream_t stream, second;         // the producer changes over from one to the other now and then
+    CHECK(hipStreamCreate(&stream) == hipSuccess && hipStreamCreate(&second) == hipSuccess);
     std::vector<uint16_t> data(64 * 512, 0x3F80);
     dmi_tensor_t t = {data.data(), DMI_DTYPE_BF16, {64, 512}, {512, 1}};
     std::vector<dmi_req_sel_t> one(16);
@@ -85,6 +86,12 @@ static void scenario(const char *name, uint32_t policy, uint32_t flags, uint64_t
             rc = dmi_observe(ring, 1, &t, &sel, &raw, (uint64_t)it, stream);
         CHECK(rc == DMI_OK);
         if (it % 5 == 0) std::this_thread::sleep_for(std::chrono::microseconds(100));
+        if (it % 23 == 22) {            // (the stand-in has no waits between streams: the captures so far have run)
+            std::atomic<bool> reached{false};
+            fake_enqueue(stream, [&] { reached.store(true); });
+            while (!reached.load()) std::this_thread::yield();
+            std::swap(stream, second);
+        }
     }
     producer_done.store(true);
     flusher.join();
@@ -100,6 +107,37 @@ static void scenario(const char *name, uint32_t policy, uint32_t flags, uint64_t
     CHECK(seen.load() == s.captured_records && seen_bytes.load() == s.captured_bytes);
     stop.store(true);
     consumer.join();
+    CHECK(hipStreamSynchronize(stream) == hipSuccess && hipStreamSynchronize(second) == hipSuccess);
+    CHECK(dmi_ring_destroy(ring) == DMI_OK);
+    CHECK(hipStreamDestroy(stream) == hipSuccess && hipStreamDestroy(second) == hipSuccess);
+}
+
+// Sixteen observes have put their probe behind them; a flush while their stream is being captured adds
+// nothing to the capture and delivers them all the same.
+static void scenario_capture()
+{
+    fprintf(stderr, "scenario flush while the stream is captured\n");
+    dmi_ring_config_t cfg;
+    memset(&cfg, 0, sizeof cfg);
+    cfg.device_ring_bytes = cfg.host_ring_bytes = 1u << 20;
+    dmi_ring_t *ring = nullptr;
+    CHECK(dmi_ring_create(&cfg, &ring) == DMI_OK);
+    hipStream_t stream;
+    CHECK(hipStreamCreate(&stream) == hipSuccess);
+    std::vector<uint16_t> data(64 * 512, 0x3F80);
+    dmi_tensor_t t = {data.data(), DMI_DTYPE_BF16, {64, 512}, {512, 1}};
+    const dmi_req_sel_t one = {1, 2, 0, 1, 1};
+    const dmi_selection_t sel = {1, &one, nullptr, nullptr};
+    const dmi_transform_t raw = {DMI_DTYPE_BF16, 0};
+    for (int i = 0; i < 16; i++) CHECK(dmi_observe(ring, 1, &t, &sel, &raw, 0, stream) == DMI_OK);
+    fake_begin_capture(stream);
+    uint64_t moved = 0;
+    CHECK(dmi_drain(ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK);
+    CHECK(fake_end_capture(stream).empty());
+    CHECK(moved == 16 * dmi_record_bytes(1, 1, 512, DMI_DTYPE_BF16, 0));
+    dmi_record_view_t v[32];
+    uint32_t n = 0;
+    CHECK(dmi_poll_host(ring, v, 32, &n) == DMI_OK && n == 16);
     CHECK(dmi_ring_destroy(ring) == DMI_OK);
     CHECK(hipStreamDestroy(stream) == hipSuccess);
 }
@@ -114,6 +152,7 @@ int main(int argc, char **argv)
     scenario("block, flushes that give up waiting", DMI_POLICY_BLOCK, 0, 1u << 20, 1u << 20, 1, n);
     scenario("drop-newest", DMI_POLICY_DROP_NEWEST, 0, 5 * rb, 6 * rb, 2000, n);
     scenario("block, copy engine by name", DMI_POLICY_BLOCK, DMI_DRAIN_COPY_ENGINE, 1u << 20, 2u << 20, 2000, n);
+    scenario_capture();
     fprintf(stderr, "all scenarios passed\n");
     return 0;
 }
