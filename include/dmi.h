@@ -298,7 +298,9 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
  * every observe issued before the call has arrived in the host ring and can be polled,
  * whoever issued its copy (this call or the library's drain thread); DMI_ERR_AGAIN if
  * the host ring filled up before everything was moved (release and call again)
- * or the observes did not commit within block_timeout_ms.
+ * or the observes did not commit within block_timeout_ms.  A drain without DMI_DRAIN_FLUSH and
+ * DMI_DRAIN_NONBLOCK returns once the copies issued so far have ended, DMI_ERR_AGAIN if one that a
+ * flush which gave up had left behind the captures did not within block_timeout_ms.
  * A flush of at most 6 MiB, on a ring without a drain thread and not created with DMI_DRAIN_COPY_ENGINE,
  * does its copy on the stream last passed to dmi_observe, behind the captures. */
 dmi_status_t dmi_drain(dmi_ring_t *ring, uint32_t flags, uint64_t *bytes_moved);

@@ -277,7 +277,8 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
 }
 
 // A drain that waits does so for a flush's span on the producer's stream too, as it does for copies
-// issued earlier (another thread's flush, or one that gave up waiting).
+// issued earlier (another thread's flush, or one that gave up waiting): at most block_timeout_ms, because
+// the producer's stream may be busy with the caller's own work.
 static dmi_status_t wait_for_direct(dmi_ring *r)
 {
     const uint64_t t0 = now_ns();
@@ -287,7 +288,8 @@ static dmi_status_t wait_for_direct(dmi_ring *r)
             dmi_status_t st = reap(r, false);
             if (st != DMI_OK || !r->direct_probe) return st;
         }
-        if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull) return DMI_OK;
+        if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
+            return fail(DMI_ERR_AGAIN, "the copy of an earlier flush did not finish within %u ms", r->block_timeout_ms);
         pause_since(t0);
         dmi_status_t st = advance_commits(r, false);
         if (st != DMI_OK) return st;

@@ -1,0 +1,125 @@
+// What a flush of a ring without a drain thread may and may not do, one scenario per rule, on the CPU
+// stand-in runtime -- TEST INFRASTRUCTURE ONLY.  A gate (a task that waits to be let go) stands for
+// work of the caller's that keeps a stream busy, so every scenario has one outcome.  Built and run, one
+// scenario per process, by tests/test_flush_rules.py.
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <chrono>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "dmi.h"
+
+#define CHECK(cond)                                                                          \
+    do {                                                                                     \
+        if (!(cond)) {                                                                       \
+            fprintf(stderr, "%s:%d: CHECK failed: %s (last error: %s)\n", __FILE__, __LINE__, #cond, \
+                    dmi_last_error());                                                       \
+            exit(3);                                                                         \
+        }                                                                                    \
+    } while (0)
+
+namespace {
+
+constexpr uint32_t kWidth = 512;
+
+struct Bench {
+    dmi_ring_t *ring = nullptr;
+    hipStream_t stream = nullptr;
+    std::vector<uint16_t> data = std::vector<uint16_t>(64 * kWidth, 0x3F80);
+    std::atomic<bool> gate_open{true};
+
+    Bench(uint32_t flags, uint32_t timeout_ms, uint64_t dev = 1u << 20, uint64_t host = 1u << 20)
+    {
+        dmi_ring_config_t cfg;
+        memset(&cfg, 0, sizeof cfg);
+        cfg.device_ring_bytes = dev;
+        cfg.host_ring_bytes = host;
+        cfg.flags = flags;
+        cfg.max_reqs_per_observe = 64;
+        cfg.block_timeout_ms = timeout_ms;
+        CHECK(dmi_ring_create(&cfg, &ring) == DMI_OK);
+        CHECK(hipStreamCreate(&stream) == hipSuccess);
+    }
+    ~Bench()
+    {
+        open_gate();
+        CHECK(hipStreamSynchronize(stream) == hipSuccess);
+        CHECK(dmi_ring_destroy(ring) == DMI_OK);
+        CHECK(hipStreamDestroy(stream) == hipSuccess);
+    }
+    // everything enqueued from here on waits until open_gate()
+    void close_gate()
+    {
+        gate_open.store(false);
+        fake_enqueue(stream, [this] {
+            while (!gate_open.load()) std::this_thread::sleep_for(std::chrono::microseconds(20));
+        });
+    }
+    void open_gate() { gate_open.store(true); }
+    // one row of `width` elements per record
+    dmi_status_t observe(uint32_t n = 1, const uint8_t *keep = nullptr)
+    {
+        dmi_tensor_t t = {data.data(), DMI_DTYPE_BF16, {64, kWidth}, {kWidth, 1}};
+        const dmi_req_sel_t one = {1, 2, 0, 1, 1};
+        const dmi_selection_t sel = {1, &one, keep, nullptr};
+        const dmi_transform_t raw = {DMI_DTYPE_BF16, 0};
+        for (uint32_t i = 0; i < n; i++) {
+            const dmi_status_t rc = dmi_observe(ring, 1, &t, &sel, &raw, 0, stream);
+            if (rc != DMI_OK) return rc;
+        }
+        return DMI_OK;
+    }
+    uint32_t poll()
+    {
+        dmi_record_view_t v[128];
+        uint32_t n = 0;
+        CHECK(dmi_poll_host(ring, v, 128, &n) == DMI_OK);
+        return n;
+    }
+    static uint64_t record() { return dmi_record_bytes(1, 1, kWidth, DMI_DTYPE_BF16, 0); }
+};
+
+// A flush that gave up leaves its copy under way: a drain that waits says so, and does not say OK
+// before the copy is over.
+void waiting_drain_after_a_flush_that_gave_up()
+{
+    Bench b(0, 5);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    CHECK(dmi_drain(b.ring, 0, nullptr) == DMI_ERR_AGAIN);
+    CHECK(b.poll() == 0);
+    b.open_gate();
+    dmi_status_t rc = DMI_ERR_AGAIN;
+    for (int i = 0; rc == DMI_ERR_AGAIN && i < 1000; i++) rc = dmi_drain(b.ring, 0, nullptr);
+    CHECK(rc == DMI_OK && b.poll() == 1);
+}
+
+struct Scenario {
+    const char *name;
+    void (*run)();
+};
+const Scenario kScenarios[] = {
+    {"waiting_drain_after_a_flush_that_gave_up", waiting_drain_after_a_flush_that_gave_up},
+};
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string want = argc > 1 ? argv[1] : "";
+    for (const Scenario &s : kScenarios)
+        if (want == s.name) {
+            s.run();
+            fprintf(stderr, "passed\n");
+            return 0;
+        }
+    fprintf(stderr, "no scenario '%s'\n", want.c_str());
+    return 2;
+}

@@ -1,0 +1,34 @@
+"""Where the copy of a flush goes, and what drains and polls report while one is under way: the host
+runtime on the CPU stand-in (tests/cpu_runtime/), one scenario of flush_rules_driver.cpp per test."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CPU = os.path.join(ROOT, "tests", "cpu_runtime")
+CSRC = os.path.join(ROOT, "paper_2605_11093_amd", "csrc")
+
+SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up"]
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    exe = str(tmp_path_factory.mktemp("flush_rules") / "driver")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=address", "-pthread",
+           "-I", CPU, "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-o", exe]
+    for src in [os.path.join(CSRC, f) for f in ("dmi_host.hip", "dmi_step.hip", "dmi_exporter.hip")] + \
+            [os.path.join(CPU, f) for f in ("fake_hip.cpp", "cpu_kernels.cpp", "flush_rules_driver.cpp")]:
+        cmd += ["-x", "c++", src]
+    subprocess.check_call(cmd)
+    return exe
+
+
+@pytest.mark.parametrize("scenario", SCENARIOS)
+def test_flush(driver, scenario):
+    p = subprocess.run([driver, scenario], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=60,
+                       env=dict(os.environ, ASAN_OPTIONS="exitcode=67"))
+    assert p.returncode == 0, p.stdout.decode(errors="replace")[-4000:]
