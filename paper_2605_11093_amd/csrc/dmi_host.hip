@@ -1329,7 +1329,9 @@ dmi_status_t poll_host_impl(dmi_ring *r, dmi_record_view_t *out, uint32_t max, u
     // with the library's drain thread running, arrivals are noted by that thread; a HIP call
     // on the drain stream's events from here would queue up behind its blocking wait
     if (!(r->cfg.flags & DMI_BG_THREAD) && !r->quiet.load(std::memory_order_acquire)) {
-        dmi_status_t st = reap(r, false);
+        // (the end of a span on the producer's stream is seen by its probe, and only there; a consumer may do nothing but poll)
+        dmi_status_t st = r->direct_probe ? advance_commits(r, false) : DMI_OK;
+        if (st == DMI_OK) st = reap(r, false);
         if (st != DMI_OK) return st;
     }
     const uint64_t done = r->drain_done.load(std::memory_order_acquire);

@@ -101,12 +101,30 @@ void waiting_drain_after_a_flush_that_gave_up()
     CHECK(rc == DMI_OK && b.poll() == 1);
 }
 
+// A consumer that only polls sees the records of a flush that gave up, once their copy is over.
+void polling_alone_sees_a_flush_that_gave_up()
+{
+    Bench b(0, 5);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    CHECK(b.poll() == 0);
+    b.open_gate();
+    uint32_t seen = 0;
+    for (int i = 0; !seen && i < 4000; i++) {
+        std::this_thread::sleep_for(std::chrono::microseconds(500));
+        seen = b.poll();
+    }
+    CHECK(seen == 1);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
     {"waiting_drain_after_a_flush_that_gave_up", waiting_drain_after_a_flush_that_gave_up},
+    {"polling_alone_sees_a_flush_that_gave_up", polling_alone_sees_a_flush_that_gave_up},
 };
 
 }  // namespace
