@@ -77,8 +77,9 @@ enum { DMI_POLICY_BLOCK = 0, DMI_POLICY_DROP_NEWEST = 1 };
 /* ring flags */
 enum {
     DMI_DRAIN_COPY_ENGINE = 1,  /* drain with hipMemcpyAsync on a side stream (the default, except that without
-                                   this flag and without a drain thread a flush moves up to 6 MiB by a copy
-                                   kernel behind the captures, on the stream last passed to dmi_observe) */
+                                   this flag and without a drain thread a flush by the thread that observes
+                                   moves up to 6 MiB by a copy kernel behind the captures, on the stream last
+                                   passed to dmi_observe) */
     DMI_DRAIN_KERNEL = 2,       /* drain with a copy kernel writing pinned host memory */
     DMI_BG_THREAD = 4           /* the library runs its own drain thread (section 4.3) */
 };
@@ -201,7 +202,8 @@ typedef struct {
  * Besides the capture kernel the library puts small operations of its own on the stream
  * most recently passed here: an event every 16 launches or so, in best-effort mode (or with
  * keep vectors) also a one-workgroup launch that copies 64 bytes to pinned memory; dmi_drain
- * and the library's drain thread may add one when the producer has paused.  Do not capture
+ * and the library's drain thread may add one when the producer has paused.  A flush by the thread
+ * that observes may add the copy of up to 6 MiB to pinned memory (see dmi_drain).  Do not capture
  * that stream into a graph by hand while captures are outstanding: use dmi_step_t.
  * Keep the stream alive until dmi_drain(DMI_DRAIN_FLUSH) has returned DMI_OK (or the ring
  * is destroyed) after the last observe on it.
@@ -301,8 +303,9 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
  * or the observes did not commit within block_timeout_ms.  A drain without DMI_DRAIN_FLUSH and
  * DMI_DRAIN_NONBLOCK returns once the copies issued so far have ended, DMI_ERR_AGAIN if one that a
  * flush which gave up had left behind the captures did not within block_timeout_ms.
- * A flush of at most 6 MiB, on a ring without a drain thread and not created with DMI_DRAIN_COPY_ENGINE,
- * does its copy on the stream last passed to dmi_observe, behind the captures. */
+ * A flush of at most 6 MiB by the thread that observes, on a ring without a drain thread and not created with
+ * DMI_DRAIN_COPY_ENGINE, does its copy on the stream last passed to dmi_observe, behind the captures; a flush
+ * by another thread never does. */
 dmi_status_t dmi_drain(dmi_ring_t *ring, uint32_t flags, uint64_t *bytes_moved);
 
 /* A whole record in the host ring: [p0, p0+n0) then, iff it straddles the end of

@@ -37,14 +37,26 @@ void atomic_max(std::atomic<uint64_t> &a, uint64_t v)
     while (cur < v && !a.compare_exchange_weak(cur, v, std::memory_order_relaxed)) {}
 }
 
+const void *this_thread()
+{
+    static thread_local char here;
+    return &here;
+}
+
+void note_producer(dmi_ring *r, void *stream)
+{
+    r->producer.store(this_thread(), std::memory_order_relaxed);
+    r->last_stream.store(stream, std::memory_order_release);
+}
+
 // Record an event behind everything launched so far (no-op if that is already covered, unless
-// asked for all the same); *no = the number of the probe that covers it, *on = the stream it is on.
+// asked for all the same); *no = the number of the probe that covers it.
 // If the host cannot tell what those launches added (drop-newest, keep vectors), the
 // newest launch's commit slot is fetched into the pinned mirror in front of the event.
 // Both go onto the producer's own stream: a launch on a second hardware queue that waits
 // for an event of this one slows every dispatch here by a microsecond or so while it
 // waits, far more than a small launch every sixteenth capture costs in line.
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no, hipStream_t *on)
+dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no)
 {
     std::lock_guard<std::mutex> lk(r->pmu);
     const uint64_t launched = r->next_seq.load(std::memory_order_acquire);
@@ -61,7 +73,6 @@ dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no, hipSt
     HIP_TRY(hipEventRecord(ev, us));
     r->probes.push_back({ev, launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made});
     if (no) *no = r->probes_made;
-    if (on) *on = us;
     r->window = Delta();
     r->window_exact = true;
     r->probed_upto = launched;
@@ -209,12 +220,14 @@ dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full)
     return DMI_OK;
 }
 
-// Between two looks at something that the GPU is about to finish: at first only the processor is
-// offered to others (a sleep of 10 us takes some 60 here, longer than most of what a flush waits
-// for), then the thread sleeps.
-static void pause_since(uint64_t t0)
+// Between two looks at something that the GPU is about to finish.  In the producer's own thread at
+// first only the processor is offered to others (a sleep of 10 us takes some 60 here, longer than most of
+// what a flush waits for).  Any other thread sleeps: every look takes a lock that each observe takes too.  A
+// second thread that flushed back to back without sleeping took a producer's observe of 64 x 4096 from 3.2 us
+// (median; nine in ten below 5.4) to 4.8 (16.1).
+static void pause_since(const dmi_ring *r, uint64_t t0)
 {
-    if (now_ns() - t0 < 500000u) std::this_thread::yield();
+    if (r->producer.load(std::memory_order_relaxed) == this_thread() && now_ns() - t0 < 500000u) std::this_thread::yield();
     else std::this_thread::sleep_for(std::chrono::microseconds(10));
 }
 
@@ -224,13 +237,16 @@ static void pause_since(uint64_t t0)
 // Measured from a capture's launch to the end of the wait, drain kernel against event and copy engine:
 // 14.6 / 18.8 us for 17 KB, 25.0 / 29.9 for 0.6 MB, 52 / 56 for 2 MB, 100 / 107 for 4.7 MB, 178 / 174
 // for 8.4 MB: from some 6 MB on the copy engine's higher rate (57 against 53 GB/s) outweighs the wait.
-// Left to the copy engine: a ring whose creator asked for it by name; a ring with a drain thread
-// (it follows the commits and issues copies by itself at any time); sizes only the device knows (drops or
-// keep vectors decided there); a span the host ring has no room for as a whole, or behind copies still under way.
+// Left to the copy engine: a flush by any other thread than the producer's, which goes on launching its
+// model's kernels meanwhile and would find the copy in front of them on their stream; a ring whose creator
+// asked for the copy engine by name; a ring with a drain thread (it follows the commits and issues copies by
+// itself at any time); sizes only the device knows (drops or keep vectors decided there); a span the host ring
+// has no room for as a whole, or behind copies still under way.
 static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *issued)
 {
     *issued = false;
     if (r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) return DMI_OK;
+    if (r->producer.load(std::memory_order_relaxed) != this_thread()) return DMI_OK;
     std::lock_guard<std::mutex> lk(r->mu);
     dmi_status_t st = reap(r, false);
     if (st != DMI_OK) return st;
@@ -249,8 +265,7 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     }
     const uint64_t from = r->drain_issued, n = target - from;
     if (n == 0 || n > kFlushKernelBytes || n > r->host_cap - (from - r->released)) return DMI_OK;
-    // The stream, asked for only now: a launch counted above has stored its own there before it was counted.  Not
-    // while that stream is being captured: the copy would end up in the graph.
+    // Not while the stream is being captured: the copy would end up in the graph.
     hipStream_t us = (hipStream_t)r->last_stream.load(std::memory_order_acquire);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (r->quiet.load(std::memory_order_acquire) || hipStreamIsCapturing(us, &cs) != hipSuccess ||
@@ -261,10 +276,7 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n,
                                 (uint32_t)(groups < 64u ? groups : 64u), us));
     uint64_t no = 0;
-    hipStream_t on = us;
-    if ((st = record_probe(r, true, &no, &on)) != DMI_OK) return st;
-    // a producer that has moved on to another stream in the meantime: the probe there does not stand behind the copy
-    if (on != us) HIP_TRY(hipStreamSynchronize(us));
+    if ((st = record_probe(r, true, &no)) != DMI_OK) return st;     // (on that stream too: its producer is this thread)
     r->direct_probe = no;
     r->drain_issued = target;
     r->drain_issued_records = records;
@@ -290,7 +302,7 @@ static dmi_status_t wait_for_direct(dmi_ring *r)
         }
         if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
             return fail(DMI_ERR_AGAIN, "the copy of an earlier flush did not finish within %u ms", r->block_timeout_ms);
-        pause_since(t0);
+        pause_since(r, t0);
         dmi_status_t st = advance_commits(r, false);
         if (st != DMI_OK) return st;
     }
@@ -645,7 +657,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
     if (st != DMI_OK) return st;
     const uint64_t ub = pl.ub;
     const uint32_t mode = r->mode.load(std::memory_order_relaxed);
-    r->last_stream.store(hip_stream, std::memory_order_release);
+    note_producer(r, hip_stream);
     // a launch of several records lays them down one behind the other from one head: under the
     // completeness policy they must fit the ring together (the kernels rely on it), so a batch
     // that does not is issued in pieces, each waiting for its room as single observes would
@@ -1307,7 +1319,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
             return fail(DMI_ERR_AGAIN, target == UINT64_MAX ? "observes did not finish within %u ms"
                                                             : "the drain did not finish within %u ms",
                         r->block_timeout_ms);
-        pause_since(t0);
+        pause_since(r, t0);
     }
 }
 

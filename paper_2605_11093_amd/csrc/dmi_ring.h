@@ -178,6 +178,7 @@ struct dmi_ring {
     // producer side
     std::atomic<uint64_t> next_seq{0};                     // launches issued so far
     std::atomic<void *> last_stream{nullptr};
+    std::atomic<const void *> producer{nullptr};           // this_thread() of whoever passed it
     std::atomic<uint64_t> last_launch_ns{0};
     std::deque<std::pair<uint64_t, uint64_t>> inflight;    // (seq, upper bound of record bytes)
     uint64_t inflight_sum = 0;
@@ -293,7 +294,9 @@ namespace dmi {
 namespace host {
 
 // dmi_host.hip
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr, hipStream_t *on = nullptr);
+const void *this_thread();                                 // the calling thread: an address that it has to itself
+void note_producer(dmi_ring *r, void *stream);             // the calling thread observes on `stream`
+dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub);

@@ -337,7 +337,7 @@ dmi_status_t dmi_step_begin(dmi_step_t *st, uint64_t step_id, void *hip_stream)
     const uint32_t k = r->sample_k.load(std::memory_order_relaxed);
     const bool skip = step_id % k != r->sample_phase.load(std::memory_order_relaxed);
     dmi_status_t rc;
-    r->last_stream.store(hip_stream, std::memory_order_release);
+    note_producer(r, hip_stream);
     if (!skip && n) {
         if (mode == DMI_POLICY_BLOCK) {
             // the flush before the forward step: the whole step must be sure to fit
@@ -392,7 +392,7 @@ dmi_status_t dmi_step_end(dmi_step_t *st, void *hip_stream)
     r->step_open = false;
     r->chain_par = (uint32_t)st->nodes.size() & 1u;
     r->last_launch_ns.store(now_ns(), std::memory_order_relaxed);
-    r->last_stream.store(hip_stream, std::memory_order_release);
+    note_producer(r, hip_stream);
     if (st->skipped || !n) return DMI_OK;
     for (auto &nd : st->nodes) {
         r->inflight.emplace_back(st->seq_base + nd.first_rec + nd.n_batch - 1u, nd.pl.ub * nd.n_batch);

@@ -8,6 +8,9 @@
 // summarised here (this shares nothing with the oracle, and proves nothing about the kernels).
 #include "dmi_ring.h"
 
+#include <map>
+#include <mutex>
+
 namespace dmi {
 
 uint32_t capture_lds_bytes(uint32_t, bool, bool) { return 0; }
@@ -161,9 +164,16 @@ hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStr
     return hipSuccess;
 }
 
+static std::mutex g_drain_mu;
+static std::map<hipStream_t, unsigned> g_drain_launches;
+
 hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap,
                                uint64_t from, uint64_t nbytes, uint32_t, hipStream_t s)
 {
+    {
+        std::lock_guard<std::mutex> lk(g_drain_mu);
+        g_drain_launches[s]++;
+    }
     fake_enqueue(s, [=] {
         for (uint64_t i = 0; i < nbytes; i += 64u)
             memcpy(host_ring + (from + i) % host_cap, ring + (from + i) % cap, 64);
@@ -172,3 +182,9 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
 }
 
 }  // namespace dmi
+
+unsigned fake_drain_launches(hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(dmi::g_drain_mu);
+    return dmi::g_drain_launches[s];
+}

@@ -1,7 +1,7 @@
-// A ring without a drain thread, flushed from a thread of its own while the producer observes and a
-// consumer polls, on the CPU stand-in runtime -- TEST INFRASTRUCTURE ONLY.  Small flushes move
-// their bytes on the producer's stream, large ones and ones the host ring has no room for on the drain
-// stream; waiting and non-blocking drains come in between.  Built with -fsanitize=thread or
+// A ring without a drain thread, flushed from a thread of its own and now and then by the producer while it
+// observes and a consumer polls, on the CPU stand-in runtime -- TEST INFRASTRUCTURE ONLY.  The producer's
+// small flushes move their bytes on its stream, all others on the drain stream; waiting and non-blocking
+// drains come in between.  Built with -fsanitize=thread or
 // -fsanitize=address by tests/test_flush_behind_captures.py.
 #include <hip/hip_runtime.h>
 
@@ -85,6 +85,10 @@ static void scenario(const char *name, uint32_t policy, uint32_t flags, uint64_t
         for (int tries = 0; rc == DMI_ERR_AGAIN && tries < 1000000; tries++)
             rc = dmi_observe(ring, 1, &t, &sel, &raw, (uint64_t)it, stream);
         CHECK(rc == DMI_OK);
+        if (it % 7 == 3) {
+            rc = dmi_drain(ring, DMI_DRAIN_FLUSH, nullptr);
+            CHECK(rc == DMI_OK || rc == DMI_ERR_AGAIN);
+        }
         if (it % 5 == 0) std::this_thread::sleep_for(std::chrono::microseconds(100));
         if (it % 23 == 22) {            // (the stand-in has no waits between streams: the captures so far have run)
             std::atomic<bool> reached{false};

@@ -118,6 +118,18 @@ void polling_alone_sees_a_flush_that_gave_up()
     CHECK(seen == 1);
 }
 
+// A thread other than the producer's leaves the producer's stream alone: its copy goes to the drain stream.
+void other_threads_flushes_stay_off_the_producers_stream()
+{
+    Bench b(0, 2000);
+    CHECK(b.observe() == DMI_OK);
+    std::thread([&] { CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK); }).join();
+    CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 1);
+    CHECK(b.observe() == DMI_OK);           // the producer's own: behind the capture
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 1 && b.poll() == 1);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -125,6 +137,7 @@ struct Scenario {
 const Scenario kScenarios[] = {
     {"waiting_drain_after_a_flush_that_gave_up", waiting_drain_after_a_flush_that_gave_up},
     {"polling_alone_sees_a_flush_that_gave_up", polling_alone_sees_a_flush_that_gave_up},
+    {"other_threads_flushes_stay_off_the_producers_stream", other_threads_flushes_stay_off_the_producers_stream},
 };
 
 }  // namespace

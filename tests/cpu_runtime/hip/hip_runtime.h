@@ -64,3 +64,5 @@ std::vector<FakeTask> fake_end_capture(hipStream_t s);
 void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s);
 // each worker sleeps a random 0..max_us microseconds in front of every task (shakes interleavings)
 void fake_set_jitter_us(unsigned max_us);
+// how many drain kernels have been launched on `s` (cpu_kernels.cpp)
+unsigned fake_drain_launches(hipStream_t s);

@@ -10,7 +10,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CPU = os.path.join(ROOT, "tests", "cpu_runtime")
 CSRC = os.path.join(ROOT, "paper_2605_11093_amd", "csrc")
 
-SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_flush_that_gave_up"]
+SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_flush_that_gave_up",
+             "other_threads_flushes_stay_off_the_producers_stream"]
 
 
 @pytest.fixture(scope="module")
