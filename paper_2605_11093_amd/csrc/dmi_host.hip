@@ -241,7 +241,10 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
 // model's kernels meanwhile and would find the copy in front of them on their stream; a ring whose creator
 // asked for the copy engine by name; a ring with a drain thread (it follows the commits and issues copies by
 // itself at any time); sizes only the device knows (drops or keep vectors decided there); a span the host ring
-// has no room for as a whole, or behind copies still under way.
+// has no room for as a whole, or behind copies still under way.  And, whole, a span part of which has a
+// probe behind it already (every sixteenth launch puts one there, and the end of a replayed step) or is known to
+// be captured: those bytes need not wait for what the caller has put on the stream since, which the copy behind
+// it all would.  A launch without a probe gets one now, behind all that, so there the copy waits for nothing more.
 static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *issued)
 {
     *issued = false;
@@ -254,14 +257,11 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     uint64_t target, records;
     {
         std::lock_guard<std::mutex> pk(r->pmu);
-        if (!r->window_exact) return DMI_OK;
-        target = read_committed(r) + r->window.bytes;
+        if (!r->window_exact || !r->probes.empty() || r->next_seq.load(std::memory_order_acquire) <= r->probed_upto ||
+            read_committed(r) != r->drain_issued)
+            return DMI_OK;
+        target = r->drain_issued + r->window.bytes;
         records = r->snap[0] + r->window.records;
-        for (const Probe &p : r->probes) {
-            if (p.fetched) return DMI_OK;
-            target += p.delta.bytes;
-            records += p.delta.records;
-        }
     }
     const uint64_t from = r->drain_issued, n = target - from;
     if (n == 0 || n > kFlushKernelBytes || n > r->host_cap - (from - r->released)) return DMI_OK;
@@ -276,7 +276,11 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n,
                                 (uint32_t)(groups < 64u ? groups : 64u), us));
     uint64_t no = 0;
-    if ((st = record_probe(r, true, &no)) != DMI_OK) return st;     // (on that stream too: its producer is this thread)
+    // (a probe of its own, even if another thread's drain has just put one there: that one may be in front of the
+    // copy; and on that stream, because its producer is this thread, whose count of launches starts again behind it)
+    if ((st = record_probe(r, true, &no)) != DMI_OK) return st;
+    r->unprobed_launches = 0;
+    r->unprobed_bytes = 0;
     r->direct_probe = no;
     r->drain_issued = target;
     r->drain_issued_records = records;
@@ -1296,6 +1300,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     const uint64_t t0 = now_ns();
     uint64_t total = 0, target = UINT64_MAX;
     bool direct = false;
+    if ((st = advance_commits(r, false)) != DMI_OK) return st;
     if ((st = flush_behind_captures(r, &total, &direct)) != DMI_OK) return st;
     if (bytes_moved) *bytes_moved = total;
     if (!direct && (st = record_probe(r)) != DMI_OK) return st;

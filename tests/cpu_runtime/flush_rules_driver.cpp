@@ -130,6 +130,62 @@ void other_threads_flushes_stay_off_the_producers_stream()
     CHECK(fake_drain_launches(b.stream) == 1 && b.poll() == 1);
 }
 
+// Records whose captures have ended are moved at once, whatever the caller has put on the stream behind them:
+// a flush does not queue their copy there.
+void captured_records_do_not_wait_for_work_behind_them()
+{
+    Bench b(0, 50);
+    CHECK(b.observe(16) == DMI_OK);         // (the sixteenth puts a probe behind them)
+    CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+    b.close_gate();
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(b.poll() == 16);
+}
+
+// The same where the captures end only while the flush waits for them.
+void records_with_a_probe_do_not_wait_for_work_behind_it()
+{
+    Bench b(0, 2000);
+    std::atomic<bool> go{false};
+    fake_enqueue(b.stream, [&] { while (!go.load()) std::this_thread::sleep_for(std::chrono::microseconds(20)); });
+    CHECK(b.observe(16) == DMI_OK);
+    b.close_gate();
+    std::thread later([&] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(20));
+        go.store(true);
+    });
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    later.join();
+    CHECK(b.poll() == 16);
+}
+
+// A flush that cannot finish still delivers the records in front of the capture it waits for.
+void a_flush_that_gives_up_delivers_what_was_captured()
+{
+    Bench b(0, 50);
+    CHECK(b.observe(16) == DMI_OK);
+    CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    CHECK(b.poll() == 16);
+    b.open_gate();
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(b.poll() == 1);
+}
+
+// Nor does it keep the room of captured records from a producer that waits for it.
+void a_flush_that_gives_up_leaves_room_to_the_producer()
+{
+    Bench b(0, 50, 24 * Bench::record());
+    CHECK(b.observe(16) == DMI_OK);
+    CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+    b.close_gate();
+    CHECK(b.observe(2) == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    CHECK(b.observe(14) == DMI_OK);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -137,6 +193,10 @@ struct Scenario {
 const Scenario kScenarios[] = {
     {"waiting_drain_after_a_flush_that_gave_up", waiting_drain_after_a_flush_that_gave_up},
     {"polling_alone_sees_a_flush_that_gave_up", polling_alone_sees_a_flush_that_gave_up},
+    {"captured_records_do_not_wait_for_work_behind_them", captured_records_do_not_wait_for_work_behind_them},
+    {"records_with_a_probe_do_not_wait_for_work_behind_it", records_with_a_probe_do_not_wait_for_work_behind_it},
+    {"a_flush_that_gives_up_delivers_what_was_captured", a_flush_that_gives_up_delivers_what_was_captured},
+    {"a_flush_that_gives_up_leaves_room_to_the_producer", a_flush_that_gives_up_leaves_room_to_the_producer},
     {"other_threads_flushes_stay_off_the_producers_stream", other_threads_flushes_stay_off_the_producers_stream},
 };
 

@@ -11,6 +11,10 @@ CPU = os.path.join(ROOT, "tests", "cpu_runtime")
 CSRC = os.path.join(ROOT, "paper_2605_11093_amd", "csrc")
 
 SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_flush_that_gave_up",
+             "captured_records_do_not_wait_for_work_behind_them",
+             "records_with_a_probe_do_not_wait_for_work_behind_it",
+             "a_flush_that_gives_up_delivers_what_was_captured",
+             "a_flush_that_gives_up_leaves_room_to_the_producer",
              "other_threads_flushes_stay_off_the_producers_stream"]
 
 
