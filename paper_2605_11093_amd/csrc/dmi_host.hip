@@ -49,6 +49,15 @@ void note_producer(dmi_ring *r, void *stream)
     r->last_stream.store(stream, std::memory_order_release);
 }
 
+// Whether `s` is being captured.  The runtime may decline to say (of the null stream, while another thread captures
+// one that waits for it); the error it leaves is cleared, or the thread's next launch would be reported as failed.
+bool capture_status(hipStream_t s, hipStreamCaptureStatus *status)
+{
+    if (hipStreamIsCapturing(s, status) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Record an event behind everything launched so far (no-op if that is already covered, unless
 // asked for all the same); *no = the number of the probe that covers it.
 // If the host cannot tell what those launches added (drop-newest, keep vectors), the
@@ -268,8 +277,7 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     // Not while the stream is being captured: the copy would end up in the graph.
     hipStream_t us = (hipStream_t)r->last_stream.load(std::memory_order_acquire);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (r->quiet.load(std::memory_order_acquire) || hipStreamIsCapturing(us, &cs) != hipSuccess ||
-        cs != hipStreamCaptureStatusNone)
+    if (r->quiet.load(std::memory_order_acquire) || !capture_status(us, &cs) || cs != hipStreamCaptureStatusNone)
         return DMI_OK;
     atomic_max(r->dev_high, n);
     const uint64_t groups = (n / 16u + kThreads - 1u) / kThreads;

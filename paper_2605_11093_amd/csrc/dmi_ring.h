@@ -296,6 +296,7 @@ namespace host {
 // dmi_host.hip
 const void *this_thread();                                 // the calling thread: an address that it has to itself
 void note_producer(dmi_ring *r, void *stream);             // the calling thread observes on `stream`
+bool capture_status(hipStream_t s, hipStreamCaptureStatus *status);
 dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);

@@ -85,7 +85,7 @@ dmi_status_t step_add(dmi_step *st, uint32_t n, const uint32_t *points, const ui
         return fail(DMI_ERR_INVALID_ARG, "the step would hold more than max_observes (%u) records", st->max_nodes);
     // outside a capture the launch would run at once, with whatever the parameter block holds
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing((hipStream_t)hip_stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusActive)
+    if (!capture_status((hipStream_t)hip_stream, &cs) || cs != hipStreamCaptureStatusActive)
         return fail(DMI_ERR_INVALID_ARG, "hip_stream is not capturing");
     StepNode nd;
     dmi_status_t rc = plan_capture(plan_env(r), points[0], sel, xf, geo, a, nd.pl, false);

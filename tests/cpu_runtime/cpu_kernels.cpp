@@ -119,7 +119,7 @@ hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t gri
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
-    return hipSuccess;
+    return hipGetLastError();       // (as the library's launchers do)
 }
 
 hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s)
@@ -128,14 +128,14 @@ hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipSt
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words, hipStream_t s)
 {
     std::vector<uint32_t> w(words, words + n_words);      // kernel arguments carry the data
     fake_enqueue(s, [dst, w] { memcpy(dst, w.data(), w.size() * 4u); });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint32_t par_from, uint32_t par_to,
@@ -149,19 +149,19 @@ hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint
             ctrl->tail_for[par_to] = ctrl->tail_for[par_from];
         }
     });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 hipError_t launch_ctrl_reset(DevCtrl *ctrl, hipStream_t s)
 {
     fake_enqueue(s, [ctrl] { memset(ctrl, 0, offsetof(DevCtrl, point_drops)); });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s)
 {
     fake_enqueue(s, [src, dst_host] { memcpy(dst_host, src, sizeof(CommitSlot)); });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 static std::mutex g_drain_mu;
@@ -178,7 +178,7 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
         for (uint64_t i = 0; i < nbytes; i += 64u)
             memcpy(host_ring + (from + i) % host_cap, ring + (from + i) % cap, 64);
     });
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 }  // namespace dmi

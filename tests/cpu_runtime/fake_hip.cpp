@@ -128,6 +128,15 @@ const char *hipGetErrorString(hipError_t e)
     default: return "invalid value";
     }
 }
+static thread_local hipError_t t_last_error = hipSuccess;
+static thread_local unsigned t_failing_queries = 0;
+hipError_t hipGetLastError()
+{
+    const hipError_t e = t_last_error;
+    t_last_error = hipSuccess;
+    return e;
+}
+void fake_fail_capture_queries(unsigned n) { t_failing_queries = n; }
 hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 hipError_t hipSetDevice(int dev) { return dev == 0 ? hipSuccess : hipErrorInvalidValue; }
 hipError_t hipDeviceSynchronize()
@@ -193,6 +202,10 @@ hipError_t hipStreamQuery(hipStream_t hs)
 }
 hipError_t hipStreamIsCapturing(hipStream_t hs, hipStreamCaptureStatus *status)
 {
+    if (t_failing_queries) {
+        t_failing_queries--;
+        return t_last_error = hipErrorInvalidValue;
+    }
     FakeStream *s = resolve(hs);
     std::lock_guard<std::mutex> lk(s->mu);
     *status = s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;

@@ -186,6 +186,23 @@ void a_flush_that_gives_up_leaves_room_to_the_producer()
     CHECK(b.observe(14) == DMI_OK);
 }
 
+// A stream of which the runtime will not say whether it is captured: the flush copies on the drain stream, and
+// the error it was answered with is not taken for that of the next launch.
+void an_unanswered_capture_query_leaves_no_error()
+{
+    for (const uint32_t flags : {0u, (uint32_t)DMI_DRAIN_KERNEL}) {
+        Bench b(flags, 2000);
+        CHECK(b.observe() == DMI_OK);
+        fake_fail_capture_queries(1);
+        uint64_t moved = 0;
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK);
+        CHECK(moved == Bench::record() && fake_drain_launches(b.stream) == 0);
+        CHECK(b.observe() == DMI_OK);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(b.poll() == 2);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -197,6 +214,7 @@ const Scenario kScenarios[] = {
     {"records_with_a_probe_do_not_wait_for_work_behind_it", records_with_a_probe_do_not_wait_for_work_behind_it},
     {"a_flush_that_gives_up_delivers_what_was_captured", a_flush_that_gives_up_delivers_what_was_captured},
     {"a_flush_that_gives_up_leaves_room_to_the_producer", a_flush_that_gives_up_leaves_room_to_the_producer},
+    {"an_unanswered_capture_query_leaves_no_error", an_unanswered_capture_query_leaves_no_error},
     {"other_threads_flushes_stay_off_the_producers_stream", other_threads_flushes_stay_off_the_producers_stream},
 };
 

@@ -30,6 +30,7 @@ enum : unsigned { hipHostMallocMapped = 2u, hipHostMallocCoherent = 0x40000000u,
                   hipEventDisableTiming = 2u };
 
 const char *hipGetErrorString(hipError_t e);
+hipError_t hipGetLastError();       // of the calling thread, which it clears; set here only by what is made to fail
 hipError_t hipGetDeviceCount(int *n);
 hipError_t hipSetDevice(int dev);
 hipError_t hipDeviceSynchronize();
@@ -64,5 +65,7 @@ std::vector<FakeTask> fake_end_capture(hipStream_t s);
 void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s);
 // each worker sleeps a random 0..max_us microseconds in front of every task (shakes interleavings)
 void fake_set_jitter_us(unsigned max_us);
+// the next n capture queries of the calling thread fail (and leave their error behind)
+void fake_fail_capture_queries(unsigned n);
 // how many drain kernels have been launched on `s` (cpu_kernels.cpp)
 unsigned fake_drain_launches(hipStream_t s);
