@@ -174,6 +174,27 @@ void a_flush_that_gives_up_delivers_what_was_captured()
     CHECK(b.poll() == 1);
 }
 
+// The same where those captures end only while it waits.
+void a_flush_that_gives_up_delivers_what_gets_captured()
+{
+    Bench b(0, 200);
+    std::atomic<bool> go{false};
+    fake_enqueue(b.stream, [&] { while (!go.load()) std::this_thread::sleep_for(std::chrono::microseconds(20)); });
+    CHECK(b.observe(16) == DMI_OK);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    std::thread later([&] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(20));
+        go.store(true);
+    });
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    later.join();
+    CHECK(b.poll() == 16);
+    b.open_gate();
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(b.poll() == 1);
+}
+
 // Nor does it keep the room of captured records from a producer that waits for it.
 void a_flush_that_gives_up_leaves_room_to_the_producer()
 {
@@ -203,6 +224,74 @@ void an_unanswered_capture_query_leaves_no_error()
     }
 }
 
+// One record of exactly `bytes` (of 64-byte rows; the stand-in's captures read no source).
+dmi_status_t observe_bytes(Bench &b, uint64_t bytes)
+{
+    const uint32_t rows = (uint32_t)((bytes - 128u) / 64u);
+    CHECK(dmi_record_bytes(1, rows, 32, DMI_DTYPE_BF16, 0) == bytes);
+    dmi_tensor_t t = {b.data.data(), DMI_DTYPE_BF16, {rows, 32}, {32, 1}};
+    const dmi_req_sel_t all = {1, 0, 0, rows, 1};
+    const dmi_selection_t sel = {1, &all, nullptr, nullptr};
+    const dmi_transform_t raw = {DMI_DTYPE_BF16, 0};
+    return dmi_observe(b.ring, 1, &t, &sel, &raw, 0, b.stream);
+}
+
+// What goes behind the captures, and what does not: how many drain kernels the producer's stream has seen.
+void spans_up_to_the_limit_go_behind_the_captures()
+{
+    constexpr uint64_t limit = 6u << 20;
+    Bench b(0, 2000, 64u << 20, 64u << 20);
+    CHECK(observe_bytes(b, limit) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 1 && b.poll() == 1);
+    CHECK(observe_bytes(b, limit + 64) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 1 && b.poll() == 1);
+    CHECK(b.observe(7) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 2 && b.poll() == 7);
+    for (int i = 0; i < 40; i++)            // eight captures and a flush in turn: always
+        CHECK(b.observe(8) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 42 && b.poll() == 128);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK && fake_drain_launches(b.stream) == 42);     // nothing to move
+}
+
+void other_rings_and_spans_do_not_go_behind_the_captures()
+{
+    for (const uint32_t flags : {(uint32_t)DMI_DRAIN_COPY_ENGINE, (uint32_t)DMI_BG_THREAD, (uint32_t)(DMI_BG_THREAD | DMI_DRAIN_KERNEL)}) {
+        Bench b(flags, 2000);
+        CHECK(b.observe() == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 1);
+    }
+    {   // a keep vector of the caller's: the size is the device's secret
+        Bench b(0, 2000);
+        const uint8_t keep = 1;
+        CHECK(b.observe(1, &keep) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 1);
+    }
+    {   // best effort, decided on the device: the host runs more launches ahead than it answers for
+        Bench b(0, 2000, 4 * Bench::record());
+        const dmi_policy_t drop = {DMI_POLICY_DROP_NEWEST, 1, 0};
+        CHECK(dmi_set_policy(b.ring, &drop) == DMI_OK);
+        b.close_gate();
+        CHECK(b.observe(12) == DMI_OK);
+        b.open_gate();
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 4);
+    }
+    {   // a host ring with room for five of six records
+        Bench b(0, 2000, 1u << 20, 5 * Bench::record());
+        CHECK(b.observe(6) == DMI_OK && dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+        CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 5);
+    }
+    {   // a stream under capture: nothing of the copy may end up in the graph
+        Bench b(0, 20);
+        CHECK(b.observe() == DMI_OK);
+        fake_begin_capture(b.stream);
+        (void)dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr);
+        CHECK(fake_drain_launches(b.stream) == 0);
+        fake_graph_launch(fake_end_capture(b.stream), b.stream);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK && b.poll() == 1);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -213,8 +302,11 @@ const Scenario kScenarios[] = {
     {"captured_records_do_not_wait_for_work_behind_them", captured_records_do_not_wait_for_work_behind_them},
     {"records_with_a_probe_do_not_wait_for_work_behind_it", records_with_a_probe_do_not_wait_for_work_behind_it},
     {"a_flush_that_gives_up_delivers_what_was_captured", a_flush_that_gives_up_delivers_what_was_captured},
+    {"a_flush_that_gives_up_delivers_what_gets_captured", a_flush_that_gives_up_delivers_what_gets_captured},
     {"a_flush_that_gives_up_leaves_room_to_the_producer", a_flush_that_gives_up_leaves_room_to_the_producer},
     {"an_unanswered_capture_query_leaves_no_error", an_unanswered_capture_query_leaves_no_error},
+    {"spans_up_to_the_limit_go_behind_the_captures", spans_up_to_the_limit_go_behind_the_captures},
+    {"other_rings_and_spans_do_not_go_behind_the_captures", other_rings_and_spans_do_not_go_behind_the_captures},
     {"other_threads_flushes_stay_off_the_producers_stream", other_threads_flushes_stay_off_the_producers_stream},
 };
 

@@ -14,8 +14,11 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "captured_records_do_not_wait_for_work_behind_them",
              "records_with_a_probe_do_not_wait_for_work_behind_it",
              "a_flush_that_gives_up_delivers_what_was_captured",
+             "a_flush_that_gives_up_delivers_what_gets_captured",
              "a_flush_that_gives_up_leaves_room_to_the_producer",
              "an_unanswered_capture_query_leaves_no_error",
+             "spans_up_to_the_limit_go_behind_the_captures",
+             "other_rings_and_spans_do_not_go_behind_the_captures",
              "other_threads_flushes_stay_off_the_producers_stream"]
 
 
