@@ -330,19 +330,12 @@ __device__ __forceinline__ float am_value(uint32_t m, uint32_t src_dtype)
     return widen16(m, src_dtype);
 }
 
-// Convert one source unit and store it; optionally accumulate the row summaries.
-template <int ES_IN, int VEC, int OUT, bool SUMM, bool LOOSE = false>
-__device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
-                                          typename UnitT<ES_IN * VEC>::T v, uint32_t src_dtype,
-                                          Accum &acc)
+// Convert one source unit and store it.
+template <int ES_IN, int VEC, int OUT, bool LOOSE = false>
+__device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off, typename UnitT<ES_IN * VEC>::T v)
 {
     if constexpr (ES_IN == 2 && VEC == 8) {
         uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-        if constexpr (SUMM) {
-            const bool is_bf16 = src_dtype == 1u;
-#pragma unroll
-            for (int k = 0; k < 4; k++) accum_pair(acc, wd[k], is_bf16);
-        }
         if constexpr (OUT == OUT_RAW) {
             unit_store<LOOSE, u32x4>(w, out_off, v);
         } else if constexpr (OUT == OUT_FP16) {
@@ -365,27 +358,20 @@ __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off,
             unit_store<LOOSE, u32x2>(w, out_off, o);
         }
     } else if constexpr (ES_IN == 4 && VEC == 4) {
-        if constexpr (SUMM) {
-            accum_f32(acc, v.x);
-            accum_f32(acc, v.y);
-            accum_f32(acc, v.z);
-            accum_f32(acc, v.w);
-        }
         if constexpr (OUT == OUT_RAW) unit_store<LOOSE, u32x4>(w, out_off, v);
     } else if constexpr (ES_IN == 2) {      // one 2-byte element
         const uint32_t b = v;
-        if constexpr (SUMM) accum_16(acc, b, src_dtype);
         if constexpr (OUT == OUT_RAW) ring_store<uint16_t>(w, out_off, (uint16_t)b);
         else if constexpr (OUT == OUT_FP16) ring_store<uint16_t>(w, out_off, (uint16_t)bf16_to_fp16(b));
         else if constexpr (OUT == OUT_FP8) ring_store<uint8_t>(w, out_off, (uint8_t)bf16_to_fp8(b));
     } else {                                // one 4-byte element
-        if constexpr (SUMM) accum_f32(acc, v);
         if constexpr (OUT == OUT_RAW) ring_store<uint32_t>(w, out_off, v);
     }
 }
 
-// Add one step's units (four per lane; a lane without that unit has zeros) to the row's partial summaries: every unit summed by itself, the four combined in pairs.  Shorter chains
-// than one running sum, in time and in rounding error.
+// Add one step's units (four per lane; a lane without that unit has zeros) to the row's partial summaries:
+// every unit summed by itself, the four combined in pairs.  Shorter chains than one running sum, in time and
+// in rounding error.
 template <int ES_IN, int VEC>
 __device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_IN * VEC>::T (&v)[4],
                                             uint32_t src_dtype)
@@ -406,7 +392,18 @@ __device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_
         if (src_dtype == 1u) all(std::true_type()); else all(std::false_type());
     } else {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; k++) emit_unit<ES_IN, VEC, OUT_NONE, true>(RingW{}, 0, v[k], src_dtype, u[k]);
+        for (uint32_t k = 0; k < 4; k++) {
+            if constexpr (VEC == 4) {
+                accum_f32(u[k], v[k].x);
+                accum_f32(u[k], v[k].y);
+                accum_f32(u[k], v[k].z);
+                accum_f32(u[k], v[k].w);
+            } else if constexpr (ES_IN == 4) {
+                accum_f32(u[k], v[k]);
+            } else {
+                accum_16(u[k], v[k], src_dtype);
+            }
+        }
     }
     acc.ss += (u[0].ss + u[1].ss) + (u[2].ss + u[3].ss);
     acc.s += (u[0].s + u[1].s) + (u[2].s + u[3].s);
@@ -987,7 +984,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 
         if constexpr (SUMM == SUMM_NO) {
             if constexpr (OUT != OUT_NONE) {
-                Accum dummy = {0.f, 0.f, 0u};
                 if (VEC > 1 && a.units_per_row >= kThreads) {
                     // ---- long rows: a work item is 1024 consecutive units: a quarter or more of one
                     //      row, or 2 / 4 whole rows of 512 / 256 units; rows are located once per
@@ -1066,8 +1062,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                             for (uint32_t k = 0; k < U; k++)
                                 if (live[k])
-                                    emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, pos[k], zero_unless((okm >> k) & 1u, v[k]),
-                                                                             a.src_dtype, dummy);
+                                    emit_unit<ES_IN, VEC, OUT, LOOSE>(w, pos[k], zero_unless((okm >> k) & 1u, v[k]));
                             if (!more) break;
                             it = nxt;
                             okm = okm_n;
@@ -1143,9 +1138,9 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                             const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
                             const uint32_t g = LOOSE ? row_of((uint32_t)u) : 0u;    // (else a record's units just follow each other)
                             if (live[k])
-                                emit_unit<ES_IN, VEC, OUT, false, LOOSE>(
+                                emit_unit<ES_IN, VEC, OUT, LOOSE>(
                                     w, LOOSE ? out_at(g, (uint32_t)u - g * upr) : off_payload + u * NB_OUT,
-                                    zero_unless(okk[k], v[k]), a.src_dtype, dummy);
+                                    zero_unless(okk[k], v[k]));
                         }
                     }
                 }
@@ -1203,11 +1198,9 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             auto process = [&](const unit_t (&v)[U], uint64_t g0) {
                 const uint64_t g = g0 + sub_r;
                 if constexpr (OUT != OUT_NONE) {
-                    Accum none = {0.f, 0.f, 0u};
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++)
-                        if (g < r1 && in_row[k])
-                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, l_r + k * lpr), v[k], a.src_dtype, none);
+                        if (g < r1 && in_row[k]) emit_unit<ES_IN, VEC, OUT, LOOSE>(w, out_at(g, l_r + k * lpr), v[k]);
                 }
                 Accum acc = {0.f, 0.f, 0u};
                 unit_t sv[U];
@@ -1259,9 +1252,9 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             // ---- summaries, a wavefront per row: where a launch has rows enough to fill the GPU that way, a row costs no
             //      barrier and a workgroup lives for four rows or more instead of one, so its prologue weighs less.
             //      The sums are taken in the order in which a workgroup takes them (the decode-shaped kernel, and
-            //      the path below): the row's lanes in parts of 64, each lane's units four at a time, then the lanes
-            //      of a part, then the (at most four) parts.  A step is one part's next four units per lane; its loads
-            //      are issued before the step in front of it is worked on.
+            //      the path below): the row's lanes in parts of 64, each lane's (at most four) units, then the lanes
+            //      of a part, then the (at most four) parts.  A step is one part of a row; its loads are issued
+            //      before the step in front of it is worked on.
             //      Bound: HBM reads.  80 x 256 rows of 512 units, statistics only: 64 -> 35 us
             //      (4.8 TB/s); plan_grid() has more figures, and says where the line lies.
             const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
@@ -1269,10 +1262,10 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint64_t per = n_rows ? (uint64_t)(n_rows - 1u) / n_waves + 1u : 0u;
             const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
-            const uint32_t parts = row_lanes >> 6, passes = cpr;
-            auto wave_unit = [&](uint32_t part, uint32_t pass, uint32_t t) { return pass * CH + part * 64u + lane + t * row_lanes; };
+            const uint32_t parts = row_lanes >> 6;
+            auto wave_unit = [&](uint32_t part, uint32_t t) { return part * 64u + lane + t * row_lanes; };
             const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
-            struct Step { uint64_t g; uint32_t part, pass; RowRef ref; };
+            struct Step { uint64_t g; uint32_t part; RowRef ref; };
             uint32_t n_bad = 0, hint = 0;
             auto begin = [&](uint64_t g) -> RowTok { return locate_begin((uint32_t)(g < r1 ? g : r1 - 1u), hint); };
             auto end = [&](const RowTok &k, uint64_t g) -> RowRef {
@@ -1285,27 +1278,26 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 const bool ok = s.g < r1 && s.ref.ok;
 #pragma unroll
                 for (uint32_t t = 0; t < U; t++) {
-                    const uint32_t c = wave_unit(s.part, s.pass, t);
+                    const uint32_t c = wave_unit(s.part, t);
                     const uint8_t *ptr = ok && c < a.units_per_row ? unit_ptr(s.ref, c) : zeros;
                     v[t] = *(global_unit_t *)ptr;
                 }
             };
-            Accum acc = {0.f, 0.f, 0u};
+            uint32_t row_am = 0;
             float ss[2] = {0.f, 0.f}, sm[2] = {0.f, 0.f};      // of parts 0 and 1; of the last part, or of 2 and 3
             auto process = [&](const Step &s, const unit_t (&v)[U]) {
                 unit_t sv[U];
 #pragma unroll
                 for (uint32_t t = 0; t < U; t++) {
-                    const uint32_t c = wave_unit(s.part, s.pass, t);
+                    const uint32_t c = wave_unit(s.part, t);
                     if constexpr (OUT != OUT_NONE) {
-                        Accum none = {0.f, 0.f, 0u};
-                        if (c < a.units_per_row)
-                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(s.g, c), v[t], a.src_dtype, none);
+                        if (c < a.units_per_row) emit_unit<ES_IN, VEC, OUT, LOOSE>(w, out_at(s.g, c), v[t]);
                     }
                     sv[t] = sum_part(v[t], c);
                 }
+                Accum acc = {0.f, 0.f, row_am};
                 accum_units<ES_IN, VEC>(acc, sv, a.src_dtype);
-                if (s.pass + 1u < passes) return;
+                row_am = acc.am;
                 if (a.summary_mask & 1u) {
                     float r = wave_sum(acc.ss);
                     if (s.part & 1u) r = ss[1] + r;
@@ -1318,17 +1310,16 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     if (s.part < 2u) sm[0] = r;
                     sm[1] = r;
                 }
-                acc.ss = acc.s = 0.f;
                 if (s.part + 1u < parts) return;
                 const uint32_t at = (uint32_t)(s.g - r0) & 63u;         // the row is complete
-                const uint32_t am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
+                const uint32_t am = wave_max_u32(fold_am<ES_IN, VEC>(row_am));
                 const bool both = parts > 2u;
                 if (lane == 0) {
                     stash[at] = both ? ss[0] + ss[1] : ss[0];
                     stash[64u + at] = both ? sm[0] + sm[1] : sm[0];
                     stash[128u + at] = __uint_as_float(am);
                 }
-                acc = Accum{0.f, 0.f, 0u};
+                row_am = 0;
                 if (at == 63u || s.g + 1u >= r1) flush_totals(s.g - at, s.g + 1u);
             };
             if (r0 < r1) {
@@ -1336,8 +1327,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 RowTok ask = begin(r0 + 1u);
                 auto next = [&](const Step &s) -> Step {        // (behind the last row: steps that read zeros)
                     Step n = s;
-                    if (++n.pass < passes) return n;
-                    n.pass = 0;
                     if (++n.part < parts) return n;
                     n.part = 0;
                     n.g++;
@@ -1345,7 +1334,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     ask = begin(n.g + 1u);
                     return n;
                 };
-                Step s = {r0, 0u, 0u, pre_ref};
+                Step s = {r0, 0u, pre_ref};
                 if (pre) {
                     n_bad += pre_ref.ok ? 0u : 1u;
 #pragma unroll
@@ -1406,13 +1395,12 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     RowRef ref_n = ref;             // a later pass of the same row keeps the row
                     unit_t v_n[U];
                     if (more) fetch(nxt_g, nxt_pass, ref_n, v_n);
-                    Accum none = {0.f, 0.f, 0u};
                     unit_t sv[U];
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++) {
                         const uint32_t c = tid + (pass * U + k) * row_lanes;
                         if (OUT != OUT_NONE && tid < row_lanes && c < a.units_per_row)
-                            emit_unit<ES_IN, VEC, OUT, false, LOOSE>(w, out_at(g, c), v[k], a.src_dtype, none);
+                            emit_unit<ES_IN, VEC, OUT, LOOSE>(w, out_at(g, c), v[k]);
                         sv[k] = sum_part(v[k], c);
                     }
                     const bool mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)tid) < row_lanes;
@@ -1753,13 +1741,12 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if (dropped || !kept) return;
     const uint32_t g = my_row;
     if (!ok && tid == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-    Accum acc = {0.f, 0.f, 0u};
     const uint64_t row_off = a.off_payload + (uint64_t)g * a.units_per_row * NB_OUT;
 #pragma unroll
     for (uint32_t k = 0; k < U; k++) {
         const uint32_t c = tid + k * ustr;
         if ((!SUMM || tid < ustr) && c < a.units_per_row)
-            emit_unit<2, 8, OUT, false>(w, row_off + (uint64_t)c * NB_OUT, v[k], a.hdr7 & 0xFFu, acc);
+            emit_unit<2, 8, OUT>(w, row_off + (uint64_t)c * NB_OUT, v[k]);
     }
     if constexpr (SUMM) {
         if (tid == 0) {
@@ -1863,6 +1850,7 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     } else if (a.summary_mask) {
         if constexpr (VEC > 1) {
+            if (a.wave_rows && a.units_per_row > 1024u) return hipErrorInvalidValue;    // four units for each of 256 lanes
             if (a.wave_rows)
                 DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_WAVE, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
             else
@@ -1870,9 +1858,18 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
         } else {
             return hipErrorInvalidValue;
         }
-    } else {
+    } else if constexpr (OUT != OUT_NONE) {
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     }
+    return hipGetLastError();
+}
+
+template <typename SRC>
+static hipError_t launch_no_rows(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
+{
+    const dim3 g(grid, a.n_batch);
+    const CaptureKernelArgs &k = a;
+    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<2, 8, OUT_NONE, SUMM_NO, SRC, false>), g, a.lds_bytes, s, k, b);
     return hipGetLastError();
 }
 
@@ -1880,7 +1877,11 @@ template <int ES_IN, int VEC, bool LOOSE, typename SRC>
 static hipError_t launch_o(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     const bool raw = a.out_dtype == a.src_dtype;
-    if (a.out_dtype == 0) return launch_t<ES_IN, VEC, OUT_NONE, LOOSE>(a, b, grid, s);
+    if (a.out_dtype == 0) {
+        // (neither rows nor summaries: header and request table alone, whatever the source)
+        if (!a.summary_mask) return launch_no_rows(a, b, grid, s);
+        return launch_t<ES_IN, VEC, OUT_NONE, LOOSE>(a, b, grid, s);
+    }
     if (raw) return launch_t<ES_IN, VEC, OUT_RAW, LOOSE>(a, b, grid, s);
     if constexpr (ES_IN == 2) {
         if (a.out_dtype == 2) return launch_t<ES_IN, VEC, OUT_FP16, LOOSE>(a, b, grid, s);

@@ -152,12 +152,6 @@ hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint
     return hipGetLastError();
 }
 
-hipError_t launch_ctrl_reset(DevCtrl *ctrl, hipStream_t s)
-{
-    fake_enqueue(s, [ctrl] { memset(ctrl, 0, offsetof(DevCtrl, point_drops)); });
-    return hipGetLastError();
-}
-
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s)
 {
     fake_enqueue(s, [src, dst_host] { memcpy(dst_host, src, sizeof(CommitSlot)); });
