@@ -275,16 +275,18 @@ dmi_status_t dmi_observe_paged_batch(dmi_ring_t *ring, uint32_t n, const uint32_
  * request table) is a 128 KiB array that the library's code object holds on every GPU for the
  * life of the process.
  * Runs on the calling thread's current HIP device.  Launches, on hip_stream, the capture kernel
- * dmi_observe would launch, with the request table among its arguments (a table of more than 832
- * words, 5 per request, is staged by small launches in front of it), and returns.  The record, byte for byte the one dmi_observe would
+ * dmi_observe would launch, with the request table among its arguments, and returns.  (A table of more
+ * than 832 words is staged by small launches in front of it.  It has 5 words per request; where
+ * requests list several rows each, at most 1024 in all, and no keep vector is given, it may have one more per
+ * listed row: 40 requests of 16 rows make 840 words.)  The record, byte for byte the one dmi_observe would
  * produce with sequence number `seq` and this rank_tag, is written at out[0 ..) [device,
  * 64-byte aligned]; its size is in its header (bytes 48..55) and, when the selection has no
  * keep vector, in *record_bytes [host, optional] (with one: an upper bound).  Bytes of `out`
  * behind the record are not touched.  No policy applies: nothing is sampled, dropped or waited for.
  * Limits: at most 1024 requests; the record's upper bound (dmi_record_bytes with every listed
  * row kept) must fit out_bytes (a multiple of 64): otherwise DMI_ERR_TOO_LARGE and nothing is
- * launched.  Every call on a GPU may use that GPU's one array, so calls whose kernels may overlap
- * there (different streams with no ordering between them) race; calls on one stream do not.
+ * launched.  A call with a staged table uses that GPU's one array, so such calls race if their kernels may
+ * overlap (different streams with no ordering between them); calls on one stream do not.
  * Under a stream capture, call it once outside first: the first call on a device looks the
  * array up and loads the kernels.
  */

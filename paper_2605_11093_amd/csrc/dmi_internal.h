@@ -77,7 +77,8 @@ struct BatchArgs {
 // (dmi_observe_into).  It has no chain of launches, no control words, no policy and no counters, and its
 // request table (laid out as selection_words() does) travels here if it fits; n_words = 0: the table is in
 // device memory, where the other arguments say.
-constexpr uint32_t kIntoWords = 832;        // 166 requests; both argument blocks stay below 4 KiB
+constexpr uint32_t kIntoWords = 832;        // 166 requests, or fewer with a word per listed row; both argument
+                                            // blocks stay below 4 KiB
 struct alignas(16) IntoArgs {
     const uint8_t *src[1];
     uint32_t point[1];
