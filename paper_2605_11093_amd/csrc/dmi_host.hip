@@ -432,7 +432,10 @@ dmi_status_t stage_selection(dmi_ring *r, const dmi_selection_t *sel, bool paged
 // Work items per launch path, and a grid that gives every workgroup the same number of them:
 // with a fixed grid of "as many as fit" the last round is run by a fraction of the
 // workgroups while the rest idle (up to half the launch for 1 < items/grid < 2).
-// kResident is what stays resident at the register budget of the widest variants.  In a batch
+// kResident is five workgroups per compute unit: what the kernels that store rows without summaries hold (84 to 90
+// vector registers).  With summaries they hold from four (rows off the 16-byte grid, up to 256 units or a wavefront
+// per row: 87 to 126 registers) to seven (a workgroup per row on the grid: 63 to 72), and eight where units are single
+// elements; they are planned for five like the others, which leaves the first a short last round.  In a batch
 // (gridDim.y = nb) each workgroup stays with one tensor.
 uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
 {
@@ -469,8 +472,14 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         // (workgroup / wavefront per row, norm and largest magnitude, us:)
         //   rows of 288 units, 1.5 k rows 7.5 / 7.5, 3 k 10.0 / 7.4, 6 k 16.6 / 9.9; of 512: 24 k 57.3 / 40.0
         //   of 640 units, 6 k rows 17.3 / 14.4; 40 x 256 rows of 768, statistics alone 34.7 / 27.7, with the rows 45 / 49
-        //   of 1024 units, 80 x 256 rows, statistics alone 67.6 / 62.5, with the rows 116 / 121; ragged 12 k rows 39.6 / 40.6
-        //   of 1792 units, 12 k rows 66.6 / 69.4
+        //   of 1024 units, 80 x 256 rows with the rows 116 / 121
+        //   statistics alone, one row per request (no scan, no search): 64 x 256 rows of 784 units 52.3 / 42.2, of 896
+        //   53.4 / 45.2, of 960 53.8 / 48.4, of 1024 54.1 / 50.2; of 1024 units, 40 x 256 rows 36.0 / 33.9, 80 x 256 67.4 / 61.5,
+        //   96 x 256 79.6 / 72.3
+        //   the same, ragged: of 1024 units, 12 k rows 38.5 / 42.2, 18 k 56.4 / 59.3, 24 k 72.5 / 76.1 (of 800: 36.1 / 32.4 and
+        //   63.7 / 62.4); of 1792 units, 12 k rows 66.6 / 69.4
+        // So at 1024 units the shape of the selection decides, not the number of rows: one row per request gains from
+        // 10 k rows on (the line at 16384 leaves a margin), ragged rows at no number measured.
         // With statistics alone a wavefront takes two rows from 4096 rows on (80 x 256 rows of 512 units: 37.2 with
         // one, 34.8 with two; 3 k rows 8.7 and 9.0), where the rows are stored too, one (61 and 64 us).
         const uint64_t rows = listed * nb;
