@@ -78,7 +78,7 @@ enum { DMI_POLICY_BLOCK = 0, DMI_POLICY_DROP_NEWEST = 1 };
 enum {
     DMI_DRAIN_COPY_ENGINE = 1,  /* drain with hipMemcpyAsync on a side stream (the default, except that without
                                    this flag and without a drain thread a flush by the thread that observes
-                                   moves up to 6 MiB by a copy kernel behind the captures, on the stream last
+                                   may move up to 6 MiB by a copy kernel behind the captures, on the stream last
                                    passed to dmi_observe) */
     DMI_DRAIN_KERNEL = 2,       /* drain with a copy kernel writing pinned host memory */
     DMI_BG_THREAD = 4           /* the library runs its own drain thread (section 4.3) */
@@ -306,8 +306,9 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
  * DMI_DRAIN_NONBLOCK returns once the copies issued so far have ended, DMI_ERR_AGAIN if one that a
  * flush which gave up had left behind the captures did not within block_timeout_ms.
  * A flush of at most 6 MiB by the thread that observes, on a ring without a drain thread and not created with
- * DMI_DRAIN_COPY_ENGINE, does its copy on the stream last passed to dmi_observe, behind the captures; a flush
- * by another thread never does. */
+ * DMI_DRAIN_COPY_ENGINE, does its copy on the stream last passed to dmi_observe, behind the captures, unless
+ * some of the records are captured already or have an event of the library's behind them; a flush by another
+ * thread never does. */
 dmi_status_t dmi_drain(dmi_ring_t *ring, uint32_t flags, uint64_t *bytes_moved);
 
 /* A whole record in the host ring: [p0, p0+n0) then, iff it straddles the end of
