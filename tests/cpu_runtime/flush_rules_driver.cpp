@@ -134,7 +134,7 @@ void other_threads_flushes_stay_off_the_producers_stream()
 // a flush does not queue their copy there.
 void captured_records_do_not_wait_for_work_behind_them()
 {
-    Bench b(0, 50);
+    Bench b(0, 2000);
     CHECK(b.observe(16) == DMI_OK);         // (the sixteenth puts a probe behind them)
     CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
     b.close_gate();
@@ -162,7 +162,7 @@ void records_with_a_probe_do_not_wait_for_work_behind_it()
 // A flush that cannot finish still delivers the records in front of the capture it waits for.
 void a_flush_that_gives_up_delivers_what_was_captured()
 {
-    Bench b(0, 50);
+    Bench b(0, 500);
     CHECK(b.observe(16) == DMI_OK);
     CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
     b.close_gate();
@@ -177,7 +177,7 @@ void a_flush_that_gives_up_delivers_what_was_captured()
 // The same where those captures end only while it waits.
 void a_flush_that_gives_up_delivers_what_gets_captured()
 {
-    Bench b(0, 200);
+    Bench b(0, 1000);
     std::atomic<bool> go{false};
     fake_enqueue(b.stream, [&] { while (!go.load()) std::this_thread::sleep_for(std::chrono::microseconds(20)); });
     CHECK(b.observe(16) == DMI_OK);
@@ -198,7 +198,7 @@ void a_flush_that_gives_up_delivers_what_gets_captured()
 // Nor does it keep the room of captured records from a producer that waits for it.
 void a_flush_that_gives_up_leaves_room_to_the_producer()
 {
-    Bench b(0, 50, 24 * Bench::record());
+    Bench b(0, 500, 24 * Bench::record());
     CHECK(b.observe(16) == DMI_OK);
     CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
     b.close_gate();
@@ -282,7 +282,7 @@ void other_rings_and_spans_do_not_go_behind_the_captures()
         CHECK(fake_drain_launches(b.stream) == 0 && b.poll() == 5);
     }
     {   // a stream under capture: nothing of the copy may end up in the graph
-        Bench b(0, 20);
+        Bench b(0, 200);
         CHECK(b.observe() == DMI_OK);
         fake_begin_capture(b.stream);
         (void)dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr);
