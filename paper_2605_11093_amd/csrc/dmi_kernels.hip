@@ -76,14 +76,13 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t lane)
+// A pointer that is the same in every lane, said to be.
+__device__ __forceinline__ const uint8_t *uniform_ptr(const uint8_t *p)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= (uint32_t)d) v += t;
-    }
-    return v;
+    const uint64_t v = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
 }
 // Wavefront reductions with DPP (data-parallel primitives: the cross-lane operand rides on the
 // ALU instruction, no trip through LDS).  quad_perm / row_half_mirror / row_mirror combine the 16
@@ -93,6 +92,18 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+// Inclusive prefix sums over the wavefront (all 64 lanes of it), the same way: within rows of 16 lanes by shifts of
+// 1, 2, 4 and 8, then the rows' totals carried forward.  Shuffles through LDS take six dependent trips of 60 ns.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+{
+    v += dpp_u32<0x111, 0xF>(v);        // row_shr:1
+    v += dpp_u32<0x112, 0xF>(v);        // row_shr:2
+    v += dpp_u32<0x114, 0xF>(v);        // row_shr:4
+    v += dpp_u32<0x118, 0xF>(v);        // row_shr:8
+    v += dpp_u32<0x142, 0xA>(v);        // row_bcast15 into rows 1, 3
+    v += dpp_u32<0x143, 0xC>(v);        // row_bcast31 into rows 2, 3
+    return v;
 }
 __device__ __forceinline__ float wave_sum(float v)
 {
@@ -634,11 +645,11 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     lrb[r] = row_first(r);
                 }
             }
-            const uint32_t inc = wave_incl_scan(cnt, lane);
+            const uint32_t inc = wave_incl_scan(cnt);
             if (r < n_reqs) pref[r] = inc - cnt;
             if (lane == 63u) { btot[b] = inc; if (nb == 1u) pref[n_reqs] = inc; }
             if (index_mode) {
-                const uint32_t inc_all = wave_incl_scan(cnt_all, lane);
+                const uint32_t inc_all = wave_incl_scan(cnt_all);
                 if (r < n_reqs) pref_all[r] = inc_all - cnt_all;
                 if (lane == 63u) { btot_all[b] = inc_all; if (nb == 1u) pref_all[n_reqs] = inc_all; }
             }
@@ -652,14 +663,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             for (uint32_t b0 = 0; b0 < nb; b0 += 64u) {
                 const uint32_t b = b0 + lane;
                 const uint32_t v = b < nb ? btot[b] : 0u;
-                const uint32_t inc = wave_incl_scan(v, lane);
+                const uint32_t inc = wave_incl_scan(v);
                 if (b < nb) btot[b] = carry + inc - v;
-                carry += __shfl(inc, 63, 64);
+                carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
                 if (index_mode) {
                     const uint32_t va = b < nb ? btot_all[b] : 0u;
-                    const uint32_t ia = wave_incl_scan(va, lane);
+                    const uint32_t ia = wave_incl_scan(va);
                     if (b < nb) btot_all[b] = carry_all + ia - va;
-                    carry_all += __shfl(ia, 63, 64);
+                    carry_all += (uint32_t)__builtin_amdgcn_readlane((int)ia, 63);
                 }
             }
             if (lane == 0) {
@@ -741,7 +752,11 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     lds_barrier();
 
     // -- record geometry
-    const uint32_t n_rows = simple ? n_reqs : pref[n_reqs];
+    // (what comes out of LDS here is the same in every lane, and said to be, so that it and all that follows from it --
+    // sizes, places in the ring -- is scalar arithmetic in scalar registers)
+    auto lds_word = [&](uint32_t i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds[i]); };
+    auto lds_pair = [&](uint32_t i) { return (uint64_t)lds_word(i) | ((uint64_t)lds_word(i + 1u) << 32); };
+    const uint32_t n_rows = simple ? n_reqs : lds_word(m.pref + n_reqs);
     const uint32_t es_out = OUT == OUT_NONE ? 0u : OUT == OUT_FP8 ? 1u : (uint32_t)ES_IN;
     const uint64_t table_bytes = ((uint64_t)n_reqs * 16u + 63u) & ~63ull;
     const uint64_t payload_bytes = (uint64_t)n_rows * a.row_elems * es_out;
@@ -753,9 +768,9 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 
     // Record y of the launch lies y records behind the head the launch found: all records of a
     // batch have the same size, so record y fits iff the y before it did, and then they were kept.
-    const uint64_t head0 = (uint64_t)lds[m.bcast + 0] | ((uint64_t)lds[m.bcast + 1] << 32);
+    const uint64_t head0 = lds_pair(m.bcast);
     const uint64_t head = head0 + (uint64_t)y * record_bytes;
-    const uint32_t flags = lds[m.bcast + 6];
+    const uint32_t flags = lds_word(m.bcast + 6u);
     const bool publisher = !INTO && blockIdx.x == 0 && y == 0 && tid == kCtlTid;
     if (!INTO && (flags & kStepSkip)) {
         // a sampled-out replay: no record, no sequence number; the chain of head and tail
@@ -766,7 +781,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         }
         return;
     }
-    const uint64_t tail = (uint64_t)lds[m.bcast + 2] | ((uint64_t)lds[m.bcast + 3] << 32);
+    const uint64_t tail = lds_pair(m.bcast + 2u);
     const bool drop_newest = (flags & kStepDropNewest) != 0;
     const bool dropped = !INTO && (a.force_drop != 0u || (drop_newest && head - tail + record_bytes > a.cap));
 
@@ -818,7 +833,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     RingW w;
     w.ring = a.ring;
     w.cap = a.cap;
-    w.base = ((uint64_t)lds[m.bcast + 4] | ((uint64_t)lds[m.bcast + 5] << 32)) + (uint64_t)y * record_bytes;
+    w.base = lds_pair(m.bcast + 4u) + (uint64_t)y * record_bytes;
     if (w.base >= w.cap) w.base -= w.cap;
 
     // row g -> request r (largest r with pref[r] <= g; requests with no rows are skipped
@@ -834,26 +849,47 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         uint32_t at;        // dense: the row; paged: the physical block (signed where it was loaded)
         uint32_t slot;
     };
+    // (where a wavefront works on one row at a time, all of this but a load's result is scalar)
+    constexpr bool ROW_PER_WAVE = SUMM == SUMM_WAVE || SUMM == SUMM_ROWS;
+    auto rd = [&](uint32_t i) -> uint32_t { return ROW_PER_WAVE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)L[i]) : L[i]; };
+    // Row g's request, for all lanes at once: they look at 64 requests (or 64 evenly spaced ones of more) together: one trip
+    // through LDS and a ballot where a binary search takes five of them for 32 requests.
+    auto find_request = [&](uint32_t g) -> uint32_t {
+        uint32_t lo = 0, span = n_reqs;                 // in [lo, lo + span)
+        while (span > 1u) {
+            const uint32_t apart = (span + 63u) >> 6, i = lane * apart;
+            const uint32_t p = i < span ? L[m.pref + lo + i] : 0xFFFFFFFFu;
+            const uint32_t k = (uint32_t)__popcll(__ballot(p <= g)) - 1u;
+            lo += k * apart;
+            span = span - k * apart < apart ? span - k * apart : apart;
+        }
+        return lo;
+    };
     // `hint`: a request at or in front of row g's, from a caller that goes through rows in ascending order;
     // the row's request comes back in it.
     auto locate_begin = [&](uint32_t g, uint32_t &hint) -> RowTok {
         uint32_t r = g, j = 0;
         if (!simple) {
-            uint32_t lo = hint, hi = L[m.pref + hint + 1u] > g ? hint + 1u : n_reqs;
-            while (hi - lo > 1u) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (L[m.pref + mid] <= g) lo = mid; else hi = mid;
+            uint32_t lo = hint;
+            if constexpr (ROW_PER_WAVE) {
+                if (rd(m.pref + hint + 1u) <= g) lo = find_request(g);
+            } else {
+                uint32_t hi = L[m.pref + hint + 1u] > g ? hint + 1u : n_reqs;
+                while (hi - lo > 1u) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (L[m.pref + mid] <= g) lo = mid; else hi = mid;
+                }
             }
             r = lo;
             hint = r;
-            j = g - L[m.pref + r];
+            j = g - rd(m.pref + r);
         }
         RowTok k = {0u, 0u};
         if (!a.paged) {
             if (index_mode) {
-                k.at = (uint32_t)a.row_index[simple ? g : L[m.pref_all + r] + j];
+                k.at = (uint32_t)a.row_index[simple ? g : rd(m.pref_all + r) + j];
             } else if (a.table_in_lds) {        // (the host keeps every listed row below 2^32)
-                k.at = L[m.rb + r] + j * L[m.tab + 4u * r + 2u];
+                k.at = rd(m.rb + r) + j * rd(m.tab + 4u * r + 2u);
             } else {
                 k.at = row_first(r);
                 if (j) k.at += j * table_entry(r).z;
@@ -861,7 +897,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         } else {
             uint32_t tok0, tstep, seq_row;
             if (a.table_in_lds) {
-                tok0 = L[m.tab + 4u * r + 1u]; tstep = L[m.tab + 4u * r + 2u]; seq_row = L[m.rb + r];
+                tok0 = rd(m.tab + 4u * r + 1u); tstep = rd(m.tab + 4u * r + 2u); seq_row = rd(m.rb + r);
             } else {
                 const uint4 e = table_entry(r);
                 tok0 = e.y; tstep = e.z; seq_row = row_first(r);
@@ -874,11 +910,63 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         return k;
     };
     auto locate_end = [&](const RowTok &k) -> RowRef {
-        const int64_t at = a.paged || index_mode ? (int64_t)(int32_t)k.at : (int64_t)k.at;
+        const uint32_t word = ROW_PER_WAVE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)k.at) : k.at;
+        const int64_t at = a.paged || index_mode ? (int64_t)(int32_t)word : (int64_t)word;
         RowRef ref;
         ref.ok = at >= 0 && at < a.n_src_rows;
         if (!a.paged) ref.base = src + (ref.ok ? at : 0) * a.row_stride_b;
         else ref.base = src + (ref.ok ? at : 0) * a.block_stride_b + (int64_t)k.slot * a.slot_stride_b;
+        return ref;
+    };
+    // Consecutive rows of a wavefront, from `from` on, none behind the last one asked for.  Where the table is in LDS the next
+    // row of a request is a stride further on, and only the next request's first row has to be looked up; rows with an
+    // index (or a table) in memory are asked for a row ahead.
+    const bool walks = !simple && !index_mode && !a.paged && a.table_in_lds != 0;
+    struct Walk {
+        const uint8_t *base;
+        int64_t step;
+        uint32_t g, last, r, end;
+        RowTok ask;
+    };
+    auto walk_into = [&](Walk &q, uint32_t j) {         // request q.r's row j
+        q.end = rd(m.pref + q.r + 1u);
+        const uint32_t tok_step = rd(m.tab + 4u * q.r + 2u);
+        q.step = (int64_t)tok_step * a.row_stride_b;
+        q.base = src + (int64_t)(uint64_t)(rd(m.rb + q.r) + j * tok_step) * a.row_stride_b;      // (the host has checked these rows)
+    };
+    auto walk_from = [&](Walk &q, uint32_t from, uint32_t last) -> RowRef {
+        q.g = from;
+        q.last = last;
+        q.r = simple ? 0u : find_request(from);
+        if (walks) {
+            walk_into(q, from - rd(m.pref + q.r));
+            return RowRef{q.base, 1u};
+        }
+        const RowRef ref = locate_end(locate_begin(from, q.r));
+        q.ask = locate_begin(from < last ? from + 1u : last, q.r);
+        return ref;
+    };
+    // the same where the first row has been found up front (only where requests have one row each)
+    auto walk_behind = [&](Walk &q, uint32_t from, uint32_t last, const RowRef &first) -> RowRef {
+        q.g = from;
+        q.last = last;
+        q.r = 0;
+        if (from < last) q.ask = locate_begin(from + 1u, q.r);
+        return RowRef{uniform_ptr(first.base), (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)first.ok)};
+    };
+    auto walk_on = [&](Walk &q) -> RowRef {
+        q.g++;
+        if (walks) {
+            if (q.g < q.end) {
+                q.base += q.step;
+            } else {
+                do q.r++; while (rd(m.pref + q.r + 1u) <= q.g);
+                walk_into(q, 0u);
+            }
+            return RowRef{q.base, 1u};
+        }
+        const RowRef ref = locate_end(q.ask);
+        q.ask = locate_begin(q.g < q.last ? q.g + 1u : q.last, q.r);
         return ref;
     };
     auto locate = [&](uint32_t g) -> RowRef {
@@ -1162,7 +1250,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint32_t sub_r = lane >> lg, l_r = lane & (lpr - 1u);
             const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
             const uint32_t n_waves = gridDim.x * (kThreads / 64u);
-            const uint64_t per = n_rows ? ((uint64_t)(n_rows - 1u) / n_waves / rpi + 1u) * rpi : 0u;
+            const uint32_t per = n_rows ? ((n_rows - 1u) / n_waves / rpi + 1u) * rpi : 0u;
             const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
             // where this lane's units lie in a row does not change from row to row
@@ -1260,20 +1348,15 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             //      (4.8 TB/s); plan_grid() has more figures, and says where the line lies.
             const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
             const uint32_t n_waves = gridDim.x * (kThreads / 64u);
-            const uint64_t per = n_rows ? (uint64_t)(n_rows - 1u) / n_waves + 1u : 0u;
+            const uint32_t per = n_rows ? (n_rows - 1u) / n_waves + 1u : 0u;
             const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
             const uint32_t parts = row_lanes >> 6;
             auto wave_unit = [&](uint32_t part, uint32_t t) { return part * 64u + lane + t * row_lanes; };
             const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
             struct Step { uint64_t g; uint32_t part; RowRef ref; };
-            uint32_t n_bad = 0, hint = 0;
-            auto begin = [&](uint64_t g) -> RowTok { return locate_begin((uint32_t)(g < r1 ? g : r1 - 1u), hint); };
-            auto end = [&](const RowTok &k, uint64_t g) -> RowRef {
-                RowRef ref = locate_end(k);
-                n_bad += g < r1 && !ref.ok ? 1u : 0u;
-                return ref;
-            };
+            uint32_t n_bad = 0;
+            Walk walk;
             // a lane with nothing to load reads zeros
             auto load = [&](const Step &s, unit_t (&v)[U]) {
                 const bool ok = s.g < r1 && s.ref.ok;
@@ -1325,26 +1408,27 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             };
             if (r0 < r1) {
                 unit_t va[U], vb[U];
-                RowTok ask = begin(r0 + 1u);
                 auto next = [&](const Step &s) -> Step {        // (behind the last row: steps that read zeros)
                     Step n = s;
                     if (++n.part < parts) return n;
                     n.part = 0;
-                    n.g++;
-                    n.ref = end(ask, n.g);
-                    ask = begin(n.g + 1u);
+                    if (++n.g >= r1) return n;
+                    n.ref = walk_on(walk);
+                    n_bad += n.ref.ok ? 0u : 1u;
                     return n;
                 };
-                Step s = {r0, 0u, pre_ref};
+                Step s;
+                s.g = r0;
+                s.part = 0;
                 if (pre) {
-                    n_bad += pre_ref.ok ? 0u : 1u;
+                    s.ref = walk_behind(walk, (uint32_t)r0, (uint32_t)r1 - 1u, pre_ref);
 #pragma unroll
                     for (uint32_t k = 0; k < U; k++) va[k] = pre_v[k];
                 } else {
-                    uint32_t first = 0;
-                    s.ref = end(locate_begin((uint32_t)r0, first), r0);
+                    s.ref = walk_from(walk, (uint32_t)r0, (uint32_t)r1 - 1u);
                     load(s, va);
                 }
+                n_bad += s.ref.ok ? 0u : 1u;
                 for (;;) {
                     Step n = next(s);
                     load(n, vb);
