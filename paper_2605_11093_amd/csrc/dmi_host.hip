@@ -446,16 +446,14 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // per item, each gone after one round trip, keeps more loads in flight than the resident
     // few looping over many items.
     const bool flat = a.simple && !a.paged;
+    a.step_per_wave = a.read_once = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
     // hardware then hands out the work as workgroups retire, which evens out how unequally the
     // workgroups are served (the five that share a compute unit oldest first: with equal shares the
     // youngest ends 1.4 times as late as the oldest; and compute units differ by +-8 %), while
     // workgroups that stay for a whole tensor all have to end before the next tensor's can start,
-    // and a resident set shared among the tensors leaves every tensor's tail to a few workgroups
-    // (measured, 8 tensors of 10.2 k rows x 4096 bf16 -> fp8: 0.65 of the HBM peak with four items
-    // per workgroup, 0.62 with two or eight, 0.59 with the resident set shared; two tensors of
-    // 10.2 k x 14336: 0.65 against 0.60 and 0.59).
+    // and a resident set shared among the tensors leaves every tensor's tail to a few workgroups.
     constexpr uint64_t kItemsPerGroupInBatch = 4u;
     auto balanced = [nb, flat](uint64_t items) -> uint64_t {
         if (flat || items * nb <= kResident) return items;
@@ -488,15 +486,11 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
                                         (alone && upr <= 1024u && flat && rows >= 16384u));
         const uint64_t per_wave = alone && rows >= 4096u && upr <= 768u ? 2u : 1u;
         groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed);
-    } else if (upr >= kThreads && upr < 4u * kThreads && (4u * kThreads) % upr == 0) {
-        groups = balanced((listed + 4u * kThreads / upr - 1u) / (4u * kThreads / upr));      // 2 or 4 rows per work item
-    } else if (upr >= kThreads) {
-        // a row's last item is shorter than its others: a grid size that shares a factor with the
-        // items per row would give some workgroups only long items and others only short ones
-        const uint64_t cpr = (upr + 4u * kThreads - 1u) / (4u * kThreads);
-        groups = balanced(listed * cpr);
-        auto gcd = [](uint64_t x, uint64_t y) { while (y) { const uint64_t t = x % y; x = y; y = t; } return x; };
-        while (!flat && groups > 1u && gcd(groups, cpr) != 1u) groups++;
+    } else if (a.out_dtype && !a.paged && upr >= kLongRowUnits && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u))) {
+        // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
+        a.step_per_wave = 1;
+        a.read_once = listed * a.row_elems * dtype_size(a.src_dtype) * nb >= 256000000ull;
+        groups = (listed * ((upr + 255u) / 256u) + 3u) / 4u;
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
         const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;
@@ -636,6 +630,13 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
     // row: a launch whose row count must be able to change later (a replayable step) does not
     pl.decode = decode_kernel_applies(a, geo.vec16) && (one_row_each || fixed_row_count_ok);
     pl.row_map = pl.decode && !one_row_each && !index_mode;
+    // (in a replayable step only where dmi_step_update() keeps it so)
+    if ((pl.decode || fixed_row_count_ok) && !index_mode && one_row_each && sel->n_reqs) {
+        a.rows_consecutive = 1u;
+        a.row_first = sel->reqs[0].row_base + sel->reqs[0].tok_start;
+        for (uint32_t i = 1; a.rows_consecutive && i < sel->n_reqs; i++)
+            a.rows_consecutive = sel->reqs[i].row_base + sel->reqs[i].tok_start == a.row_first + i;
+    }
     if (pl.decode) {
         // the host knows this record exactly: geometry and header travel as kernel arguments
         // (the kernel itself puts sequence number and step id into the header)
@@ -645,10 +646,6 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
         a.off_sum = a.off_payload + pad64(a.payload_bytes);
         a.sum_arr = pad64(listed * 4u);
         a.record_bytes = ub;
-        a.rows_consecutive = sel->row_index_dev == nullptr && one_row_each;
-        a.row_first = sel->reqs[0].row_base + sel->reqs[0].tok_start;
-        for (uint32_t i = 1; a.rows_consecutive && i < sel->n_reqs; i++)
-            a.rows_consecutive = sel->reqs[i].row_base + sel->reqs[i].tok_start == a.row_first + i;
         a.hdr[0] = DMI_MAGIC;
         a.hdr[1] = 1u | (DMI_HEADER_BYTES << 16);
         a.hdr[6] = point_id;

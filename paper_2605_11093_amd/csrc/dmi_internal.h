@@ -10,6 +10,7 @@ constexpr uint32_t kThreads = 256;          // 4 wavefronts of 64 lanes per work
 constexpr uint32_t kMaxGrid = 1u << 22;     // workgroups per tensor of one launch
 constexpr uint32_t kLdsTableMax = 1024;     // request tables up to this size are cached in LDS
 constexpr uint32_t kDecodeMaxListed = 1024; // most rows a ragged selection may list to take the decode-shaped kernel
+constexpr uint32_t kLongRowUnits = 64;      // rows from this length on, stored without summaries: capture_rows_kernel
 constexpr uint32_t kMaxBatch = 128;         // most tensors one batched launch captures
 
 // One slot per launch, written by workgroup 0 of the launch: where the head stands
@@ -38,6 +39,8 @@ struct CommitSlot {
 // for it) and leaves it for the next launch.
 struct DevCtrl {
     uint64_t head[2];               // next free stream byte, double buffered by launch parity
+    uint64_t head_at[2];            // where in the ring that is (head modulo capacity, carried along: the division costs a
+                                    // lane that everybody waits for half a microsecond)
     uint64_t tail_for[2];           // the tail as the previous launch saw it, same scheme
     uint64_t tail;                  // drained-up-to mark as the last replayable step's begin launch read it
     uint64_t captured_records, captured_rows, captured_bytes;
@@ -148,6 +151,8 @@ struct CaptureArgs : CaptureKernelArgs {
                                     // output row, written by the host behind the request table
     uint32_t lds_bytes;
     uint32_t wave_rows;             // summaries of rows of more than 256 units: a wavefront per row, not a workgroup
+    uint32_t step_per_wave;         // capture_rows_kernel takes the launch: a wavefront per 256 units of a row
+    uint32_t read_once;             // it reads more than the memory-side cache holds
     uint32_t loose;                 // not on a 16-byte grid, but long enough for 16-byte units
     uint32_t limit_units;           // units per row by which a record's size is limited
     // record geometry and header words, filled by the host when it knows them exactly (no keep

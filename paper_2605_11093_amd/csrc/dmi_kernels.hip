@@ -187,24 +187,40 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef short s16x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ s16x2_t bf16x2_to_fp8x2(uint32_t w, s16x2_t acc, bool hi)
+__device__ __forceinline__ s16x2_t bf16x2_to_fp8x2(uint32_t w, s16x2_t acc, bool hi, uint32_t &nan)
 {
     const uint32_t mag = w & 0x7FFF7FFFu;
     const u16x2_t lim = {0x43E0u, 0x43E0u};                                   // 448.0
     const u16x2_t cl = __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, mag), lim);
     const uint32_t x = __builtin_bit_cast(uint32_t, cl) | (w & 0x80008000u);
     const bf16x2_t v = __builtin_bit_cast(bf16x2_t, x);
-    acc = hi ? __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(acc, v, 1.0f, true)
-             : __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(acc, v, 1.0f, false);
     const u16x2_t inf = {0x7F80u, 0x7F80u};
-    const u16x2_t over = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, mag), inf);
-    if (__builtin_bit_cast(uint32_t, over) != 0u) {                           // a NaN: sign | 0x7F
-        uint32_t pair = (uint32_t)(unsigned short)(hi ? acc.y : acc.x);
-        if (over.x) pair = (pair & 0xFF00u) | ((w >> 8) & 0x80u) | 0x7Fu;
-        if (over.y) pair = (pair & 0x00FFu) | (((w >> 24) & 0x80u) << 8) | 0x7F00u;
-        if (hi) acc.y = (short)pair; else acc.x = (short)pair;
+    nan |= __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, mag), inf));
+    return hi ? __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(acc, v, 1.0f, true)
+              : __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(acc, v, 1.0f, false);
+}
+
+// Eight bf16 -> eight fp8.
+__device__ __forceinline__ u32x2 bf16x8_to_fp8x8(u32x4 v)
+{
+    uint32_t nan = 0;
+    s16x2_t lo = {0, 0}, hi = {0, 0};
+    lo = bf16x2_to_fp8x2(v.x, lo, false, nan);
+    lo = bf16x2_to_fp8x2(v.y, lo, true, nan);
+    hi = bf16x2_to_fp8x2(v.z, hi, false, nan);
+    hi = bf16x2_to_fp8x2(v.w, hi, true, nan);
+    u32x2 o = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+    if (__builtin_expect(nan != 0u, 0)) {       // a NaN somewhere in the eight: sign | 0x7F
+        for (uint32_t i = 0; i < 8u; i++) {
+            const uint32_t word = i < 4u ? (i < 2u ? v.x : v.y) : (i < 6u ? v.z : v.w);
+            const uint32_t e = (i & 1u ? word >> 16 : word) & 0xFFFFu, sh = 8u * (i & 3u);
+            if ((e & 0x7FFFu) <= 0x7F80u) continue;
+            const uint32_t code = ((e >> 8) & 0x80u) | 0x7Fu;
+            if (i < 4u) o.x = (o.x & ~(0xFFu << sh)) | (code << sh);
+            else o.y = (o.y & ~(0xFFu << sh)) | (code << sh);
+        }
     }
-    return acc;
+    return o;
 }
 
 // bf16 -> fp16: exact widening to f32, then the hardware's round-to-nearest-even
@@ -254,16 +270,21 @@ __device__ __forceinline__ void ring_store(const RingW &w, uint64_t off, T v)
 // The same at any address, also across the end of the ring: rows that do not sit on a 16-byte grid are moved in
 // 16-byte units all the same (the memory system takes such accesses; only a unit that wraps is taken apart).
 template <bool LOOSE, typename T>
+__device__ __forceinline__ void store_out(uint8_t *p, T v)
+{
+    typedef T __attribute__((aligned(LOOSE ? 1 : sizeof(T)))) any_t;
+    __builtin_nontemporal_store(v, reinterpret_cast<any_t *>(p));
+}
+template <bool LOOSE, typename T>
 __device__ __forceinline__ void unit_store(const RingW &w, uint64_t off, T v)
 {
     if constexpr (!LOOSE) {
         ring_store<T>(w, off, v);
     } else {
-        typedef T __attribute__((aligned(1))) any_t;
         uint64_t p = w.base + off;
         if (p >= w.cap) p -= w.cap;
         if (p + sizeof(T) <= w.cap) {
-            __builtin_nontemporal_store(v, reinterpret_cast<any_t *>(w.ring + p));
+            store_out<true>(w.ring + p, v);
         } else {
             constexpr uint32_t n = sizeof(T) / 4u;
             const auto words = __builtin_bit_cast(typename UnitT<sizeof(T)>::T, v);
@@ -341,43 +362,34 @@ __device__ __forceinline__ float am_value(uint32_t m, uint32_t src_dtype)
     return widen16(m, src_dtype);
 }
 
+// One source unit as the record stores it.
+template <int ES_IN, int VEC, int OUT>
+__device__ __forceinline__ auto convert_unit(typename UnitT<ES_IN * VEC>::T v)
+{
+    if constexpr (OUT == OUT_FP16 && ES_IN == 2 && VEC == 8) {
+        const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+        uint32_t ow[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            ow[k] = bf16_to_fp16(wd[k] & 0xFFFFu) | (bf16_to_fp16(wd[k] >> 16) << 16);
+        return u32x4{ow[0], ow[1], ow[2], ow[3]};
+    } else if constexpr (OUT == OUT_FP8 && ES_IN == 2 && VEC == 8) {
+        return bf16x8_to_fp8x8(v);
+    } else if constexpr (OUT == OUT_FP16 && ES_IN == 2) {
+        return (uint16_t)bf16_to_fp16(v);
+    } else if constexpr (OUT == OUT_FP8 && ES_IN == 2) {
+        return (uint8_t)bf16_to_fp8(v);
+    } else {
+        static_assert(OUT == OUT_RAW, "a source of this size is stored as it is");
+        return v;
+    }
+}
+
 // Convert one source unit and store it.
 template <int ES_IN, int VEC, int OUT, bool LOOSE = false>
 __device__ __forceinline__ void emit_unit(const RingW &w, uint64_t out_off, typename UnitT<ES_IN * VEC>::T v)
 {
-    if constexpr (ES_IN == 2 && VEC == 8) {
-        uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-        if constexpr (OUT == OUT_RAW) {
-            unit_store<LOOSE, u32x4>(w, out_off, v);
-        } else if constexpr (OUT == OUT_FP16) {
-            u32x4 o;
-            uint32_t ow[4];
-#pragma unroll
-            for (int k = 0; k < 4; k++)
-                ow[k] = bf16_to_fp16(wd[k] & 0xFFFFu) | (bf16_to_fp16(wd[k] >> 16) << 16);
-            o.x = ow[0]; o.y = ow[1]; o.z = ow[2]; o.w = ow[3];
-            unit_store<LOOSE, u32x4>(w, out_off, o);
-        } else if constexpr (OUT == OUT_FP8) {
-            s16x2_t lo = {0, 0}, hi = {0, 0};
-            lo = bf16x2_to_fp8x2(wd[0], lo, false);
-            lo = bf16x2_to_fp8x2(wd[1], lo, true);
-            hi = bf16x2_to_fp8x2(wd[2], hi, false);
-            hi = bf16x2_to_fp8x2(wd[3], hi, true);
-            u32x2 o;
-            o.x = __builtin_bit_cast(uint32_t, lo);
-            o.y = __builtin_bit_cast(uint32_t, hi);
-            unit_store<LOOSE, u32x2>(w, out_off, o);
-        }
-    } else if constexpr (ES_IN == 4 && VEC == 4) {
-        if constexpr (OUT == OUT_RAW) unit_store<LOOSE, u32x4>(w, out_off, v);
-    } else if constexpr (ES_IN == 2) {      // one 2-byte element
-        const uint32_t b = v;
-        if constexpr (OUT == OUT_RAW) ring_store<uint16_t>(w, out_off, (uint16_t)b);
-        else if constexpr (OUT == OUT_FP16) ring_store<uint16_t>(w, out_off, (uint16_t)bf16_to_fp16(b));
-        else if constexpr (OUT == OUT_FP8) ring_store<uint8_t>(w, out_off, (uint8_t)bf16_to_fp8(b));
-    } else {                                // one 4-byte element
-        if constexpr (OUT == OUT_RAW) ring_store<uint32_t>(w, out_off, v);
-    }
+    if constexpr (OUT != OUT_NONE) unit_store<LOOSE && (VEC > 1)>(w, out_off, convert_unit<ES_IN, VEC, OUT>(v));
 }
 
 // Add one step's units (four per lane; a lane without that unit has zeros) to the row's partial summaries:
@@ -479,7 +491,7 @@ struct RowRef {
 // before any result is used, whether or not this launch needs it: loads issued together
 // cost one trip to memory, loads issued as their conditions become known cost one each.
 struct RawControl {
-    uint64_t head, tail_for, sp_seq, sp_step, sp_floor;
+    uint64_t head, head_at, tail_for, sp_seq, sp_step, sp_floor;
     uint64_t cap[3], drop[3];
     uint32_t sp_flags;
 };
@@ -496,6 +508,7 @@ __device__ __forceinline__ RawControl fetch_control(const DevCtrl *c, uint32_t p
     // a launch outside a replayable step reads (and ignores) the head of the control block instead
     const StepParams *spp = step ? step : reinterpret_cast<const StepParams *>(c);
     r.head = c->head[par];
+    r.head_at = c->head_at[par];
     r.tail_for = c->tail_for[par];
     r.sp_seq = spp->seq_base; r.sp_step = spp->step_id; r.sp_floor = spp->tail_floor;
     r.sp_flags = spp->flags;
@@ -517,6 +530,36 @@ __device__ __forceinline__ Control resolve_control(const RawControl &r, bool in_
     return o;
 }
 
+// How many of a launch's n records, all of one size, fit behind the head it found (a prefix of them).
+__device__ __forceinline__ uint64_t records_that_fit(uint64_t n, uint64_t head, uint64_t tail, uint64_t record_bytes,
+                                                     uint64_t cap, bool drop_newest)
+{
+    if (!drop_newest) return n;
+    const uint64_t used = head - tail, fit = used < cap ? (cap - used) / record_bytes : 0u;
+    return fit < n ? fit : n;
+}
+
+// One lane of a launch leaves head and counters for the next launch and fills the commit slot of its last record
+// (slot: NULL in a replayable step, where it follows from the sequence number).  Device memory only; it becomes visible to
+// the next launch, and to the copy that fetches the slot, with the kernel-end release.
+__device__ __forceinline__ void publish_launch(DevCtrl *c, uint32_t par, uint64_t head, uint64_t head_at, const uint64_t (&captured)[3],
+                                               const uint64_t (&dropped)[3], uint64_t record_bytes, uint64_t n_rows,
+                                               uint64_t n_fit, uint64_t n_drop, uint64_t cap, uint64_t last_seq, CommitSlot *slot)
+{
+    const uint64_t cap3[3] = {captured[0] + n_fit, captured[1] + n_fit * n_rows, captured[2] + n_fit * record_bytes};
+    const uint64_t drop3[3] = {dropped[0] + n_drop, dropped[1] + n_drop * n_rows, dropped[2] + n_drop * record_bytes};
+    if (n_drop) { c->dropped_records = drop3[0]; c->dropped_rows = drop3[1]; c->dropped_bytes = drop3[2]; }
+    if (n_fit) { c->captured_records = cap3[0]; c->captured_rows = cap3[1]; c->captured_bytes = cap3[2]; }
+    const uint64_t at = head_at + n_fit * record_bytes;     // (what is kept fits the ring: less than one lap further on)
+    c->head[par ^ 1u] = head + n_fit * record_bytes;
+    c->head_at[par ^ 1u] = at < cap ? at : at - cap;
+    CommitSlot *h = slot ? slot : &c->slots[last_seq % kCommitSlots];
+    h->head = head + n_fit * record_bytes;
+    h->captured_records = cap3[0]; h->captured_rows = cap3[1]; h->captured_bytes = cap3[2];
+    h->dropped_records = drop3[0]; h->dropped_rows = drop3[1]; h->dropped_bytes = drop3[2];
+    h->seq_plus1 = last_seq + 1u;
+}
+
 // Fetch every line of a by-value kernel argument block now, together, along with this
 // workgroup's entry of the batch block (its tensor and observation point).
 template <typename T>
@@ -531,9 +574,10 @@ __device__ __forceinline__ void touch_argument_lines(const T &a, const uint8_t *
 }
 
 // ---------------------------------------------------------------- capture kernel
-// Summaries per row: none; a workgroup per row; several rows per wavefront, at most 256 units each; a
-// wavefront per row (kernels of their own, or their registers would cost the others a workgroup per compute unit).
-enum SummMode { SUMM_NO = 0, SUMM_ROWS = 1, SUMM_SHORT = 2, SUMM_WAVE = 3 };
+// How a launch of the general kernel goes through its rows (kernels of their own, or the registers of one would cost the
+// others a workgroup per compute unit).  Without summaries: units dealt to lanes in order, whatever row they are of.
+// With summaries: a workgroup per row; several rows per wavefront, at most 256 units each; a wavefront per row.
+enum RowMode { ROWS_FLAT = 0, SUMM_ROWS = 1, SUMM_SHORT = 2, SUMM_WAVE = 3 };
 
 // The request table of a launch into the caller's memory, where the launch carries it: in the second block of
 // the kernel's own arguments, `first` bytes in.  Memory like any other to lanes that read entries of their own; and
@@ -553,12 +597,12 @@ static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) 
 // LOOSE: rows of at least 16 bytes that do not sit on a 16-byte grid.  They are moved in 16-byte units too,
 // a row's (or head's) last unit ending where the row does and so covering some elements a second time: those
 // are stored twice with the same value and left out of the second unit's sums.
-template <int ES_IN, int VEC, int OUT, int SUMM, typename SRC, bool LOOSE>
+template <int ES_IN, int VEC, int OUT, int MODE, typename SRC, bool LOOSE>
 __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const SRC b)
 {
     constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    __shared__ float row_sums[SUMM == SUMM_SHORT || SUMM == SUMM_WAVE ? 4 * 192 : 1];   // per wavefront: totals of 64 rows
+    __shared__ float row_sums[MODE == SUMM_SHORT || MODE == SUMM_WAVE ? 4 * 192 : 1];   // per wavefront: totals of 64 rows
     const uint32_t y = INTO ? 0u : blockIdx.y;      // which tensor of the batch this workgroup works on
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
@@ -614,9 +658,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                                            a.drop_newest);
         seq = ct.seq;
         for (int i = 0; i < 3; i++) { cnt_cap[i] = raw.cap[i]; cnt_drop[i] = raw.drop[i]; }
-        const uint64_t base = ct.head % a.cap;
-        lds[m.bcast + 4] = (uint32_t)base;
-        lds[m.bcast + 5] = (uint32_t)(base >> 32);
+        lds[m.bcast + 4] = (uint32_t)raw.head_at;
+        lds[m.bcast + 5] = (uint32_t)(raw.head_at >> 32);
         lds[m.bcast + 0] = (uint32_t)ct.head;
         lds[m.bcast + 1] = (uint32_t)(ct.head >> 32);
         lds[m.bcast + 2] = (uint32_t)ct.tail;
@@ -699,36 +742,34 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     //    item's rows do not depend on anything computed above, so their loads are issued
     //    now and travel together with the control fetch instead of behind it
     constexpr uint32_t U = 4;                               // loads in flight per lane
-    constexpr uint32_t CH = U * kThreads;                   // units per long-row work item
-    const uint32_t cpr = (a.units_per_row + CH - 1u) / CH;  // long-row items per row
+    constexpr uint32_t CH = U * kThreads;                   // units of one step of a workgroup
+    const uint32_t cpr = (a.units_per_row + CH - 1u) / CH;  // SUMM_ROWS: steps of a workgroup per row
+    const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
+    const uint32_t wave_at = blockIdx.x * (kThreads / 64u) + wv, n_waves = gridDim.x * (kThreads / 64u);
     // summaries: the lanes that share a row; lane l takes units l, l + row_lanes, ..., four at a time
-    const uint32_t row_lanes = SUMM ? a.row_lanes : kThreads;
+    const uint32_t row_lanes = MODE == ROWS_FLAT ? kThreads : a.row_lanes;
     bool first_row_inline = false;
     if constexpr (INTO) first_row_inline = b.n_words != 0u;
     unit_t pre_v[U];
     RowRef pre_ref = {nullptr, 0};
     bool pre = false;
-    const bool multi_row_items = a.units_per_row < CH && CH % a.units_per_row == 0u;
     // (not in a launch of several records some of which may turn out to be dropped: a dropped
     // record's rows would have been read for nothing)
     const bool may_drop_some = a.n_batch > 1u && (a.drop_newest != 0u || a.step != nullptr);
-    if (simple && !a.paged && !may_drop_some && SUMM != SUMM_SHORT &&
-        (SUMM || (OUT != OUT_NONE && a.units_per_row >= kThreads && !multi_row_items))) {
-        uint32_t g, c_begin = SUMM == SUMM_WAVE ? lane : tid;
-        if constexpr (SUMM == SUMM_WAVE) g = (blockIdx.x * (kThreads / 64u) + wave) * ((n_reqs - 1u) / (gridDim.x * (kThreads / 64u)) + 1u);
-        else if constexpr (SUMM != SUMM_NO) g = blockIdx.x;
-        else { g = blockIdx.x / cpr; c_begin = (blockIdx.x - g * cpr) * CH + tid; }
+    if (simple && !a.paged && !may_drop_some && (MODE == SUMM_ROWS || MODE == SUMM_WAVE)) {
+        const uint32_t g = MODE == SUMM_WAVE ? wave_at * ((n_reqs - 1u) / n_waves + 1u) : blockIdx.x;
+        const uint32_t c_begin = MODE == SUMM_WAVE ? lane : tid;
         if (g < n_reqs) {
             int64_t row;
             if (index_mode) row = (int64_t)a.row_index[g];
-            else if (INTO && SUMM != SUMM_WAVE && first_row_inline) row = (int64_t)inline_table_uniform(sizeof(CaptureKernelArgs))[4u * n_reqs + g];
+            else if (INTO && MODE == SUMM_ROWS && first_row_inline) row = (int64_t)inline_table_uniform(sizeof(CaptureKernelArgs))[4u * n_reqs + g];
             else row = (int64_t)row_first(g);
             pre_ref.ok = row >= 0 && row < a.n_src_rows;
             pre_ref.base = src + (pre_ref.ok ? row : 0) * a.row_stride_b;
 #pragma unroll
             for (uint32_t k = 0; k < U; k++) {
                 const uint32_t c = c_begin + k * row_lanes;
-                const bool want = pre_ref.ok && c < a.units_per_row && (SUMM != SUMM_ROWS || tid < row_lanes);
+                const bool want = pre_ref.ok && c < a.units_per_row && (MODE != SUMM_ROWS || tid < row_lanes);
                 const uint8_t *p = want ? pre_ref.base + elem_in_seg(c) * ES_IN : reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
                 pre_v[k] = *(global_unit_t *)p;     // zeroed where it is used if not wanted
             }
@@ -777,6 +818,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         // copies still has to reach the next launch
         if (publisher) {
             a.ctrl->head[par ^ 1u] = head0;
+            a.ctrl->head_at[par ^ 1u] = raw.head_at;
             a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
         }
         return;
@@ -790,40 +832,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     //      Everything here is device memory; it becomes visible to the next launch and to the copy
     //      that fetches the slot with the kernel-end release.
     if (publisher) {
-        DevCtrl *c = a.ctrl;
-        const uint64_t nb_rec = gridDim.y;
-        uint64_t n_fit = nb_rec;
-        if (drop_newest) {
-            const uint64_t used = head0 - tail;
-            n_fit = used < a.cap ? (a.cap - used) / record_bytes : 0u;
-            n_fit = n_fit < nb_rec ? n_fit : nb_rec;
-        }
-        if (a.force_drop) n_fit = 0;
-        const uint64_t n_drop = nb_rec - n_fit + a.n_tail_drop;
-        const uint64_t new_head = head0 + n_fit * record_bytes;
-        if (n_drop) {
-            cnt_drop[0] += n_drop; cnt_drop[1] += n_drop * n_rows; cnt_drop[2] += n_drop * record_bytes;
-            c->dropped_records = cnt_drop[0]; c->dropped_rows = cnt_drop[1]; c->dropped_bytes = cnt_drop[2];
-        }
-        if (n_fit) {
-            cnt_cap[0] += n_fit; cnt_cap[1] += n_fit * n_rows; cnt_cap[2] += n_fit * record_bytes;
-            c->captured_records = cnt_cap[0]; c->captured_rows = cnt_cap[1]; c->captured_bytes = cnt_cap[2];
-        }
-        c->head[par ^ 1u] = new_head;
-        c->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
-        const uint64_t last_seq = seq + nb_rec + a.n_tail_drop - 1u;
+        const uint64_t last_seq = seq + gridDim.y + a.n_tail_drop - 1u;
+        a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
         // (a loop of one lane over a uniform index: the points come straight out of the argument block)
         for (uint32_t i = 0; i < a.n_tail_drop; i++)
-            atomicAdd(&c->point_drops[b.point[nb_rec + i] & 4095u], 1u);
-        CommitSlot *h = a.step ? &c->slots[last_seq % kCommitSlots] : a.cslot;
-        h->head = new_head;
-        h->captured_records = cnt_cap[0];
-        h->captured_rows = cnt_cap[1];
-        h->captured_bytes = cnt_cap[2];
-        h->dropped_records = cnt_drop[0];
-        h->dropped_rows = cnt_drop[1];
-        h->dropped_bytes = cnt_drop[2];
-        h->seq_plus1 = last_seq + 1u;
+            atomicAdd(&a.ctrl->point_drops[b.point[gridDim.y + i] & 4095u], 1u);
+        const uint64_t n_fit = a.force_drop ? 0u : records_that_fit(gridDim.y, head0, tail, record_bytes, a.cap, drop_newest);
+        publish_launch(a.ctrl, par, head0, raw.head_at, cnt_cap, cnt_drop, record_bytes, n_rows, n_fit,
+                       gridDim.y - n_fit + a.n_tail_drop, a.cap, last_seq, a.step ? nullptr : a.cslot);
     }
     if (dropped && blockIdx.x == 0 && tid == kCtlTid)
         atomicAdd(&a.ctrl->point_drops[point_id & 4095u], 1u);
@@ -850,7 +866,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         uint32_t slot;
     };
     // (where a wavefront works on one row at a time, all of this but a load's result is scalar)
-    constexpr bool ROW_PER_WAVE = SUMM == SUMM_WAVE || SUMM == SUMM_ROWS;
+    constexpr bool ROW_PER_WAVE = MODE == SUMM_WAVE || MODE == SUMM_ROWS;
     auto rd = [&](uint32_t i) -> uint32_t { return ROW_PER_WAVE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)L[i]) : L[i]; };
     // Row g's request, for all lanes at once: they look at 64 requests (or 64 evenly spaced ones of more) together: one trip
     // through LDS and a ballot where a binary search takes five of them for 32 requests.
@@ -1013,7 +1029,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto zero_unless = [](bool keep, unit_t v) -> unit_t { return keep ? v : unit_t{}; };
 
     // Row totals of a wavefront's 64 rows at most, [from, upto), from its part of LDS to the record.
-    float *const stash = row_sums + (SUMM == SUMM_SHORT || SUMM == SUMM_WAVE ? wave * 192u : 0u);       // [3][64]
+    float *const stash = row_sums + (MODE == SUMM_SHORT || MODE == SUMM_WAVE ? wave * 192u : 0u);       // [3][64]
     auto flush_totals = [&](uint64_t from, uint64_t upto) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1071,170 +1087,82 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             }
         }
 
-        if constexpr (SUMM == SUMM_NO) {
+        if constexpr (MODE == ROWS_FLAT) {
             if constexpr (OUT != OUT_NONE) {
-                if (VEC > 1 && a.units_per_row >= kThreads) {
-                    // ---- long rows: a work item is 1024 consecutive units: a quarter or more of one
-                    //      row, or 2 / 4 whole rows of 512 / 256 units; rows are located once per
-                    //      item, not per unit.  Software pipelined: the next item's 4 loads per lane
-                    //      are in flight while this one is converted and stored.
-                    const uint32_t rpi = (a.units_per_row < CH && CH % a.units_per_row == 0u)
-                                             ? CH / a.units_per_row : 1u;          // rows per item
-                    const uint64_t n_items = rpi > 1u ? ((uint64_t)n_rows + rpi - 1u) / rpi
-                                                      : (uint64_t)n_rows * cpr;
-                    // unit k of this lane in item `it`: where it goes, loaded value
-                    auto fetch = [&](uint64_t it, unit_t (&v)[U], uint64_t (&pos)[U], bool (&live)[U], uint32_t &okm) {
-                        RowRef ref = {nullptr, 0}, refs[U];
-                        uint32_t g_prev = 0xFFFFFFFFu, cs[U];
-                        okm = 0;
-                        // first where every unit comes from (a row's place may take a load of its own to
-                        // find), then all the unit loads together
-#pragma unroll
-                        for (uint32_t k = 0; k < U; k++) {
-                            uint32_t g, c;
-                            if (rpi > 1u) {
-                                const uint32_t idx = k * kThreads + tid;
-                                const uint32_t rk = idx >> a.upr_shift;        // units_per_row is 256 or 512
-                                g = (uint32_t)it * rpi + rk;
-                                c = idx - (rk << a.upr_shift);
-                            } else {
-                                g = cpr == 1u ? (uint32_t)it : (uint32_t)(it / cpr);
-                                c = (uint32_t)(it - (uint64_t)g * cpr) * CH + k * kThreads + tid;
+                // ---- units dealt flat: the n_rows x units_per_row units are dealt to lanes in order,
+                //      so stores stay fully coalesced; 4 loads in flight per lane.
+                //      A wavefront's 64 units of one slice lie in at most 64/upr + 2 rows.  When
+                //      the rows of its four slices fit the 64 lanes, each lane locates one row
+                //      (all of them in a single pass) and every unit picks up its row's place by
+                //      shuffle: locating a row costs on the order of a hundred instructions, and
+                //      done per unit that, not memory, is what the launch spends its time on.
+                const uint32_t total = (uint32_t)((uint64_t)n_rows * a.units_per_row);  // host keeps it below 2^32
+                const uint32_t upr = a.units_per_row;
+                auto row_of = [&](uint32_t u) { return a.upr_shift < 32u ? u >> a.upr_shift : u / upr; };
+                const bool shared_locate = 64u / upr + 2u <= 16u;
+                const uint32_t slice_stride = gridDim.x * kThreads;
+                for (uint64_t t0 = (uint64_t)blockIdx.x * kThreads; t0 < total; t0 += (uint64_t)slice_stride * U) {
+                    unit_t v[U];
+                    bool live[U], okk[U];
+                    uint32_t my_lo = 0, my_hi = 0, my_ok = 0, my_first = 0;
+                    if (shared_locate) {
+                        const uint32_t sl = lane >> 4, j = lane & 15u;
+                        const uint64_t us = t0 + (uint64_t)sl * slice_stride + wave * 64u;
+                        if (us < total) {
+                            const uint32_t ue = us + 63u < total ? (uint32_t)us + 63u : total - 1u;
+                            my_first = row_of((uint32_t)us);
+                            const uint32_t g = my_first + j;
+                            if (g <= row_of(ue)) {
+                                const RowRef ref = locate(g);
+                                my_lo = (uint32_t)(uintptr_t)ref.base;
+                                my_hi = (uint32_t)((uintptr_t)ref.base >> 32);
+                                my_ok = ref.ok ? 1u : 0u;
+                                // a bad row is counted where its first unit lies
+                                const uint64_t fu = (uint64_t)g * upr;
+                                if (!ref.ok && fu >= us && fu <= ue)
+                                    atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
                             }
-                            live[k] = g < n_rows && c < a.units_per_row;
-                            pos[k] = out_at(g, c);
-                            if (live[k] && g != g_prev) {
-                                ref = locate(g);
-                                g_prev = g;
-                                if (!ref.ok && c == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-                            }
-                            refs[k] = ref;
-                            cs[k] = c;
-                        }
-                        asm volatile("" ::: "memory");      // keep the two phases apart
-#pragma unroll
-                        for (uint32_t k = 0; k < U; k++) {
-                            const bool want = live[k] && refs[k].ok != 0;
-                            okm |= want ? 1u << k : 0u;
-                            v[k] = load_unit(refs[k], cs[k], want);
-                        }
-                    };
-                    uint64_t it = blockIdx.x;
-                    if (it < n_items) {
-                        unit_t v[U];
-                        uint64_t pos[U];
-                        bool live[U];
-                        uint32_t okm = 0;
-                        if (pre) {      // decode-shaped, rows of >= 1024 units handled one per item
-                            const uint32_t g = cpr == 1u ? (uint32_t)it : (uint32_t)(it / cpr);
-                            const uint32_t c0 = (uint32_t)(it - (uint64_t)g * cpr) * CH + tid;
-#pragma unroll
-                            for (uint32_t k = 0; k < U; k++) {
-                                const uint32_t c = c0 + k * kThreads;
-                                v[k] = pre_v[k];
-                                live[k] = c < a.units_per_row;
-                                okm |= live[k] && pre_ref.ok ? 1u << k : 0u;
-                                pos[k] = out_at(g, c);
-                            }
-                            if (!pre_ref.ok && c0 == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-                        } else {
-                            fetch(it, v, pos, live, okm);
-                        }
-                        for (;;) {
-                            const uint64_t nxt = it + gridDim.x;
-                            const bool more = nxt < n_items;
-                            unit_t v_n[U];
-                            uint64_t pos_n[U];
-                            bool live_n[U];
-                            uint32_t okm_n = 0;
-                            if (more) fetch(nxt, v_n, pos_n, live_n, okm_n);
-#pragma unroll
-                            for (uint32_t k = 0; k < U; k++)
-                                if (live[k])
-                                    emit_unit<ES_IN, VEC, OUT, LOOSE>(w, pos[k], zero_unless((okm >> k) & 1u, v[k]));
-                            if (!more) break;
-                            it = nxt;
-                            okm = okm_n;
-#pragma unroll
-                            for (uint32_t k = 0; k < U; k++) { v[k] = v_n[k]; pos[k] = pos_n[k]; live[k] = live_n[k]; }
                         }
                     }
-                } else {
-                    // ---- short rows: the n_rows x units_per_row units are dealt to lanes in order,
-                    //      so stores stay fully coalesced; 4 loads in flight per lane.
-                    //      A wavefront's 64 units of one slice lie in at most 64/upr + 2 rows.  When
-                    //      the rows of its four slices fit the 64 lanes, each lane locates one row
-                    //      (all of them in a single pass) and every unit picks up its row's place by
-                    //      shuffle: locating a row costs on the order of a hundred instructions, and
-                    //      done per unit that, not memory, is what the launch spends its time on.
-                    const uint32_t total = (uint32_t)((uint64_t)n_rows * a.units_per_row);  // host keeps it below 2^32
-                    const uint32_t upr = a.units_per_row;
-                    auto row_of = [&](uint32_t u) { return a.upr_shift < 32u ? u >> a.upr_shift : u / upr; };
-                    const bool shared_locate = 64u / upr + 2u <= 16u;
-                    const uint32_t slice_stride = gridDim.x * kThreads;
-                    for (uint64_t t0 = (uint64_t)blockIdx.x * kThreads; t0 < total; t0 += (uint64_t)slice_stride * U) {
-                        unit_t v[U];
-                        bool live[U], okk[U];
-                        uint32_t my_lo = 0, my_hi = 0, my_ok = 0, my_first = 0;
+#pragma unroll
+                    for (uint32_t k = 0; k < U; k++) {
+                        const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
+                        live[k] = u < total;
+                        const uint32_t u32 = live[k] ? (uint32_t)u : total - 1u;
+                        const uint32_t g = row_of(u32);
+                        const uint32_t c = u32 - g * upr;
+                        RowRef ref;
                         if (shared_locate) {
-                            const uint32_t sl = lane >> 4, j = lane & 15u;
-                            const uint64_t us = t0 + (uint64_t)sl * slice_stride + wave * 64u;
-                            if (us < total) {
-                                const uint32_t ue = us + 63u < total ? (uint32_t)us + 63u : total - 1u;
-                                my_first = row_of((uint32_t)us);
-                                const uint32_t g = my_first + j;
-                                if (g <= row_of(ue)) {
-                                    const RowRef ref = locate(g);
-                                    my_lo = (uint32_t)(uintptr_t)ref.base;
-                                    my_hi = (uint32_t)((uintptr_t)ref.base >> 32);
-                                    my_ok = ref.ok ? 1u : 0u;
-                                    // a bad row is counted where its first unit lies
-                                    const uint64_t fu = (uint64_t)g * upr;
-                                    if (!ref.ok && fu >= us && fu <= ue)
-                                        atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-                                }
+                            // executed by all 64 lanes: a shuffle reads nothing useful from a lane that is off
+                            const uint32_t first_k = __shfl(my_first, (int)(k << 4), 64);
+                            const int src = (int)(((k << 4) + (g - first_k)) & 63u);
+                            const uint32_t lo = __shfl(my_lo, src, 64), hi = __shfl(my_hi, src, 64);
+                            ref.ok = __shfl(my_ok, src, 64);
+                            ref.base = reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+                            if (!live[k]) ref.ok = 0;
+                        } else {
+                            ref.base = nullptr;
+                            ref.ok = 0;
+                            if (live[k]) {
+                                ref = locate(g);
+                                if (!ref.ok && c == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
                             }
                         }
+                        okk[k] = live[k] && ref.ok != 0;
+                        v[k] = load_unit(ref, c, okk[k]);
+                    }
 #pragma unroll
-                        for (uint32_t k = 0; k < U; k++) {
-                            const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
-                            live[k] = u < total;
-                            const uint32_t u32 = live[k] ? (uint32_t)u : total - 1u;
-                            const uint32_t g = row_of(u32);
-                            const uint32_t c = u32 - g * upr;
-                            RowRef ref;
-                            if (shared_locate) {
-                                // executed by all 64 lanes: a shuffle reads nothing useful from a lane that is off
-                                const uint32_t first_k = __shfl(my_first, (int)(k << 4), 64);
-                                const int src = (int)(((k << 4) + (g - first_k)) & 63u);
-                                const uint32_t lo = __shfl(my_lo, src, 64), hi = __shfl(my_hi, src, 64);
-                                ref.ok = __shfl(my_ok, src, 64);
-                                ref.base = reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
-                                if (!live[k]) ref.ok = 0;
-                            } else {
-                                ref.base = nullptr;
-                                ref.ok = 0;
-                                if (live[k]) {
-                                    ref = locate(g);
-                                    if (!ref.ok && c == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-                                }
-                            }
-                            okk[k] = live[k] && ref.ok != 0;
-                            v[k] = load_unit(ref, c, okk[k]);
-                        }
-#pragma unroll
-                        for (uint32_t k = 0; k < U; k++) {
-                            const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
-                            const uint32_t g = LOOSE ? row_of((uint32_t)u) : 0u;    // (else a record's units just follow each other)
-                            if (live[k])
-                                emit_unit<ES_IN, VEC, OUT, LOOSE>(
-                                    w, LOOSE ? out_at(g, (uint32_t)u - g * upr) : off_payload + u * NB_OUT,
-                                    zero_unless(okk[k], v[k]));
-                        }
+                    for (uint32_t k = 0; k < U; k++) {
+                        const uint64_t u = t0 + (uint64_t)k * slice_stride + tid;
+                        const uint32_t g = LOOSE ? row_of((uint32_t)u) : 0u;    // (else a record's units just follow each other)
+                        if (live[k])
+                            emit_unit<ES_IN, VEC, OUT, LOOSE>(
+                                w, LOOSE ? out_at(g, (uint32_t)u - g * upr) : off_payload + u * NB_OUT,
+                                zero_unless(okk[k], v[k]));
                     }
                 }
             }
-        } else if constexpr (SUMM == SUMM_SHORT) {
+        } else if constexpr (MODE == SUMM_SHORT) {
             // ---- summaries of short rows (up to 256 units): 4 to 64 lanes share a row, each with up to four
             //      of its units, so one step of a wavefront is 64 / row_lanes whole rows and a row costs one
             //      reduction over few lanes (a row of 32 units used to take a wavefront of its own, half of its
@@ -1248,10 +1176,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             const uint32_t lpr = row_lanes, lg = 31u - (uint32_t)__builtin_clz(lpr);
             const uint32_t rpi = 64u >> lg;                             // rows per step, at most 16
             const uint32_t sub_r = lane >> lg, l_r = lane & (lpr - 1u);
-            const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
-            const uint32_t n_waves = gridDim.x * (kThreads / 64u);
             const uint32_t per = n_rows ? ((n_rows - 1u) / n_waves / rpi + 1u) * rpi : 0u;
-            const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
+            const uint64_t r0 = (uint64_t)wave_at * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
             // where this lane's units lie in a row does not change from row to row
             bool in_row[U];
@@ -1337,7 +1263,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 }
                 if (n_bad) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
             }
-        } else if constexpr (SUMM == SUMM_WAVE) {
+        } else if constexpr (MODE == SUMM_WAVE) {
             // ---- summaries, a wavefront per row: where a launch has rows enough to fill the GPU that way, a row costs no
             //      barrier and a workgroup lives for four rows or more instead of one, so its prologue weighs less.
             //      The sums are taken in the order in which a workgroup takes them (the decode-shaped kernel, and
@@ -1346,10 +1272,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             //      before the step in front of it is worked on.
             //      Bound: HBM reads.  80 x 256 rows of 512 units, statistics only: 64 -> 35 us
             //      (4.8 TB/s); plan_grid() has more figures, and says where the line lies.
-            const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
-            const uint32_t n_waves = gridDim.x * (kThreads / 64u);
             const uint32_t per = n_rows ? (n_rows - 1u) / n_waves + 1u : 0u;
-            const uint64_t r0 = ((uint64_t)blockIdx.x * (kThreads / 64u) + wv) * per;
+            const uint64_t r0 = (uint64_t)wave_at * per;
             const uint64_t r1 = r0 + per < n_rows ? r0 + per : n_rows;
             const uint32_t parts = row_lanes >> 6;
             auto wave_unit = [&](uint32_t part, uint32_t t) { return part * 64u + lane + t * row_lanes; };
@@ -1674,10 +1598,9 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
                                            a.flags & kDecDropNewest);
         seq = ct.seq;
         for (int i = 0; i < 3; i++) { cnt_cap[i] = raw.cap[i]; cnt_drop[i] = raw.drop[i]; }
-        const uint64_t base = ct.head % a.cap;
         sh[0] = (uint32_t)ct.head;  sh[1] = (uint32_t)(ct.head >> 32);
         sh[2] = (uint32_t)ct.tail;  sh[3] = (uint32_t)(ct.tail >> 32);
-        sh[4] = (uint32_t)base;     sh[5] = (uint32_t)(base >> 32);
+        sh[4] = (uint32_t)raw.head_at;  sh[5] = (uint32_t)(raw.head_at >> 32);
         sh[6] = ct.flags;
         sh[24] = (uint32_t)ct.seq;      sh[25] = (uint32_t)(ct.seq >> 32);
         sh[26] = (uint32_t)ct.step_id;  sh[27] = (uint32_t)(ct.step_id >> 32);
@@ -1714,6 +1637,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     if (!INTO && (flags & kStepSkip)) {    // sampled-out replay: pass head and tail on, capture nothing
         if (publisher) {
             a.ctrl->head[par ^ 1u] = head0;
+            a.ctrl->head_at[par ^ 1u] = raw.head_at;
             a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
         }
         return;
@@ -1755,32 +1679,10 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 
     if (meta_wg) {
         if (publisher) {
-            DevCtrl *c = a.ctrl;
-            const uint64_t nb_rec = gridDim.y;
-            uint64_t n_fit = nb_rec;
-            if (drop_newest) {
-                const uint64_t used = head0 - tail;
-                n_fit = used < a.cap ? (a.cap - used) / record_bytes : 0u;
-                n_fit = n_fit < nb_rec ? n_fit : nb_rec;
-            }
-            const uint64_t n_drop = nb_rec - n_fit;
-            const uint64_t new_head = head0 + n_fit * record_bytes;
-            if (n_drop) {
-                cnt_drop[0] += n_drop; cnt_drop[1] += n_drop * n_rows; cnt_drop[2] += n_drop * record_bytes;
-                c->dropped_records = cnt_drop[0]; c->dropped_rows = cnt_drop[1]; c->dropped_bytes = cnt_drop[2];
-            }
-            if (n_fit) {
-                cnt_cap[0] += n_fit; cnt_cap[1] += n_fit * n_rows; cnt_cap[2] += n_fit * record_bytes;
-                c->captured_records = cnt_cap[0]; c->captured_rows = cnt_cap[1]; c->captured_bytes = cnt_cap[2];
-            }
-            c->head[par ^ 1u] = new_head;
-            c->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
-            const uint64_t last_seq = seq + nb_rec - 1u;
-            CommitSlot *h = a.step ? &c->slots[last_seq % kCommitSlots] : a.cslot;
-            h->head = new_head;
-            h->captured_records = cnt_cap[0]; h->captured_rows = cnt_cap[1]; h->captured_bytes = cnt_cap[2];
-            h->dropped_records = cnt_drop[0]; h->dropped_rows = cnt_drop[1]; h->dropped_bytes = cnt_drop[2];
-            h->seq_plus1 = last_seq + 1u;
+            a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
+            const uint64_t n_fit = records_that_fit(gridDim.y, head0, tail, record_bytes, a.cap, drop_newest);
+            publish_launch(a.ctrl, par, head0, raw.head_at, cnt_cap, cnt_drop, record_bytes, n_rows, n_fit, gridDim.y - n_fit, a.cap,
+                           seq + gridDim.y - 1u, a.step ? nullptr : a.cslot);
         }
         if (dropped && tid == kCtlTid) atomicAdd(&a.ctrl->point_drops[point_id & 4095u], 1u);
         if (dropped) return;
@@ -1848,6 +1750,274 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     }
 }
 
+// ---------------------------------------------------------------- rows stored, no summaries
+// Dense rows of at least kLongRowUnits units, stored as they are or converted: the largest records there are (ragged
+// prompts, the tensors of a batch).  A wavefront takes up to 256 consecutive units of one row, and everything but its
+// lanes' places in them is the same for the whole wavefront and kept in scalar registers.
+// Bound: HBM.  What a launch loses on top is the time until its first loads leave, and the unequal ends of its
+// workgroups.  Time stamps in the general kernel, which took these rows before, showed 5 us in front of the first loads of
+// a full GPU where memory answers in 0.6: a thousand instructions (fetched cold), scans and searches through LDS, a
+// barrier.  So there is hardly anything in front of the loads here: each wavefront scans the request table by itself
+// (at most 64 requests, one per lane; none at all where requests have one row each), there is no LDS and no
+// barrier, and header, table and publishing are a workgroup of their own behind the others (the last blockIdx.x), whose
+// code the others do not run through.  And there is one step to a wavefront, many more workgroups than fit at once, and no
+// software pipeline: seven workgroups per compute unit hide each other's trips (54 registers; two steps in
+// a pipeline take 93, five workgroups).  Steps per wavefront 1 / 2 / 4: 19.1 / 20.4 / 23.7 us; units per lane 2 / 4 / 8:
+// 21.8 / 18.8 / 20.0 (9.3 k rows x 4096 bf16 -> fp8).
+// Kernel times, before and after: bf16 -> fp8, 32 requests: 9.3 k x 4096 (every fourth token) 23.5 -> 18.8 us (6.1 TB/s),
+// 9.3 k x 14336 85 -> 69.4 (5.8 TB/s), 37 k x 4096 93 -> 79, 9.3 k x 2304 25 -> 13, 2000 x 4096 9.1 -> 5.9; raw: 9.3 k x 4096
+// 28.6 -> 24.2, 9.3 k x 14336 106 -> 92; one row per request, 80 tensors of 256 x 8192 raw in one launch 111 -> 107.
+// ONCE: launches that read more than the 256 MB memory-side cache holds do so past it (non-temporal loads): 9.3 k x 14336
+// 73.4 -> 69.4 us; where what is read may still be there from the kernel that wrote it they lose (9.3 k x 4096: 18.8
+// and 21.8), and between 133 and 256 MB it depends on what ran before.
+// Shorter rows are dealt flat by the general kernel (20 k x 256: 6.2 us there, 10.6 here; from 64 units on: 3000 x 512
+// 5.0 and 4.1, 9.3 k x 512 raw 6.0 and 5.3, 20 k x 640 raw 11.6 and 10.0, to fp8 11.0 and 11.7, 9.3 k x 1536 11.1 and 9.4), and
+// so are rows of more than 64 ragged requests.
+struct RowsArgs {
+    // lines 0 and 1: what the row workgroups need
+    int64_t row_stride_b, n_src_rows;
+    const uint4 *req_table;
+    const uint32_t *row0;           // first source row of each request
+    const uint8_t *keep_mask;
+    const int32_t *row_index;
+    uint8_t *ring;
+    uint64_t cap;
+    DevCtrl *ctrl;
+    const StepParams *step;
+    uint64_t tail_floor;
+    uint32_t flags;                 // kRows*
+    uint32_t n_reqs, units_per_row, row_elems;
+    uint32_t parts, parts_magic, parts_shift;   // steps per row; x / parts = (x * parts_magic >> 32) >> parts_shift, x below 2^31
+    uint32_t row_groups;            // workgroups that move rows (gridDim.x - 1)
+    uint32_t row_first, pad;
+    // line 2: header and publishing
+    uint64_t seq, step_id;
+    CommitSlot *cslot;
+    const uint64_t *tail_src;
+    uint32_t node, hdr7, rank_tag, n_tail_drop;
+};
+static_assert(sizeof(RowsArgs) % 16u == 0, "the block behind it is read as 16-byte entries");
+constexpr uint32_t kRowsSimple = 1u;        // no keep vector, one row per request
+constexpr uint32_t kRowsConsecutive = 2u;   // and request i's row is row_first + i
+constexpr uint32_t kRowsDropNewest = 4u, kRowsParIn = 8u;
+
+template <int ES_IN, int OUT, typename SRC, bool LOOSE, bool ONCE>
+__global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a, const SRC b)
+{
+    constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
+    constexpr int VEC = 16 / ES_IN;
+    constexpr uint32_t U = 4, SU = U * 64u;                 // units of a step
+    constexpr uint32_t NB_IN = 16u, NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>(), ES_OUT = NB_OUT / VEC;
+    typedef typename UnitT<ES_IN * VEC>::T unit_t;
+    typedef __attribute__((address_space(1))) const unit_t __attribute__((aligned(LOOSE ? ES_IN : ES_IN * VEC))) global_unit_t;
+    typedef __attribute__((address_space(4))) const uint64_t constant_u64;
+    typedef __attribute__((address_space(4))) const int32_t constant_i32;
+    const uint32_t y = INTO ? 0u : blockIdx.y;
+    const uint8_t *const src = b.src[y];
+    const uint32_t lane = threadIdx.x & 63u, wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool simple = (a.flags & kRowsSimple) != 0u, meta = blockIdx.x == a.row_groups;
+    const bool index_mode = a.row_index != nullptr;
+    const uint32_t n_reqs = a.n_reqs, par = a.flags & kRowsParIn ? 1u : 0u;
+
+    // -- control words, the same for everybody: through the scalar cache
+    uint64_t head0 = 0, at0 = 0, tail = 0;
+    uint32_t policy = 0;
+    if constexpr (!INTO) {
+        head0 = ((constant_u64 *)a.ctrl->head)[par];
+        at0 = ((constant_u64 *)a.ctrl->head_at)[par];
+        policy = a.flags & kRowsDropNewest ? kStepDropNewest : 0u;
+        tail = a.tail_floor;
+        if (a.step) {
+            policy = (uint32_t)((constant_u64 *)a.step)[3];
+            tail = ((constant_u64 *)a.step)[2];
+        }
+        if (policy & kStepDropNewest) {
+            const uint64_t seen = ((constant_u64 *)a.ctrl->tail_for)[par];
+            tail = seen > tail ? seen : tail;
+        }
+    }
+
+    // -- the request table, a request per lane: kept rows in front of it, first source row, rows between two of its rows
+    u32x4 entry = {0u, 0u, 0u, 0u};
+    uint32_t first_row = 0, kept = 0, upto = 0, listed_upto = 0;
+    uint32_t n_rows = n_reqs;
+    if (!simple) {
+        const uint32_t r = lane < n_reqs ? lane : 0u;
+        bool have = false;
+        if constexpr (INTO) {
+            if (b.n_words) {
+                entry = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(RowsArgs)) + 4u * r);
+                first_row = inline_table(sizeof(RowsArgs))[4u * n_reqs + r];
+                have = true;
+            }
+        }
+        if (!have) {
+            const uint4 e = a.req_table[r];
+            entry = u32x4{e.x, e.y, e.z, e.w};
+            first_row = a.row0[r];
+        }
+        const bool keep = a.keep_mask ? a.keep_mask[r] != 0 : true;
+        const uint32_t listed = lane < n_reqs ? entry.w : 0u;
+        kept = keep ? listed : 0u;
+        upto = wave_incl_scan(kept);
+        n_rows = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        if (index_mode) listed_upto = wave_incl_scan(listed);
+    }
+    auto of_request = [](uint32_t v, uint32_t r) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)r); };
+
+    // -- record geometry, and whether the record fits
+    const uint64_t row_in = (uint64_t)a.row_elems * ES_IN, row_out = (uint64_t)a.row_elems * ES_OUT;
+    const uint64_t off_payload = 64u + (((uint64_t)n_reqs * 16u + 63u) & ~63ull);
+    const uint64_t payload_bytes = n_rows * row_out;
+    const uint64_t record_bytes = off_payload + ((payload_bytes + 63u) & ~63ull);
+    const bool dropped = !INTO && (policy & kStepDropNewest) && head0 + (y + 1ull) * record_bytes - tail > a.cap;
+    RingW w;
+    w.ring = a.ring;
+    w.cap = a.cap;
+    w.base = at0 + (uint64_t)y * record_bytes;  // (the issuer made sure a launch's records fit the ring together)
+    if (w.base >= w.cap) w.base -= w.cap;
+
+    if (!meta) {
+        if (!INTO && ((policy & kStepSkip) || dropped)) return;
+        const uint32_t n_steps = n_rows * a.parts;          // (the host keeps rows x units below 2^32)
+        const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
+        struct Step { uint32_t g, part; const uint8_t *base; bool ok; };
+        auto listed_row = [&](uint32_t i) -> int64_t {      // a row that is listed somewhere
+            if constexpr (INTO)
+                if (b.n_words && !index_mode) return (int64_t)inline_table_uniform(sizeof(RowsArgs))[4u * n_reqs + i];
+            const int32_t v = ((constant_i32 *)(index_mode ? a.row_index : reinterpret_cast<const int32_t *>(a.row0)))[i];
+            return index_mode ? (int64_t)v : (int64_t)(uint32_t)v;
+        };
+        auto step_at = [&](uint32_t s) -> Step {
+            Step st;
+            st.g = a.parts == 1u ? s : __umulhi(s, a.parts_magic) >> a.parts_shift;
+            st.part = s - st.g * a.parts;
+            int64_t row;
+            if (simple) {
+                row = a.flags & kRowsConsecutive ? (int64_t)a.row_first + st.g : listed_row(st.g);
+            } else {
+                const uint32_t r = (uint32_t)__popcll(__ballot(lane < n_reqs && upto - kept <= st.g)) - 1u;
+                const uint32_t j = st.g - (of_request(upto, r) - of_request(kept, r));      // the request's kept row j
+                if (index_mode) row = listed_row(of_request(listed_upto, r) - of_request(entry.w, r) + j);
+                else row = (int64_t)(uint64_t)(of_request(first_row, r) + j * of_request(entry.z, r));
+            }
+            st.ok = row >= 0 && row < a.n_src_rows;
+            st.base = src + (st.ok ? row : 0) * a.row_stride_b;
+            return st;
+        };
+        // where a lane's unit t of a step lies, in bytes from the step's first (a row that is not a whole number of
+        // units ends with one that reaches back, which is why other parts than the first count from a unit earlier);
+        // lanes behind the end of the row get its last unit
+        auto lane_at = [&](uint32_t part, uint32_t t, uint64_t row_bytes, uint32_t nb) -> uint32_t {
+            const uint32_t back = LOOSE && part ? nb : 0u;
+            const uint64_t rest = row_bytes - (uint64_t)part * (SU * nb);
+            const uint32_t last = (rest < SU * nb ? (uint32_t)rest : SU * nb) + back - nb;
+            const uint32_t off = (lane + t * 64u) * nb + back;
+            return off < last ? off : last;
+        };
+        auto load = [&](const Step &st, u32x4 (&v)[U]) {    // (a row that lies outside the source: zeros)
+            const uint8_t *const base = st.ok ? st.base + (uint64_t)st.part * (SU * NB_IN) - (LOOSE && st.part ? NB_IN : 0u) : zeros;
+            const uint32_t mask = st.ok ? ~0u : 0u;
+#pragma unroll
+            for (uint32_t t = 0; t < U; t++) {
+                const uint8_t *p = base + (lane_at(st.part, t, row_in, NB_IN) & mask);
+                v[t] = ONCE ? __builtin_nontemporal_load((global_unit_t *)p) : *(global_unit_t *)p;
+            }
+        };
+        auto store = [&](const Step &st, const u32x4 (&v)[U]) {
+            const uint32_t c0 = st.part * SU;
+            const uint64_t pos = off_payload + st.g * row_out + (uint64_t)c0 * NB_OUT - (LOOSE && st.part ? NB_OUT : 0u);
+            uint64_t p = w.base + pos;
+            if (p >= w.cap) p -= w.cap;
+            if (p + (SU + 1u) * NB_OUT <= w.cap) {          // all of it in front of the ring's end: no lane needs to look
+#pragma unroll
+                for (uint32_t t = 0; t < U; t++) {
+                    const auto o = convert_unit<ES_IN, VEC, OUT>(v[t]);
+                    if (c0 + lane + t * 64u < a.units_per_row) store_out<LOOSE>(w.ring + p + lane_at(st.part, t, row_out, NB_OUT), o);
+                }
+            } else {
+#pragma unroll
+                for (uint32_t t = 0; t < U; t++)
+                    if (c0 + lane + t * 64u < a.units_per_row)
+                        unit_store<LOOSE>(w, pos + lane_at(st.part, t, row_out, NB_OUT), convert_unit<ES_IN, VEC, OUT>(v[t]));
+            }
+        };
+        // (one step each, unless a replayed step's selection has grown since its grid was made)
+        uint32_t n_bad = 0;
+        for (uint64_t s = blockIdx.x * (kThreads / 64u) + wv; s < n_steps; s += a.row_groups * (kThreads / 64u)) {
+            const Step st = step_at((uint32_t)s);
+            u32x4 v[U];
+            load(st, v);
+            n_bad += st.part == 0u && !st.ok ? 1u : 0u;     // a bad row is counted where it begins
+            store(st, v);
+        }
+        if (n_bad && lane == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
+        return;
+    }
+
+    // -- the last workgroup: header, request table, pads; and, of the launch's first record, the chain of launches
+    const uint32_t tid = threadIdx.x, point_id = b.point[y];
+    uint64_t seq = a.seq, step_id = a.step_id;
+    if constexpr (!INTO) {
+        if (a.step) {
+            seq = ((constant_u64 *)a.step)[0] + a.node;
+            step_id = ((constant_u64 *)a.step)[1];
+        }
+        if (y == 0 && tid == kThreads - 64u) {
+            DevCtrl *c = a.ctrl;
+            const uint64_t tail_now = ld_system(a.tail_src ? a.tail_src : &c->tail);
+            const RawControl raw = fetch_control(c, par, nullptr);
+            c->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
+            if (policy & kStepSkip) {
+                c->head[par ^ 1u] = head0;
+                c->head_at[par ^ 1u] = at0;
+            } else {
+                const uint64_t n_fit = records_that_fit(gridDim.y, head0, tail, record_bytes, a.cap, (policy & kStepDropNewest) != 0u);
+                publish_launch(c, par, head0, at0, raw.cap, raw.drop, record_bytes, n_rows, n_fit, gridDim.y - n_fit + a.n_tail_drop,
+                               a.cap, seq + gridDim.y + a.n_tail_drop - 1u, a.step ? nullptr : a.cslot);
+                for (uint32_t i = 0; i < a.n_tail_drop; i++) atomicAdd(&c->point_drops[b.point[gridDim.y + i] & 4095u], 1u);
+            }
+        }
+        if (policy & kStepSkip) return;
+        if (dropped) {
+            if (tid == 0) atomicAdd(&a.ctrl->point_drops[point_id & 4095u], 1u);
+            return;
+        }
+    }
+    if (tid < 4u) {
+        const uint64_t seq_y = seq + y;
+        u32x4 hv;
+        if (tid == 0) hv = u32x4{0x32494D44u, 1u | (64u << 16), (uint32_t)seq_y, (uint32_t)(seq_y >> 32)};
+        else if (tid == 1) hv = u32x4{(uint32_t)step_id, (uint32_t)(step_id >> 32), point_id, a.hdr7};
+        else if (tid == 2) hv = u32x4{n_reqs, n_rows, a.row_elems, a.rank_tag};
+        else hv = u32x4{(uint32_t)record_bytes, (uint32_t)(record_bytes >> 32), (uint32_t)payload_bytes, (uint32_t)(payload_bytes >> 32)};
+        ring_store<u32x4>(w, 16u * tid, hv);
+    }
+    const uint32_t tab_slots = (uint32_t)((off_payload - 64u) / 16u);
+    for (uint32_t r = tid; r < tab_slots; r += kThreads) {
+        u32x4 tv = {0u, 0u, 0u, 0u};
+        if (r < n_reqs) {
+            if (!simple) {                  // (one request per lane: the first wavefront's own)
+                tv = u32x4{entry.x, entry.y, entry.z, kept};
+            } else {
+                bool have = false;
+                if constexpr (INTO)
+                    if (b.n_words) {
+                        tv = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(RowsArgs)) + 4u * r);
+                        have = true;
+                    }
+                if (!have) {
+                    const uint4 e = a.req_table[r];
+                    tv = u32x4{e.x, e.y, e.z, e.w};
+                }
+            }
+        }
+        ring_store<u32x4>(w, 64u + 16ull * r, tv);
+    }
+    const uint32_t pad = (uint32_t)(record_bytes - off_payload - payload_bytes);
+    if (tid < pad) ring_store<uint8_t>(w, off_payload + payload_bytes + tid, (uint8_t)0);
+}
+
 // ---------------------------------------------------------------- small kernels
 struct UploadChunk {
     uint32_t w[896];
@@ -1868,6 +2038,7 @@ __global__ void step_begin_kernel(DevCtrl *ctrl, StepParams *step, const StepPar
     if (host_tail) ctrl->tail = ld_system(host_tail);    // the step's launches read this copy
     if (par_from != par_to) {
         ctrl->head[par_to] = ctrl->head[par_from];
+        ctrl->head_at[par_to] = ctrl->head_at[par_from];
         ctrl->tail_for[par_to] = ctrl->tail_for[par_from];
     }
 }
@@ -1925,6 +2096,54 @@ extern "C" dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop
         }                                                                                                             \
     } while (0)
 
+template <int ES_IN, int OUT, bool LOOSE, typename SRC>
+static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
+{
+    if (a.paged || (!a.simple && a.n_reqs > 64u)) return hipErrorInvalidValue;
+    RowsArgs d;
+    std::memset(&d, 0, sizeof d);
+    d.row_stride_b = a.row_stride_b;
+    d.n_src_rows = a.n_src_rows;
+    d.req_table = a.req_table;
+    d.row0 = a.row0;
+    d.keep_mask = a.keep_mask;
+    d.row_index = a.row_index;
+    d.ring = a.ring;
+    d.cap = a.cap;
+    d.ctrl = a.ctrl;
+    d.step = a.step;
+    d.tail_floor = a.tail_floor;
+    d.flags = (a.simple ? kRowsSimple : 0u) | (a.rows_consecutive ? kRowsConsecutive : 0u) |
+              (a.drop_newest ? kRowsDropNewest : 0u) | (a.par_in ? kRowsParIn : 0u);
+    d.n_reqs = a.n_reqs;
+    d.units_per_row = a.units_per_row;
+    d.row_elems = a.row_elems;
+    d.parts = (a.units_per_row + 255u) / 256u;
+    if (d.parts > 1u) {             // magic = ceil(2^(31 + l) / parts) with l = ceil(log2(parts)): exact for 31 bits
+        d.parts_shift = 31u - (uint32_t)__builtin_clz(d.parts - 1u);
+        d.parts_magic = (uint32_t)(((1ull << (32u + d.parts_shift)) + d.parts - 1u) / d.parts);
+    }
+    d.row_groups = grid;
+    d.row_first = a.row_first;
+    d.seq = a.seq;
+    d.step_id = a.step_id;
+    d.cslot = a.cslot;
+    d.tail_src = a.tail_src;
+    d.node = a.node;
+    d.hdr7 = a.src_dtype | (a.out_dtype << 8) | (a.summary_mask << 16) | (a.rec_flags << 24);
+    d.rank_tag = a.rank_tag;
+    d.n_tail_drop = a.n_tail_drop;
+    const dim3 g(grid + 1u, a.n_batch);
+    if constexpr (!LOOSE) {
+        if (a.read_once) {
+            DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SRC, LOOSE, true>), g, 0, s, d, b);
+            return hipGetLastError();
+        }
+    }
+    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SRC, LOOSE, false>), g, 0, s, d, b);
+    return hipGetLastError();
+}
+
 template <int ES_IN, int VEC, int OUT, bool LOOSE, typename SRC>
 static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
@@ -1944,7 +2163,9 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
             return hipErrorInvalidValue;
         }
     } else if constexpr (OUT != OUT_NONE) {
-        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_NO, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
+        if constexpr (VEC > 1)
+            if (a.step_per_wave && !a.force_drop) return launch_rows<ES_IN, OUT, LOOSE>(a, b, grid, s);
+        DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, ROWS_FLAT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     }
     return hipGetLastError();
 }
@@ -1954,7 +2175,7 @@ static hipError_t launch_no_rows(const CaptureArgs &a, const SRC &b, uint32_t gr
 {
     const dim3 g(grid, a.n_batch);
     const CaptureKernelArgs &k = a;
-    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<2, 8, OUT_NONE, SUMM_NO, SRC, false>), g, a.lds_bytes, s, k, b);
+    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<2, 8, OUT_NONE, ROWS_FLAT, SRC, false>), g, a.lds_bytes, s, k, b);
     return hipGetLastError();
 }
 
