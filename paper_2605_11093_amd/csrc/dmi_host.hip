@@ -446,7 +446,15 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // per item, each gone after one round trip, keeps more loads in flight than the resident
     // few looping over many items.
     const bool flat = a.simple && !a.paged;
-    a.step_per_wave = a.read_once = 0;
+    // capture_rows_kernel scans the table with a request per lane
+    const bool finds_rows_itself = !a.paged && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u));
+    const uint64_t source_bytes = listed * nb * a.row_elems * dtype_size(a.src_dtype);
+    constexpr uint64_t kMemorySideCache = 256000000u;
+    // With a keep vector half of the listed rows are planned for: a workgroup that finds itself behind the last kept row has
+    // spent a microsecond and a place on a compute unit to learn that, one that gets a second row little more than its
+    // time (6.4 k kept of 12.8 k listed rows of 1024 units: 23.5 us planned for all, 21.1 like this).
+    const uint64_t planned = a.keep_mask ? (listed + 1u) / 2u : listed;
+    a.step_per_wave = a.read_once = a.wave_rows = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
     // hardware then hands out the work as workgroups retire, which evens out how unequally the
@@ -465,32 +473,43 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     if (a.summary_mask && a.row_lanes <= 64u) {
         const uint64_t rows = 4u * (64u / a.row_lanes);             // what a workgroup takes in one step
         groups = balanced((listed + rows - 1u) / rows);
+    } else if (a.summary_mask && finds_rows_itself) {
+        // capture_rows_kernel: a wavefront per row while a launch has rows enough to fill the GPU that way and they are
+        // short enough for one wavefront's trips, else a workgroup per row, a quarter of it to each wavefront.
+        // (workgroup / wavefront per row / the general kernel, norm and largest magnitude, us; ragged, 16 to 32 requests:)
+        //   statistics alone: 12.8 k rows of 264 units 21.9 / 12.6 / 15.1, 9.3 k rows of 512 17.2 / 13.9 / 16.4, of 513 off the
+        //   16-byte grid 22.6 / 17.4 / 24.0, of 768 24.1 / 22.9 / 24.4, of 1024 27.6 / 32.7 / 32.4, of 2048 54.1 / 67.8 / 60.5,
+        //   200 of 6283 9.2 / 25.4 / 13.3
+        //   rows stored too: 9.3 k of 384 21.4 / 20.5 / 20.7, of 512 26.1 / 25.4 / 25.5, of 768 40.4 / 47.4 / 46.4, of 1024
+        //   53.2 / 66.8 / 63.8, of 2048 113.8 / 153.6 / 129.4
+        //   batches, one row per request: 80 x 256 rows of 512 39.5 / 30.9 / 33.1, of 1024 57.4 / 62.5 / 62.6 (rows stored too 120 / 138
+        //   / 116, and 115 past the cache)
+        a.step_per_wave = 1;
+        a.wave_rows = upr <= 640u && planned * nb >= 2048u;
+        // past the memory-side cache what does not fit it; and, of a batch's tensors, which have been waiting for each
+        // other, already from half of that on if nothing is stored (32 x 256 rows of 1024 units 24.7 -> 21.9, 80 x 256 57.4 -> 49.7)
+        a.read_once = source_bytes >= kMemorySideCache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);
+        groups = a.wave_rows ? (planned + 3u) / 4u : planned;
     } else if (a.summary_mask) {
-        // Rows of more than 256 units: a workgroup per row, or, where a launch has rows enough, a wavefront per row.
+        // Rows of more than 256 units of paged caches, or of more than 64 ragged requests: a workgroup per row, or, where a
+        // launch has rows enough, a wavefront per row.
         // (workgroup / wavefront per row, norm and largest magnitude, us:)
         //   rows of 288 units, 1.5 k rows 7.5 / 7.5, 3 k 10.0 / 7.4, 6 k 16.6 / 9.9; of 512: 24 k 57.3 / 40.0
         //   of 640 units, 6 k rows 17.3 / 14.4; 40 x 256 rows of 768, statistics alone 34.7 / 27.7, with the rows 45 / 49
-        //   of 1024 units, 80 x 256 rows with the rows 116 / 121
-        //   statistics alone, one row per request (no scan, no search): 64 x 256 rows of 784 units 52.3 / 42.2, of 896
-        //   53.4 / 45.2, of 960 53.8 / 48.4, of 1024 54.1 / 50.2; of 1024 units, 40 x 256 rows 36.0 / 33.9, 80 x 256 67.4 / 61.5,
-        //   96 x 256 79.6 / 72.3
-        //   the same, ragged: of 1024 units, 12 k rows 38.5 / 42.2, 18 k 56.4 / 59.3, 24 k 72.5 / 76.1 (of 800: 36.1 / 32.4 and
+        //   of 1024 units, 12 k rows 38.5 / 42.2, 18 k 56.4 / 59.3, 24 k 72.5 / 76.1 (of 800: 36.1 / 32.4 and
         //   63.7 / 62.4); of 1792 units, 12 k rows 66.6 / 69.4
-        // So at 1024 units the shape of the selection decides, not the number of rows: one row per request gains from
-        // 10 k rows on (the line at 16384 leaves a margin), ragged rows at no number measured.
         // With statistics alone a wavefront takes two rows from 4096 rows on (80 x 256 rows of 512 units: 37.2 with
         // one, 34.8 with two; 3 k rows 8.7 and 9.0), where the rows are stored too, one (61 and 64 us).
         const uint64_t rows = listed * nb;
         const bool alone = a.out_dtype == 0u;
-        a.wave_rows = rows >= 2048u && (upr <= 512u || (alone && upr <= 768u) ||
-                                        (alone && upr <= 1024u && flat && rows >= 16384u));
-        const uint64_t per_wave = alone && rows >= 4096u && upr <= 768u ? 2u : 1u;
+        a.wave_rows = rows >= 2048u && (upr <= 512u || (alone && upr <= 768u));
+        const uint64_t per_wave = alone && rows >= 4096u ? 2u : 1u;
         groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed);
-    } else if (a.out_dtype && !a.paged && upr >= kLongRowUnits && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u))) {
+    } else if (a.out_dtype && upr >= kLongRowUnits && finds_rows_itself) {
         // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
         a.step_per_wave = 1;
-        a.read_once = listed * a.row_elems * dtype_size(a.src_dtype) * nb >= 256000000ull;
-        groups = (listed * ((upr + 255u) / 256u) + 3u) / 4u;
+        a.read_once = source_bytes >= kMemorySideCache;
+        groups = (planned * ((upr + 255u) / 256u) + 3u) / 4u;
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
         const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;

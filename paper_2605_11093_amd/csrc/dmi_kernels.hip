@@ -76,13 +76,12 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// A pointer that is the same in every lane, said to be.
-__device__ __forceinline__ const uint8_t *uniform_ptr(const uint8_t *p)
+// A value that is the same in every lane, said to be.
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
 {
-    const uint64_t v = (uint64_t)(uintptr_t)p;
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+    return ((uint64_t)hi << 32) | lo;
 }
 // Wavefront reductions with DPP (data-parallel primitives: the cross-lane operand rides on the
 // ALU instruction, no trip through LDS).  quad_perm / row_half_mirror / row_mirror combine the 16
@@ -444,6 +443,19 @@ __device__ __forceinline__ void accum_units(Accum &acc, const typename UnitT<ES_
     }
 }
 
+// A unit of VEC elements with its first n set to zero.
+template <int VEC>
+__device__ __forceinline__ u32x4 without_first(u32x4 v, uint32_t n)
+{
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) {
+        const uint32_t per = VEC / 4u;      // elements of a 32-bit word
+        const uint32_t gone = n <= i * per ? 0u : n - i * per < per ? n - i * per : per;
+        v[i] &= gone == 0u ? 0xFFFFFFFFu : gone == per ? 0u : 0xFFFF0000u;
+    }
+    return v;
+}
+
 template <int ES_IN, int VEC, int OUT>
 __host__ __device__ constexpr uint32_t out_unit_bytes()
 {
@@ -738,9 +750,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         if constexpr (LOOSE) return e + VEC <= a.seg_elems ? e : a.seg_elems - VEC;
         else return e;
     };
-    // -- decode-shaped selections (no mask, one row per request, dense): the first work
-    //    item's rows do not depend on anything computed above, so their loads are issued
-    //    now and travel together with the control fetch instead of behind it
     constexpr uint32_t U = 4;                               // loads in flight per lane
     constexpr uint32_t CH = U * kThreads;                   // units of one step of a workgroup
     const uint32_t cpr = (a.units_per_row + CH - 1u) / CH;  // SUMM_ROWS: steps of a workgroup per row
@@ -748,34 +757,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     const uint32_t wave_at = blockIdx.x * (kThreads / 64u) + wv, n_waves = gridDim.x * (kThreads / 64u);
     // summaries: the lanes that share a row; lane l takes units l, l + row_lanes, ..., four at a time
     const uint32_t row_lanes = MODE == ROWS_FLAT ? kThreads : a.row_lanes;
-    bool first_row_inline = false;
-    if constexpr (INTO) first_row_inline = b.n_words != 0u;
-    unit_t pre_v[U];
-    RowRef pre_ref = {nullptr, 0};
-    bool pre = false;
-    // (not in a launch of several records some of which may turn out to be dropped: a dropped
-    // record's rows would have been read for nothing)
-    const bool may_drop_some = a.n_batch > 1u && (a.drop_newest != 0u || a.step != nullptr);
-    if (simple && !a.paged && !may_drop_some && (MODE == SUMM_ROWS || MODE == SUMM_WAVE)) {
-        const uint32_t g = MODE == SUMM_WAVE ? wave_at * ((n_reqs - 1u) / n_waves + 1u) : blockIdx.x;
-        const uint32_t c_begin = MODE == SUMM_WAVE ? lane : tid;
-        if (g < n_reqs) {
-            int64_t row;
-            if (index_mode) row = (int64_t)a.row_index[g];
-            else if (INTO && MODE == SUMM_ROWS && first_row_inline) row = (int64_t)inline_table_uniform(sizeof(CaptureKernelArgs))[4u * n_reqs + g];
-            else row = (int64_t)row_first(g);
-            pre_ref.ok = row >= 0 && row < a.n_src_rows;
-            pre_ref.base = src + (pre_ref.ok ? row : 0) * a.row_stride_b;
-#pragma unroll
-            for (uint32_t k = 0; k < U; k++) {
-                const uint32_t c = c_begin + k * row_lanes;
-                const bool want = pre_ref.ok && c < a.units_per_row && (MODE != SUMM_ROWS || tid < row_lanes);
-                const uint8_t *p = want ? pre_ref.base + elem_in_seg(c) * ES_IN : reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
-                pre_v[k] = *(global_unit_t *)p;     // zeroed where it is used if not wanted
-            }
-            pre = true;
-        }
-    }
     if (INTO && tid < 12u) lds[m.bcast + tid] = tid == 8u    ? (uint32_t)a.seq
                                                 : tid == 9u  ? (uint32_t)(a.seq >> 32)
                                                 : tid == 10u ? (uint32_t)a.step_id
@@ -962,14 +943,6 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
         q.ask = locate_begin(from < last ? from + 1u : last, q.r);
         return ref;
     };
-    // the same where the first row has been found up front (only where requests have one row each)
-    auto walk_behind = [&](Walk &q, uint32_t from, uint32_t last, const RowRef &first) -> RowRef {
-        q.g = from;
-        q.last = last;
-        q.r = 0;
-        if (from < last) q.ask = locate_begin(from + 1u, q.r);
-        return RowRef{uniform_ptr(first.base), (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)first.ok)};
-    };
     auto walk_on = [&](Walk &q) -> RowRef {
         q.g++;
         if (walks) {
@@ -1007,13 +980,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto sum_part = [&](unit_t v, uint32_t c) -> unit_t {
         if constexpr (LOOSE) {
             const uint32_t cc = !a.paged ? c : a.seg_shift < 32u ? c & ((1u << a.seg_shift) - 1u) : c % a.seg_units;
-            const uint32_t twice = cc + 1u == a.seg_units ? a.seg_units * VEC - a.seg_elems : 0u;
-#pragma unroll
-            for (uint32_t i = 0; i < 4; i++) {
-                const uint32_t per = VEC / 4u;      // elements of a 32-bit word
-                const uint32_t gone = twice <= i * per ? 0u : twice - i * per < per ? twice - i * per : per;
-                v[i] &= gone == 0u ? 0xFFFFFFFFu : gone == per ? 0u : 0xFFFF0000u;
-            }
+            return without_first<VEC>(v, cc + 1u == a.seg_units ? a.seg_units * VEC - a.seg_elems : 0u);
         }
         return v;
     };
@@ -1264,8 +1231,9 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 if (n_bad) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
             }
         } else if constexpr (MODE == SUMM_WAVE) {
-            // ---- summaries, a wavefront per row: where a launch has rows enough to fill the GPU that way, a row costs no
-            //      barrier and a workgroup lives for four rows or more instead of one, so its prologue weighs less.
+            // ---- summaries, a wavefront per row (paged rows, or of more than 64 ragged requests): where a launch has rows enough
+            //      to fill the GPU that way, a row costs no barrier and a workgroup lives for four rows or more
+            //      instead of one, so its prologue weighs less.
             //      The sums are taken in the order in which a workgroup takes them (the decode-shaped kernel, and
             //      the path below): the row's lanes in parts of 64, each lane's (at most four) units, then the lanes
             //      of a part, then the (at most four) parts.  A step is one part of a row; its loads are issued
@@ -1344,14 +1312,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                 Step s;
                 s.g = r0;
                 s.part = 0;
-                if (pre) {
-                    s.ref = walk_behind(walk, (uint32_t)r0, (uint32_t)r1 - 1u, pre_ref);
-#pragma unroll
-                    for (uint32_t k = 0; k < U; k++) va[k] = pre_v[k];
-                } else {
-                    s.ref = walk_from(walk, (uint32_t)r0, (uint32_t)r1 - 1u);
-                    load(s, va);
-                }
+                s.ref = walk_from(walk, (uint32_t)r0, (uint32_t)r1 - 1u);
+                load(s, va);
                 n_bad += s.ref.ok ? 0u : 1u;
                 for (;;) {
                     Step n = next(s);
@@ -1386,15 +1348,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             if (g < n_rows) {
                 RowRef ref = {nullptr, 0};
                 unit_t v[U];
-                if (pre) {
-                    ref = pre_ref;
-#pragma unroll
-                    for (uint32_t k = 0; k < U; k++) v[k] = pre_v[k];
-                    // (fetch() counts the rows it locates; this one was located up front)
-                    if (!ref.ok && tid == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, 1ull);
-                } else {
-                    fetch(g, pass, ref, v);
-                }
+                fetch(g, pass, ref, v);
                 Accum acc = {0.f, 0.f, 0u};
                 for (;;) {
                     uint64_t nxt_g = g;
@@ -1750,9 +1704,9 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
     }
 }
 
-// ---------------------------------------------------------------- rows stored, no summaries
-// Dense rows of at least kLongRowUnits units, stored as they are or converted: the largest records there are (ragged
-// prompts, the tensors of a batch).  A wavefront takes up to 256 consecutive units of one row, and everything but its
+// ---------------------------------------------------------------- dense rows that a launch finds by itself
+// Dense rows of one row per request or of up to 64 ragged requests: the largest records there are (ragged prompts, the
+// tensors of a batch).  Without summaries, of at least kLongRowUnits units: a wavefront takes up to 256 consecutive units of one row, and everything but its
 // lanes' places in them is the same for the whole wavefront and kept in scalar registers.
 // Bound: HBM.  What a launch loses on top is the time until its first loads leave, and the unequal ends of its
 // workgroups.  Time stamps in the general kernel, which took these rows before, showed 5 us in front of the first loads of
@@ -1770,6 +1724,10 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 // ONCE: launches that read more than the 256 MB memory-side cache holds do so past it (non-temporal loads): 9.3 k x 14336
 // 73.4 -> 69.4 us; where what is read may still be there from the kernel that wrote it they lose (9.3 k x 4096: 18.8
 // and 21.8), and between 133 and 256 MB it depends on what ran before.
+// With summaries (SUMM), of more than 256 units: a wavefront per row, or a workgroup per row with a quarter of it to each
+// wavefront (plan_grid() says which, with figures); lanes, parts and the order of the sums are the general and the
+// decode-shaped kernel's, so a row's summaries have the same bits wherever it is captured.  80 tensors of 256 x 8192,
+// statistics alone: 61 -> 49.5 us (6.8 TB/s read).
 // Shorter rows are dealt flat by the general kernel (20 k x 256: 6.2 us there, 10.6 here; from 64 units on: 3000 x 512
 // 5.0 and 4.1, 9.3 k x 512 raw 6.0 and 5.3, 20 k x 640 raw 11.6 and 10.0, to fp8 11.0 and 11.7, 9.3 k x 1536 11.1 and 9.4), and
 // so are rows of more than 64 ragged requests.
@@ -1789,7 +1747,9 @@ struct RowsArgs {
     uint32_t n_reqs, units_per_row, row_elems;
     uint32_t parts, parts_magic, parts_shift;   // steps per row; x / parts = (x * parts_magic >> 32) >> parts_shift, x below 2^31
     uint32_t row_groups;            // workgroups that move rows (gridDim.x - 1)
-    uint32_t row_first, pad;
+    uint32_t row_first;
+    uint32_t summary_mask, src_dtype, row_lanes, passes;     // summaries: lanes that share a row, as in the general kernel
+    uint32_t pad;
     // line 2: header and publishing
     uint64_t seq, step_id;
     CommitSlot *cslot;
@@ -1801,7 +1761,8 @@ constexpr uint32_t kRowsSimple = 1u;        // no keep vector, one row per reque
 constexpr uint32_t kRowsConsecutive = 2u;   // and request i's row is row_first + i
 constexpr uint32_t kRowsDropNewest = 4u, kRowsParIn = 8u;
 
-template <int ES_IN, int OUT, typename SRC, bool LOOSE, bool ONCE>
+// SUMM: 0 no summaries, 1 a wavefront per row, 2 a workgroup per row.
+template <int ES_IN, int OUT, int SUMM, typename SRC, bool LOOSE, bool ONCE>
 __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a, const SRC b)
 {
     constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
@@ -1811,6 +1772,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     typedef typename UnitT<ES_IN * VEC>::T unit_t;
     typedef __attribute__((address_space(1))) const unit_t __attribute__((aligned(LOOSE ? ES_IN : ES_IN * VEC))) global_unit_t;
     typedef __attribute__((address_space(4))) const uint64_t constant_u64;
+    typedef __attribute__((address_space(1))) const uint64_t global_u64;
     typedef __attribute__((address_space(4))) const int32_t constant_i32;
     const uint32_t y = INTO ? 0u : blockIdx.y;
     const uint8_t *const src = b.src[y];
@@ -1819,12 +1781,15 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     const bool index_mode = a.row_index != nullptr;
     const uint32_t n_reqs = a.n_reqs, par = a.flags & kRowsParIn ? 1u : 0u;
 
-    // -- control words, the same for everybody: through the scalar cache
-    uint64_t head0 = 0, at0 = 0, tail = 0;
+    // -- control words.  Where the record lies is asked for here, by vector loads (said to be), and waited for when the
+    //    first rows are on their way; what decides whether there is a record at all comes through the scalar cache.
+    uint64_t head_v = 0, at_v = 0, tail = 0;
     uint32_t policy = 0;
     if constexpr (!INTO) {
-        head0 = ((constant_u64 *)a.ctrl->head)[par];
-        at0 = ((constant_u64 *)a.ctrl->head_at)[par];
+        uint64_t ctrl_v = (uint64_t)(uintptr_t)a.ctrl;
+        asm volatile("" : "+v"(ctrl_v));
+        head_v = ((global_u64 *)(ctrl_v + offsetof(DevCtrl, head)))[par];
+        at_v = ((global_u64 *)(ctrl_v + offsetof(DevCtrl, head_at)))[par];
         policy = a.flags & kRowsDropNewest ? kStepDropNewest : 0u;
         tail = a.tail_floor;
         if (a.step) {
@@ -1869,13 +1834,22 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     const uint64_t row_in = (uint64_t)a.row_elems * ES_IN, row_out = (uint64_t)a.row_elems * ES_OUT;
     const uint64_t off_payload = 64u + (((uint64_t)n_reqs * 16u + 63u) & ~63ull);
     const uint64_t payload_bytes = n_rows * row_out;
-    const uint64_t record_bytes = off_payload + ((payload_bytes + 63u) & ~63ull);
-    const bool dropped = !INTO && (policy & kStepDropNewest) && head0 + (y + 1ull) * record_bytes - tail > a.cap;
+    const uint64_t off_sum = off_payload + ((payload_bytes + 63u) & ~63ull), sum_arr = ((uint64_t)n_rows * 4u + 63u) & ~63ull;
+    const uint32_t n_sum = SUMM ? (uint32_t)__popc(a.summary_mask) : 0u;
+    const uint64_t record_bytes = off_sum + n_sum * sum_arr;
+    bool dropped = false;
+    if constexpr (!INTO)
+        if (policy & kStepDropNewest) dropped = uniform_u64(head_v) + (y + 1ull) * record_bytes - tail > a.cap;
     RingW w;
     w.ring = a.ring;
     w.cap = a.cap;
-    w.base = at0 + (uint64_t)y * record_bytes;  // (the issuer made sure a launch's records fit the ring together)
-    if (w.base >= w.cap) w.base -= w.cap;
+    w.base = 0;
+    auto settle = [&]() {
+        if constexpr (!INTO) {
+            w.base = uniform_u64(at_v) + (uint64_t)y * record_bytes;    // (the issuer made sure a launch's records fit the ring together)
+            if (w.base >= w.cap) w.base -= w.cap;
+        }
+    };
 
     if (!meta) {
         if (!INTO && ((policy & kStepSkip) || dropped)) return;
@@ -1905,57 +1879,141 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
             st.base = src + (st.ok ? row : 0) * a.row_stride_b;
             return st;
         };
-        // where a lane's unit t of a step lies, in bytes from the step's first (a row that is not a whole number of
-        // units ends with one that reaches back, which is why other parts than the first count from a unit earlier);
-        // lanes behind the end of the row get its last unit
-        auto lane_at = [&](uint32_t part, uint32_t t, uint64_t row_bytes, uint32_t nb) -> uint32_t {
-            const uint32_t back = LOOSE && part ? nb : 0u;
-            const uint64_t rest = row_bytes - (uint64_t)part * (SU * nb);
-            const uint32_t last = (rest < SU * nb ? (uint32_t)rest : SU * nb) + back - nb;
-            const uint32_t off = (lane + t * 64u) * nb + back;
-            return off < last ? off : last;
-        };
-        auto load = [&](const Step &st, u32x4 (&v)[U]) {    // (a row that lies outside the source: zeros)
-            const uint8_t *const base = st.ok ? st.base + (uint64_t)st.part * (SU * NB_IN) - (LOOSE && st.part ? NB_IN : 0u) : zeros;
-            const uint32_t mask = st.ok ? ~0u : 0u;
+        uint32_t n_bad = 0;
+        if constexpr (SUMM != 0) {
+            constexpr bool WG = SUMM == 2;              // a workgroup per row, a part of it to each wavefront
+            __shared__ float red[WG ? 12 : 1];
+            const uint32_t rl = a.row_lanes, parts = rl >> 6;
+            const uint32_t rows_at_once = a.row_groups * (WG ? 1u : kThreads / 64u);
+            for (uint64_t g = WG ? blockIdx.x : blockIdx.x * (kThreads / 64u) + wv; g < n_rows; g += rows_at_once) {
+                const Step st = step_at((uint32_t)g);
+                n_bad += st.ok || (WG && wv != 0u) ? 0u : 1u;
+                float ss[4] = {0.f, 0.f, 0.f, 0.f}, sm[4] = {0.f, 0.f, 0.f, 0.f};       // of each part
+                uint32_t am = 0;
+                auto one_part = [&](uint32_t part) -> Accum {
+                    Accum acc = {0.f, 0.f, 0u};
+#pragma unroll 1
+                    for (uint32_t pass = 0; pass < a.passes; pass++) {
+                        const uint32_t c0 = pass * U * rl + part * 64u + lane;
+                        u32x4 v[U];
 #pragma unroll
-            for (uint32_t t = 0; t < U; t++) {
-                const uint8_t *p = base + (lane_at(st.part, t, row_in, NB_IN) & mask);
-                v[t] = ONCE ? __builtin_nontemporal_load((global_unit_t *)p) : *(global_unit_t *)p;
+                        for (uint32_t t = 0; t < U; t++) {          // (a lane with nothing to load reads zeros)
+                            const uint32_t c = c0 + t * rl;
+                            const uint64_t e = (uint64_t)c * VEC, last = (uint64_t)a.row_elems - VEC;
+                            const uint8_t *p = st.ok && c < a.units_per_row ? st.base + (LOOSE && e > last ? last : e) * ES_IN : zeros;
+                            v[t] = ONCE ? __builtin_nontemporal_load((global_unit_t *)p) : *(global_unit_t *)p;
+                        }
+                        settle();
+                        if constexpr (OUT != OUT_NONE) {
+#pragma unroll
+                            for (uint32_t t = 0; t < U; t++) {
+                                const uint32_t c = c0 + t * rl;
+                                const uint64_t e = (uint64_t)c * VEC, last = (uint64_t)a.row_elems - VEC;
+                                if (c < a.units_per_row)
+                                    emit_unit<ES_IN, VEC, OUT, LOOSE>(w, off_payload + g * row_out + (LOOSE && e > last ? last : e) * ES_OUT, v[t]);
+                            }
+                        }
+                        if constexpr (LOOSE) {          // the last unit's elements that the one in front of it has as well
+#pragma unroll
+                            for (uint32_t t = 0; t < U; t++)
+                                if (c0 + t * rl + 1u == a.units_per_row) v[t] = without_first<VEC>(v[t], a.units_per_row * VEC - a.row_elems);
+                        }
+                        accum_units<ES_IN, VEC>(acc, v, a.src_dtype);
+                    }
+                    if (a.summary_mask & 1u) acc.ss = wave_sum(acc.ss);
+                    if (a.summary_mask & 2u) acc.s = wave_sum(acc.s);
+                    if (a.summary_mask & 4u) acc.am = wave_max_u32(fold_am<ES_IN, VEC>(acc.am));
+                    return acc;
+                };
+                if constexpr (WG) {
+                    Accum acc = {0.f, 0.f, 0u};
+                    if (wv < parts) acc = one_part(wv);
+                    if (g >= rows_at_once) lds_barrier();       // (the row before this one has been read)
+                    if (lane == 0) {
+                        red[wv] = acc.ss;
+                        red[4 + wv] = acc.s;
+                        red[8 + wv] = __uint_as_float(acc.am);
+                    }
+                    lds_barrier();
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; i++) {
+                        ss[i] = red[i];
+                        sm[i] = red[4 + i];
+                        const uint32_t x = __float_as_uint(red[8 + i]);
+                        am = x > am ? x : am;
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t part = 0; part < 4u; part++) {
+                        if (part >= parts) break;
+                        const Accum acc = one_part(part);
+                        ss[part] = acc.ss;
+                        sm[part] = acc.s;
+                        am = acc.am > am ? acc.am : am;
+                    }
+                }
+                if (lane == 0 && (!WG || wv == 0u)) {           // (the order in which every kernel here takes them)
+                    uint64_t o = off_sum + g * 4u;
+                    if (a.summary_mask & 1u) { ring_store<float>(w, o, sqrtf((ss[0] + ss[1]) + (ss[2] + ss[3]))); o += sum_arr; }
+                    if (a.summary_mask & 2u) { ring_store<float>(w, o, ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)a.row_elems); o += sum_arr; }
+                    if (a.summary_mask & 4u) ring_store<float>(w, o, am_value(am, a.src_dtype));
+                }
             }
-        };
-        auto store = [&](const Step &st, const u32x4 (&v)[U]) {
-            const uint32_t c0 = st.part * SU;
-            const uint64_t pos = off_payload + st.g * row_out + (uint64_t)c0 * NB_OUT - (LOOSE && st.part ? NB_OUT : 0u);
-            uint64_t p = w.base + pos;
-            if (p >= w.cap) p -= w.cap;
-            if (p + (SU + 1u) * NB_OUT <= w.cap) {          // all of it in front of the ring's end: no lane needs to look
+        } else {
+            // where a lane's unit t of a step lies, in bytes from the step's first (a row that is not a whole number of
+            // units ends with one that reaches back, which is why other parts than the first count from a unit earlier);
+            // lanes behind the end of the row get its last unit
+            auto lane_at = [&](uint32_t part, uint32_t t, uint64_t row_bytes, uint32_t nb) -> uint32_t {
+                const uint32_t back = LOOSE && part ? nb : 0u;
+                const uint64_t rest = row_bytes - (uint64_t)part * (SU * nb);
+                const uint32_t last = (rest < SU * nb ? (uint32_t)rest : SU * nb) + back - nb;
+                const uint32_t off = (lane + t * 64u) * nb + back;
+                return off < last ? off : last;
+            };
+            auto load = [&](const Step &st, u32x4 (&v)[U]) {    // (a row that lies outside the source: zeros)
+                const uint8_t *const base = st.ok ? st.base + (uint64_t)st.part * (SU * NB_IN) - (LOOSE && st.part ? NB_IN : 0u) : zeros;
+                const uint32_t mask = st.ok ? ~0u : 0u;
 #pragma unroll
                 for (uint32_t t = 0; t < U; t++) {
-                    const auto o = convert_unit<ES_IN, VEC, OUT>(v[t]);
-                    if (c0 + lane + t * 64u < a.units_per_row) store_out<LOOSE>(w.ring + p + lane_at(st.part, t, row_out, NB_OUT), o);
+                    const uint8_t *p = base + (lane_at(st.part, t, row_in, NB_IN) & mask);
+                    v[t] = ONCE ? __builtin_nontemporal_load((global_unit_t *)p) : *(global_unit_t *)p;
                 }
-            } else {
+            };
+            auto store = [&](const Step &st, const u32x4 (&v)[U]) {
+                const uint32_t c0 = st.part * SU;
+                const uint64_t pos = off_payload + st.g * row_out + (uint64_t)c0 * NB_OUT - (LOOSE && st.part ? NB_OUT : 0u);
+                uint64_t p = w.base + pos;
+                if (p >= w.cap) p -= w.cap;
+                if (p + (SU + 1u) * NB_OUT <= w.cap) {          // all of it in front of the ring's end: no lane needs to look
 #pragma unroll
-                for (uint32_t t = 0; t < U; t++)
-                    if (c0 + lane + t * 64u < a.units_per_row)
-                        unit_store<LOOSE>(w, pos + lane_at(st.part, t, row_out, NB_OUT), convert_unit<ES_IN, VEC, OUT>(v[t]));
+                    for (uint32_t t = 0; t < U; t++) {
+                        const auto o = convert_unit<ES_IN, VEC, OUT>(v[t]);
+                        if (c0 + lane + t * 64u < a.units_per_row) store_out<LOOSE>(w.ring + p + lane_at(st.part, t, row_out, NB_OUT), o);
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t t = 0; t < U; t++)
+                        if (c0 + lane + t * 64u < a.units_per_row)
+                            unit_store<LOOSE>(w, pos + lane_at(st.part, t, row_out, NB_OUT), convert_unit<ES_IN, VEC, OUT>(v[t]));
+                }
+            };
+            // (one step each, unless a replayed step's selection has grown since its grid was made)
+            for (uint64_t s = blockIdx.x * (kThreads / 64u) + wv; s < n_steps; s += a.row_groups * (kThreads / 64u)) {
+                const Step st = step_at((uint32_t)s);
+                u32x4 v[U];
+                load(st, v);
+                settle();
+                n_bad += st.part == 0u && !st.ok ? 1u : 0u;     // a bad row is counted where it begins
+                store(st, v);
             }
-        };
-        // (one step each, unless a replayed step's selection has grown since its grid was made)
-        uint32_t n_bad = 0;
-        for (uint64_t s = blockIdx.x * (kThreads / 64u) + wv; s < n_steps; s += a.row_groups * (kThreads / 64u)) {
-            const Step st = step_at((uint32_t)s);
-            u32x4 v[U];
-            load(st, v);
-            n_bad += st.part == 0u && !st.ok ? 1u : 0u;     // a bad row is counted where it begins
-            store(st, v);
         }
         if (n_bad && lane == 0) atomicAdd((unsigned long long *)&a.ctrl->bad_rows, (unsigned long long)n_bad);
         return;
     }
 
     // -- the last workgroup: header, request table, pads; and, of the launch's first record, the chain of launches
+    settle();
+    const uint64_t head0 = uniform_u64(head_v), at0 = uniform_u64(at_v);
     const uint32_t tid = threadIdx.x, point_id = b.point[y];
     uint64_t seq = a.seq, step_id = a.step_id;
     if constexpr (!INTO) {
@@ -2014,8 +2072,11 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         }
         ring_store<u32x4>(w, 64u + 16ull * r, tv);
     }
-    const uint32_t pad = (uint32_t)(record_bytes - off_payload - payload_bytes);
+    const uint32_t pad = (uint32_t)(off_sum - off_payload - payload_bytes);
     if (tid < pad) ring_store<uint8_t>(w, off_payload + payload_bytes + tid, (uint8_t)0);
+    const uint32_t spad = (uint32_t)(sum_arr - (uint64_t)n_rows * 4u) / 4u;
+    if (tid < n_sum * 16u && (tid & 15u) < spad)
+        ring_store<uint32_t>(w, off_sum + (tid >> 4) * sum_arr + (uint64_t)n_rows * 4u + 4u * (tid & 15u), 0u);
 }
 
 // ---------------------------------------------------------------- small kernels
@@ -2096,7 +2157,7 @@ extern "C" dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop
         }                                                                                                             \
     } while (0)
 
-template <int ES_IN, int OUT, bool LOOSE, typename SRC>
+template <int ES_IN, int OUT, int SUMM, bool LOOSE, typename SRC>
 static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     if (a.paged || (!a.simple && a.n_reqs > 64u)) return hipErrorInvalidValue;
@@ -2118,7 +2179,11 @@ static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid,
     d.n_reqs = a.n_reqs;
     d.units_per_row = a.units_per_row;
     d.row_elems = a.row_elems;
-    d.parts = (a.units_per_row + 255u) / 256u;
+    d.parts = SUMM ? 1u : (a.units_per_row + 255u) / 256u;      // (with summaries a wavefront takes the row)
+    d.summary_mask = a.summary_mask;
+    d.src_dtype = a.src_dtype;
+    d.row_lanes = a.row_lanes;
+    d.passes = SUMM ? (a.units_per_row + 4u * a.row_lanes - 1u) / (4u * a.row_lanes) : 0u;
     if (d.parts > 1u) {             // magic = ceil(2^(31 + l) / parts) with l = ceil(log2(parts)): exact for 31 bits
         d.parts_shift = 31u - (uint32_t)__builtin_clz(d.parts - 1u);
         d.parts_magic = (uint32_t)(((1ull << (32u + d.parts_shift)) + d.parts - 1u) / d.parts);
@@ -2136,11 +2201,11 @@ static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid,
     const dim3 g(grid + 1u, a.n_batch);
     if constexpr (!LOOSE) {
         if (a.read_once) {
-            DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SRC, LOOSE, true>), g, 0, s, d, b);
+            DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SUMM, SRC, LOOSE, true>), g, 0, s, d, b);
             return hipGetLastError();
         }
     }
-    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SRC, LOOSE, false>), g, 0, s, d, b);
+    DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_rows_kernel<ES_IN, OUT, SUMM, SRC, LOOSE, false>), g, 0, s, d, b);
     return hipGetLastError();
 }
 
@@ -2154,6 +2219,8 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     } else if (a.summary_mask) {
         if constexpr (VEC > 1) {
+            if (a.step_per_wave && !a.force_drop)
+                return a.wave_rows ? launch_rows<ES_IN, OUT, 1, LOOSE>(a, b, grid, s) : launch_rows<ES_IN, OUT, 2, LOOSE>(a, b, grid, s);
             if (a.wave_rows && a.units_per_row > 1024u) return hipErrorInvalidValue;    // four units for each of 256 lanes
             if (a.wave_rows)
                 DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_WAVE, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
@@ -2164,7 +2231,7 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
         }
     } else if constexpr (OUT != OUT_NONE) {
         if constexpr (VEC > 1)
-            if (a.step_per_wave && !a.force_drop) return launch_rows<ES_IN, OUT, LOOSE>(a, b, grid, s);
+            if (a.step_per_wave && !a.force_drop) return launch_rows<ES_IN, OUT, 0, LOOSE>(a, b, grid, s);
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, ROWS_FLAT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     }
     return hipGetLastError();

@@ -1,14 +1,17 @@
-"""Rows of 64 units and more stored without summaries, a wavefront per 256 units: row lengths at the edges of a
+"""Rows that a launch finds by itself (dense, one row per request or up to 64 ragged requests): those of 64 units and more
+stored without summaries, a wavefront per 256 units, and those of more than 256 units with them, a wavefront or a
+workgroup per row: row lengths at the edges of a
 step (one unit, a part and a unit, odd numbers of units), rows off the 16-byte grid, requests without rows, keep
 vectors, bad indexes, one row per request in and out of order, 64 requests and 65 (the general kernel again),
 records that wrap at the end of the ring, NaN and infinities; singly, batched, partly dropped, into the caller's
-memory, and in replayed steps whose selection grows.  Byte for byte against the oracle."""
+memory, and in replayed steps whose selection grows.  Byte for byte against the oracle (summaries: _util's tolerances)."""
 import numpy as np
 import pytest
 import torch
 
 import oracle as orc
 from workloads import prng
+from _util import compare_record
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -103,6 +106,44 @@ def test_records_against_the_oracle(B, elems, lead, src, out):
                                    row_index=idx)
             got = dst.cpu().numpy()
             assert np.array_equal(got[:ref.size], ref) and np.all(got[bound:] == 0xC3), (name, elems)
+
+
+@pytest.mark.parametrize("elems,lead", [(2056, 0), (5120, 0), (5128, 0), (8192, 0), (8200, 0), (16400, 0), (2057, 1), (5125, 0), (8191, 3), (20001, 0)])
+@pytest.mark.parametrize("src,out,mask", [(1, 0, 7), (1, 1, 5), (1, 4, 2), (2, 0, 3), (3, 3, 7)])
+@pytest.mark.parametrize("many", [False, True])     # rows enough for a wavefront each, or not
+def test_summaries_against_the_oracle(B, elems, lead, src, out, mask, many):
+    if src == 3:
+        elems //= 2
+    rows = 260
+    x = _source(rows, elems, lead, src)
+    xc = torch.cat([x.cpu(), torch.zeros(1, elems, dtype=TORCH[src])])
+    scale = np.nan_to_num(xc.float().abs().mean(1).numpy(), posinf=0.0)
+    rng = np.random.default_rng(elems)
+    counts = [0, 1, 40, 0, 63, 30, 0] if not many else [0, 1, 230, 1400, 0, 500, 36]
+    ragged = np.array([[i, int(rng.integers(0, rows - min(c, 250) - 1)), 0, c, 1] for i, c in enumerate(counts)], dtype=np.uint32)
+    index = rng.integers(0, rows, sum(counts)).astype(np.int32)
+    index[::29] = rows
+    keep = np.array([1, 1, 0, 1, 1, 1, 0], dtype=np.uint8)
+    spread = np.array([[i, i % rows, 0, 1, 1] for i in range(1200 if not many else 2300)], dtype=np.uint32)
+    lots = np.array([[i, (i * 3) % 200, 0, 2 if not many else 33, 1] for i in range(70)], dtype=np.uint32)
+    cases = [(ragged, None, index), (ragged, keep, index), (spread, None, None), (lots, None, None), (lots[:64], None, None)]
+    s = torch.cuda.current_stream().cuda_stream
+    for reqs, k, idx in cases:
+        at = idx if idx is not None else np.concatenate([q[1] + np.arange(q[3]) for q in reqs])
+        kept = np.ones(at.size, bool) if k is None else np.repeat(k, reqs[:, 3]).astype(bool)
+        size = B.record_bytes(len(reqs), at.size, elems, out, mask)
+        with B.Ring(2 * size + 4096, 2 * size + 4096, max_reqs_per_observe=4096) as ring:
+            for seq in range(2):        # (the second one wraps)
+                ring.observe_tensor(2, x, reqs, step_id=seq, stream=s, out_dtype=out, summary_mask=mask,
+                                    keep_mask=None if k is None else torch.from_numpy(k).to(DEV),
+                                    row_index=None if idx is None else torch.from_numpy(idx).to(DEV))
+                ring.drain(B.DRAIN_FLUSH)
+                (view,) = ring.poll_host()
+                ref = orc.build_record(xc, reqs, seq=seq, step_id=seq, point_id=2, out_dtype=out, summary_mask=mask, keep_mask=k,
+                                       row_index=idx)
+                compare_record(view.bytes(), ref, what=f"{elems} {len(reqs)}", mean_abs=scale[at[kept]])
+                ring.release_host(view.seq)
+            assert ring.get_stats().bad_rows == (0 if idx is None else 2 * int(((idx == rows) & kept).sum()))
 
 
 @pytest.mark.parametrize("elems,lead,shape", [(4096, 0, "one"), (2056, 0, "slots"), (4096, 0, "ragged"), (4099, 0, "ragged")])
