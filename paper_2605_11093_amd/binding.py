@@ -13,6 +13,12 @@ from typing import List, Optional, Sequence
 
 import numpy as np
 
+try:                        # native marshalling of the per-tensor calls; without it (or torch) they go through ctypes
+    import torch as _torch_first                                    # noqa: F401  (its libraries are what the module links)
+    from . import _dmi_python as _native
+except ImportError:
+    _native = None
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "libdmi.so")
 _lib = None
@@ -226,6 +232,8 @@ def lib():
                  "dmi_exporter_release_many"):
         getattr(L, name).restype = C.c_int32
     _lib = L
+    if _native is not None:
+        _native.bind_into(C.cast(L.dmi_observe_into, C.c_void_p).value)
     return L
 
 
@@ -283,19 +291,22 @@ def _reqs_buffer(reqs):
 _PACK_TENSOR = struct.Struct("=QI4xqqqq").pack
 _PACK_SELECTION = struct.Struct("=I4xQQQ").pack
 _PACK_TRANSFORM = struct.Struct("=II").pack
-_into_fn = None
+_into_fn = None             # set: what observe_into calls in place of the library's entry point, structs as bytes
+_into_bytes = None
 
 
 def _into_raw():
     """dmi_observe_into taking its structs as bytes."""
-    global _into_fn
-    if _into_fn is None:
+    global _into_bytes
+    if _into_fn is not None:
+        return _into_fn
+    if _into_bytes is None:
         f = lib()["dmi_observe_into"]
         f.restype = C.c_int32
         f.argtypes = [C.c_uint32, C.c_char_p, C.c_char_p, C.c_char_p, C.c_uint64, C.c_uint64, C.c_uint32, C.c_void_p,
                       C.c_uint64, C.c_void_p, C.c_void_p]
-        _into_fn = f
-    return _into_fn
+        _into_bytes = f
+    return _into_bytes
 
 
 def observe_into(point_id: int, tensor, reqs, out, *, seq: int, step_id: int, rank_tag: int = 0,
@@ -329,7 +340,12 @@ def observe_into(point_id: int, tensor, reqs, out, *, seq: int, step_id: int, ra
     return n.value
 
 
-class PreparedObserve:
+if _native is not None:     # the plain case without Python in between; all else comes back to the function above
+    _native.setup(observe_into, _check, globals())
+    observe_into = _native.observe_into
+
+
+class PreparedObserve(_native.Prepared if _native is not None else object):
     """The argument structs of one dmi_observe / dmi_observe_paged call, built once so
     that a per-step loop pays only the foreign call itself.  Calling it returns the
     raw status code."""
@@ -356,9 +372,15 @@ class PreparedObserve:
                                 (C.c_uint32 * 8)(*paged.heads_sel))
             self._fn = lib().dmi_observe_paged
         self._a = (C.byref(self._src), C.byref(self._sel), C.byref(self._xf))
+        if _native is not None and type(point_id) is int and self._h:
+            self._bind(C.cast(self._fn, C.c_void_p).value, self._h.value, point_id & 0xFFFFFFFF, C.addressof(self._src),
+                       C.addressof(self._sel), C.addressof(self._xf))
 
-    def __call__(self, step_id: int, stream: int) -> int:
+    def _call(self, step_id: int, stream: int) -> int:
         return self._fn(self._h, self._point, self._a[0], self._a[1], self._a[2], step_id, stream)
+
+    if _native is None:
+        __call__ = _call
 
 
 def _paged_struct(cache, paged_or_table, *, block_size=None, n_heads=None, head_dim=None, heads_sel=None):

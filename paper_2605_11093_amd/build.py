@@ -69,6 +69,27 @@ def build_torch_op() -> str:
     return TORCH_SO
 
 
+PY_SO = os.path.join(HERE, "_dmi_python.so")
+PY_SRC = os.path.join(HERE, "csrc", "dmi_python.cpp")
+
+
+def build_python() -> str:
+    """Native marshalling of the binding's per-tensor calls (host code only: g++ against Python and libtorch)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension as ce
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"]]
+    for inc in ce.include_paths("cuda"):
+        cmd += ["-isystem", inc]
+    cmd += [PY_SRC, "-o", PY_SO, "-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + tlib]
+    subprocess.check_call(cmd)
+    return PY_SO
+
+
 C_CLIENT_SRC = os.path.join(ROOT, "examples", "c_client.c")
 C_CLIENT = os.path.join(ROOT, "examples", "c_client")
 
@@ -88,4 +109,5 @@ if __name__ == "__main__":
     print(build())
     print(build_bench())
     print(build_torch_op())
+    print(build_python())
     print(build_c_client())
