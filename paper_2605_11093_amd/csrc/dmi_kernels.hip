@@ -588,8 +588,9 @@ __device__ __forceinline__ void touch_argument_lines(const T &a, const uint8_t *
 // ---------------------------------------------------------------- capture kernel
 // How a launch of the general kernel goes through its rows (kernels of their own, or the registers of one would cost the
 // others a workgroup per compute unit).  Without summaries: units dealt to lanes in order, whatever row they are of.
-// With summaries: a workgroup per row; several rows per wavefront, at most 256 units each; a wavefront per row.
-enum RowMode { ROWS_FLAT = 0, SUMM_ROWS = 1, SUMM_SHORT = 2, SUMM_WAVE = 3 };
+// With summaries: a workgroup per row; several rows per wavefront, at most 256 units each (ONCE: read past the
+// memory-side cache); a wavefront per row.
+enum RowMode { ROWS_FLAT = 0, SUMM_ROWS = 1, SUMM_SHORT = 2, SUMM_WAVE = 3, SUMM_SHORT_ONCE = 4 };
 
 // The request table of a launch into the caller's memory, where the launch carries it: in the second block of
 // the kernel's own arguments, `first` bytes in.  Memory like any other to lanes that read entries of their own; and
@@ -613,8 +614,9 @@ template <int ES_IN, int VEC, int OUT, int MODE, typename SRC, bool LOOSE>
 __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelArgs a, const SRC b)
 {
     constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
+    constexpr bool SHORT_ROWS = MODE == SUMM_SHORT || MODE == SUMM_SHORT_ONCE;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    __shared__ float row_sums[MODE == SUMM_SHORT || MODE == SUMM_WAVE ? 4 * 192 : 1];   // per wavefront: totals of 64 rows
+    __shared__ float row_sums[SHORT_ROWS || MODE == SUMM_WAVE ? 4 * 192 : 1];   // per wavefront: totals of 64 rows
     const uint32_t y = INTO ? 0u : blockIdx.y;      // which tensor of the batch this workgroup works on
     const uint8_t *const src = b.src[y];
     const uint32_t point_id = b.point[y];
@@ -996,7 +998,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto zero_unless = [](bool keep, unit_t v) -> unit_t { return keep ? v : unit_t{}; };
 
     // Row totals of a wavefront's 64 rows at most, [from, upto), from its part of LDS to the record.
-    float *const stash = row_sums + (MODE == SUMM_SHORT || MODE == SUMM_WAVE ? wave * 192u : 0u);       // [3][64]
+    float *const stash = row_sums + (SHORT_ROWS || MODE == SUMM_WAVE ? wave * 192u : 0u);       // [3][64]
     auto flush_totals = [&](uint64_t from, uint64_t upto) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1129,7 +1131,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
                     }
                 }
             }
-        } else if constexpr (MODE == SUMM_SHORT) {
+        } else if constexpr (SHORT_ROWS) {
             // ---- summaries of short rows (up to 256 units): 4 to 64 lanes share a row, each with up to four
             //      of its units, so one step of a wavefront is 64 / row_lanes whole rows and a row costs one
             //      reduction over few lanes (a row of 32 units used to take a wavefront of its own, half of its
@@ -1139,7 +1141,8 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
             //      LDS until 64 rows are together: memory operations of a wavefront complete in order, so a row's
             //      place asked for behind a step's loads, or a store inside the loop, would make every step wait.
             //      Bound: HBM reads.  8 caches x 72.7 k rows of 32 units, norms and largest magnitudes:
-            //      297 -> 69 us (1.0 -> 4.4 TB/s read).
+            //      297 -> 69 us (1.0 -> 4.4 TB/s read), 66 -> 60 us past the memory-side cache, which holds less than a launch like
+            //      this reads.
             const uint32_t lpr = row_lanes, lg = 31u - (uint32_t)__builtin_clz(lpr);
             const uint32_t rpi = 64u >> lg;                             // rows per step, at most 16
             const uint32_t sub_r = lane >> lg, l_r = lane & (lpr - 1u);
@@ -1174,7 +1177,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
 #pragma unroll
                 for (uint32_t k = 0; k < U; k++) {
                     const uint8_t *ptr = ref.ok && in_row[k] ? ref.base + unit_off[k] : zeros;
-                    v[k] = *(global_unit_t *)ptr;
+                    v[k] = MODE == SUMM_SHORT_ONCE ? __builtin_nontemporal_load((global_unit_t *)ptr) : *(global_unit_t *)ptr;
                 }
             };
             auto process = [&](const unit_t (&v)[U], uint64_t g0) {
@@ -2080,11 +2083,15 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
 }
 
 // ---------------------------------------------------------------- small kernels
+// Words for device memory, carried by the launch.  Up to 896 of them in 3.6 KB of arguments, larger tables 3072 at a time:
+// a launch of 12 KB of arguments takes the host as long as one of 4 KB (3.3 us; 24 KB: 6.9).
+template <uint32_t N>
 struct UploadChunk {
-    uint32_t w[896];
+    uint32_t w[N];
 };
 
-__global__ void __launch_bounds__(kThreads) upload_kernel(uint32_t *dst, const UploadChunk c, uint32_t n)
+template <uint32_t N>
+__global__ void __launch_bounds__(kThreads) upload_kernel(uint32_t *dst, const UploadChunk<N> c, uint32_t n)
 {
     for (uint32_t i = threadIdx.x; i < n; i += kThreads) dst[i] = c.w[i];
 }
@@ -2216,6 +2223,12 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
     const CaptureKernelArgs &k = a;
     if (VEC == 1 && a.units_per_row >= kThreads) return hipErrorInvalidValue;   // rows go by elements only if they are short
     if (a.summary_mask && a.row_lanes <= 64u) {
+        if constexpr (OUT == OUT_NONE && VEC > 1 && !LOOSE) {
+            if (a.read_once) {
+                DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT_ONCE, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
+                return hipGetLastError();
+            }
+        }
         DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT, SRC, LOOSE>), g, a.lds_bytes, s, k, b);
     } else if (a.summary_mask) {
         if constexpr (VEC > 1) {
@@ -2357,15 +2370,23 @@ hipError_t launch_capture_into(const CaptureArgs &a, const IntoArgs &b, bool dec
     return decode ? launch_decode_any(a, b, s) : launch_any(a, b, grid, vec16, s);
 }
 
+template <uint32_t N>
+static hipError_t launch_upload_chunk(uint32_t *dst, const uint32_t *words, uint32_t n, hipStream_t s)
+{
+    UploadChunk<N> c;
+    std::memcpy(c.w, words, n * 4u);
+    hipLaunchKernelGGL((upload_kernel<N>), dim3(1), dim3(kThreads), 0, s, dst, c, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words, hipStream_t s)
 {
-    for (uint32_t o = 0; o < n_words; o += 896u) {
-        UploadChunk c;
-        const uint32_t n = n_words - o < 896u ? n_words - o : 896u;
-        std::memcpy(c.w, words + o, n * 4u);
-        hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kThreads), 0, s, dst + o, c, n);
-        hipError_t e = hipGetLastError();
+    for (uint32_t o = 0; o < n_words;) {
+        const uint32_t left = n_words - o, n = left < 3072u ? left : 3072u;
+        const hipError_t e = n <= 896u ? launch_upload_chunk<896>(dst + o, words + o, n, s)
+                                       : launch_upload_chunk<3072>(dst + o, words + o, n, s);
         if (e != hipSuccess) return e;
+        o += n;
     }
     return hipSuccess;
 }
