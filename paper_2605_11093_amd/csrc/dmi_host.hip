@@ -462,7 +462,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // youngest ends 1.4 times as late as the oldest; and compute units differ by +-8 %), while
     // workgroups that stay for a whole tensor all have to end before the next tensor's can start,
     // and a resident set shared among the tensors leaves every tensor's tail to a few workgroups.
-    constexpr uint64_t kItemsPerGroupInBatch = 4u;
+    static constexpr uint64_t kItemsPerGroupInBatch = 4u;
     auto balanced = [nb, flat](uint64_t items, uint64_t most = kItemsPerGroupInBatch) -> uint64_t {
         if (flat || items * nb <= kResident) return items;
         uint64_t rounds = (items * nb + kResident - 1u) / kResident;
