@@ -462,8 +462,8 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // youngest ends 1.4 times as late as the oldest; and compute units differ by +-8 %), while
     // workgroups that stay for a whole tensor all have to end before the next tensor's can start,
     // and a resident set shared among the tensors leaves every tensor's tail to a few workgroups.
-    static constexpr uint64_t kItemsPerGroupInBatch = 4u;
-    auto balanced = [nb, flat](uint64_t items, uint64_t most = kItemsPerGroupInBatch) -> uint64_t {
+    constexpr uint64_t kItemsPerGroupInBatch = 4u;
+    auto balanced = [nb, flat](uint64_t items, uint64_t most) -> uint64_t {
         if (flat || items * nb <= kResident) return items;
         uint64_t rounds = (items * nb + kResident - 1u) / kResident;
         if (nb > 1u && rounds > most) rounds = most;
@@ -507,7 +507,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         const bool alone = a.out_dtype == 0u;
         a.wave_rows = rows >= 2048u && (upr <= 512u || (alone && upr <= 768u));
         const uint64_t per_wave = alone && rows >= 4096u ? 2u : 1u;
-        groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed);
+        groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed, kItemsPerGroupInBatch);
     } else if (a.out_dtype && upr >= kLongRowUnits && finds_rows_itself) {
         // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
         a.step_per_wave = 1;
@@ -516,7 +516,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
         const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;
-        groups = slices * nb <= kResident ? slices : balanced((slices + 3u) / 4u);
+        groups = slices * nb <= kResident ? slices : balanced((slices + 3u) / 4u, kItemsPerGroupInBatch);
     }
     return groups < 1u ? 1u : groups > kMaxGrid ? kMaxGrid : (uint32_t)groups;
 }
