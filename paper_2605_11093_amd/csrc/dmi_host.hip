@@ -470,7 +470,12 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         return (items + rounds - 1u) / rounds;
     };
     uint64_t groups;
-    if (a.summary_mask && a.row_lanes <= 64u) {
+    // Rows of 129 to 256 units have a wavefront's lanes to themselves either way; in capture_rows_kernel they come without the
+    // general kernel's prologue (12.8 k rows of 256 units, statistics 13.8 -> 10.9 us, stored too 20.9 -> 18.4; 3 k of 192
+    // 6.3 -> 4.1; off the 16-byte grid 19.0 -> 13.2; 80 x 256 rows of 256 in one launch 27.1 -> 18.4).  Not statistics alone of
+    // very many of the shortest of them (40 k rows of 130 units: 20.4 and 21.9).
+    const bool own_wavefront = finds_rows_itself && a.row_lanes == 64u && (upr >= 192u || a.out_dtype || listed * nb < 32768u);
+    if (a.summary_mask && a.row_lanes <= 64u && !own_wavefront) {
         const uint64_t rows = 4u * (64u / a.row_lanes);             // what a workgroup takes in one step
         // (statistics alone, 8 caches x 72.7 k rows of 32 units: 66 us, past the cache 60; of 128 units 118, 104, and with eight
         // items per workgroup 101)
@@ -488,7 +493,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         //   batches, one row per request: 80 x 256 rows of 512 39.5 / 30.9 / 33.1, of 1024 57.4 / 62.5 / 62.6 (rows stored too 120 / 138
         //   / 116, and 115 past the cache)
         a.step_per_wave = 1;
-        a.wave_rows = upr <= 640u && planned * nb >= 2048u;
+        a.wave_rows = upr <= 256u || (upr <= 640u && planned * nb >= 2048u);
         // past the memory-side cache what does not fit it; and, of a batch's tensors, which have been waiting for each
         // other, already from half of that on if nothing is stored (32 x 256 rows of 1024 units 24.7 -> 21.9, 80 x 256 57.4 -> 49.7)
         a.read_once = source_bytes >= kMemorySideCache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);

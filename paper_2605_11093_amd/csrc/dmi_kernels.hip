@@ -1727,7 +1727,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 // ONCE: launches that read more than the 256 MB memory-side cache holds do so past it (non-temporal loads): 9.3 k x 14336
 // 73.4 -> 69.4 us; where what is read may still be there from the kernel that wrote it they lose (9.3 k x 4096: 18.8
 // and 21.8), and between 133 and 256 MB it depends on what ran before.
-// With summaries (SUMM), of more than 256 units: a wavefront per row, or a workgroup per row with a quarter of it to each
+// With summaries (SUMM), of more than 128 units: a wavefront per row, or a workgroup per row with a quarter of it to each
 // wavefront (plan_grid() says which, with figures); lanes, parts and the order of the sums are the general and the
 // decode-shaped kernel's, so a row's summaries have the same bits wherever it is captured.  80 tensors of 256 x 8192,
 // statistics alone: 61 -> 49.5 us (6.8 TB/s read).
@@ -2222,7 +2222,7 @@ static hipError_t launch_t(const CaptureArgs &a, const SRC &b, uint32_t grid, hi
     const dim3 g(grid, a.n_batch);
     const CaptureKernelArgs &k = a;
     if (VEC == 1 && a.units_per_row >= kThreads) return hipErrorInvalidValue;   // rows go by elements only if they are short
-    if (a.summary_mask && a.row_lanes <= 64u) {
+    if (a.summary_mask && a.row_lanes <= 64u && !(a.step_per_wave && !a.force_drop)) {
         if constexpr (OUT == OUT_NONE && VEC > 1 && !LOOSE) {
             if (a.read_once) {
                 DMI_LAUNCH_CAPTURE(a.step != nullptr, (capture_kernel<ES_IN, VEC, OUT, SUMM_SHORT_ONCE, SRC, LOOSE>), g, a.lds_bytes, s, k, b);

@@ -1,5 +1,5 @@
 """Rows that a launch finds by itself (dense, one row per request or up to 64 ragged requests): those of 64 units and more
-stored without summaries, a wavefront per 256 units, and those of more than 256 units with them, a wavefront or a
+stored without summaries, a wavefront per 256 units, and those of more than 128 units with them, a wavefront or a
 workgroup per row: row lengths at the edges of a
 step (one unit, a part and a unit, odd numbers of units), rows off the 16-byte grid, requests without rows, keep
 vectors, bad indexes, one row per request in and out of order, 64 requests and 65 (the general kernel again),
@@ -108,7 +108,7 @@ def test_records_against_the_oracle(B, elems, lead, src, out):
             assert np.array_equal(got[:ref.size], ref) and np.all(got[bound:] == 0xC3), (name, elems)
 
 
-@pytest.mark.parametrize("elems,lead", [(2056, 0), (5120, 0), (5128, 0), (8192, 0), (8200, 0), (16400, 0), (2057, 1), (5125, 0), (8191, 3), (20001, 0)])
+@pytest.mark.parametrize("elems,lead", [(1040, 0), (2048, 0), (2047, 0), (1101, 3), (2056, 0), (5120, 0), (5128, 0), (8192, 0), (8200, 0), (16400, 0), (2057, 1), (5125, 0), (8191, 3), (20001, 0)])
 @pytest.mark.parametrize("src,out,mask", [(1, 0, 7), (1, 1, 5), (1, 4, 2), (2, 0, 3), (3, 3, 7)])
 @pytest.mark.parametrize("many", [False, True])     # rows enough for a wavefront each, or not
 def test_summaries_against_the_oracle(B, elems, lead, src, out, mask, many):
