@@ -1043,7 +1043,7 @@ def main():
     cap_us = head["launch_us_mean"]
     cap_gbs = alg_total / n_launch / cap_us / 1e3
     roofline = {"bound": "hbm",
-                "kernel": "capture_kernel<bf16, 16-byte units, raw, no summaries>, one launch for the step's 80 "
+                "kernel": "capture_rows_kernel<bf16, raw, no summaries>, one launch for the step's 80 "
                           "tensors (config 5), every launch of the headline's timed region",
                 "timing": "HIP events that take the launch's own start and end time stamps from the hardware "
                           "(hipExtLaunchKernelGGL on the launch stream): the kernel's duration as a profiler reports it",

@@ -432,11 +432,9 @@ dmi_status_t stage_selection(dmi_ring *r, const dmi_selection_t *sel, bool paged
 // Work items per launch path, and a grid that gives every workgroup the same number of them:
 // with a fixed grid of "as many as fit" the last round is run by a fraction of the
 // workgroups while the rest idle (up to half the launch for 1 < items/grid < 2).
-// kResident is five workgroups per compute unit: what the kernels that store rows without summaries hold (84 to 90
-// vector registers).  With summaries they hold from four (rows off the 16-byte grid, up to 256 units or a wavefront
-// per row: 87 to 126 registers) to seven (a workgroup per row on the grid: 63 to 72), and eight where units are single
-// elements; they are planned for five like the others, which leaves the first a short last round.  In a batch
-// (gridDim.y = nb) each workgroup stays with one tensor.
+// kResident is five workgroups per compute unit: the kernels hold from four (summaries of short rows off the 16-byte grid:
+// up to 118 vector registers) to seven (rows dealt flat: 52, or a workgroup per row: 63 to 72); they are all planned for
+// five.  In a batch (gridDim.y = nb) each workgroup stays with one tensor.
 uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
 {
     constexpr uint64_t kResident = 5u * 256u;
@@ -448,12 +446,12 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     const bool flat = a.simple && !a.paged;
     // capture_rows_kernel scans the table with a request per lane
     const bool finds_rows_itself = !a.paged && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u));
-    const uint64_t source_bytes = listed * nb * a.row_elems * dtype_size(a.src_dtype);
     constexpr uint64_t kMemorySideCache = 256000000u;
     // With a keep vector half of the listed rows are planned for: a workgroup that finds itself behind the last kept row has
     // spent a microsecond and a place on a compute unit to learn that, one that gets a second row little more than its
     // time (6.4 k kept of 12.8 k listed rows of 1024 units: 23.5 us planned for all, 21.1 like this).
     const uint64_t planned = a.keep_mask ? (listed + 1u) / 2u : listed;
+    const uint64_t source_bytes = planned * nb * a.row_elems * dtype_size(a.src_dtype);
     a.step_per_wave = a.read_once = a.wave_rows = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
