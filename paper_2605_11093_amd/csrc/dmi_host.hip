@@ -447,10 +447,20 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // capture_rows_kernel scans the table with a request per lane
     const bool finds_rows_itself = !a.paged && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u));
     constexpr uint64_t kMemorySideCache = 256000000u;
-    // With a keep vector half of the listed rows are planned for: a workgroup that finds itself behind the last kept row has
-    // spent a microsecond and a place on a compute unit to learn that, one that gets a second row little more than its
-    // time (6.4 k kept of 12.8 k listed rows of 1024 units: 23.5 us planned for all, 21.1 like this).
-    const uint64_t planned = a.keep_mask ? (listed + 1u) / 2u : listed;
+    // Rows that a record is expected to have.  With a keep vector that the host does not know: half of the listed ones, but
+    // never fewer workgroups than fill the GPU while there are rows for them.  A workgroup that finds itself behind the last kept
+    // row has spent a microsecond and a place on a compute unit to learn that; on a GPU that is not full that costs nothing, and
+    // a row that waits for another one costs a trip to memory.  (Planned for the kept rows / half / all, us: 16.4 k listed rows of
+    // 1024 units fp32, statistics, 14 % kept 9.5 / 11.3 / 14.1, 52 % 23.1 / 23.1 / 24.6, 100 % 39.1 / 40.4 / 39.1; stored 14.3 / 15.3 / 18.3,
+    // 43.0 / 43.0 / 45.3, 80.0 / 81.2 / 80.0; 1 k listed rows of 1024, 100 % 4.4 / 5.7 / 4.4; 4.1 k of 512, statistics, 45 % - / 5.6 / 4.3,
+    // 100 % 6.1 / 9.0 / 6.1; 55 rows of 1024, 100 % 4.1 / 4.6 / 4.1.)
+    constexpr uint64_t kFull = 8u * 256u;       // workgroups
+    const bool guess = a.keep_mask && !a.rows_known;
+    const uint64_t expected = a.rows_known ? a.kept_rows : guess ? (listed + 1u) / 2u : listed;
+    auto planned = [&](auto groups_for) -> uint64_t {       // workgroups for as many rows
+        const uint64_t n = groups_for(expected), full = (kFull + nb - 1u) / nb;
+        return guess && n < full ? std::min(groups_for(listed), full) : n;
+    };
     // (what is listed, also with a keep vector: 6.4 k kept of the rows above 21.1 us past the cache, 21.6 through it)
     const uint64_t source_bytes = listed * nb * a.row_elems * dtype_size(a.src_dtype);
     a.step_per_wave = a.read_once = a.wave_rows = 0;
@@ -492,11 +502,11 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         //   batches, one row per request: 80 x 256 rows of 512 39.5 / 30.9 / 33.1, of 1024 57.4 / 62.5 / 62.6 (rows stored too 120 / 138
         //   / 116, and 115 past the cache)
         a.step_per_wave = 1;
-        a.wave_rows = upr <= 256u || (upr <= 640u && planned * nb >= 2048u);
+        a.wave_rows = upr <= 256u || (upr <= 640u && (guess ? listed : expected) * nb >= 2048u);
         // past the memory-side cache what does not fit it; and, of a batch's tensors, which have been waiting for each
         // other, already from half of that on if nothing is stored (32 x 256 rows of 1024 units 24.7 -> 21.9, 80 x 256 57.4 -> 49.7)
         a.read_once = source_bytes >= kMemorySideCache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);
-        groups = a.wave_rows ? (planned + 3u) / 4u : planned;
+        groups = planned([&](uint64_t rows) { return a.wave_rows ? (rows + 3u) / 4u : rows; });
     } else if (a.summary_mask) {
         // Rows of more than 256 units of paged caches, or of more than 64 ragged requests: a workgroup per row, or, where a
         // launch has rows enough, a wavefront per row.
@@ -516,7 +526,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
         a.step_per_wave = 1;
         a.read_once = source_bytes >= kMemorySideCache;
-        groups = (planned * ((upr + 255u) / 256u) + 3u) / 4u;
+        groups = planned([&](uint64_t rows) { return (rows * ((upr + 255u) / 256u) + 3u) / 4u; });
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
         const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;
@@ -618,6 +628,8 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
     bool one_row_each = true;
     for (uint32_t i = 0; one_row_each && i < sel->n_reqs; i++) one_row_each = sel->reqs[i].tok_count == 1u;
     const bool simple = one_row_each && sel->keep_mask_dev == nullptr;
+    a.rows_known = pl.size_known ? 1u : 0u;
+    a.kept_rows = (uint32_t)pl.rows_known;
     a.one_row_each = one_row_each ? 1u : 0u;
     a.listed_rows = (uint32_t)listed;
     const bool tab_lds = !simple && sel->n_reqs <= kLdsTableMax;

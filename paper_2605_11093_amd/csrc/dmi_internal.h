@@ -147,6 +147,7 @@ struct CaptureArgs : CaptureKernelArgs {
     uint32_t point_id;              // same, BatchArgs::point
     uint32_t one_row_each;          // every request lists exactly one row (a keep vector may still drop some)
     uint32_t listed_rows;           // rows the selection lists (all requests kept)
+    uint32_t rows_known, kept_rows; // whether the host knows the keep vector (or there is none), and how many rows that keeps
     const uint32_t *row_map;        // decode-shaped kernel, requests listing several rows: source row of every
                                     // output row, written by the host behind the request table
     uint32_t lds_bytes;
