@@ -446,7 +446,6 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     const bool flat = a.simple && !a.paged;
     // capture_rows_kernel scans the table with a request per lane
     const bool finds_rows_itself = !a.paged && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u));
-    constexpr uint64_t kMemorySideCache = 256000000u;
     // Rows that a record is expected to have.  With a keep vector that the host does not know: half of the listed ones, but
     // never fewer workgroups than fill the GPU while there are rows for them.  A workgroup that finds itself behind the last kept
     // row has spent a microsecond and a place on a compute unit to learn that; on a GPU that is not full that costs nothing, and
@@ -461,8 +460,14 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         const uint64_t n = groups_for(expected), full = (kFull + nb - 1u) / nb;
         return guess && n < full ? std::min(groups_for(listed), full) : n;
     };
-    // (what is listed, also with a keep vector: 6.4 k kept of the rows above 21.1 us past the cache, 21.6 through it)
-    const uint64_t source_bytes = listed * nb * a.row_elems * dtype_size(a.src_dtype);
+    // Where a launch reads more than the memory-side cache holds, it does so past it (non-temporal loads).  What such a launch
+    // leaves in the cache is no use to anyone, and what others have left there it would throw out before it gets to it (300 MB, written by the
+    // kernel before, through / past the cache: bf16 -> fp8 84.8 / 66.9 us, raw 107 / 90, statistics 59.9 / 43.7).  Below that the launch itself gains
+    // little (266 MB cold 70.7 / 69.0, raw 94.9 / 88.9, statistics 44.9 / 43.8; just written 58.7 / 58.6, 78.5 / 79.0, 38.3 / 38.2), and the next
+    // kernel that reads the rows finds them gone, also where they were there (a sum over them: 60 / 87 us at 266 MB, 49 / 69 at 200, 30 / 37 at 76).
+    constexpr uint64_t kMemorySideCache = 256ull << 20;
+    const uint64_t source_bytes = expected * nb * a.row_elems * dtype_size(a.src_dtype);
+    const bool past_the_cache = source_bytes > kMemorySideCache;
     a.step_per_wave = a.read_once = a.wave_rows = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
@@ -488,7 +493,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         const uint64_t rows = 4u * (64u / a.row_lanes);             // what a workgroup takes in one step
         // (statistics alone, 8 caches x 72.7 k rows of 32 units: 66 us, past the cache 60; of 128 units 118, 104, and with eight
         // items per workgroup 101)
-        a.read_once = !a.out_dtype && source_bytes >= kMemorySideCache;
+        a.read_once = !a.out_dtype && past_the_cache;
         groups = balanced((listed + rows - 1u) / rows, a.out_dtype ? kItemsPerGroupInBatch : 8u);
     } else if (a.summary_mask && finds_rows_itself) {
         // capture_rows_kernel: a wavefront per row while a launch has rows enough to fill the GPU that way and they are
@@ -503,9 +508,9 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         //   / 116, and 115 past the cache)
         a.step_per_wave = 1;
         a.wave_rows = upr <= 256u || (upr <= 640u && (guess ? listed : expected) * nb >= 2048u);
-        // past the memory-side cache what does not fit it; and, of a batch's tensors, which have been waiting for each
-        // other, already from half of that on if nothing is stored (32 x 256 rows of 1024 units 24.7 -> 21.9, 80 x 256 57.4 -> 49.7)
-        a.read_once = source_bytes >= kMemorySideCache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);
+        // (a batch's tensors have been kept for this launch, nothing reads them behind it: from half of the cache on if nothing is
+        // stored.  134 MB, cold 25.1 -> 24.4 us, just written 21.3 -> 20.9; 200 MB 34.9 -> 34.1 and 29.7 -> 29.0)
+        a.read_once = past_the_cache || (nb > 1u && !a.out_dtype && source_bytes > kMemorySideCache / 2u);
         groups = planned([&](uint64_t rows) { return a.wave_rows ? (rows + 3u) / 4u : rows; });
     } else if (a.summary_mask) {
         // Rows of more than 256 units of paged caches, or of more than 64 ragged requests: a workgroup per row, or, where a
@@ -525,7 +530,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     } else if (a.out_dtype && upr >= kLongRowUnits && finds_rows_itself) {
         // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
         a.step_per_wave = 1;
-        a.read_once = source_bytes >= kMemorySideCache;
+        a.read_once = past_the_cache;
         groups = planned([&](uint64_t rows) { return (rows * ((upr + 255u) / 256u) + 3u) / 4u; });
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough

@@ -153,7 +153,7 @@ struct CaptureArgs : CaptureKernelArgs {
     uint32_t lds_bytes;
     uint32_t wave_rows;             // summaries of rows of more than 256 units: a wavefront per row, not a workgroup
     uint32_t step_per_wave;         // capture_rows_kernel takes the launch: a wavefront per 256 units of a row
-    uint32_t read_once;             // it reads more than the memory-side cache holds
+    uint32_t read_once;             // rows are read past the memory-side cache (plan_grid() says when)
     uint32_t loose;                 // not on a 16-byte grid, but long enough for 16-byte units
     uint32_t limit_units;           // units per row by which a record's size is limited
     // record geometry and header words, filled by the host when it knows them exactly (no keep

@@ -1724,9 +1724,7 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 // Kernel times, before and after: bf16 -> fp8, 32 requests: 9.3 k x 4096 (every fourth token) 23.5 -> 18.8 us (6.1 TB/s),
 // 9.3 k x 14336 85 -> 69.4 (5.8 TB/s), 37 k x 4096 93 -> 79, 9.3 k x 2304 25 -> 13, 2000 x 4096 9.1 -> 5.9; raw: 9.3 k x 4096
 // 28.6 -> 24.2, 9.3 k x 14336 106 -> 92; one row per request, 80 tensors of 256 x 8192 raw in one launch 111 -> 107.
-// ONCE: launches that read more than the 256 MB memory-side cache holds do so past it (non-temporal loads): 9.3 k x 14336
-// 73.4 -> 69.4 us; where what is read may still be there from the kernel that wrote it they lose (9.3 k x 4096: 18.8
-// and 21.8), and between 133 and 256 MB it depends on what ran before.
+// ONCE: launches that read more than the memory-side cache holds do so past it (non-temporal loads; plan_grid() has the figures).
 // With summaries (SUMM), of more than 128 units: a wavefront per row, or a workgroup per row with a quarter of it to each
 // wavefront (plan_grid() says which, with figures); lanes, parts and the order of the sums are the general and the
 // decode-shaped kernel's, so a row's summaries have the same bits wherever it is captured.  80 tensors of 256 x 8192,

@@ -1,5 +1,6 @@
 """How launches are planned (host runtime on the CPU stand-in, tests/cpu_runtime/): the number of workgroups follows the
-rows that a keep vector is expected to keep."""
+rows that a keep vector is expected to keep, and a launch reads past the memory-side cache if what it is expected to read does not
+fit there."""
 import os
 import shutil
 import subprocess
@@ -53,3 +54,25 @@ def test_keep_vectors(plan, how, each, tensors):
     want = max(groups(8 * each), min(groups(16 * each), -(-FULL // tensors)))
     assert plan(**ask, keep="unknown")["grid"] == want
     assert plan(**ask, keep="1" * 16, step=1)["grid"] == want
+
+
+MB = 1 << 20
+
+
+@pytest.mark.parametrize("src,width,out,mask", [(BF16, 4096, FP8, 0), (BF16, 4096, BF16, 0), (FP32, 4096, 0, 7), (BF16, 4096, 0, 5),
+                                                (BF16, 4096, BF16, 5), (BF16, 512, 0, 5)])
+def test_past_the_cache(plan, src, width, out, mask):
+    row = width * (4 if src == FP32 else 2)
+
+    def reads(mb, **how):
+        return plan(src, width, 16, mb * MB // row // 16 // how.get("tensors", 1), out, mask, **how)["read_once"]
+
+    assert (reads(200), reads(255), reads(257), reads(400)) == (0, 0, 1, 1)
+    # of a launch with a keep vector counts what it is expected to read, not what is listed
+    half = "10" * 8
+    assert (reads(400, keep=half), reads(500, keep=half), reads(520, keep=half)) == (0, 0, 1)
+    assert (reads(1600, keep="1" + "0" * 15), reads(270, keep="1" * 16)) == (0, 1)
+    assert (reads(400, keep="unknown"), reads(500, keep="unknown"), reads(520, keep="unknown")) == (0, 0, 1)
+    # statistics of rows that a wavefront or more takes, of a batch: from half of the cache on
+    early = 0 if out or width == 512 else 1
+    assert (reads(120, tensors=8), reads(136, tensors=8), reads(260, tensors=8)) == (0, early, 1)
