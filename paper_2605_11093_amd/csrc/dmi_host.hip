@@ -510,7 +510,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         a.wave_rows = upr <= 256u || (upr <= 640u && (guess ? listed : expected) * nb >= 2048u);
         // (a batch's tensors have been kept for this launch, nothing reads them behind it: from half of the cache on if nothing is
         // stored.  134 MB, cold 25.1 -> 24.4 us, just written 21.3 -> 20.9; 200 MB 34.9 -> 34.1 and 29.7 -> 29.0)
-        a.read_once = past_the_cache || (nb > 1u && !a.out_dtype && source_bytes > kMemorySideCache / 2u);
+        a.read_once = past_the_cache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);
         groups = planned([&](uint64_t rows) { return a.wave_rows ? (rows + 3u) / 4u : rows; });
     } else if (a.summary_mask) {
         // Rows of more than 256 units of paged caches, or of more than 64 ragged requests: a workgroup per row, or, where a

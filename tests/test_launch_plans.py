@@ -75,4 +75,4 @@ def test_past_the_cache(plan, src, width, out, mask):
     assert (reads(400, keep="unknown"), reads(500, keep="unknown"), reads(520, keep="unknown")) == (0, 0, 1)
     # statistics of rows that a wavefront or more takes, of a batch: from half of the cache on
     early = 0 if out or width == 512 else 1
-    assert (reads(120, tensors=8), reads(136, tensors=8), reads(260, tensors=8)) == (0, early, 1)
+    assert (reads(127, tensors=8), reads(128, tensors=8), reads(260, tensors=8)) == (0, early, 1)
