@@ -1724,6 +1724,9 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 // Kernel times, before and after: bf16 -> fp8, 32 requests: 9.3 k x 4096 (every fourth token) 23.5 -> 18.8 us (6.1 TB/s),
 // 9.3 k x 14336 85 -> 69.4 (5.8 TB/s), 37 k x 4096 93 -> 79, 9.3 k x 2304 25 -> 13, 2000 x 4096 9.1 -> 5.9; raw: 9.3 k x 4096
 // 28.6 -> 24.2, 9.3 k x 14336 106 -> 92; one row per request, 80 tensors of 256 x 8192 raw in one launch 111 -> 107.
+// Under best effort the head, which tells whether the record fits, is asked for with everything else and looked at when the first
+// rows have been asked for: waited for in front of them it cost the launch of 80 tensors of 256 x 8192 raw 6 us (cold, all kept:
+// 116.5 -> 109.9, under the completeness policy 111; the general kernel 114).  A record that is dropped has read a step for nothing.
 // ONCE: launches that read more than the memory-side cache holds do so past it (non-temporal loads; plan_grid() has the figures).
 // With summaries (SUMM), of more than 128 units: a wavefront per row, or a workgroup per row with a quarter of it to each
 // wavefront (plan_grid() says which, with figures); lanes, parts and the order of the sums are the general and the
@@ -1838,9 +1841,11 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     const uint64_t off_sum = off_payload + ((payload_bytes + 63u) & ~63ull), sum_arr = ((uint64_t)n_rows * 4u + 63u) & ~63ull;
     const uint32_t n_sum = SUMM ? (uint32_t)__popc(a.summary_mask) : 0u;
     const uint64_t record_bytes = off_sum + n_sum * sum_arr;
-    bool dropped = false;
-    if constexpr (!INTO)
-        if (policy & kStepDropNewest) dropped = uniform_u64(head_v) + (y + 1ull) * record_bytes - tail > a.cap;
+    // (where the launch found the head is what it waits for longest: not before the first rows are on their way)
+    auto dropped = [&]() -> bool {
+        if constexpr (INTO) return false;
+        return (policy & kStepDropNewest) && uniform_u64(head_v) + (y + 1ull) * record_bytes - tail > a.cap;
+    };
     RingW w;
     w.ring = a.ring;
     w.cap = a.cap;
@@ -1853,7 +1858,10 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     };
 
     if (!meta) {
-        if (!INTO && ((policy & kStepSkip) || dropped)) return;
+        if (!INTO && (policy & kStepSkip)) return;
+        if constexpr (SUMM != 0) {
+            if (dropped()) return;
+        }
         const uint32_t n_steps = n_rows * a.parts;          // (the host keeps rows x units below 2^32)
         const uint8_t *const zeros = reinterpret_cast<const uint8_t *>(a.ctrl->zeros);
         struct Step { uint32_t g, part; const uint8_t *base; bool ok; };
@@ -2003,6 +2011,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
                 const Step st = step_at((uint32_t)s);
                 u32x4 v[U];
                 load(st, v);
+                if (dropped()) return;
                 settle();
                 n_bad += st.part == 0u && !st.ok ? 1u : 0u;     // a bad row is counted where it begins
                 store(st, v);
@@ -2038,7 +2047,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
             }
         }
         if (policy & kStepSkip) return;
-        if (dropped) {
+        if (dropped()) {
             if (tid == 0) atomicAdd(&a.ctrl->point_drops[point_id & 4095u], 1u);
             return;
         }

@@ -1,0 +1,63 @@
+"""Launches that should take as long as one another.  Kernel durations by the dispatches' own time stamps, the two sides in
+turn on rotating inputs; medians, and one good attempt of four is enough (a slow kernel has none)."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def B():
+    assert torch.cuda.is_available()
+    from paper_2605_11093_amd import binding
+    binding.lib()
+    return binding
+
+
+def _ratio(B, first, second, most, reps=21):
+    """second's time over first's; each is called with the number of the call and returns what ends it"""
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record(), e1.record()
+    torch.cuda.synchronize()
+    for attempt in range(4):
+        us, call = ([], []), attempt
+        for rep in range(reps + 2):
+            for k, side in enumerate((first, second)):
+                B.time_next_launch(e0.cuda_event, e1.cuda_event)
+                end = side(call)
+                torch.cuda.synchronize()
+                if rep >= 2:
+                    us[k].append(e0.elapsed_time(e1) * 1e3)
+                end()
+                call += 1
+        r = statistics.median(us[1]) / statistics.median(us[0])
+        print(f"attempt {attempt}: {statistics.median(us[0]):.2f} and {statistics.median(us[1]):.2f} us")
+        if r < most:
+            break
+    return r
+
+
+def test_best_effort_costs_a_launch_nothing(B):
+    """80 tensors of 256 x 8192 in one launch: the loads must not wait for the head (that took 1.055 times as long)."""
+    n = 80
+    pools = [[torch.randn(256, 8192, device=DEV, dtype=torch.bfloat16) for _ in range(n)] for _ in range(5)]
+    reqs = np.array([[i, i, 0, 1, 1] for i in range(256)], dtype=np.uint32)
+    size = B.record_bytes(256, 256, 8192, 1, 0)
+    s = torch.cuda.current_stream().cuda_stream
+    with B.Ring(2 * n * size + 4096, n * size + 4096) as block, B.Ring(2 * n * size + 4096, n * size + 4096) as drop:
+        drop.set_policy(B.POLICY_DROP_NEWEST)
+
+        def side(ring):
+            def call(k):
+                ring.observe_batch(range(n), pools[k % 5], reqs, step_id=0, stream=s, out_dtype=1, summary_mask=0)
+
+                def end():
+                    ring.drain(B.DRAIN_FLUSH)
+                    ring.release_host(ring.poll_host(n)[-1].seq)
+                return end
+            return call
+        assert _ratio(B, side(block), side(drop), 1.04) < 1.04
