@@ -1716,8 +1716,9 @@ __global__ void __launch_bounds__(kThreads) capture_decode_kernel(const DecodeAr
 // a full GPU where memory answers in 0.6: a thousand instructions (fetched cold), scans and searches through LDS, a
 // barrier.  So there is hardly anything in front of the loads here: each wavefront scans the request table by itself
 // (at most 64 requests, one per lane; none at all where requests have one row each), there is no LDS and no
-// barrier, and header, table and publishing are a workgroup of their own behind the others (the last blockIdx.x), whose
-// code the others do not run through.  And there is one step to a wavefront, many more workgroups than fit at once, and no
+// barrier, and header, table and publishing are a workgroup of their own, whose code the others do not run through.  It is the first
+// one of its record: a table of many requests takes it several trips, and as the last one to start it kept the GPU waiting (4096
+// requests x 4096 fp32 stored 32.7 us and 27.4 like this, 2048 x 14336 bf16 26.4 and 23.5, 1024 x 14336 15.1 and 13.7).  And there is one step to a wavefront, many more workgroups than fit at once, and no
 // software pipeline: seven workgroups per compute unit hide each other's trips (54 registers; two steps in
 // a pipeline take 93, five workgroups).  Steps per wavefront 1 / 2 / 4: 19.1 / 20.4 / 23.7 us; units per lane 2 / 4 / 8:
 // 21.8 / 18.8 / 20.0 (9.3 k rows x 4096 bf16 -> fp8).
@@ -1750,7 +1751,7 @@ struct RowsArgs {
     uint32_t flags;                 // kRows*
     uint32_t n_reqs, units_per_row, row_elems;
     uint32_t parts, parts_magic, parts_shift;   // steps per row; x / parts = (x * parts_magic >> 32) >> parts_shift, x below 2^31
-    uint32_t row_groups;            // workgroups that move rows (gridDim.x - 1)
+    uint32_t row_groups;            // workgroups that move rows (gridDim.x - 1: the first one does not)
     uint32_t row_first;
     uint32_t summary_mask, src_dtype, row_lanes, passes;     // summaries: lanes that share a row, as in the general kernel
     uint32_t pad;
@@ -1781,7 +1782,8 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
     const uint32_t y = INTO ? 0u : blockIdx.y;
     const uint8_t *const src = b.src[y];
     const uint32_t lane = threadIdx.x & 63u, wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool simple = (a.flags & kRowsSimple) != 0u, meta = blockIdx.x == a.row_groups;
+    const bool simple = (a.flags & kRowsSimple) != 0u, meta = blockIdx.x == 0u;
+    const uint32_t group = blockIdx.x - 1u;                 // of the workgroups that move rows
     const bool index_mode = a.row_index != nullptr;
     const uint32_t n_reqs = a.n_reqs, par = a.flags & kRowsParIn ? 1u : 0u;
 
@@ -1894,7 +1896,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
             __shared__ float red[WG ? 12 : 1];
             const uint32_t rl = a.row_lanes, parts = rl >> 6;
             const uint32_t rows_at_once = a.row_groups * (WG ? 1u : kThreads / 64u);
-            for (uint64_t g = WG ? blockIdx.x : blockIdx.x * (kThreads / 64u) + wv; g < n_rows; g += rows_at_once) {
+            for (uint64_t g = WG ? group : group * (kThreads / 64u) + wv; g < n_rows; g += rows_at_once) {
                 const Step st = step_at((uint32_t)g);
                 n_bad += st.ok || (WG && wv != 0u) ? 0u : 1u;
                 float ss[4] = {0.f, 0.f, 0.f, 0.f}, sm[4] = {0.f, 0.f, 0.f, 0.f};       // of each part
@@ -2007,7 +2009,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
                 }
             };
             // (one step each, unless a replayed step's selection has grown since its grid was made)
-            for (uint64_t s = blockIdx.x * (kThreads / 64u) + wv; s < n_steps; s += a.row_groups * (kThreads / 64u)) {
+            for (uint64_t s = group * (kThreads / 64u) + wv; s < n_steps; s += a.row_groups * (kThreads / 64u)) {
                 const Step st = step_at((uint32_t)s);
                 u32x4 v[U];
                 load(st, v);
@@ -2021,7 +2023,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         return;
     }
 
-    // -- the last workgroup: header, request table, pads; and, of the launch's first record, the chain of launches
+    // -- the first workgroup: header, request table, pads; and, of the launch's first record, the chain of launches
     settle();
     const uint64_t head0 = uniform_u64(head_v), at0 = uniform_u64(at_v);
     const uint32_t tid = threadIdx.x, point_id = b.point[y];
@@ -2062,25 +2064,30 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         ring_store<u32x4>(w, 16u * tid, hv);
     }
     const uint32_t tab_slots = (uint32_t)((off_payload - 64u) / 16u);
-    for (uint32_t r = tid; r < tab_slots; r += kThreads) {
-        u32x4 tv = {0u, 0u, 0u, 0u};
-        if (r < n_reqs) {
-            if (!simple) {                  // (one request per lane: the first wavefront's own)
-                tv = u32x4{entry.x, entry.y, entry.z, kept};
-            } else {
-                bool have = false;
-                if constexpr (INTO)
-                    if (b.n_words) {
-                        tv = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(RowsArgs)) + 4u * r);
-                        have = true;
-                    }
-                if (!have) {
-                    const uint4 e = a.req_table[r];
-                    tv = u32x4{e.x, e.y, e.z, e.w};
-                }
+    if (!simple) {                          // (one request per lane: the first wavefront's own)
+        if (tid < tab_slots) {
+            const u32x4 tv = {entry.x, entry.y, entry.z, kept};
+            ring_store<u32x4>(w, 64u + 16ull * tid, tid < n_reqs ? tv : u32x4{0u, 0u, 0u, 0u});
+        }
+    } else {
+        typedef __attribute__((address_space(1))) const u32x4 global_entry;
+        global_entry *table = (global_entry *)a.req_table;
+        if constexpr (INTO)
+            if (b.n_words) table = (global_entry *)inline_table(sizeof(RowsArgs));
+        // (up to 4096 of them: four trips in flight)
+        for (uint32_t r0 = tid; r0 < tab_slots; r0 += 4u * kThreads) {
+            u32x4 tv[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) {
+                const uint32_t r = r0 + k * kThreads;
+                tv[k] = table[r < n_reqs ? r : n_reqs - 1u];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) {
+                const uint32_t r = r0 + k * kThreads;
+                if (r < tab_slots) ring_store<u32x4>(w, 64u + 16ull * r, r < n_reqs ? tv[k] : u32x4{0u, 0u, 0u, 0u});
             }
         }
-        ring_store<u32x4>(w, 64u + 16ull * r, tv);
     }
     const uint32_t pad = (uint32_t)(off_sum - off_payload - payload_bytes);
     if (tid < pad) ring_store<uint8_t>(w, off_payload + payload_bytes + tid, (uint8_t)0);
