@@ -483,6 +483,18 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         if (nb > 1u && rounds > most) rounds = most;
         return (items + rounds - 1u) / rounds;
     };
+    // Rows stored without summaries, of at least kLongRowUnits units: a wavefront per 256 units of one (capture_rows_kernel).  It
+    // takes its time also where its step is short: from 12 k steps on rows go there if those are long enough, else they are dealt flat.
+    // (rows kernel / dealt flat, us; one row per request: 32.8 k rows of 64 units raw 15.5 / 14.9, of 80 16.5 / 16.9; fp16 of 72
+    // 18.7 / 16.7, of 80 18.8 / 18.0, of 96 21.5 / 22.8; fp8 of 64 18.5 / 14.0, of 96 21.2 / 19.3, of 112 21.6 / 21.9; 24 k to fp8 of 104 15.4 / 15.5;
+    // ragged: 40 k of 64 raw 21.1 / 17.3, of 72 20.9 / 19.2, of 80 21.1 / 21.8; fp16 of 96 30.1 / 27.6, 24 k of 104 17.1 / 18.3; fp8 of 64
+    // 23.8 / 14.9, of 128 30.1 / 28.1, of 136 32.3 / 32.5, of 257 59.1 / 51.5.  Smaller launches: 8 k of 64 raw 7.4 / 7.4, fp8 8.0 / 9.2,
+    // 1.5 k 4.2 / 6.1 and 4.9 / 6.8; 12 k of 64 ragged raw 9.1 / 8.0, 10 k 8.1 / 7.9.)
+    const uint64_t steps_per_row = (upr + 255u) / 256u;
+    const uint64_t least = a.out_dtype == a.src_dtype ? (a.simple ? 72u : 80u) : a.out_dtype == DMI_DTYPE_FP8_E4M3FN ? (a.simple ? 104u : 136u)
+                                                                                                                      : (a.simple ? 80u : 104u);
+    const bool rows_of_steps = finds_rows_itself && upr >= kLongRowUnits &&
+                               (upr >= least * steps_per_row || expected * nb * steps_per_row < 12000u);
     uint64_t groups;
     // Rows of 129 to 256 units have a wavefront's lanes to themselves either way; in capture_rows_kernel they come without the
     // general kernel's prologue (12.8 k rows of 256 units, statistics 13.8 -> 10.9 us, stored too 20.9 -> 18.4; 3 k of 192
@@ -527,11 +539,10 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         a.wave_rows = rows >= 2048u && (upr <= 512u || (alone && upr <= 768u));
         const uint64_t per_wave = alone && rows >= 4096u ? 2u : 1u;
         groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed, kItemsPerGroupInBatch);
-    } else if (a.out_dtype && upr >= kLongRowUnits && finds_rows_itself) {
-        // a wavefront per 256 units of a row (capture_rows_kernel, where the figures are)
+    } else if (a.out_dtype && rows_of_steps) {
         a.step_per_wave = 1;
         a.read_once = past_the_cache;
-        groups = planned([&](uint64_t rows) { return (rows * ((upr + 255u) / 256u) + 3u) / 4u; });
+        groups = planned([&](uint64_t rows) { return (rows * steps_per_row + 3u) / 4u; });
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
         const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;

@@ -10,7 +10,7 @@ constexpr uint32_t kThreads = 256;          // 4 wavefronts of 64 lanes per work
 constexpr uint32_t kMaxGrid = 1u << 22;     // workgroups per tensor of one launch
 constexpr uint32_t kLdsTableMax = 1024;     // request tables up to this size are cached in LDS
 constexpr uint32_t kDecodeMaxListed = 1024; // most rows a ragged selection may list to take the decode-shaped kernel
-constexpr uint32_t kLongRowUnits = 64;      // rows from this length on, stored without summaries: capture_rows_kernel
+constexpr uint32_t kLongRowUnits = 64;      // rows from this length on, stored without summaries: capture_rows_kernel (plan_grid(): which)
 constexpr uint32_t kMaxBatch = 128;         // most tensors one batched launch captures
 
 // One slot per launch, written by workgroup 0 of the launch: where the head stands

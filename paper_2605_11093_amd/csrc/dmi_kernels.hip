@@ -1737,9 +1737,8 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
 // wavefront (plan_grid() says which, with figures); lanes, parts and the order of the sums are the general and the
 // decode-shaped kernel's, so a row's summaries have the same bits wherever it is captured.  80 tensors of 256 x 8192,
 // statistics alone: 61 -> 49.5 us (6.8 TB/s read).
-// Shorter rows are dealt flat by the general kernel (20 k x 256: 6.2 us there, 10.6 here; from 64 units on: 3000 x 512
-// 5.0 and 4.1, 9.3 k x 512 raw 6.0 and 5.3, 20 k x 640 raw 11.6 and 10.0, to fp8 11.0 and 11.7, 9.3 k x 1536 11.1 and 9.4), and
-// so are rows of more than 64 ragged requests.
+// Shorter rows, and in large launches those that leave many of a step's lanes idle, are dealt flat by the general kernel (plan_grid()
+// says which, with figures), and so are rows of more than 64 ragged requests.
 struct RowsArgs {
     // lines 0 and 1: what the row workgroups need
     int64_t row_stride_b, n_src_rows;

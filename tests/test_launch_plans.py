@@ -76,3 +76,18 @@ def test_past_the_cache(plan, src, width, out, mask):
     # statistics of rows that a wavefront or more takes, of a batch: from half of the cache on
     early = 0 if out or width == 512 else 1
     assert (reads(127, tensors=8), reads(128, tensors=8), reads(260, tensors=8)) == (0, early, 1)
+
+
+@pytest.mark.parametrize("out,least", [(BF16, (72, 80)), (2, (80, 104)), (FP8, (104, 136))])
+def test_short_steps_of_large_launches_are_dealt_flat(plan, out, least):
+    def rows_kernel(units, rows, ragged):
+        return plan(BF16, 8 * units, 50 if ragged else 250, rows // 50 if ragged else 1, out, tensors=1 if ragged else rows // 250)["rows_kernel"]
+
+    for ragged in (0, 1):
+        at = least[ragged]
+        for parts in (1, 2, 3):                     # steps per row
+            if parts > 1 and at * parts <= 256 * (parts - 1):
+                continue
+            assert rows_kernel(at * parts, 25000, ragged) == 1 and rows_kernel(at * parts - 1, 25000, ragged) == 0
+        assert rows_kernel(64, 11500, ragged) == 1 and rows_kernel(64, 12250, ragged) == 0
+        assert rows_kernel(63, 1000, ragged) == 0 and rows_kernel(256, 100000, ragged) == 1
