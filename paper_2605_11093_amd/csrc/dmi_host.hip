@@ -468,6 +468,11 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     constexpr uint64_t kMemorySideCache = 256ull << 20;
     const uint64_t source_bytes = expected * nb * a.row_elems * dtype_size(a.src_dtype);
     const bool past_the_cache = source_bytes > kMemorySideCache;
+    // A batch's tensors have been kept for this launch and nothing reads them behind it: from half of the cache on.  (Through / past the
+    // cache, cold and just written: statistics alone 134 MB 25.1 / 24.4 and 21.3 / 20.9, 200 MB 34.9 / 34.1 and 29.7 / 29.0; 256 x 8192 raw, 24 tensors
+    // 37.0 / 37.0 and 31.5 / 31.5, 32 49.2 / 47.2 and 40.8 / 40.8, 40 60.5 / 57.7 and 50.4 / 49.9, 48 72.0 / 67.9 and 59.9 / 59.5; with statistics 48
+    // 71.1 / 69.6 and 62.9 / 63.0; to fp8 56.9 / 56.4 and 49.2 / 49.3; 3 x 9.2 k x 4096 raw 80.6 / 79.4 and 66.7 / 67.5.)
+    const bool batch_past_the_cache = nb > 1u && source_bytes >= kMemorySideCache / 2u;
     a.step_per_wave = a.read_once = a.wave_rows = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
@@ -520,9 +525,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         //   / 116, and 115 past the cache)
         a.step_per_wave = 1;
         a.wave_rows = upr <= 256u || (upr <= 640u && (guess ? listed : expected) * nb >= 2048u);
-        // (a batch's tensors have been kept for this launch, nothing reads them behind it: from half of the cache on if nothing is
-        // stored.  134 MB, cold 25.1 -> 24.4 us, just written 21.3 -> 20.9; 200 MB 34.9 -> 34.1 and 29.7 -> 29.0)
-        a.read_once = past_the_cache || (nb > 1u && !a.out_dtype && source_bytes >= kMemorySideCache / 2u);
+        a.read_once = past_the_cache || batch_past_the_cache;
         groups = planned([&](uint64_t rows) { return a.wave_rows ? (rows + 3u) / 4u : rows; });
     } else if (a.summary_mask) {
         // Rows of more than 256 units of paged caches, or of more than 64 ragged requests: a workgroup per row, or, where a
@@ -541,7 +544,7 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         groups = a.wave_rows ? (listed + 4u * per_wave - 1u) / (4u * per_wave) : balanced(listed, kItemsPerGroupInBatch);
     } else if (a.out_dtype && rows_of_steps) {
         a.step_per_wave = 1;
-        a.read_once = past_the_cache;
+        a.read_once = past_the_cache || batch_past_the_cache;
         groups = planned([&](uint64_t rows) { return (rows * steps_per_row + 3u) / 4u; });
     } else {
         // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough

@@ -73,8 +73,8 @@ def test_past_the_cache(plan, src, width, out, mask):
     assert (reads(400, keep=half), reads(500, keep=half), reads(520, keep=half)) == (0, 0, 1)
     assert (reads(1600, keep="1" + "0" * 15), reads(270, keep="1" * 16)) == (0, 1)
     assert (reads(400, keep="unknown"), reads(500, keep="unknown"), reads(520, keep="unknown")) == (0, 0, 1)
-    # statistics of rows that a wavefront or more takes, of a batch: from half of the cache on
-    early = 0 if out or width == 512 else 1
+    # a batch of rows that a wavefront or more takes: from half of the cache on
+    early = int(width != 512)
     assert (reads(127, tensors=8), reads(128, tensors=8), reads(260, tensors=8)) == (0, early, 1)
 
 
