@@ -26,6 +26,10 @@ dmi_status_t dmi_debug_exporter_allocs(dmi_ring_t *ring, uint64_t *allocated, ui
  * replayable step (a stream that is being captured records no events of this kind). */
 dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop_event);
 
+/* A digest of the dmi.h that the library was built with (0: built without one).  The binding's native modules, which call the
+ * library through addresses, are used only if theirs is the same. */
+uint64_t dmi_debug_header_digest(void);
+
 #ifdef __cplusplus
 }
 #endif

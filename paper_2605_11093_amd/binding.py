@@ -8,14 +8,16 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+import sys
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 import numpy as np
 
-try:                        # native marshalling of the per-tensor calls; without it (or torch) they go through ctypes
-    import torch as _torch_first                                    # noqa: F401  (its libraries are what the module links)
+try:                        # native marshalling of the per-tensor calls; without it they go through ctypes
     from . import _dmi_python as _native
+    if getattr(_native, "INTERFACE", 0) != 2:       # (built from other sources, and about to be built again)
+        _native = None
 except ImportError:
     _native = None
 
@@ -233,8 +235,35 @@ def lib():
         getattr(L, name).restype = C.c_int32
     _lib = L
     if _native is not None:
-        _native.bind_into(C.cast(L.dmi_observe_into, C.c_void_p).value)
+        _native_calls(L)
     return L
+
+
+_native_ok = False          # the native modules were built with the library's dmi.h
+
+
+def _native_calls(L):
+    """The library's entry points for the native modules, if the structs they hand over are the library's."""
+    global _native_ok
+    try:
+        L.dmi_debug_header_digest.restype = C.c_uint64
+        _native_ok = L.dmi_debug_header_digest() == _native.HEADER_DIGEST
+    except AttributeError:                          # (an older library)
+        _native_ok = False
+    if _native_ok:
+        _native.bind_into(C.cast(L.dmi_observe_into, C.c_void_p).value)
+
+
+def _load_reader():
+    """The native module that reads tensors: not before torch is there, and asked for once."""
+    if "torch" not in sys.modules:
+        return
+    _native.setup(_general_into, _check, globals(), None)
+    try:
+        from . import _dmi_python_torch
+        _native.set_reader(_dmi_python_torch.reader)
+    except Exception:                               # (another torch than it was built for: ctypes does)
+        pass
 
 
 def version() -> str:
@@ -341,7 +370,8 @@ def observe_into(point_id: int, tensor, reqs, out, *, seq: int, step_id: int, ra
 
 
 if _native is not None:     # the plain case without Python in between; all else comes back to the function above
-    _native.setup(observe_into, _check, globals())
+    _general_into = observe_into
+    _native.setup(_general_into, _check, globals(), _load_reader)
     observe_into = _native.observe_into
 
 
@@ -372,9 +402,12 @@ class PreparedObserve(_native.Prepared if _native is not None else object):
                                 (C.c_uint32 * 8)(*paged.heads_sel))
             self._fn = lib().dmi_observe_paged
         self._a = (C.byref(self._src), C.byref(self._sel), C.byref(self._xf))
-        if _native is not None and type(point_id) is int and self._h:
+        if _native_ok and type(point_id) is int and self._h:
             self._bind(C.cast(self._fn, C.c_void_p).value, self._h.value, point_id & 0xFFFFFFFF, C.addressof(self._src),
                        C.addressof(self._sel), C.addressof(self._xf))
+
+    def __getstate__(self):                         # (a copy calls through Python)
+        return self.__dict__
 
     def _call(self, step_id: int, stream: int) -> int:
         return self._fn(self._h, self._point, self._a[0], self._a[1], self._a[2], step_id, stream)

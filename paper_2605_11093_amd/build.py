@@ -1,6 +1,7 @@
 """Builds libdmi.so (HIP, gfx950) in-tree with hipcc."""
 from __future__ import annotations
 
+import hashlib
 import os
 import shutil
 import subprocess
@@ -12,6 +13,15 @@ SOURCES = [os.path.join(HERE, "csrc", f) for f in ("dmi_kernels.hip", "dmi_host.
                                                      "dmi_exporter.hip", "dmi_noalloc.hip")]
 HEADERS = [os.path.join(HERE, "csrc", "dmi_internal.h"), os.path.join(HERE, "csrc", "dmi_ring.h"),
            os.path.join(ROOT, "include", "dmi.h"), os.path.join(ROOT, "include", "dmi_debug.h")]
+
+
+def _digest() -> str:
+    """What tells libdmi.so and the binding's native modules that they were built with the same dmi.h."""
+    with open(os.path.join(ROOT, "include", "dmi.h"), "rb") as f:
+        return "-DDMI_HEADER_DIGEST=0x" + hashlib.sha256(f.read()).hexdigest()[:16] + "ull"
+
+
+DIGEST = _digest()
 
 
 def hipcc() -> str:
@@ -39,7 +49,7 @@ def build(force: bool = True) -> str:
             return SO
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-I", os.path.join(ROOT, "include"),
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", DIGEST,
            *SOURCES, "-o", SO, "-lpthread"]
     subprocess.check_call(cmd)
     return SO
@@ -71,22 +81,26 @@ def build_torch_op() -> str:
 
 PY_SO = os.path.join(HERE, "_dmi_python.so")
 PY_SRC = os.path.join(HERE, "csrc", "dmi_python.cpp")
+PY_TORCH_SO = os.path.join(HERE, "_dmi_python_torch.so")
+PY_TORCH_SRC = os.path.join(HERE, "csrc", "dmi_python_torch.cpp")
 
 
 def build_python() -> str:
-    """Native marshalling of the binding's per-tensor calls (host code only: g++ against Python and libtorch)."""
+    """Native marshalling of the binding's per-tensor calls (host code only: g++ against Python, and against libtorch
+    what reads tensors)."""
     import sysconfig
     import torch
     from torch.utils import cpp_extension as ce
     tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", DIGEST,
            "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"]]
+    subprocess.check_call(cmd + [PY_SRC, "-o", PY_SO])
+    cmd += ["-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     for inc in ce.include_paths("cuda"):
         cmd += ["-isystem", inc]
-    cmd += [PY_SRC, "-o", PY_SO, "-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + tlib]
-    subprocess.check_call(cmd)
+    subprocess.check_call(cmd + [PY_TORCH_SRC, "-o", PY_TORCH_SO, "-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+                                 "-Wl,-rpath," + tlib])
     return PY_SO
 
 

@@ -1020,6 +1020,11 @@ extern "C" {
 const char *dmi_last_error(void) { return last_error_cstr(); }
 const char *dmi_version(void) { return "dmi-ring 0.1 (gfx950)"; }
 
+#ifndef DMI_HEADER_DIGEST
+#define DMI_HEADER_DIGEST 0
+#endif
+uint64_t dmi_debug_header_digest(void) { return DMI_HEADER_DIGEST; }
+
 uint64_t dmi_record_bytes(uint32_t n_reqs, uint64_t n_rows, uint32_t row_elems, uint32_t out_dtype,
                           uint32_t summary_mask)
 {

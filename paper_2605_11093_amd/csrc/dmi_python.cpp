@@ -5,13 +5,9 @@
 // observe_into and 0.8 us per prepared observe on top (with it a call of 4 rows x 256 takes 8.1 us, with this 6.5).  Only the plain case is handled: exact torch
 // tensors, a C-contiguous uint32 table, ints.  Whatever else comes -- other types, subclasses, wrong or missing
 // arguments, tensors without storage -- is handed to the Python function of the same meaning, which converts or refuses
-// it as it always has.  The library's entry points come in as addresses, so this module loads without libdmi.so.
-#define PY_SSIZE_T_CLEAN
-#include <Python.h>
-
-#include <torch/csrc/autograd/python_variable.h>
-
-#include "dmi.h"
+// it as it always has.  The library's entry points come in as addresses, so this module loads without libdmi.so; and what reads
+// tensors (dmi_python_torch.cpp) comes in when there is one to read, so that it loads without torch too.
+#include "dmi_python.h"
 
 namespace {
 
@@ -24,6 +20,8 @@ into_fn g_into = nullptr;
 PyObject *g_general = nullptr;      // binding's own observe_into: everything but the plain case
 PyObject *g_check = nullptr;        // binding._check(code, allow)
 PyObject *g_module = nullptr;       // binding's namespace, where _into_fn may name another foreign function
+PyObject *g_load = nullptr;         // called once a tensor may be at hand: has set_reader() called, or not
+dmi_py_reader g_reader = nullptr;
 PyObject *g_names[12];              // observe_into's parameters, interned
 PyObject *g_into_name = nullptr;
 const char *const kNames[12] = {"point_id", "tensor", "reqs", "out", "seq", "step_id", "rank_tag", "out_dtype", "summary_mask",
@@ -36,15 +34,13 @@ bool as_u64(PyObject *o, uint64_t *v)       // an int's low 64 bits, as ctypes t
     return !(*v == (uint64_t)-1 && PyErr_Occurred());
 }
 
-const at::Tensor *plain_tensor(PyObject *o) { return THPVariable_CheckExact(o) ? &THPVariable_Unpack(o) : nullptr; }
-
 bool optional_address(PyObject *o, const void **p)
 {
     *p = nullptr;
     if (!o || o == Py_None) return true;
-    const at::Tensor *t = plain_tensor(o);
-    if (!t) return false;
-    *p = t->data_ptr();
+    dmi_py_tensor t;
+    if (!g_reader(o, &t)) return false;
+    *p = t.data;
     return true;
 }
 
@@ -52,14 +48,9 @@ bool optional_address(PyObject *o, const void **p)
 bool plain_into(PyObject *const (&v)[12], Py_buffer *table, bool *have_table, dmi_tensor_t *t, dmi_selection_t *sel,
                 dmi_transform_t *xf, uint64_t (&n)[4], void **out, uint64_t *out_bytes)
 {
-    const at::Tensor *x = plain_tensor(v[1]), *dst = plain_tensor(v[3]);
-    if (!x || !dst || x->dim() != 2) return false;
-    switch (x->scalar_type()) {
-    case at::kBFloat16: t->dtype = DMI_DTYPE_BF16; break;
-    case at::kHalf: t->dtype = DMI_DTYPE_FP16; break;
-    case at::kFloat: t->dtype = DMI_DTYPE_FP32; break;
-    default: return false;
-    }
+    dmi_py_tensor x, dst;
+    if (!g_reader(v[1], &x) || !g_reader(v[3], &dst) || x.dim != 2 || !x.dtype) return false;
+    t->dtype = x.dtype;
     uint64_t od = 0, mask = 0, stream = 0;
     if (!as_u64(v[0], &n[0]) || !as_u64(v[4], &n[1]) || !as_u64(v[5], &n[2])) return false;
     n[3] = 0;
@@ -74,16 +65,16 @@ bool plain_into(PyObject *const (&v)[12], Py_buffer *table, bool *have_table, dm
     if (table->ndim != 2 || table->shape[1] != 5 || table->itemsize != 4 || !table->format || table->format[0] != 'I' ||
         table->format[1] || table->shape[0] > 0x7FFFFFFF)
         return false;
-    t->data = x->data_ptr();
-    for (int i = 0; i < 2; i++) { t->shape[i] = x->size(i); t->stride[i] = x->stride(i); }
+    t->data = x.data;
+    for (int i = 0; i < 2; i++) { t->shape[i] = x.shape[i]; t->stride[i] = x.stride[i]; }
     sel->n_reqs = (uint32_t)table->shape[0];
     sel->reqs = static_cast<const dmi_req_sel_t *>(table->buf);
     sel->keep_mask_dev = static_cast<const uint8_t *>(keep);
     sel->row_index_dev = static_cast<const int32_t *>(index);
     xf->out_dtype = (uint32_t)od;
     xf->summary_mask = (uint32_t)mask;
-    *out = dst->data_ptr();
-    *out_bytes = (uint64_t)dst->numel() * dst->element_size();
+    *out = dst.data;
+    *out_bytes = dst.bytes;
     n[0] = (uint32_t)n[0];
     n[3] = (uint32_t)n[3];
     return true;
@@ -108,6 +99,11 @@ PyObject *observe_into(PyObject *, PyObject *const *args, Py_ssize_t n_args, PyO
         PyObject *other = PyDict_GetItem(g_module, g_into_name);        // (borrowed)
         plain = other == nullptr || other == Py_None;
     }
+    if (plain && !g_reader) {
+        if (PyObject *r = g_load && g_load != Py_None ? PyObject_CallNoArgs(g_load) : nullptr) Py_DECREF(r);
+        if (PyErr_Occurred()) return nullptr;
+        plain = g_reader != nullptr && g_into != nullptr;
+    }
     if (plain) {
         Py_buffer table;
         bool have_table = false, failed = false;
@@ -117,11 +113,7 @@ PyObject *observe_into(PyObject *, PyObject *const *args, Py_ssize_t n_args, PyO
         uint64_t n[4], out_bytes = 0, record = 0;
         void *out = nullptr;
         dmi_status_t code = DMI_OK;
-        try {
-            plain = plain_into(v, &table, &have_table, &t, &sel, &xf, n, &out, &out_bytes);
-        } catch (...) {                 // (a tensor without storage or plain sizes: the general function says what is wrong)
-            plain = false;
-        }
+        plain = plain_into(v, &table, &have_table, &t, &sel, &xf, n, &out, &out_bytes);
         if (plain) {
             uint64_t stream = 0;
             if (v[11]) as_u64(v[11], &stream);
@@ -202,9 +194,10 @@ PyTypeObject prepared_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
 PyObject *setup(PyObject *, PyObject *args)
 {
-    PyObject *general, *check, *module;
-    if (!PyArg_ParseTuple(args, "OOO!", &general, &check, &PyDict_Type, &module)) return nullptr;
-    Py_INCREF(general); Py_INCREF(check); Py_INCREF(module);
+    PyObject *general, *check, *module, *load;
+    if (!PyArg_ParseTuple(args, "OOO!O", &general, &check, &PyDict_Type, &module, &load)) return nullptr;
+    Py_INCREF(general); Py_INCREF(check); Py_INCREF(module); Py_INCREF(load);
+    Py_XSETREF(g_load, load);
     Py_XSETREF(g_general, general);
     Py_XSETREF(g_check, check);
     Py_XSETREF(g_module, module);
@@ -219,13 +212,22 @@ PyObject *bind_into(PyObject *, PyObject *arg)
     Py_RETURN_NONE;
 }
 
+PyObject *set_reader(PyObject *, PyObject *arg)
+{
+    void *p = PyCapsule_GetPointer(arg, DMI_PY_READER);
+    if (!p) return nullptr;
+    g_reader = reinterpret_cast<dmi_py_reader>(p);
+    Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
     {"observe_into", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(observe_into)), METH_FASTCALL | METH_KEYWORDS,
      "observe_into(point_id, tensor, reqs, out, *, seq, step_id, rank_tag=0, out_dtype=None, summary_mask=0, keep_mask=None, "
      "row_index=None, stream=0, allow=())\n--\n\n"
      "dmi_observe_into: one record into `out` (a uint8 device tensor), no ring, no allocation.\n"
      "Returns the record's size (an upper bound if a keep vector is given)."},
-    {"setup", setup, METH_VARARGS, "the binding's general observe_into, its status check, its namespace"},
+    {"setup", setup, METH_VARARGS, "the binding's general observe_into, its status check, its namespace, what loads the tensor reader"},
+    {"set_reader", set_reader, METH_O, "capsule with the function that reads torch tensors"},
     {"bind_into", bind_into, METH_O, "address of dmi_observe_into"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_dmi_python", "native marshalling of per-tensor calls", -1, methods,
@@ -247,6 +249,8 @@ PyMODINIT_FUNC PyInit__dmi_python(void)
     if (PyType_Ready(&prepared_type) < 0) return nullptr;
     PyObject *m = PyModule_Create(&module_def);
     if (!m) return nullptr;
+    if (PyModule_AddIntConstant(m, "INTERFACE", 2) < 0) { Py_DECREF(m); return nullptr; }      // (of this module to binding.py)
+    if (PyModule_AddObject(m, "HEADER_DIGEST", PyLong_FromUnsignedLongLong(DMI_HEADER_DIGEST)) < 0) { Py_DECREF(m); return nullptr; }
     Py_INCREF(&prepared_type);
     if (PyModule_AddObject(m, "Prepared", reinterpret_cast<PyObject *>(&prepared_type)) < 0) { Py_DECREF(m); return nullptr; }
     return m;
