@@ -239,6 +239,7 @@ def lib():
     return L
 
 
+_reader_asked = False
 _native_ok = False          # the native modules were built with the library's dmi.h
 
 
@@ -251,14 +252,17 @@ def _native_calls(L):
     except AttributeError:                          # (an older library)
         _native_ok = False
     if _native_ok:
+        _load_reader()
         _native.bind_into(C.cast(L.dmi_observe_into, C.c_void_p).value)
 
 
 def _load_reader():
-    """The native module that reads tensors: not before torch is there, and asked for once."""
-    if "torch" not in sys.modules:
+    """The native module that reads tensors, once, as soon as torch is there: a library that a process loads with its GPU in use already
+    costs every later launch 0.2 us."""
+    global _reader_asked
+    if _reader_asked or _native is None or "torch" not in sys.modules:
         return
-    _native.setup(_general_into, _check, globals(), None)
+    _reader_asked = True
     try:
         from . import _dmi_python_torch
         _native.set_reader(_dmi_python_torch.reader)
@@ -373,6 +377,7 @@ if _native is not None:     # the plain case without Python in between; all else
     _general_into = observe_into
     _native.setup(_general_into, _check, globals(), _load_reader)
     observe_into = _native.observe_into
+    _load_reader()
 
 
 class PreparedObserve(_native.Prepared if _native is not None else object):

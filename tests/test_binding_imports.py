@@ -57,16 +57,18 @@ def test_a_torch_that_cannot_be_imported(tmp_path, error):
 
 
 @pytest.mark.skipif(not NATIVE, reason="the native module has not been built")
-@pytest.mark.parametrize("first", ["torch", "binding"])
+@pytest.mark.parametrize("first", ["torch", "binding", "library"])
 def test_the_first_call_with_a_tensor_is_native(first):
     _run(f"""
         import sys
         if {first == "torch"}:
             import torch
         from paper_2605_11093_amd import binding as B
+        if {first == "library"}:
+            B.lib()
         import torch
         B.lib()
-        assert B._native_ok and "paper_2605_11093_amd._dmi_python_torch" not in sys.modules
+        assert B._native_ok and ("paper_2605_11093_amd._dmi_python_torch" in sys.modules) == {first != "library"}
         B._native.bind_into(C.cast(entry, C.c_void_p).value)
         B._into_raw = lambda: lambda *a: general.append(a) or 0
         call(torch)
@@ -78,12 +80,13 @@ def test_the_first_call_with_a_tensor_is_native(first):
 def test_a_reader_that_cannot_be_loaded():
     _run("""
         import sys
+        import paper_2605_11093_amd.build
+        sys.modules["paper_2605_11093_amd._dmi_python_torch"] = None        # (an import of it fails)
         from paper_2605_11093_amd import binding as B
         import torch
         B.lib()
         B._native.bind_into(C.cast(entry, C.c_void_p).value)
         B._into_raw = lambda: lambda *a: general.append(a) or 0
-        sys.modules["paper_2605_11093_amd._dmi_python_torch"] = None        # (an import of it fails)
         call(torch)
         assert not native and len(general) == 2
     """)
