@@ -1,6 +1,6 @@
 """Request tables that are staged by a launch of their own, at the sizes where the number and kind of those launches
-changes (896 and 3072 words), called directly and replayed from a graph; and statistics of short rows by a launch that
-reads more than the memory-side cache holds."""
+changes (896 and 3072 words), called directly and replayed from a graph; and statistics of rows of 256 units, a wavefront
+each, by a launch that reads more than the memory-side cache holds (shorter rows: test_gpu_row_routes.py)."""
 import numpy as np
 import pytest
 import torch

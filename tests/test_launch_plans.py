@@ -91,3 +91,10 @@ def test_short_steps_of_large_launches_are_dealt_flat(plan, out, least):
             assert rows_kernel(at * parts, 25000, ragged) == 1 and rows_kernel(at * parts - 1, 25000, ragged) == 0
         assert rows_kernel(64, 11500, ragged) == 1 and rows_kernel(64, 12250, ragged) == 0
         assert rows_kernel(63, 1000, ragged) == 0 and rows_kernel(256, 100000, ragged) == 1
+
+
+@pytest.mark.parametrize("src,elems,rows", [(BF16, 1024, 132000), (BF16, 256, 530000), (2, 1000, 135000), (FP32, 512, 132000), (BF16, 2040, 66500)])
+def test_statistics_of_short_rows_past_the_cache(plan, src, elems, rows):
+    """What tests/test_gpu_row_routes.py compares with the oracle takes the variant it is about."""
+    p = plan(src, elems, 40, rows // 40 - 1, 0, 7)
+    assert p["read_once"] == 1 and p["rows_kernel"] == int(elems * (4 if src == FP32 else 2) // 16 >= 192)
