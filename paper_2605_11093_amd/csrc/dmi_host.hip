@@ -433,16 +433,14 @@ dmi_status_t stage_selection(dmi_ring *r, const dmi_selection_t *sel, bool paged
 // with a fixed grid of "as many as fit" the last round is run by a fraction of the
 // workgroups while the rest idle (up to half the launch for 1 < items/grid < 2).
 // kResident is five workgroups per compute unit: the kernels hold from four (summaries of short rows off the 16-byte grid:
-// up to 118 vector registers) to seven (rows dealt flat: 52, or a workgroup per row: 63 to 72); they are all planned for
-// five.  In a batch (gridDim.y = nb) each workgroup stays with one tensor.
+// up to 118 vector registers) to eight (rows dealt flat: 45 to 51); they are all planned for five.  In a batch (gridDim.y = nb) each workgroup stays with one tensor.
 uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
 {
     constexpr uint64_t kResident = 5u * 256u;
     const uint64_t listed = a.listed_rows, upr = a.units_per_row;
     // Decode-like selections (one row per request, no keep vector, dense) need no scan and no
-    // search, and a workgroup's first item is loaded along with its control words: a workgroup
-    // per item, each gone after one round trip, keeps more loads in flight than the resident
-    // few looping over many items.
+    // search: a workgroup per item, each gone after one round trip, keeps more loads in flight
+    // than the resident few looping over many items.
     const bool flat = a.simple && !a.paged;
     // capture_rows_kernel scans the table with a request per lane
     const bool finds_rows_itself = !a.paged && (a.simple || (a.n_reqs >= 1u && a.n_reqs <= 64u));
@@ -460,14 +458,20 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         const uint64_t n = groups_for(expected), full = (kFull + nb - 1u) / nb;
         return guess && n < full ? std::min(groups_for(listed), full) : n;
     };
-    // Where a launch reads more than the memory-side cache holds, it does so past it (non-temporal loads).  What such a launch
-    // leaves in the cache is no use to anyone, and what others have left there it would throw out before it gets to it (300 MB, written by the
-    // kernel before, through / past the cache: bf16 -> fp8 84.8 / 66.9 us, raw 107 / 90, statistics 59.9 / 43.7).  Below that the launch itself gains
-    // little (266 MB cold 70.7 / 69.0, raw 94.9 / 88.9, statistics 44.9 / 43.8; just written 58.7 / 58.6, 78.5 / 79.0, 38.3 / 38.2), and the next
-    // kernel that reads the rows finds them gone, also where they were there (a sum over them: 60 / 87 us at 266 MB, 49 / 69 at 200, 30 / 37 at 76).
+    // A launch reads past the memory-side cache (non-temporal loads) if it reads more than that holds, or at least half as much out of a
+    // stretch of rows that is larger: such a stretch has just gone through the cache and left its end there, in lines that have to be
+    // written back for every row that is brought in, and the next kernel that goes through it finds next to nothing of it either way.
+    // (Through / past the cache, us, rows written by the kernel before; behind the + a sum over the whole stretch behind the launch.  To fp8,
+    // 265 MB of 1063 113 + 301 / 73 + 314, of 531 109 + 163 / 72 + 174, 132 of 1061 59 + 309 / 38 + 319, of 530 51 + 171 / 39 + 177, all of
+    // 300 85 + 95 / 67 + 94; raw 265 of 1063 139 + 302 / 94 + 316; statistics 85 + 300 / 44 + 315.  On cold rows 74 / 71, 72 / 70, 40 / 39, 40 / 39,
+    // 80 / 77.)  Of a smaller part enough may have stayed in the cache (75 MB of 303, cold 25 + 95 / 24 + 99, written 22 + 106 / 20 + 111), and a
+    // stretch that it holds is found there, and left there, only through it (265 MB, all read: 62 + 74 / 59 + 88, cold 71 + 68 / 70 + 88; 132
+    // of 265 33 + 71 / 32 + 86; statistics 22 + 73 / 26 + 86).
     constexpr uint64_t kMemorySideCache = 256ull << 20;
-    const uint64_t source_bytes = expected * nb * a.row_elems * dtype_size(a.src_dtype);
-    const bool past_the_cache = source_bytes > kMemorySideCache;
+    const uint64_t row_bytes = (uint64_t)a.row_elems * dtype_size(a.src_dtype), source_bytes = expected * nb * row_bytes;
+    const uint64_t stretch_bytes = a.stretch_rows ? nb * ((a.stretch_rows - 1u) * (uint64_t)a.row_stride_b + row_bytes) : 0u;
+    const bool past_the_cache = source_bytes > kMemorySideCache ||
+                                (stretch_bytes > kMemorySideCache && source_bytes >= kMemorySideCache / 2u);
     // A batch's tensors have been kept for this launch and nothing reads them behind it: from half of the cache on.  (Through / past the
     // cache, cold and just written: statistics alone 134 MB 25.1 / 24.4 and 21.3 / 20.9, 200 MB 34.9 / 34.1 and 29.7 / 29.0; 256 x 8192 raw, 24 tensors
     // 37.0 / 37.0 and 31.5 / 31.5, 32 49.2 / 47.2 and 40.8 / 40.8, 40 60.5 / 57.7 and 50.4 / 49.9, 48 72.0 / 67.9 and 59.9 / 59.5; with statistics 48
@@ -572,7 +576,7 @@ namespace dmi { namespace host {
 
 // Which kernel a launch of `nb` decode-shaped tensors takes.  The decode-shaped kernel is the
 // quickest way through a small launch, where every dependent trip to memory counts; from
-// some eight thousand rows on the general kernel's one-item workgroups are as quick or quicker
+// some eight thousand rows on capture_rows_kernel's one-step wavefronts are as quick or quicker
 // (measured on 256 x 8192 bf16 tensors: 13.3 against 15.2 us for 8 tensors, 44 us either way for
 // 32, 116 against 113 us for 80).  The caller has set a.drop_newest and a.step.
 bool batch_takes_decode_kernel(const CaptureArgs &a, uint32_t nb)
@@ -604,8 +608,16 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
 {
     const dmi_ring *r = env.masks;
     const uint32_t es_in = dtype_size(geo.src_dtype);
-    uint64_t listed = 0;
-    for (uint32_t i = 0; i < sel->n_reqs; i++) listed += sel->reqs[i].tok_count;
+    uint64_t listed = 0, first = UINT64_MAX, end = 0;
+    for (uint32_t i = 0; i < sel->n_reqs; i++) {
+        const dmi_req_sel_t &q = sel->reqs[i];
+        listed += q.tok_count;
+        if (!q.tok_count) continue;
+        const uint64_t at = (uint64_t)q.row_base + q.tok_start;
+        first = std::min(first, at);
+        end = std::max(end, at + (uint64_t)(q.tok_count - 1u) * q.tok_step + 1u);
+    }
+    a.stretch_rows = a.paged || sel->row_index_dev || end <= first ? 0u : end - first;     // (rows of a table or an index: unknown)
     // 16-byte units wherever a row (a head's part of a paged row) has 16 bytes, on a 16-byte grid or not;
     // shorter rows that are not on one go element by element.  64 rows x 50257 bf16: 12.0 us by elements, 4.9 in units; 9.3 k x 4099 to fp8: 133 and 34 us.
     a.loose = !geo.vec16 && geo.seg_elems >= 16u / es_in;

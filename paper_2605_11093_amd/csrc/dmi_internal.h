@@ -147,12 +147,14 @@ struct CaptureArgs : CaptureKernelArgs {
     uint32_t point_id;              // same, BatchArgs::point
     uint32_t one_row_each;          // every request lists exactly one row (a keep vector may still drop some)
     uint32_t listed_rows;           // rows the selection lists (all requests kept)
+    uint64_t stretch_rows;          // dense: source rows from the first listed one to the last (0: not known)
     uint32_t rows_known, kept_rows; // whether the host knows the keep vector (or there is none), and how many rows that keeps
     const uint32_t *row_map;        // decode-shaped kernel, requests listing several rows: source row of every
                                     // output row, written by the host behind the request table
     uint32_t lds_bytes;
-    uint32_t wave_rows;             // summaries of rows of more than 256 units: a wavefront per row, not a workgroup
-    uint32_t step_per_wave;         // capture_rows_kernel takes the launch: a wavefront per 256 units of a row
+    uint32_t wave_rows;             // summaries of rows of more than 128 units: a wavefront per row, not a workgroup
+    uint32_t step_per_wave;         // capture_rows_kernel takes the launch: a wavefront per 256 units of a row, with summaries
+                                    // per row, or a workgroup (wave_rows)
     uint32_t read_once;             // rows are read past the memory-side cache (plan_grid() says when)
     uint32_t loose;                 // not on a 16-byte grid, but long enough for 16-byte units
     uint32_t limit_units;           // units per row by which a record's size is limited

@@ -8,13 +8,14 @@
 // launch costs microseconds whatever it moves, and only more bytes per launch amortise
 // that).  The paper's kernel (1-64 blocks, grid-stride 16-byte copies, last block
 // publishes) is prior art for other hardware; here
-//   * every workgroup rebuilds the per-request prefix sums in LDS with wavefront
-//     shuffle scans, so row -> (request, token) needs no pre-pass launch;
+//   * every workgroup scans the per-request row counts for itself (DPP prefix sums of 64
+//     requests at a time, kept in LDS; capture_rows_kernel: every wavefront, in registers),
+//     so row -> (request, token) needs no pre-pass launch;
 //   * rows are read with 16-byte vector loads and written with non-temporal
 //     16-byte stores (the ring is not read again by the GPU, so it should not
 //     displace the model's working set from the 4 MB per-XCD L2);
-//   * downcasts and fp32 row summaries happen in the same pass, summaries by
-//     wavefront shuffles (no matrix cores: nothing here is a contraction);
+//   * downcasts and fp32 row summaries happen in the same pass, summaries reduced
+//     by DPP (no matrix cores: nothing here is a contraction);
 //   * the record's place in the ring comes from a device-resident head, and the
 //     drop-newest decision from the drained mark as an earlier launch read it from a
 //     word the host keeps current, both double buffered along the chain of launches:
@@ -24,7 +25,7 @@
 //   * there is no fence and no completion counter in the kernel: on this GPU a
 //     device-scope fence writes back a whole L2, once per wavefront that issues it
 //     (measured: 19 us for a 64-workgroup capture, 300 us for 2048 workgroups).
-//     Workgroup 0 writes where the head stands into this launch's commit slot in
+//     One lane of one workgroup writes where the head stands into this launch's commit slot in
 //     device memory, and the host fetches a slot only behind an event recorded after
 //     the launch (the kernel-end release makes payload and slot visible);
 //   * a small capture is a chain of dependent trips to memory and little else, so every
@@ -687,7 +688,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     if (tid < 8) lds[m.heads + tid] = a.heads_sel[tid];
 
     if (!simple) {
-        // -- per-request kept row counts -> exclusive prefix sums (wavefront shuffle scans)
+        // -- per-request kept row counts -> exclusive prefix sums (a wavefront's 64 by DPP)
         for (uint32_t b = wave; b < nb; b += kThreads / 64u) {
             const uint32_t r = b * 64u + lane;
             uint32_t cnt = 0, cnt_all = 0;
@@ -1723,7 +1724,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
 // barrier, and header, table and publishing are a workgroup of their own, whose code the others do not run through.  It is the first
 // one of its record: a table of many requests takes it several trips, and as the last one to start it kept the GPU waiting (4096
 // requests x 4096 fp32 stored 32.7 us and 27.4 like this, 2048 x 14336 bf16 26.4 and 23.5, 1024 x 14336 15.1 and 13.7).  And there is one step to a wavefront, many more workgroups than fit at once, and no
-// software pipeline: seven workgroups per compute unit hide each other's trips (54 registers; two steps in
+// software pipeline: eight workgroups per compute unit hide each other's trips (55 to 58 registers; two steps in
 // a pipeline take 93, five workgroups).  Steps per wavefront 1 / 2 / 4: 19.1 / 20.4 / 23.7 us; units per lane 2 / 4 / 8:
 // 21.8 / 18.8 / 20.0 (9.3 k rows x 4096 bf16 -> fp8).
 // Kernel times, before and after: bf16 -> fp8, 32 requests: 9.3 k x 4096 (every fourth token) 23.5 -> 18.8 us (6.1 TB/s),
@@ -1740,7 +1741,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
 // Shorter rows, and in large launches those that leave many of a step's lanes idle, are dealt flat by the general kernel (plan_grid()
 // says which, with figures), and so are rows of more than 64 ragged requests.
 struct RowsArgs {
-    // lines 0 and 1: what the row workgroups need
+    // lines 0 and 1, for summaries also the start of line 2: what the row workgroups need
     int64_t row_stride_b, n_src_rows;
     const uint4 *req_table;
     const uint32_t *row0;           // first source row of each request
@@ -1758,7 +1759,7 @@ struct RowsArgs {
     uint32_t row_first;
     uint32_t summary_mask, src_dtype, row_lanes, passes;     // summaries: lanes that share a row, as in the general kernel
     uint32_t pad;
-    // line 2: header and publishing
+    // the rest of line 2: header and publishing
     uint64_t seq, step_id;
     CommitSlot *cslot;
     const uint64_t *tail_src;

@@ -1,7 +1,7 @@
 // Which kernel a dense capture takes and over how many workgroups, as the host plans it -- TEST INFRASTRUCTURE ONLY.
-//   plan_driver SRC_DTYPE WIDTH REQS ROWS_EACH OUT_DTYPE SUMMARY_MASK TENSORS KEEP STEP
+//   plan_driver SRC_DTYPE WIDTH REQS ROWS_EACH OUT_DTYPE SUMMARY_MASK TENSORS KEEP STEP EVERY INDEXED
 // KEEP: none; unknown (a keep vector of the caller's); or a string of 0 and 1, one per request (dmi_set_keep_mask).
-// STEP: 1 if the launch sits in a replayable step.  Prints the fields that plan_grid() decides.
+// STEP: 1 if the launch sits in a replayable step.  EVERY: rows of the source to one listed.  Prints the fields that plan_grid() decides.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -20,7 +20,7 @@ using namespace dmi::host;
 
 int main(int argc, char **argv)
 {
-    CHECK(argc == 10);
+    CHECK(argc == 12);
     auto num = [&](int i) { return (uint32_t)strtoul(argv[i], nullptr, 10); };
     const uint32_t dtype = num(1), width = num(2), n = num(3), each = num(4), nb = num(7);
     const std::string keep = argv[8];
@@ -34,7 +34,7 @@ int main(int argc, char **argv)
     CHECK(hipStreamCreate(&stream) == hipSuccess);
 
     std::vector<dmi_req_sel_t> reqs;
-    for (uint32_t i = 0; i < n; i++) reqs.push_back({i, i * each, 0u, each, 1u});
+    for (uint32_t i = 0; i < n; i++) reqs.push_back({i, i * each * num(10), 0u, each, num(10)});
     const uint8_t *mask = nullptr;
     uint8_t callers[1] = {1};
     if (keep == "unknown") {
@@ -46,8 +46,9 @@ int main(int argc, char **argv)
         CHECK(dmi_set_keep_mask(ring, k.data(), n, stream, &mask) == DMI_OK);
     }
     alignas(16) static uint8_t data[16];            // (nothing is read: only the plan is made)
-    dmi_tensor_t t = {data, dtype, {(int64_t)n * each, (int64_t)width}, {(int64_t)width, 1}};
-    dmi_selection_t sel = {n, reqs.data(), mask, nullptr};
+    dmi_tensor_t t = {data, dtype, {(int64_t)n * each * num(10), (int64_t)width}, {(int64_t)width, 1}};
+    static const int32_t index[1] = {0};
+    dmi_selection_t sel = {n, reqs.data(), mask, num(11) ? index : nullptr};
     dmi_transform_t xf = {num(5), num(6)};
     Geometry geo;
     CaptureArgs a;

@@ -1,6 +1,6 @@
 """How launches are planned (host runtime on the CPU stand-in, tests/cpu_runtime/): the number of workgroups follows the
-rows that a keep vector is expected to keep, and a launch reads past the memory-side cache if what it is expected to read does not
-fit there."""
+rows that a keep vector is expected to keep, and what a launch reads, and out of which stretch, decides whether it does so past the memory-side
+cache."""
 import os
 import shutil
 import subprocess
@@ -26,8 +26,8 @@ def plan(tmp_path_factory):
         cmd += ["-x", "c++", src]
     subprocess.check_call(cmd)
 
-    def run(src, width, reqs, each, out, mask=0, tensors=1, keep="none", step=0):
-        p = subprocess.run([exe, *map(str, (src, width, reqs, each, out, mask, tensors, keep, step))], timeout=60,
+    def run(src, width, reqs, each, out, mask=0, tensors=1, keep="none", step=0, every=1, indexed=0):
+        p = subprocess.run([exe, *map(str, (src, width, reqs, each, out, mask, tensors, keep, step, every, indexed))], timeout=60,
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, env=dict(os.environ, ASAN_OPTIONS="exitcode=67"))
         assert p.returncode == 0, p.stdout.decode(errors="replace")[-4000:]
         return {k: int(v) for k, v in (f.split("=") for f in p.stdout.decode().split())}
@@ -68,11 +68,17 @@ def test_past_the_cache(plan, src, width, out, mask):
         return plan(src, width, 16, mb * MB // row // 16 // how.get("tensors", 1), out, mask, **how)["read_once"]
 
     assert (reads(200), reads(255), reads(257), reads(400)) == (0, 0, 1, 1)
-    # of a launch with a keep vector counts what it is expected to read, not what is listed
-    half = "10" * 8
-    assert (reads(400, keep=half), reads(500, keep=half), reads(520, keep=half)) == (0, 0, 1)
-    assert (reads(1600, keep="1" + "0" * 15), reads(270, keep="1" * 16)) == (0, 1)
-    assert (reads(400, keep="unknown"), reads(500, keep="unknown"), reads(520, keep="unknown")) == (0, 0, 1)
+    # at least half as much out of a larger stretch
+    assert (reads(126, every=4), reads(130, every=4), reads(125, every=2), reads(130, every=2), reads(90, every=30)) == (0, 1, 0, 1, 0)
+    for keep in ("10" * 8, "unknown"):
+        assert (reads(254, keep=keep), reads(260, keep=keep)) == (0, 1)
+    assert (reads(400, keep="1" + "0" * 15), reads(800, keep="1110" + "0" * 12)) == (0, 1)
+    # where that is not known, what is expected to be read: of a launch with a keep vector not what is listed
+    assert (reads(255, indexed=1), reads(257, indexed=1), reads(100, every=4, indexed=1)) == (0, 1, 0)
+    half = dict(indexed=1, keep="10" * 8)
+    assert (reads(400, **half), reads(500, **half), reads(520, **half)) == (0, 0, 1)
+    assert (reads(1600, indexed=1, keep="1" + "0" * 15), reads(270, indexed=1, keep="1" * 16)) == (0, 1)
+    assert (reads(400, indexed=1, keep="unknown"), reads(520, indexed=1, keep="unknown")) == (0, 1)
     # a batch of rows that a wavefront or more takes: from half of the cache on
     early = int(width != 512)
     assert (reads(127, tensors=8), reads(128, tensors=8), reads(260, tensors=8)) == (0, early, 1)
