@@ -551,9 +551,16 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
         a.read_once = past_the_cache || batch_past_the_cache;
         groups = planned([&](uint64_t rows) { return (rows * steps_per_row + 3u) / 4u; });
     } else {
-        // short rows: slices of 256 units; a workgroup takes 4 per round once there are enough
-        const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads;
-        groups = slices * nb <= kResident ? slices : balanced((slices + 3u) / 4u, kItemsPerGroupInBatch);
+        // Short rows: slices of 256 units; a workgroup takes 4 per round once there are enough.  In a batch of up to nine rounds
+        // the resident set shared evenly, then two items per workgroup, from twenty on four as above: eight workgroups of this path
+        // share a compute unit, and with four items each the middling sizes left the last of them alone.  (Four / two / shared, cold
+        // and just written, us; paged, rows of 32 units raw: 6.5 rounds 62.5 / 56.8 / 57.4 and 77.0 / 70.6 / 65.3, 7.8 68.6 / 68.5 / 67.1 and
+        // 83.2 / 83.8 / 76.7, 9.0 76.3 / 76.2 / 79.2 and 95.1 / 94.2 / 92.9, 10.3 91.2 / 87.5 / 87.0 and 110.6 / 106.0 / 101.4, 11.6 99.6 / 94.8 and
+        // 120.7 / 115.0, 23 183.4 / 181.7 / 192.1 and 206.1 / 202.6 / 215.7, 94 594 / 601 and 646 / 667; to fp8 6.5 52.8 / 46.9 / 48.0, 11.6 80.3 / 76.9, 23
+        // 143.8 / 145.1 / 154.7, 94 430 / 446; 12 x 5.1 k ragged rows of 512 units to fp8, 24 rounds 142.8 / 149.5.)
+        const uint64_t slices = (listed * upr + kThreads - 1u) / kThreads, items = (slices + 3u) / 4u;
+        const uint64_t most = items * nb <= 9u * kResident ? 9u : items * nb <= 20u * kResident ? 2u : kItemsPerGroupInBatch;
+        groups = slices * nb <= kResident ? slices : balanced(items, most);
     }
     return groups < 1u ? 1u : groups > kMaxGrid ? kMaxGrid : (uint32_t)groups;
 }

@@ -1,6 +1,6 @@
-"""Rows of 64 units and more that a large launch deals flat, beside the same rows in a launch that is a little smaller and gives each a
+"""Rows that a launch deals flat: of 64 units and more in large launches, beside the same rows in a launch that is a little smaller and gives each a
 wavefront: one row per request in a batch and ragged, raw, fp16 and fp8, on and off the 16-byte grid, with a keep vector, an
-index and a record that wraps in the ring."""
+index and a record that wraps in the ring; shorter ones in batches of several sizes."""
 import numpy as np
 import pytest
 import torch
@@ -67,3 +67,24 @@ def test_batches(B, elems, out):
                     ref = orc.build_record(xs[p].cpu(), reqs, seq=step * n + p, step_id=step, point_id=p, out_dtype=out, summary_mask=0)
                     assert np.array_equal(v.bytes(), ref), (n, step, p)
                 ring.release_host(views[-1].seq)
+
+
+@pytest.mark.parametrize("elems,out", [(256, 1), (250, 4)])
+@pytest.mark.parametrize("rounds", [5, 9, 10, 20, 21])
+def test_ragged_batches(B, elems, out, rounds):
+    """Both sides of the lines where a batch's workgroups are given another share of it (1280 items of 1024 units to a round)."""
+    s = torch.cuda.current_stream().cuda_stream
+    n, units = 8, -(-elems * 2 // 16)
+    each = (rounds * 1280 - 60) * 1024 // units // n // 50
+    reqs = np.array([[i, each * i, 0, each - (i % 3), 1] for i in range(50)], dtype=np.uint32)
+    xs = [prng.randn_bf16(p, 50 * each * elems, DEV).view(-1, elems) for p in range(n)]
+    size = B.record_bytes(50, int(reqs[:, 3].sum()), elems, out, 0)
+    with B.Ring((n + 1) * size, (n + 1) * size) as ring:
+        ring.observe_batch(range(n), xs, reqs, step_id=3, stream=s, out_dtype=out, summary_mask=0)
+        ring.drain(B.DRAIN_FLUSH)
+        views = ring.poll_host(n)
+        assert len(views) == n
+        for p in (0, 3, n - 1):
+            ref = orc.build_record(xs[p].cpu(), reqs, seq=p, step_id=3, point_id=p, out_dtype=out, summary_mask=0)
+            assert np.array_equal(views[p].bytes(), ref), p
+        ring.release_host(views[-1].seq)

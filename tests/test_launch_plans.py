@@ -99,6 +99,19 @@ def test_short_steps_of_large_launches_are_dealt_flat(plan, out, least):
         assert rows_kernel(63, 1000, ragged) == 0 and rows_kernel(256, 100000, ragged) == 1
 
 
+@pytest.mark.parametrize("out", [BF16, FP8])
+@pytest.mark.parametrize("tensors", [1, 2, 8, 16])
+def test_batches_of_short_rows_dealt_flat(plan, out, tensors):
+    """Shared evenly among five workgroups per compute unit, beyond nine rounds of a batch two items each, beyond twenty four."""
+    for rounds in (1, 2, 4, 5, 8, 9, 10, 20, 21, 40):
+        each = (rounds * 1280 * 32 - 1600) // tensors // 50     # rows of 32 units, 32 to an item
+        items = -(-(-(-50 * each * 32 // 256)) // 4)
+        share = rounds if tensors == 1 or rounds <= 9 else 2 if rounds <= 20 else 4
+        assert -(-items * tensors // 1280) == rounds
+        got = plan(BF16, 256, 50, each, out, tensors=tensors)
+        assert got["rows_kernel"] == 0 and got["grid"] == (items if rounds == 1 else -(-items // share))
+
+
 @pytest.mark.parametrize("src,elems,rows", [(BF16, 1024, 132000), (BF16, 256, 530000), (2, 1000, 135000), (FP32, 512, 132000), (BF16, 2040, 66500)])
 def test_statistics_of_short_rows_past_the_cache(plan, src, elems, rows):
     """What tests/test_gpu_row_routes.py compares with the oracle takes the variant it is about."""
