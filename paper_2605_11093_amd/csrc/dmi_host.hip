@@ -58,18 +58,17 @@ bool capture_status(hipStream_t s, hipStreamCaptureStatus *status)
     return false;
 }
 
-// Record an event behind everything launched so far (no-op if that is already covered, unless
-// asked for all the same); *no = the number of the probe that covers it.
+// Record an event behind everything launched so far (no-op if that is already covered).
 // If the host cannot tell what those launches added (drop-newest, keep vectors), the
 // newest launch's commit slot is fetched into the pinned mirror in front of the event.
 // Both go onto the producer's own stream: a launch on a second hardware queue that waits
 // for an event of this one slows every dispatch here by a microsecond or so while it
 // waits, far more than a small launch every sixteenth capture costs in line.
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no)
+dmi_status_t record_probe(dmi_ring *r)
 {
     std::lock_guard<std::mutex> lk(r->pmu);
     const uint64_t launched = r->next_seq.load(std::memory_order_acquire);
-    if (launched <= r->probed_upto && !even_if_covered) return DMI_OK;
+    if (launched <= r->probed_upto) return DMI_OK;
     hipEvent_t ev;
     if (r->probe_pool.empty()) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     else { ev = r->probe_pool.back(); r->probe_pool.pop_back(); }
@@ -80,12 +79,23 @@ dmi_status_t record_probe(dmi_ring *r, bool even_if_covered, uint64_t *no)
         HIP_TRY(launch_fetch_slot(&r->dctrl->slots[slot], r->hslots_dev + slot, us));
     }
     HIP_TRY(hipEventRecord(ev, us));
-    r->probes.push_back({ev, launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made});
-    if (no) *no = r->probes_made;
+    r->probes.push_back({ev, DrainNote(), launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made});
     r->window = Delta();
     r->window_exact = true;
     r->probed_upto = launched;
     return DMI_OK;
+}
+
+// The same where a drain kernel that says itself when it is over has gone behind everything launched so far.  Caller
+// has seen that the host can tell what those launches add.
+static uint64_t probe_by_drain(dmi_ring *r, const DrainNote &note)
+{
+    std::lock_guard<std::mutex> lk(r->pmu);
+    const uint64_t launched = r->next_seq.load(std::memory_order_acquire);
+    r->probes.push_back({nullptr, note, launched, r->launches.load(std::memory_order_relaxed), false, r->window, ++r->probes_made});
+    r->window = Delta();
+    r->probed_upto = launched;
+    return r->probes_made;
 }
 
 // Take note of finished probes: the slot of the newest launch they cover says where the
@@ -95,7 +105,18 @@ dmi_status_t advance_commits(dmi_ring *r, bool block)
     std::lock_guard<std::mutex> lk(r->pmu);
     while (!r->probes.empty()) {
         Probe &p = r->probes.front();
-        hipError_t e = block ? hipEventSynchronize(p.ev) : hipEventQuery(p.ev);
+        hipError_t e;
+        if (p.ev) {
+            e = block ? hipEventSynchronize(p.ev) : hipEventQuery(p.ev);
+        } else {
+            const uint64_t t0 = now_ns();
+            while (!p.note.over() && block) {
+                if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
+                    return fail(DMI_ERR_AGAIN, "the copy of an earlier flush did not finish within %u ms", r->block_timeout_ms);
+                std::this_thread::yield();
+            }
+            e = p.note.over() ? hipSuccess : hipErrorNotReady;
+        }
         block = false;
         if (e == hipErrorNotReady) break;
         if (e != hipSuccess) return fail(DMI_ERR_HIP, "commit event: %s", hipGetErrorString(e));
@@ -118,7 +139,7 @@ dmi_status_t advance_commits(dmi_ring *r, bool block)
         r->confirmed.store(p.covers, std::memory_order_release);
         r->confirmed_launches.store(p.launches, std::memory_order_release);
         r->probes_done.store(p.no, std::memory_order_release);
-        r->probe_pool.push_back(p.ev);
+        if (p.ev) r->probe_pool.push_back(p.ev);
         r->probes.pop_front();
     }
     return DMI_OK;
@@ -179,8 +200,8 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full)
         if (r->cfg.flags & DMI_DRAIN_KERNEL) {
             uint64_t units = n / 16u;
             uint32_t grid = (uint32_t)((units + kThreads - 1) / kThreads);
-            if (grid > 128u) grid = 128u;
-            HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, grid,
+            if (grid > kDrainGroups) grid = kDrainGroups;
+            HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, grid, nullptr, 0u,
                                         r->drain_stream));
         } else {
             uint64_t off = from, left = n;
@@ -241,11 +262,11 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
 }
 
 // A flush whose bytes the host can tell in advance: the drain kernel moves them on the producer's
-// own stream, right behind the captures, and one event covers both.  Otherwise the host waits
+// own stream, right behind the captures, and says itself when it is over.  Otherwise the host waits
 // for the captures' event, only then starts a copy, and waits for that.  *issued says whether this was done.
 // Measured from a capture's launch to the end of the wait, drain kernel against event and copy engine:
-// 14.6 / 18.8 us for 17 KB, 25.0 / 29.9 for 0.6 MB, 52 / 56 for 2 MB, 100 / 107 for 4.7 MB, 178 / 174
-// for 8.4 MB: from some 6 MB on the copy engine's higher rate (57 against 53 GB/s) outweighs the wait.
+// 10.0 / 23.4 us for 4 KB, 21.4 / 31.5 for 0.6 MB, 47.5 / 57.5 for 2 MB, 85 / 99.5 for 4.2 MB.  Not above 6 MiB, where the kernel's 64
+// workgroups would be on the GPU for more than 100 us to save a tenth of that.
 // Left to the copy engine: a flush by any other thread than the producer's, which goes on launching its
 // model's kernels meanwhile and would find the copy in front of them on their stream; a ring whose creator
 // asked for the copy engine by name; a ring with a drain thread (it follows the commits and issues copies by
@@ -281,12 +302,11 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
         return DMI_OK;
     atomic_max(r->dev_high, n);
     const uint64_t groups = (n / 16u + kThreads - 1u) / kThreads;
-    HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n,
-                                (uint32_t)(groups < 64u ? groups : 64u), us));
-    uint64_t no = 0;
+    const DrainNote note = {r->hdone, (uint32_t)(groups < kDrainGroups ? groups : kDrainGroups), ++r->drain_tick};
+    HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, note.groups, r->hdone_dev, note.tick, us));
     // (a probe of its own, even if another thread's drain has just put one there: that one may be in front of the
-    // copy; and on that stream, because its producer is this thread, whose count of launches starts again behind it)
-    if ((st = record_probe(r, true, &no)) != DMI_OK) return st;
+    // copy; this thread is the producer, whose count of launches starts again behind it)
+    const uint64_t no = probe_by_drain(r, note);
     r->unprobed_launches = 0;
     r->unprobed_bytes = 0;
     r->direct_probe = no;
@@ -1018,7 +1038,8 @@ void free_ring(dmi_ring *r)
     if (r->drain_stream) { (void)hipStreamSynchronize(r->drain_stream); (void)hipStreamDestroy(r->drain_stream); }
     if (r->ctl_stream) { (void)hipStreamSynchronize(r->ctl_stream); (void)hipStreamDestroy(r->ctl_stream); }
     if (r->htail) (void)hipHostFree((void *)r->htail);
-    for (auto &p : r->probes) (void)hipEventDestroy(p.ev);
+    if (r->hdone) (void)hipHostFree(r->hdone);
+    for (auto &p : r->probes) if (p.ev) (void)hipEventDestroy(p.ev);
     for (auto ev : r->probe_pool) (void)hipEventDestroy(ev);
     if (r->dev_ring) (void)hipFree(r->dev_ring);
     if (r->dctrl) (void)hipFree(r->dctrl);
@@ -1131,6 +1152,11 @@ dmi_status_t dmi_ring_create(const dmi_ring_config_t *cfg, dmi_ring_t **out)
     if ((e = hipHostGetDevicePointer((void **)&r->htail_dev, (void *)r->htail, 0)) != hipSuccess)
         return bail(e, "hipHostGetDevicePointer(tail word)");
     *r->htail = 0;
+    if ((e = hipHostMalloc((void **)&r->hdone, kDrainGroups * 8u, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
+        return bail(e, "hipHostMalloc(drain words)");
+    if ((e = hipHostGetDevicePointer((void **)&r->hdone_dev, r->hdone, 0)) != hipSuccess)
+        return bail(e, "hipHostGetDevicePointer(drain words)");
+    memset(r->hdone, 0, kDrainGroups * 8u);
     if ((e = hipStreamCreateWithFlags(&r->drain_stream, hipStreamNonBlocking)) != hipSuccess)
         return bail(e, "hipStreamCreate");
     if ((e = hipStreamCreateWithFlags(&r->ctl_stream, hipStreamNonBlocking)) != hipSuccess)

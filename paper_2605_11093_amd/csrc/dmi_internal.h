@@ -11,6 +11,7 @@ constexpr uint32_t kMaxGrid = 1u << 22;     // workgroups per tensor of one laun
 constexpr uint32_t kLdsTableMax = 1024;     // request tables up to this size are cached in LDS
 constexpr uint32_t kDecodeMaxListed = 1024; // most rows a ragged selection may list to take the decode-shaped kernel
 constexpr uint32_t kLongRowUnits = 64;      // rows from this length on, stored without summaries: capture_rows_kernel (plan_grid(): which)
+constexpr uint32_t kDrainGroups = 64;       // most workgroups of a drain kernel
 constexpr uint32_t kMaxBatch = 128;         // most tensors one batched launch captures
 
 // One slot per launch, written by workgroup 0 of the launch: where the head stands
@@ -166,6 +167,36 @@ struct CaptureArgs : CaptureKernelArgs {
     uint32_t row_first;
 };
 
+// What one launch of the drain kernel copies: up to three spans, each of which lies in one piece in both rings.
+struct DrainSpan {
+    const uint8_t *src;
+    uint8_t *dst;
+    uint32_t n;                     // bytes, a multiple of 64
+    uint32_t pad;
+};
+struct DrainSpans {
+    DrainSpan span[3];
+};
+constexpr uint64_t kDrainMost = 1ull << 30;     // bytes of one launch (the kernel's offsets have 32 bits)
+
+// The spans of stream bytes [from, from + n) with n <= kDrainMost as large as nbytes allows; returns n.  nbytes is no more than
+// either ring holds, so each of them ends at most once on the way.
+inline uint64_t drain_spans(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap, uint64_t from, uint64_t nbytes,
+                            DrainSpans &d)
+{
+    const uint64_t all = nbytes < kDrainMost ? nbytes : kDrainMost;
+    uint64_t done = 0;
+    for (uint32_t i = 0; i < 3u; i++) {
+        const uint64_t at = (from + done) % cap, to = (from + done) % host_cap;
+        uint64_t n = all - done;
+        if (n > cap - at) n = cap - at;
+        if (n > host_cap - to) n = host_cap - to;
+        d.span[i] = DrainSpan{ring + at, host_ring + to, (uint32_t)n, 0u};
+        done += n;
+    }
+    return done;
+}
+
 // Launchers (dmi_kernels.hip).  All return the launch's hipError_t.
 hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool vec16, hipStream_t s);
 // decode-shaped captures: bf16 source (fp16 if stored as it is), dense, one row per request (with or without a keep
@@ -182,8 +213,10 @@ hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words,
 hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint32_t par_from, uint32_t par_to,
                              const uint64_t *host_tail, hipStream_t s);
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s);
+// nbytes: at most what either ring holds; grid: at most kDrainGroups.  done (or NULL): words in pinned host memory, one per
+// workgroup, which takes the value `tick` once what that workgroup has copied can be read on the host
 hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap,
-                               uint64_t from, uint64_t nbytes, uint32_t grid, hipStream_t s);
+                               uint64_t from, uint64_t nbytes, uint32_t grid, uint64_t *done, uint64_t tick, hipStream_t s);
 uint32_t capture_lds_bytes(uint32_t n_reqs, bool index_mode, bool table_in_lds);
 
 }  // namespace dmi

@@ -132,8 +132,22 @@ struct Delta {
     uint64_t drop_bytes = 0, drop_records = 0, drop_rows = 0;   // dropped, by the host's own decision
 };
 
+// A drain kernel that says itself what of it is over (launch_drain_kernel()): each of its workgroups in a word of its own.
+struct DrainNote {
+    const uint64_t *words = nullptr;
+    uint32_t groups = 0;
+    uint64_t tick = 0;
+    bool over() const
+    {
+        for (uint32_t g = 0; g < groups; g++)
+            if (__atomic_load_n(words + g, __ATOMIC_ACQUIRE) < tick) return false;
+        return true;
+    }
+};
+
 struct Probe {
-    hipEvent_t ev;          // recorded on the producer's stream behind the launches (and the slot fetch)
+    hipEvent_t ev;          // recorded on the producer's stream behind the launches (and the slot fetch); or NULL:
+    DrainNote note;         // a drain kernel behind the launches, which says itself when it is over
     uint64_t covers;        // every launch with seq < covers was enqueued before ev
     uint64_t launches;      // how many capture launches that is
     bool fetched;           // the commit slot of launch covers-1 was copied to the host mirror
@@ -223,6 +237,9 @@ struct dmi_ring {
     // pinned host word that they read themselves.
     volatile uint64_t *htail = nullptr;                    // pinned, coherent
     const uint64_t *htail_dev = nullptr;                   // its device address
+    uint64_t *hdone = nullptr, *hdone_dev = nullptr;       // pinned, coherent: kDrainGroups words of the drain kernel that a
+                                                           // flush puts behind the captures (one at a time: direct_probe)
+    uint64_t drain_tick = 0;                               // how many of those there have been (under mu)
     // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over
     // once probe number `direct_probe` is.  0: none; no other copy is issued while there is one.
     uint64_t direct_probe = 0;
@@ -297,7 +314,7 @@ namespace host {
 const void *this_thread();                                 // the calling thread: an address that it has to itself
 void note_producer(dmi_ring *r, void *stream);             // the calling thread observes on `stream`
 bool capture_status(hipStream_t s, hipStreamCaptureStatus *status);
-dmi_status_t record_probe(dmi_ring *r, bool even_if_covered = false, uint64_t *no = nullptr);
+dmi_status_t record_probe(dmi_ring *r);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub);

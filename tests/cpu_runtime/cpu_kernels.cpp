@@ -162,7 +162,7 @@ static std::mutex g_drain_mu;
 static std::map<hipStream_t, unsigned> g_drain_launches;
 
 hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap,
-                               uint64_t from, uint64_t nbytes, uint32_t, hipStream_t s)
+                               uint64_t from, uint64_t nbytes, uint32_t grid, uint64_t *done, uint64_t tick, hipStream_t s)
 {
     {
         std::lock_guard<std::mutex> lk(g_drain_mu);
@@ -171,6 +171,7 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
     fake_enqueue(s, [=] {
         for (uint64_t i = 0; i < nbytes; i += 64u)
             memcpy(host_ring + (from + i) % host_cap, ring + (from + i) % cap, 64);
+        for (uint32_t g = 0; done && g < grid; g++) __atomic_store_n(done + g, tick, __ATOMIC_RELEASE);
     });
     return hipGetLastError();
 }
