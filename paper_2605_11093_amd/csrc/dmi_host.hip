@@ -147,15 +147,22 @@ dmi_status_t advance_commits(dmi_ring *r, bool block)
 
 uint64_t read_committed(const dmi_ring *r) { return r->committed.load(std::memory_order_acquire); }
 
+// Up to where the device ring is complete: the head as the last probe has confirmed it or as a launch has noted it since.
+static uint64_t read_complete(const dmi_ring *r)
+{
+    const uint64_t noted = __atomic_load_n(r->hwords + kWordNote, __ATOMIC_ACQUIRE);
+    return std::max(read_committed(r), noted);
+}
+
 // The drained-up-to mark, where the kernels read it: one pinned word, written here and read by a
 // lane of a running kernel across the host link at any time, so the store is an atomic one.
 static void publish_tail(dmi_ring *r, uint64_t mark)
 {
-    __atomic_store_n(const_cast<uint64_t *>(r->htail), mark, __ATOMIC_RELEASE);
+    __atomic_store_n(r->htail, mark, __ATOMIC_RELEASE);
 }
 
 // Retire finished copies (all of them at once: the drain stream is idle).  Caller holds r->mu.
-dmi_status_t reap(dmi_ring *r, bool wait)
+dmi_status_t reap(dmi_ring *r)
 {
     if (r->drain_done.load(std::memory_order_relaxed) == r->drain_issued) return DMI_OK;
     if (r->direct_probe) {      // on the producer's stream: the drain stream's being idle says nothing
@@ -165,20 +172,69 @@ dmi_status_t reap(dmi_ring *r, bool wait)
         publish_tail(r, r->drain_issued);
         return DMI_OK;
     }
-    hipError_t e = wait ? hipStreamSynchronize(r->drain_stream) : hipStreamQuery(r->drain_stream);
-    if (e == hipErrorNotReady) return DMI_OK;
-    if (e != hipSuccess) return fail(DMI_ERR_HIP, "drain stream: %s", hipGetErrorString(e));
+    if (r->copy_note.groups && !r->copy_note.over()) return DMI_OK;
+    r->copy_note.groups = 0;
+    if (r->copies) {
+        hipError_t e = hipStreamQuery(r->drain_stream);
+        if (e == hipErrorNotReady) return DMI_OK;
+        if (e != hipSuccess) return fail(DMI_ERR_HIP, "drain stream: %s", hipGetErrorString(e));
+        r->copies = false;
+    }
     r->drain_done.store(r->drain_issued, std::memory_order_release);
     publish_tail(r, r->drain_issued);
     return DMI_OK;
 }
 
-// Issue copies for what is committed and fits the host ring.  Caller holds r->mu.
-dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full)
+// Workgroups of a drain kernel for n bytes.
+static uint32_t drain_groups(uint64_t n)
+{
+    const uint64_t groups = (n / 16u + kThreads - 1u) / kThreads;
+    return (uint32_t)(groups < kDrainGroups ? groups : kDrainGroups);
+}
+
+// Copy stream bytes [from, from + n) on the drain stream.  Caller holds r->mu.
+static dmi_status_t copy_span(dmi_ring *r, uint64_t from, uint64_t n)
+{
+    r->copies = true;
+    if (r->cfg.flags & DMI_DRAIN_KERNEL) {
+        HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, drain_groups(n), nullptr, 0u,
+                                    r->drain_stream));
+        return DMI_OK;
+    }
+    while (n) {
+        const uint64_t s = from % r->dev_cap, d = from % r->host_cap;
+        uint64_t len = n;
+        if (len > r->dev_cap - s) len = r->dev_cap - s;
+        if (len > r->host_cap - d) len = r->host_cap - d;
+        HIP_TRY(hipMemcpyAsync(r->host_ring + d, r->dev_ring + s, len, hipMemcpyDeviceToHost, r->drain_stream));
+        from += len;
+        n -= len;
+    }
+    return DMI_OK;
+}
+
+// The same by a drain kernel that says itself when it is over, on a stream of its own (nothing is in front of it there and it
+// waits for nothing).  One at a time.
+static dmi_status_t copy_span_noted(dmi_ring *r, uint64_t from, uint64_t n)
+{
+    const DrainNote note = {r->hwords + kWordsDrain, drain_groups(n), ++r->drain_tick};
+    HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, note.groups,
+                                r->hwords_dev + kWordsDrain, note.tick, r->ctl_stream));
+    r->copy_note = note;
+    return DMI_OK;
+}
+
+// Issue copies for what is complete and fits the host ring.  Caller holds r->mu.
+// `flush`: for a flush by the producer's own thread, which polls.  While captures are still running, one copy at a time of at
+// least flush->least bytes, by the copy engine: a drain kernel beside them has them wait behind its stores across the link (32
+// captures of 64 x 4096 took ten times as long as long as one ran).  Behind the captures a drain kernel, which starts 5 us
+// sooner than the copy engine (from the captures' end to the host's knowing of the copy's: 4 KB 7.7 / 12.3 us, 2 MB 45.5 / 46.5, 4.2 MB
+// 83 / 88, 16.8 MB 311 / 311), also beside a copy that is under way.
+dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, const ChunkRule *flush)
 {
     if (moved) *moved = 0;
     if (host_full) *host_full = false;
-    dmi_status_t st = reap(r, false);
+    dmi_status_t st = reap(r);
     if (st != DMI_OK) return st;
     if (r->direct_probe) return DMI_OK;
     uint64_t committed, committed_records;
@@ -187,8 +243,12 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full)
         committed = read_committed(r);
         committed_records = r->snap[0];
     }
-    atomic_max(r->dev_high, committed - r->drain_done.load(std::memory_order_relaxed));
-    const uint64_t avail = committed - r->drain_issued;
+    const uint64_t complete = std::max(read_complete(r), committed);
+    atomic_max(r->dev_high, complete - r->drain_done.load(std::memory_order_relaxed));
+    const uint64_t avail = complete - r->drain_issued;
+    const bool by_kernel = (r->cfg.flags & DMI_DRAIN_KERNEL) != 0;
+    if (flush && flush->more && (r->copies || by_kernel || avail < flush->least)) return DMI_OK;
+    if (flush && r->copy_note.groups) return DMI_OK;
     const uint64_t host_free = r->host_cap - (r->drain_issued - r->released);
     uint64_t n = avail < host_free ? avail : host_free;
     if (host_full) *host_full = avail > 0 && host_free == 0;
@@ -197,24 +257,10 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full)
     if (n > batch) n = batch;
     if (n > 0) {
         const uint64_t from = r->drain_issued;
-        if (r->cfg.flags & DMI_DRAIN_KERNEL) {
-            uint64_t units = n / 16u;
-            uint32_t grid = (uint32_t)((units + kThreads - 1) / kThreads);
-            if (grid > kDrainGroups) grid = kDrainGroups;
-            HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, grid, nullptr, 0u,
-                                        r->drain_stream));
+        if (flush && !flush->more && n <= kChunkKernelBytes) {
+            if ((st = copy_span_noted(r, from, n)) != DMI_OK) return st;
         } else {
-            uint64_t off = from, left = n;
-            while (left) {
-                const uint64_t s = off % r->dev_cap, d = off % r->host_cap;
-                uint64_t len = left;
-                if (len > r->dev_cap - s) len = r->dev_cap - s;
-                if (len > r->host_cap - d) len = r->host_cap - d;
-                HIP_TRY(hipMemcpyAsync(r->host_ring + d, r->dev_ring + s, len, hipMemcpyDeviceToHost,
-                                       r->drain_stream));
-                off += len;
-                left -= len;
-            }
+            if ((st = copy_span(r, from, n)) != DMI_OK) return st;
         }
         r->drain_issued = from + n;
         if (r->drain_issued == committed) r->drain_issued_records = committed_records;
@@ -229,23 +275,28 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full)
 // Issue the copies and, if asked, wait for them.  The ring's lock is held only while the
 // bookkeeping is touched, never across the wait: the consumer polls and releases, and the
 // producer asks for room, while a copy is in flight.
-dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full)
+dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full, const ChunkRule *flush)
 {
     uint64_t mark;
+    bool noted;
     {
         std::lock_guard<std::mutex> lk(r->mu);
-        dmi_status_t st = drain_issue_locked(r, moved, host_full);
+        dmi_status_t st = drain_issue_locked(r, moved, host_full, flush);
         if (st != DMI_OK) return st;
         mark = r->drain_issued;
         if (!wait || r->direct_probe || r->drain_done.load(std::memory_order_relaxed) == mark) return DMI_OK;
+        if (flush && (flush->more || r->copy_note.groups)) return DMI_OK;       // (polled)
+        noted = r->copy_note.groups != 0;
     }
-    // everything issued up to `mark` was on the stream before this call
+    // everything issued up to `mark` was on these streams before this call
     hipError_t e = hipStreamSynchronize(r->drain_stream);
+    if (e == hipSuccess && noted) e = hipStreamSynchronize(r->ctl_stream);
     if (e != hipSuccess) return fail(DMI_ERR_HIP, "drain stream: %s", hipGetErrorString(e));
     std::lock_guard<std::mutex> lk(r->mu);
     if (r->drain_done.load(std::memory_order_relaxed) < mark) {
         r->drain_done.store(mark, std::memory_order_release);
         publish_tail(r, mark);  // the span may be reused only now that its copies have run
+        if (mark == r->drain_issued) { r->copies = false; r->copy_note.groups = 0; }
     }
     return DMI_OK;
 }
@@ -281,29 +332,32 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     if (r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) return DMI_OK;
     if (r->producer.load(std::memory_order_relaxed) != this_thread()) return DMI_OK;
     std::lock_guard<std::mutex> lk(r->mu);
-    dmi_status_t st = reap(r, false);
+    dmi_status_t st = reap(r);
     if (st != DMI_OK) return st;
     if (r->direct_probe || r->drain_done.load(std::memory_order_relaxed) != r->drain_issued) return DMI_OK;
     uint64_t target, records;
     {
         std::lock_guard<std::mutex> pk(r->pmu);
         if (!r->window_exact || !r->probes.empty() || r->next_seq.load(std::memory_order_acquire) <= r->probed_upto ||
-            read_committed(r) != r->drain_issued)
+            read_committed(r) > r->drain_issued)
             return DMI_OK;
-        target = r->drain_issued + r->window.bytes;
+        target = read_committed(r) + r->window.bytes;
         records = r->snap[0] + r->window.records;
     }
     const uint64_t from = r->drain_issued, n = target - from;
     if (n == 0 || n > kFlushKernelBytes || n > r->host_cap - (from - r->released)) return DMI_OK;
+    // what notes say, or will still say while later captures run, need not wait for those
+    const uint64_t complete = read_complete(r);
+    if (complete >= from + kLeastChunk || target >= r->unnoted_bytes + complete + kWorthNotes) return DMI_OK;
     // Not while the stream is being captured: the copy would end up in the graph.
     hipStream_t us = (hipStream_t)r->last_stream.load(std::memory_order_acquire);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (r->quiet.load(std::memory_order_acquire) || !capture_status(us, &cs) || cs != hipStreamCaptureStatusNone)
         return DMI_OK;
     atomic_max(r->dev_high, n);
-    const uint64_t groups = (n / 16u + kThreads - 1u) / kThreads;
-    const DrainNote note = {r->hdone, (uint32_t)(groups < kDrainGroups ? groups : kDrainGroups), ++r->drain_tick};
-    HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, note.groups, r->hdone_dev, note.tick, us));
+    const DrainNote note = {r->hwords + kWordsBehind, drain_groups(n), ++r->drain_tick};
+    HIP_TRY(launch_drain_kernel(r->dev_ring, r->dev_cap, r->host_ring_dev, r->host_cap, from, n, note.groups,
+                                r->hwords_dev + kWordsBehind, note.tick, us));
     // (a probe of its own, even if another thread's drain has just put one there: that one may be in front of the
     // copy; this thread is the producer, whose count of launches starts again behind it)
     const uint64_t no = probe_by_drain(r, note);
@@ -329,7 +383,7 @@ static dmi_status_t wait_for_direct(dmi_ring *r)
     for (;;) {
         {
             std::lock_guard<std::mutex> lk(r->mu);
-            dmi_status_t st = reap(r, false);
+            dmi_status_t st = reap(r);
             if (st != DMI_OK || !r->direct_probe) return st;
         }
         if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
@@ -353,6 +407,10 @@ uint64_t head_upper_bound(dmi_ring *r)
     return committed + r->inflight_sum;
 }
 
+// Bytes that the ring holds at most, of an upper bound of the head.  (The captures of a replay count in that from dmi_step_end
+// on, and by their notes may have been drained before.)
+static uint64_t held(uint64_t head_ub, uint64_t tail) { return head_ub > tail ? head_ub - tail : 0u; }
+
 // Completeness policy: wait on the host until a record of `ub` bytes is sure to fit
 // (the paper's flush before the forward step, section 4.4).  Never a device-side wait.
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub)
@@ -364,11 +422,11 @@ dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub)
         // (an older view only makes the bound more cautious)
         uint64_t head_ub = head_upper_bound(r);
         uint64_t tail = r->drain_done.load(std::memory_order_acquire);
-        if (head_ub - tail + ub <= r->dev_cap) break;
+        if (held(head_ub, tail) + ub <= r->dev_cap) break;
         if ((st = advance_commits(r, false)) != DMI_OK) return st;
         head_ub = head_upper_bound(r);
         tail = r->drain_done.load(std::memory_order_acquire);
-        if (head_ub - tail + ub <= r->dev_cap) break;
+        if (held(head_ub, tail) + ub <= r->dev_cap) break;
         if (!t0) t0 = now_ns();
         uint64_t moved = 0;
         if ((st = drain(r, true, &moved)) != DMI_OK) return st;
@@ -810,6 +868,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
         a.par_in = r->chain_par;
         a.step = nullptr;
         a.node = 0;
+        a.note = r->notes && r->unnoted_bytes >= kNoteBytes ? r->hwords_dev + kWordNote : nullptr;
         for (uint32_t i = 0; i < cnt; i++) b.src[i] = srcs[first + i];
         for (uint32_t i = 0; i < cnt + tail; i++) b.point[i] = points[first + i];
 
@@ -845,6 +904,8 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
         r->inflight_sum += bytes;
         r->unprobed_launches += 1;
         r->unprobed_bytes += bytes;
+        if (a.note) r->unnoted_bytes = 0;
+        r->unnoted_bytes += bytes;
         return DMI_OK;
     };
 
@@ -1004,7 +1065,7 @@ void bg_loop(dmi_ring *r)
             std::lock_guard<std::mutex> lk(r->mu);
             // copies issued by somebody's non-blocking dmi_drain are noted here as they finish: with
             // this thread running, nobody else looks at the drain stream
-            (void)reap(r, false);
+            (void)reap(r);
             uint64_t committed, committed_records;
             {
                 std::lock_guard<std::mutex> pk(r->pmu);
@@ -1037,8 +1098,7 @@ void free_ring(dmi_ring *r)
     if (!r) return;
     if (r->drain_stream) { (void)hipStreamSynchronize(r->drain_stream); (void)hipStreamDestroy(r->drain_stream); }
     if (r->ctl_stream) { (void)hipStreamSynchronize(r->ctl_stream); (void)hipStreamDestroy(r->ctl_stream); }
-    if (r->htail) (void)hipHostFree((void *)r->htail);
-    if (r->hdone) (void)hipHostFree(r->hdone);
+    if (r->hwords) (void)hipHostFree(r->hwords);
     for (auto &p : r->probes) if (p.ev) (void)hipEventDestroy(p.ev);
     for (auto ev : r->probe_pool) (void)hipEventDestroy(ev);
     if (r->dev_ring) (void)hipFree(r->dev_ring);
@@ -1147,16 +1207,19 @@ dmi_status_t dmi_ring_create(const dmi_ring_config_t *cfg, dmi_ring_t **out)
         delete init;
         if (e != hipSuccess) return bail(e, "hipMemcpy(ctrl)");
     }
-    if ((e = hipHostMalloc((void **)&r->htail, 64, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
-        return bail(e, "hipHostMalloc(tail word)");
-    if ((e = hipHostGetDevicePointer((void **)&r->htail_dev, (void *)r->htail, 0)) != hipSuccess)
-        return bail(e, "hipHostGetDevicePointer(tail word)");
-    *r->htail = 0;
-    if ((e = hipHostMalloc((void **)&r->hdone, kDrainGroups * 8u, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
-        return bail(e, "hipHostMalloc(drain words)");
-    if ((e = hipHostGetDevicePointer((void **)&r->hdone_dev, r->hdone, 0)) != hipSuccess)
-        return bail(e, "hipHostGetDevicePointer(drain words)");
-    memset(r->hdone, 0, kDrainGroups * 8u);
+    if ((e = hipHostMalloc((void **)&r->hwords, kWords * 8u, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
+        return bail(e, "hipHostMalloc(words)");
+    if ((e = hipHostGetDevicePointer((void **)&r->hwords_dev, r->hwords, 0)) != hipSuccess)
+        return bail(e, "hipHostGetDevicePointer(words)");
+    memset(r->hwords, 0, kWords * 8u);
+    r->htail = r->hwords + kWordTail;
+    r->htail_dev = r->hwords_dev + kWordTail;
+    // Notes, which say that what earlier launches have written can be copied while a later one runs: the release at a launch's end
+    // reaches memory, not only L2, where the compute units that the next launch may run on do not share one L2 (32 of them do).
+    int units = 0;
+    if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, r->dev)) != hipSuccess)
+        return bail(e, "hipDeviceGetAttribute");
+    r->notes = units > 32 && !(flags & DMI_BG_THREAD);
     if ((e = hipStreamCreateWithFlags(&r->drain_stream, hipStreamNonBlocking)) != hipSuccess)
         return bail(e, "hipStreamCreate");
     if ((e = hipStreamCreateWithFlags(&r->ctl_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -1425,6 +1488,17 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     if ((st = flush_behind_captures(r, &total, &direct)) != DMI_OK) return st;
     if (bytes_moved) *bytes_moved = total;
     if (!direct && (st = record_probe(r)) != DMI_OK) return st;
+    // The producer's own thread (unless the ring has a drain thread, or was asked for the copy engine by name) does not wait for
+    // all captures before it copies the first: it polls the notes that they leave, and starts a copy of what is complete as soon
+    // as that is worth one (an eighth of it all; every copy costs the link some 8 us).
+    const bool by_chunks = !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) &&
+                           r->producer.load(std::memory_order_relaxed) == this_thread();
+    ChunkRule rule = {0, true};
+    uint64_t least = 0, last_move = t0;
+    if (by_chunks) {
+        const uint64_t all = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
+        least = std::min(std::max(all / 8u, kLeastChunk), 16u * kLeastChunk);
+    }
     for (;;) {
         if ((st = advance_commits(r, false)) != DMI_OK) return st;
         // once the launches issued before the call are known to have finished, their records lie
@@ -1432,20 +1506,23 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
         // whatever a producer thread commits behind it in the meantime
         if (target == UINT64_MAX && r->confirmed.load(std::memory_order_acquire) >= want_seq)
             target = read_committed(r);
+        // (what is complete waits for more of it while there may soon be more)
+        rule.more = target == UINT64_MAX;
+        rule.least = now_ns() - last_move < kChunkPatienceNs ? least : 1u;
         uint64_t moved = 0;
         bool host_full = false;
-        if ((st = drain(r, true, &moved, &host_full)) != DMI_OK) return st;
+        if ((st = drain(r, true, &moved, &host_full, by_chunks ? &rule : nullptr)) != DMI_OK) return st;
         total += moved;
         if (bytes_moved) *bytes_moved = total;
         if (target != UINT64_MAX && r->drain_done.load(std::memory_order_acquire) >= target) return DMI_OK;
-        if (moved) continue;
+        if (moved) { last_move = now_ns(); continue; }
         if (target != UINT64_MAX && host_full)
             return fail(DMI_ERR_AGAIN, "host ring is full: release records and drain again");
         if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
             return fail(DMI_ERR_AGAIN, target == UINT64_MAX ? "observes did not finish within %u ms"
                                                             : "the drain did not finish within %u ms",
                         r->block_timeout_ms);
-        pause_since(r, t0);
+        pause_since(r, last_move);
     }
 }
 
@@ -1469,7 +1546,7 @@ dmi_status_t poll_host_impl(dmi_ring *r, dmi_record_view_t *out, uint32_t max, u
     if (!(r->cfg.flags & DMI_BG_THREAD) && !r->quiet.load(std::memory_order_acquire)) {
         // (the end of a span on the producer's stream is seen by its probe, and only there; a consumer may do nothing but poll)
         dmi_status_t st = r->direct_probe ? advance_commits(r, false) : DMI_OK;
-        if (st == DMI_OK) st = reap(r, false);
+        if (st == DMI_OK) st = reap(r);
         if (st != DMI_OK) return st;
     }
     const uint64_t done = r->drain_done.load(std::memory_order_acquire);
@@ -1571,7 +1648,7 @@ dmi_status_t dmi_ring_free_bytes(dmi_ring_t *r, uint64_t *free_bytes)
     (void)hipSetDevice(r->dev);
     dmi_status_t st = advance_commits(r, false);
     if (st != DMI_OK) return st;
-    const uint64_t used = head_upper_bound(r) - r->drain_done.load(std::memory_order_acquire);
+    const uint64_t used = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
     *free_bytes = used < r->dev_cap ? r->dev_cap - used : 0;
     return DMI_OK;
 }

@@ -139,6 +139,8 @@ struct alignas(16) CaptureKernelArgs {
     // replayable steps: seq = step->seq_base + node, step id, tail floor and policy from *step
     uint32_t node;
     const StepParams *step;
+    uint64_t *note;                 // pinned host word, or NULL: the launch puts there where it finds the head, up to which the ring
+                                    // is then complete (what a launch finds has been left by launches that are over)
 };
 
 // The host's plan of one launch: the kernel's arguments plus what only the launchers need

@@ -60,9 +60,10 @@ __device__ __forceinline__ uint64_t ld_system(const uint64_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ void st_agent(uint64_t *p, uint64_t v)
+// the same the other way: past every cache, and on its way at once
+__device__ __forceinline__ void st_system(uint64_t *p, uint64_t v)
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------- wavefront helpers
@@ -816,6 +817,7 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     //      Everything here is device memory; it becomes visible to the next launch and to the copy
     //      that fetches the slot with the kernel-end release.
     if (publisher) {
+        if (a.note) st_system(a.note, head0);
         const uint64_t last_seq = seq + gridDim.y + a.n_tail_drop - 1u;
         a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
         // (a loop of one lane over a uniform index: the points come straight out of the argument block)
@@ -1453,7 +1455,8 @@ struct DecodeArgs {
     uint32_t unit_stride;           // lane l < unit_stride takes units l, l + unit_stride, ...: all lanes of the
                                     // workgroup, or with summaries the general kernel's row_lanes (the sums are
                                     // then taken in the same order there and here)
-    uint64_t spare[6];
+    uint64_t *note;                 // where the extra workgroup says where it found the head (may be NULL)
+    uint64_t spare[5];
 };
 static_assert(sizeof(DecodeArgs) == 256, "four lines");
 constexpr uint32_t kDecDropNewest = 1u, kDecConsecutive = 2u, kDecIndexed = 4u, kDecParIn = 8u, kDecRowMap = 16u;
@@ -1641,6 +1644,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
 
     if (meta_wg) {
         if (publisher) {
+            if (a.note) st_system(a.note, head0);
             a.ctrl->tail_for[par ^ 1u] = tail_now > raw.tail_for ? tail_now : raw.tail_for;
             const uint64_t n_fit = records_that_fit(gridDim.y, head0, tail, record_bytes, a.cap, drop_newest);
             publish_launch(a.ctrl, par, head0, head_at, cnt_cap, cnt_drop, record_bytes, n_rows, n_fit, gridDim.y - n_fit, a.cap,
@@ -1764,6 +1768,8 @@ struct RowsArgs {
     CommitSlot *cslot;
     const uint64_t *tail_src;
     uint32_t node, hdr7, rank_tag, n_tail_drop;
+    uint64_t *note;
+    uint64_t spare;
 };
 static_assert(sizeof(RowsArgs) % 16u == 0, "the block behind it is read as 16-byte entries");
 constexpr uint32_t kRowsSimple = 1u;        // no keep vector, one row per request
@@ -2046,6 +2052,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
                 c->head[par ^ 1u] = head0;
                 c->head_at[par ^ 1u] = at0;
             } else {
+                if (a.note) st_system(a.note, head0);
                 const uint64_t n_fit = records_that_fit(gridDim.y, head0, tail, record_bytes, a.cap, (policy & kStepDropNewest) != 0u);
                 publish_launch(c, par, head0, at0, raw.cap, raw.drop, record_bytes, n_rows, n_fit, gridDim.y - n_fit + a.n_tail_drop,
                                a.cap, seq + gridDim.y + a.n_tail_drop - 1u, a.step ? nullptr : a.cslot);
@@ -2164,7 +2171,7 @@ __global__ void __launch_bounds__(kThreads) drain_kernel(const DrainSpans d, uin
     if (!done) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's stores have arrived
     __syncthreads();                                    // and so have the others'
-    if (threadIdx.x == 0) __hip_atomic_store(done + blockIdx.x, tick, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0) st_system(done + blockIdx.x, tick);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -2227,6 +2234,7 @@ static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid,
     d.step_id = a.step_id;
     d.cslot = a.cslot;
     d.tail_src = a.tail_src;
+    d.note = a.note;
     d.node = a.node;
     d.hdr7 = a.src_dtype | (a.out_dtype << 8) | (a.summary_mask << 16) | (a.rec_flags << 24);
     d.rank_tag = a.rank_tag;
@@ -2372,6 +2380,7 @@ static hipError_t launch_decode_any(const CaptureArgs &a, const SRC &b, hipStrea
     d.hdr7 = a.hdr[7];
     d.rank_tag = a.rank_tag;
     d.tail_src = a.tail_src;
+    d.note = a.note;
     d.keep_mask = a.keep_mask;
     if (a.keep_mask && a.n_reqs > 1024u) return hipErrorInvalidValue;
     const bool summ = a.summary_mask != 0;

@@ -157,6 +157,22 @@ struct Probe {
 
 // Largest span a flush moves with the drain kernel behind the captures (flush_behind_captures()).
 constexpr uint64_t kFlushKernelBytes = 6u << 20;
+// A launch in front of which as much has been captured since the last note leaves one (of a ring without a drain thread).
+constexpr uint64_t kNoteBytes = 512u << 10;
+// Notes still to come for as many bytes: a flush copies by them, instead of all at once behind the captures.
+constexpr uint64_t kWorthNotes = 1536u << 10;
+// Largest span that a flush moves with a drain kernel of its own when it has been captured.
+constexpr uint64_t kChunkKernelBytes = 8u << 20;
+constexpr uint64_t kLeastChunk = 1u << 20;          // (every copy costs the link some 8 us)
+// How a flush that polls wants its copies (drain_issue_locked()).
+struct ChunkRule {
+    uint64_t least;             // while captures are running, no copy of fewer bytes
+    bool more;                  // captures of the flush are running
+};
+constexpr uint64_t kChunkPatienceNs = 300000;       // how long a flush waits for that many
+// Where the words of dmi_ring::hwords lie.
+constexpr uint32_t kWordsBehind = 0, kWordsDrain = kDrainGroups, kWordNote = 2u * kDrainGroups,
+                   kWordTail = kWordNote + 16u, kWords = kWordTail + 16u;
 
 }  // namespace host
 }  // namespace dmi
@@ -173,7 +189,7 @@ struct dmi_ring {
     uint64_t host_cap = 0;
     DevCtrl *dctrl = nullptr;
     CommitSlot *hslots = nullptr, *hslots_dev = nullptr;   // pinned mirror of DevCtrl::slots
-    hipStream_t ctl_stream = nullptr;                      // statistics reads, set-up launches
+    hipStream_t ctl_stream = nullptr;                      // statistics reads, set-up launches, drain kernels of flushes
     uint8_t *mask_buf = nullptr;                           // 4 rotating keep vectors of max_reqs bytes
     uint32_t mask_rr = 0, mask_stride = 0;
     std::vector<uint8_t> mask_host[4];                     // what dmi_set_keep_mask last put into each of them
@@ -235,11 +251,17 @@ struct dmi_ring {
     // a waiting packet there slows every dispatch of the producer's queue by a microsecond or so).  A batch is known to be
     // done when the whole stream is idle; the drained-up-to mark reaches the kernels through a
     // pinned host word that they read themselves.
-    volatile uint64_t *htail = nullptr;                    // pinned, coherent
+    uint64_t *htail = nullptr;                             // in hwords
     const uint64_t *htail_dev = nullptr;                   // its device address
-    uint64_t *hdone = nullptr, *hdone_dev = nullptr;       // pinned, coherent: kDrainGroups words of the drain kernel that a
-                                                           // flush puts behind the captures (one at a time: direct_probe)
-    uint64_t drain_tick = 0;                               // how many of those there have been (under mu)
+    // Words that kernels write and the host polls (pinned, coherent): kDrainGroups of the drain kernel that a flush puts
+    // behind the captures (one at a time: direct_probe), as many of the one it starts on the drain stream (copy_note),
+    // and the note that captures leave (CaptureKernelArgs::note).  In the last line the word that goes the other way, htail.
+    uint64_t *hwords = nullptr, *hwords_dev = nullptr;
+    uint64_t drain_tick = 0;                               // how many such drain kernels there have been (under mu)
+    DrainNote copy_note;                                   // a drain kernel of a flush on ctl_stream (under mu); groups = 0: none
+    bool copies = false;                                   // the drain stream has not been seen idle since the last copy (under mu)
+    bool notes = false;                                    // whether captures leave notes
+    uint64_t unnoted_bytes = 0;                            // producer: launched since, and by, the last launch with a note
     // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over
     // once probe number `direct_probe` is.  0: none; no other copy is issued while there is one.
     uint64_t direct_probe = 0;
@@ -305,6 +327,7 @@ struct dmi_step {
     uint32_t *slab = nullptr;       // device: max_nodes table slots
     bool open = false, sealed = false, begun = false, skipped = false, drop_newest = false;
     uint64_t sum_ub = 0, sum_listed = 0, seq_base = 0;
+    uint64_t unnoted_bytes = 0;         // captured into the step since, and by, the last launch with a note
 };
 
 namespace dmi {
@@ -318,7 +341,7 @@ dmi_status_t record_probe(dmi_ring *r);
 dmi_status_t advance_commits(dmi_ring *r, bool block);
 uint64_t head_upper_bound(dmi_ring *r);
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub);
-dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full = nullptr);
+dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full = nullptr, const ChunkRule *flush = nullptr);
 dmi_status_t commit_slot_room(dmi_ring *r, uint32_t n);
 void selection_words(const dmi_req_sel_t *reqs, uint32_t n, bool paged, bool row_map, std::vector<uint32_t> &words);
 PlanEnv plan_env(const dmi_ring *r);

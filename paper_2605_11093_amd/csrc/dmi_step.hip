@@ -126,6 +126,12 @@ dmi_status_t step_add(dmi_step *st, uint32_t n, const uint32_t *points, const ui
         a.tail_src = nullptr;           // the device copy that the step's begin launch refreshes
         a.par_in = launch & 1u;         // dmi_step_begin leaves head and tail in copy 0
         a.step = st->dparams;
+        a.note = nullptr;
+        if (r->notes && st->unnoted_bytes >= kNoteBytes) {
+            a.note = r->hwords_dev + kWordNote;
+            st->unnoted_bytes = 0;
+        }
+        st->unnoted_bytes += nd.pl.ub * nb;
         a.node = first_rec;             // sequence number of the launch's first record, relative to the step's
         for (uint32_t i = 0; i < nb; i++) { b.src[i] = srcs[done + i]; b.point[i] = points[done + i]; }
         const bool decode = nd.pl.decode && batch_takes_decode_kernel(a, nb);
@@ -415,6 +421,7 @@ dmi_status_t dmi_step_end(dmi_step_t *st, void *hip_stream)
     }
     r->unprobed_launches = 0;
     r->unprobed_bytes = 0;
+    r->unnoted_bytes = 0;
     return record_probe(r);
 }
 }  // extern "C"

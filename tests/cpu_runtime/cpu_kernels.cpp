@@ -58,6 +58,7 @@ void model_capture(const CaptureArgs &a, const BatchArgs &b)
         c->tail_for[par ^ 1u] = next_tail_for;
         return;
     }
+    if (a.note) __atomic_store_n(a.note, head0, __ATOMIC_RELEASE);
     // rows kept: the listed ones, or what the keep vector leaves
     std::vector<uint32_t> kept(a.n_reqs);
     uint64_t n_rows = 0;

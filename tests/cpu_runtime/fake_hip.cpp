@@ -139,6 +139,7 @@ hipError_t hipGetLastError()
 void fake_fail_capture_queries(unsigned n) { t_failing_queries = n; }
 hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 hipError_t hipSetDevice(int dev) { return dev == 0 ? hipSuccess : hipErrorInvalidValue; }
+hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t, int) { *value = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize()
 {
     std::vector<FakeStream *> all;

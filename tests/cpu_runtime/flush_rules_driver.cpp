@@ -292,11 +292,42 @@ void other_rings_and_spans_do_not_go_behind_the_captures()
     }
 }
 
+// A launch behind enough bytes notes where it finds the head: what is in front of it is copied while the flush still waits for
+// captures behind it.
+void noted_records_do_not_wait_for_the_captures_behind_them()
+{
+    Bench b(0, 500, 64u << 20, 64u << 20);
+    constexpr uint64_t bytes = 600u << 10;
+    for (int i = 0; i < 4; i++) CHECK(observe_bytes(b, bytes) == DMI_OK);
+    b.close_gate();
+    CHECK(observe_bytes(b, bytes) == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    CHECK(b.poll() == 3);                   // (the fourth launch is the last to have started)
+    uint64_t room = 0;
+    CHECK(dmi_ring_free_bytes(b.ring, &room) == DMI_OK && room == (64u << 20) - 2 * bytes);
+    b.open_gate();
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(b.poll() == 2 && fake_drain_launches(b.stream) == 0);
+    dmi_stats_t s;
+    CHECK(dmi_get_stats(b.ring, &s) == DMI_OK && s.captured_records == 5 && s.drained_bytes == 5 * bytes);
+}
+
+// Few bytes that have been noted go with the rest, behind the captures.
+void a_small_noted_part_goes_with_the_rest()
+{
+    Bench b(0, 2000, 64u << 20, 64u << 20);
+    for (int i = 0; i < 2; i++) CHECK(observe_bytes(b, 600u << 10) == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(fake_drain_launches(b.stream) == 1 && b.poll() == 2);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"noted_records_do_not_wait_for_the_captures_behind_them", noted_records_do_not_wait_for_the_captures_behind_them},
+    {"a_small_noted_part_goes_with_the_rest", a_small_noted_part_goes_with_the_rest},
     {"waiting_drain_after_a_flush_that_gave_up", waiting_drain_after_a_flush_that_gave_up},
     {"polling_alone_sees_a_flush_that_gave_up", polling_alone_sees_a_flush_that_gave_up},
     {"captured_records_do_not_wait_for_work_behind_them", captured_records_do_not_wait_for_work_behind_them},

@@ -33,6 +33,8 @@ const char *hipGetErrorString(hipError_t e);
 hipError_t hipGetLastError();       // of the calling thread, which it clears; set here only by what is made to fail
 hipError_t hipGetDeviceCount(int *n);
 hipError_t hipSetDevice(int dev);
+enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount = 63 };
+hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t which, int dev);
 hipError_t hipDeviceSynchronize();
 hipError_t hipMalloc(void **p, size_t n);
 hipError_t hipFree(void *p);

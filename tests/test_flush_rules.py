@@ -19,7 +19,9 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "an_unanswered_capture_query_leaves_no_error",
              "spans_up_to_the_limit_go_behind_the_captures",
              "other_rings_and_spans_do_not_go_behind_the_captures",
-             "other_threads_flushes_stay_off_the_producers_stream"]
+             "other_threads_flushes_stay_off_the_producers_stream",
+             "noted_records_do_not_wait_for_the_captures_behind_them",
+             "a_small_noted_part_goes_with_the_rest"]
 
 
 @pytest.fixture(scope="module")
