@@ -1682,11 +1682,11 @@ dmi_status_t dmi_get_stats(dmi_ring_t *r, dmi_stats_t *o)
     if (!r || !o) return fail(DMI_ERR_INVALID_ARG, "NULL argument");
     memset(o, 0, sizeof *o);
     o->observed_calls = r->observed_calls;
-    o->launched_records = r->next_seq.load();
     (void)hipSetDevice(r->dev);
     (void)advance_commits(r, false);
     {
         std::lock_guard<std::mutex> lk(r->pmu);
+        o->launched_records = r->next_seq.load();       // (with the counters: what has been captured has been launched)
         o->captured_records = r->snap[0];
         o->captured_rows = r->snap[1];
         o->captured_bytes = r->snap[2];
