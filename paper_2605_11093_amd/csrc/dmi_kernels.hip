@@ -610,6 +610,30 @@ __device__ __forceinline__ constant_u32 *inline_table_uniform(uint32_t first)
 }
 static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
 
+// Entry r of such a table of n, and its first source row.
+__device__ __forceinline__ u32x4 inline_entry(const IntoArgs &b, uint32_t first, uint32_t n, uint32_t r)
+{
+    global_u32 *const w = inline_table(first);
+    if (__builtin_expect(!b.by_column, 1)) return *(__attribute__((address_space(1))) const u32x4 *)(w + 4u * r);
+    u32x4 e;
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; k++) {
+        if (b.even >> k & 1u) {
+            e[k] = b.base[k] + r * b.stride[k];
+        } else {
+            e[k] = w[at + r];
+            at += n;
+        }
+    }
+    return e;
+}
+__device__ __forceinline__ uint32_t inline_row(const IntoArgs &b, uint32_t first, uint32_t n, uint32_t r)
+{
+    if (b.even & 16u) return b.base[4] + r * b.stride[4];
+    return inline_table(first)[(b.by_column ? b.rows_at : 4u * n) + r];
+}
+
 // LOOSE: rows of at least 16 bytes that do not sit on a 16-byte grid.  They are moved in 16-byte units too,
 // a row's (or head's) last unit ending where the row does and so covering some elements a second time: those
 // are stored twice with the same value and left out of the second unit's sums.
@@ -628,14 +652,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto table_entry = [&](uint32_t r) -> uint4 {
         if constexpr (INTO)
             if (b.n_words) {
-                const u32x4 e = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(CaptureKernelArgs)) + 4u * r);
+                const u32x4 e = inline_entry(b, sizeof(CaptureKernelArgs), a.n_reqs, r);
                 return make_uint4(e.x, e.y, e.z, e.w);
             }
         return a.req_table[r];
     };
     auto row_first = [&](uint32_t r) -> uint32_t {
         if constexpr (INTO)
-            if (b.n_words) return inline_table(sizeof(CaptureKernelArgs))[4u * a.n_reqs + r];
+            if (b.n_words) return inline_row(b, sizeof(CaptureKernelArgs), a.n_reqs, r);
         return a.row0[r];
     };
     constexpr uint32_t NB_IN = ES_IN * VEC;
@@ -1448,7 +1472,8 @@ struct DecodeArgs {
     const uint4 *req_table;
     CommitSlot *cslot;
     uint64_t payload_bytes;
-    uint32_t spare1, hdr7, rank_tag, pad;
+    uint32_t rows_at;               // launches into the caller's memory: the word of their table from which on rows are listed
+    uint32_t hdr7, rank_tag, pad;
     const uint64_t *tail_src;       // where the extra workgroup reads the drained-up-to mark (may be NULL)
     // line 3
     const uint8_t *keep_mask;       // keep vector (MASK variants): request r is captured iff keep_mask[r] != 0
@@ -1513,7 +1538,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
             uint32_t at = 0;
             if constexpr (INTO) {       // the row of every request, or of every listed row behind those
                 in_args = b.n_words && !(a.flags & kDecIndexed);
-                if (in_args) at = inline_table_uniform(sizeof(DecodeArgs))[(a.flags & kDecRowMap ? 5u : 4u) * a.n_reqs + g];
+                if (in_args) at = inline_table_uniform(sizeof(DecodeArgs))[a.rows_at + g];
             }
             // (the same in every lane, and said so here: the wait for it then stays on this branch, and the common case
             // above does not wait for the control words before it loads its row)
@@ -1670,7 +1695,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
                 bool have = false;
                 if constexpr (INTO)
                     if (b.n_words) {
-                        tv = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(DecodeArgs)) + 4u * r);
+                        tv = inline_entry(b, sizeof(DecodeArgs), a.n_reqs, r);
                         have = true;
                     }
                 if (!have) {
@@ -1770,18 +1795,23 @@ struct RowsArgs {
     const uint64_t *tail_src;
     uint32_t node, hdr7, rank_tag, n_tail_drop;
     uint64_t *note;
-    uint64_t spare;
+    uint32_t rows_at;               // launches into the caller's memory: the word of their table from which on rows are listed
+    uint32_t spare;
 };
 static_assert(sizeof(RowsArgs) % 16u == 0, "the block behind it is read as 16-byte entries");
 constexpr uint32_t kRowsSimple = 1u;        // no keep vector, one row per request
 constexpr uint32_t kRowsConsecutive = 2u;   // and request i's row is row_first + i
 constexpr uint32_t kRowsDropNewest = 4u, kRowsParIn = 8u;
 
+// A table by columns has variants of its own: asked for at run time it cost the others, which run through the code around it, 0.6 % (9.3 k
+// x 4096 to fp8 20.4 -> 20.55 us, statistics of 6.4 k kept rows 18.0 -> 18.15).
+struct IntoColumns : IntoArgs {};
+
 // SUMM: 0 no summaries, 1 a wavefront per row, 2 a workgroup per row.
 template <int ES_IN, int OUT, int SUMM, typename SRC, bool LOOSE, bool ONCE>
 __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a, const SRC b)
 {
-    constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
+    constexpr bool INTO = std::is_base_of<IntoArgs, SRC>::value, BY_COLUMN = std::is_same<SRC, IntoColumns>::value;
     constexpr int VEC = 16 / ES_IN;
     constexpr uint32_t U = 4, SU = U * 64u;                 // units of a step
     constexpr uint32_t NB_IN = 16u, NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>(), ES_OUT = NB_OUT / VEC;
@@ -1828,6 +1858,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         bool have = false;
         if constexpr (INTO) {
             if (b.n_words) {
+                // (at most 64 requests: their table fits as it is)
                 entry = *(__attribute__((address_space(1))) const u32x4 *)(inline_table(sizeof(RowsArgs)) + 4u * r);
                 first_row = inline_table(sizeof(RowsArgs))[4u * n_reqs + r];
                 have = true;
@@ -1880,7 +1911,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         struct Step { uint32_t g, part; const uint8_t *base; bool ok; };
         auto listed_row = [&](uint32_t i) -> int64_t {      // a row that is listed somewhere
             if constexpr (INTO)
-                if (b.n_words && !index_mode) return (int64_t)inline_table_uniform(sizeof(RowsArgs))[4u * n_reqs + i];
+                if (b.n_words && !index_mode) return (int64_t)inline_table_uniform(sizeof(RowsArgs))[(BY_COLUMN ? a.rows_at : 4u * n_reqs) + i];
             const int32_t v = ((constant_i32 *)(index_mode ? a.row_index : reinterpret_cast<const int32_t *>(a.row0)))[i];
             return index_mode ? (int64_t)v : (int64_t)(uint32_t)v;
         };
@@ -2086,8 +2117,14 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         global_entry *table = (global_entry *)a.req_table;
         if constexpr (INTO)
             if (b.n_words) table = (global_entry *)inline_table(sizeof(RowsArgs));
+        if constexpr (BY_COLUMN) {
+            for (uint32_t r = tid; r < tab_slots; r += kThreads) {
+                const u32x4 tv = inline_entry(b, sizeof(RowsArgs), n_reqs, r < n_reqs ? r : n_reqs - 1u);
+                ring_store<u32x4>(w, 64u + 16ull * r, r < n_reqs ? tv : u32x4{0u, 0u, 0u, 0u});
+            }
+        }
         // (up to 4096 of them: four trips in flight)
-        for (uint32_t r0 = tid; r0 < tab_slots; r0 += 4u * kThreads) {
+        for (uint32_t r0 = tid; !BY_COLUMN && r0 < tab_slots; r0 += 4u * kThreads) {
             u32x4 tv[4];
 #pragma unroll
             for (uint32_t k = 0; k < 4; k++) {
@@ -2240,6 +2277,10 @@ template <int ES_IN, int OUT, int SUMM, bool LOOSE, typename SRC>
 static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     if (a.paged || (!a.simple && a.n_reqs > 64u)) return hipErrorInvalidValue;
+    if constexpr (std::is_same<SRC, IntoArgs>::value) {
+        if (b.by_column && !a.simple) return hipErrorInvalidValue;
+        if (b.by_column) return launch_rows<ES_IN, OUT, SUMM, LOOSE>(a, static_cast<const IntoColumns &>(b), grid, s);
+    }
     RowsArgs d;
     std::memset(&d, 0, sizeof d);
     d.row_stride_b = a.row_stride_b;
@@ -2268,6 +2309,7 @@ static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid,
         d.parts_magic = (uint32_t)(((1ull << (32u + d.parts_shift)) + d.parts - 1u) / d.parts);
     }
     d.row_groups = grid;
+    if constexpr (std::is_same<SRC, IntoColumns>::value) d.rows_at = b.rows_at;
     d.row_first = a.row_first;
     d.seq = a.seq;
     d.step_id = a.step_id;
@@ -2409,6 +2451,7 @@ static hipError_t launch_decode_any(const CaptureArgs &a, const SRC &b, hipStrea
     d.flags = (a.drop_newest ? kDecDropNewest : 0u) | (a.rows_consecutive ? kDecConsecutive : 0u) |
               (a.row_index ? kDecIndexed : 0u) | (a.par_in ? kDecParIn : 0u) | (a.row_map ? kDecRowMap : 0u);
     d.node = a.node;
+    if constexpr (std::is_same<SRC, IntoArgs>::value) d.rows_at = b.by_column ? b.rows_at : (a.row_map ? 5u : 4u) * a.n_reqs;
     d.summary_mask = a.summary_mask;
     d.row_elems = a.row_elems;
     d.seq = a.seq;
