@@ -610,17 +610,24 @@ __device__ __forceinline__ constant_u32 *inline_table_uniform(uint32_t first)
 }
 static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
 
-// Entry r of such a table of n, and its first source row.
-__device__ __forceinline__ u32x4 inline_entry(const IntoArgs &b, uint32_t first, uint32_t n, uint32_t r)
+// Entry r of such a table of n, and its first source row.  (What says how the table lies is read where it is, through the scalar
+// cache: the block's arrays by name would be copied out of it first.)
+__device__ __forceinline__ constant_u32 *inline_block(uint32_t first)
+{
+    return (constant_u32 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first);
+}
+__device__ __forceinline__ u32x4 inline_entry(uint32_t first, uint32_t n, uint32_t r)
 {
     global_u32 *const w = inline_table(first);
-    if (__builtin_expect(!b.by_column, 1)) return *(__attribute__((address_space(1))) const u32x4 *)(w + 4u * r);
+    constant_u32 *const b = inline_block(first);
+    if (!b[offsetof(IntoArgs, by_column) / 4u]) return *(__attribute__((address_space(1))) const u32x4 *)(w + 4u * r);
+    const uint32_t even = b[offsetof(IntoArgs, even) / 4u];
     u32x4 e;
     uint32_t at = 0;
 #pragma unroll
     for (uint32_t k = 0; k < 4u; k++) {
-        if (b.even >> k & 1u) {
-            e[k] = b.base[k] + r * b.stride[k];
+        if (even >> k & 1u) {
+            e[k] = b[offsetof(IntoArgs, base) / 4u + k] + r * b[offsetof(IntoArgs, stride) / 4u + k];
         } else {
             e[k] = w[at + r];
             at += n;
@@ -628,10 +635,12 @@ __device__ __forceinline__ u32x4 inline_entry(const IntoArgs &b, uint32_t first,
     }
     return e;
 }
-__device__ __forceinline__ uint32_t inline_row(const IntoArgs &b, uint32_t first, uint32_t n, uint32_t r)
+__device__ __forceinline__ uint32_t inline_row(uint32_t first, uint32_t n, uint32_t r)
 {
-    if (b.even & 16u) return b.base[4] + r * b.stride[4];
-    return inline_table(first)[(b.by_column ? b.rows_at : 4u * n) + r];
+    constant_u32 *const b = inline_block(first);
+    if (b[offsetof(IntoArgs, even) / 4u] & 16u)
+        return b[offsetof(IntoArgs, base) / 4u + 4u] + r * b[offsetof(IntoArgs, stride) / 4u + 4u];
+    return inline_table(first)[(b[offsetof(IntoArgs, by_column) / 4u] ? b[offsetof(IntoArgs, rows_at) / 4u] : 4u * n) + r];
 }
 
 // LOOSE: rows of at least 16 bytes that do not sit on a 16-byte grid.  They are moved in 16-byte units too,
@@ -652,14 +661,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto table_entry = [&](uint32_t r) -> uint4 {
         if constexpr (INTO)
             if (b.n_words) {
-                const u32x4 e = inline_entry(b, sizeof(CaptureKernelArgs), a.n_reqs, r);
+                const u32x4 e = inline_entry(sizeof(CaptureKernelArgs), a.n_reqs, r);
                 return make_uint4(e.x, e.y, e.z, e.w);
             }
         return a.req_table[r];
     };
     auto row_first = [&](uint32_t r) -> uint32_t {
         if constexpr (INTO)
-            if (b.n_words) return inline_row(b, sizeof(CaptureKernelArgs), a.n_reqs, r);
+            if (b.n_words) return inline_row(sizeof(CaptureKernelArgs), a.n_reqs, r);
         return a.row0[r];
     };
     constexpr uint32_t NB_IN = ES_IN * VEC;
@@ -1695,7 +1704,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
                 bool have = false;
                 if constexpr (INTO)
                     if (b.n_words) {
-                        tv = inline_entry(b, sizeof(DecodeArgs), a.n_reqs, r);
+                        tv = inline_entry(sizeof(DecodeArgs), a.n_reqs, r);
                         have = true;
                     }
                 if (!have) {
@@ -2119,7 +2128,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
             if (b.n_words) table = (global_entry *)inline_table(sizeof(RowsArgs));
         if constexpr (BY_COLUMN) {
             for (uint32_t r = tid; r < tab_slots; r += kThreads) {
-                const u32x4 tv = inline_entry(b, sizeof(RowsArgs), n_reqs, r < n_reqs ? r : n_reqs - 1u);
+                const u32x4 tv = inline_entry(sizeof(RowsArgs), n_reqs, r < n_reqs ? r : n_reqs - 1u);
                 ring_store<u32x4>(w, 64u + 16ull * r, r < n_reqs ? tv : u32x4{0u, 0u, 0u, 0u});
             }
         }
