@@ -254,7 +254,9 @@ dmi_status_t dmi_observe_paged(dmi_ring_t *ring, uint32_t point_id, const dmi_pa
  * tensor passing hook filtering on its own (a disabled point is skipped and counted), sampling
  * applied to the step, drop-newest deciding per record (the records that still fit are kept, the
  * rest of the batch is dropped and counted per point).  Under DMI_POLICY_BLOCK the batch is
- * issued in as few launches as the device ring's size allows, each waiting for its room.
+ * issued in as few launches as the device ring's size allows, each waiting for its room; or, where
+ * capture and host link both take long and the ring has no drain thread, in one more, so that a
+ * flush can copy what the first has captured while the second runs.
  * *n_done [host, optional]: how many positions of the arrays have been dealt with (captured or
  * skipped) when the call returns: n unless it fails; after DMI_ERR_AGAIN call again from there.
  * Returns DMI_OK if anything was launched, else DMI_SAMPLED_OUT or DMI_POINT_DISABLED.

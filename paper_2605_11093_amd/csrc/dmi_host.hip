@@ -512,8 +512,11 @@ dmi_status_t stage_selection(dmi_ring *r, const dmi_selection_t *sel, bool paged
 // workgroups while the rest idle (up to half the launch for 1 < items/grid < 2).
 // kResident is five workgroups per compute unit: the kernels hold from four (summaries of short rows off the 16-byte grid:
 // up to 118 vector registers) to eight (rows dealt flat: 45 to 51); they are all planned for five.  In a batch (gridDim.y = nb) each workgroup stays with one tensor.
-uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
+// `of`: the tensors that this launch and its neighbours read one after the other, if those are more (what is left of them in the
+// memory-side cache is a matter of them all).
+uint32_t plan_grid(CaptureArgs &a, uint32_t nb, uint32_t of)
 {
+    if (of < nb) of = nb;
     constexpr uint64_t kResident = 5u * 256u;
     const uint64_t listed = a.listed_rows, upr = a.units_per_row;
     // Decode-like selections (one row per request, no keep vector, dense) need no scan and no
@@ -546,15 +549,15 @@ uint32_t plan_grid(CaptureArgs &a, uint32_t nb)
     // stretch that it holds is found there, and left there, only through it (265 MB, all read: 62 + 74 / 59 + 88, cold 71 + 68 / 70 + 88; 132
     // of 265 33 + 71 / 32 + 86; statistics 22 + 73 / 26 + 86).
     constexpr uint64_t kMemorySideCache = 256ull << 20;
-    const uint64_t row_bytes = (uint64_t)a.row_elems * dtype_size(a.src_dtype), source_bytes = expected * nb * row_bytes;
-    const uint64_t stretch_bytes = a.stretch_rows ? nb * ((a.stretch_rows - 1u) * (uint64_t)a.row_stride_b + row_bytes) : 0u;
+    const uint64_t row_bytes = (uint64_t)a.row_elems * dtype_size(a.src_dtype), source_bytes = expected * of * row_bytes;
+    const uint64_t stretch_bytes = a.stretch_rows ? of * ((a.stretch_rows - 1u) * (uint64_t)a.row_stride_b + row_bytes) : 0u;
     const bool past_the_cache = source_bytes > kMemorySideCache ||
                                 (stretch_bytes > kMemorySideCache && source_bytes >= kMemorySideCache / 2u);
     // A batch's tensors have been kept for this launch and nothing reads them behind it: from half of the cache on.  (Through / past the
     // cache, cold and just written: statistics alone 134 MB 25.1 / 24.4 and 21.3 / 20.9, 200 MB 34.9 / 34.1 and 29.7 / 29.0; 256 x 8192 raw, 24 tensors
     // 37.0 / 37.0 and 31.5 / 31.5, 32 49.2 / 47.2 and 40.8 / 40.8, 40 60.5 / 57.7 and 50.4 / 49.9, 48 72.0 / 67.9 and 59.9 / 59.5; with statistics 48
     // 71.1 / 69.6 and 62.9 / 63.0; to fp8 56.9 / 56.4 and 49.2 / 49.3; 3 x 9.2 k x 4096 raw 80.6 / 79.4 and 66.7 / 67.5.)
-    const bool batch_past_the_cache = nb > 1u && source_bytes >= kMemorySideCache / 2u;
+    const bool batch_past_the_cache = of > 1u && source_bytes >= kMemorySideCache / 2u;
     a.step_per_wave = a.read_once = a.wave_rows = 0;
     // A launch of several tensors works through them one after the other (the y index of a workgroup
     // is the slow one), and does best with short-lived workgroups of about four items each: the
@@ -811,6 +814,29 @@ dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selec
     return DMI_OK;
 }
 
+// While captures run, a flush by the producer's thread copies no fewer bytes at a time than this, of as many in all.
+static uint64_t least_chunk(uint64_t all) { return std::min(std::max(all / 8u, kLeastChunk), 16u * kLeastChunk); }
+
+// Tensors of a batch's first launch where two launches reach the host sooner than one: the flush behind them copies what
+// the first has captured (the second's note says so) while the second runs.  A batch of which both the capture and the way over
+// the link take long is cut where the first part is across as the second has been captured, at the earliest where a flush takes notice.
+// That saves capture * link / (capture + link); it costs some 4 us for the launch and 8 for the copy, and has to be a sixteenth of
+// both together (of a batch that is mostly link, one launch is as well).
+// (One launch / two, delivered, us: statistics of 8 caches, 298 MB read, 4.7 MB stored, 0.4 of them first, 157 / 142 after four and 145.5 after three; more parts: three 148,
+// four 148, eight 163.  Not worth it: 80 x 256 x 8192, statistics, 0.6 MB, in two 83.2 / 85.4; 32 x 64 x 4096 raw 341.6 / 347.5; 8 caches raw, 298 MB 5390 / 5300.)
+static uint32_t first_launch(const CaptureArgs &a, uint64_t ub, uint32_t n)
+{
+    constexpr uint64_t kReadRate = 5500, kLinkRate = 57;        // bytes per ns
+    constexpr uint64_t kWorthNs = 25000;
+    const uint64_t rows = a.rows_known ? a.kept_rows : a.listed_rows, all = n * ub;
+    const uint64_t capture = n * rows * a.row_elems * dtype_size(a.src_dtype) / kReadRate, link = all / kLinkRate;      // ns
+    const uint64_t both = capture + link;
+    if (n < 2u || capture * link < std::max(kWorthNs, both / 16u) * both) return n;
+    const uint64_t part = all / 1000u * (capture * 1000u / both), least = std::max(least_chunk(all), kWorthNotes);
+    if ((n - 1u) * ub < least) return n;
+    return (uint32_t)std::min<uint64_t>((std::max(part, least) + ub - 1u) / ub, n - 1u);
+}
+
 // Issue the captures of `n` tensors of one shape that share selection and transform (n = 1: an
 // ordinary observe): as few launches as the ring and kMaxBatch allow, each of them producing
 // the records, sequence numbers and counters that single launches in the same order would.
@@ -834,6 +860,9 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
     // completeness policy they must fit the ring together (the kernels rely on it), so a batch
     // that does not is issued in pieces, each waiting for its room as single observes would
     const uint64_t fit = r->dev_cap / ub < kMaxBatch ? r->dev_cap / ub : kMaxBatch;
+    // (for a flush that copies by notes)
+    const bool by_notes = r->notes && !(r->cfg.flags & (DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL));
+    const uint32_t n_first = by_notes && mode == DMI_POLICY_BLOCK ? first_launch(a, ub, n) : n;
     uint32_t slot = 0;
     bool staged = false, host_decides = false;
     BatchArgs b;
@@ -874,7 +903,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
 
         // (only the general kernel counts a tail)
         const bool decode = !force_drop && !tail && pl.decode && batch_takes_decode_kernel(a, cnt);
-        const uint32_t grid = force_drop ? 1u : plan_grid(a, cnt);
+        const uint32_t grid = force_drop ? 1u : plan_grid(a, cnt, n_first < n ? n : cnt);
         const hipError_t e = decode ? launch_capture_decode(a, b, s) : launch_capture(a, b, grid, geo.vec16, s);
         if (e != hipSuccess) return fail(DMI_ERR_HIP, "capture launch failed: %s", hipGetErrorString(e));
         const uint64_t bytes = force_drop ? 0u : ub * cnt;      // what the launch may add to the ring
@@ -914,6 +943,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
         uint32_t n_keep = nb;
         if (mode == DMI_POLICY_BLOCK) {
             if (nb > fit) nb = (uint32_t)fit;
+            if (!done && nb > n_first) nb = n_first;
             n_keep = nb;
             if ((st = wait_for_room(r, ub * nb)) != DMI_OK) return st;
         } else {
@@ -1497,7 +1527,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     uint64_t least = 0, last_move = t0;
     if (by_chunks) {
         const uint64_t all = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
-        least = std::min(std::max(all / 8u, kLeastChunk), 16u * kLeastChunk);
+        least = least_chunk(all);
     }
     for (;;) {
         if ((st = advance_commits(r, false)) != DMI_OK) return st;

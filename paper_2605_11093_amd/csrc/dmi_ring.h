@@ -345,7 +345,7 @@ dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full = nu
 dmi_status_t commit_slot_room(dmi_ring *r, uint32_t n);
 void selection_words(const dmi_req_sel_t *reqs, uint32_t n, bool paged, bool row_map, std::vector<uint32_t> &words);
 PlanEnv plan_env(const dmi_ring *r);
-uint32_t plan_grid(CaptureArgs &a, uint32_t nb);
+uint32_t plan_grid(CaptureArgs &a, uint32_t nb, uint32_t of = 0);
 bool batch_takes_decode_kernel(const CaptureArgs &a, uint32_t nb);
 dmi_status_t check_batch_sources(uint32_t n, const void *const *data, uint32_t es, bool *all16);
 dmi_status_t plan_capture(const PlanEnv &env, uint32_t point_id, const dmi_selection_t *sel, const dmi_transform_t *xf,
