@@ -838,7 +838,7 @@ static uint32_t first_launch(const CaptureArgs &a, uint64_t ub, uint32_t n)
 }
 
 // Issue the captures of `n` tensors of one shape that share selection and transform (n = 1: an
-// ordinary observe): as few launches as the ring and kMaxBatch allow, each of them producing
+// ordinary observe): as few launches as the ring and kMaxBatch allow, or one more (first_launch()), each of them producing
 // the records, sequence numbers and counters that single launches in the same order would.
 // points / srcs list the tensors that passed the gate; *n_launched counts how many of them
 // have been issued when the call returns (all of them unless it fails).
