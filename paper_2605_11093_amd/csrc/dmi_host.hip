@@ -79,7 +79,8 @@ dmi_status_t record_probe(dmi_ring *r)
         HIP_TRY(launch_fetch_slot(&r->dctrl->slots[slot], r->hslots_dev + slot, us));
     }
     HIP_TRY(hipEventRecord(ev, us));
-    r->probes.push_back({ev, DrainNote(), launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made});
+    r->probes.push_back({ev, DrainNote(), launched, r->launches.load(std::memory_order_relaxed), fetch, r->window, ++r->probes_made, us,
+                         hipSuccess});
     r->window = Delta();
     r->window_exact = true;
     r->probed_upto = launched;
@@ -88,34 +89,58 @@ dmi_status_t record_probe(dmi_ring *r)
 
 // The same where a drain kernel that says itself when it is over has gone behind everything launched so far.  Caller
 // has seen that the host can tell what those launches add.
-static uint64_t probe_by_drain(dmi_ring *r, const DrainNote &note)
+static uint64_t probe_by_drain(dmi_ring *r, const DrainNote &note, hipStream_t us)
 {
     std::lock_guard<std::mutex> lk(r->pmu);
     const uint64_t launched = r->next_seq.load(std::memory_order_acquire);
-    r->probes.push_back({nullptr, note, launched, r->launches.load(std::memory_order_relaxed), false, r->window, ++r->probes_made});
+    r->probes.push_back({nullptr, note, launched, r->launches.load(std::memory_order_relaxed), false, r->window, ++r->probes_made, us,
+                         hipSuccess});
     r->window = Delta();
     r->probed_upto = launched;
     return r->probes_made;
+}
+
+// An event behind the drain kernel of such a probe, once a flush has polled its words for kPollNs, and so in any case before the flush
+// gives up: whoever comes upon the probe from then on can wait for it like for any other, and learns of a GPU that has failed.
+static dmi_status_t event_behind(dmi_ring *r, uint64_t no)
+{
+    std::lock_guard<std::mutex> lk(r->pmu);
+    for (Probe &p : r->probes) {
+        if (p.no != no || p.ev) continue;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (!capture_status(p.stream, &cs) || cs != hipStreamCaptureStatusNone) return DMI_OK;      // (it would end up in the graph)
+        hipEvent_t ev = nullptr;
+        p.failed = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (p.failed == hipSuccess && (p.failed = hipEventRecord(ev, p.stream)) != hipSuccess) (void)hipEventDestroy(ev);
+        if (p.failed != hipSuccess) return fail(DMI_ERR_HIP, "event behind a flush's copy: %s", hipGetErrorString(p.failed));
+        p.ev = ev;
+    }
+    return DMI_OK;
 }
 
 // Take note of finished probes: the slot of the newest launch they cover says where the
 // device head stands.  With block=true waits for the oldest outstanding probe.
 dmi_status_t advance_commits(dmi_ring *r, bool block)
 {
-    std::lock_guard<std::mutex> lk(r->pmu);
+    std::unique_lock<std::mutex> lk(r->pmu);
+    const uint64_t oldest = r->probes.empty() ? 0u : r->probes.front().no;
     while (!r->probes.empty()) {
         Probe &p = r->probes.front();
+        block = block && p.no == oldest;
         hipError_t e;
-        if (p.ev) {
+        if (p.failed != hipSuccess) {
+            e = p.failed;
+        } else if (p.note.groups && p.note.over()) {
+            e = hipSuccess;
+        } else if (p.ev) {
             e = block ? hipEventSynchronize(p.ev) : hipEventQuery(p.ev);
+        } else if (block) {         // (another thread's flush polls it, and will put an event there)
+            lk.unlock();
+            std::this_thread::yield();
+            lk.lock();
+            continue;
         } else {
-            const uint64_t t0 = now_ns();
-            while (!p.note.over() && block) {
-                if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
-                    return fail(DMI_ERR_AGAIN, "the copy of an earlier flush did not finish within %u ms", r->block_timeout_ms);
-                std::this_thread::yield();
-            }
-            e = p.note.over() ? hipSuccess : hipErrorNotReady;
+            e = hipErrorNotReady;
         }
         block = false;
         if (e == hipErrorNotReady) break;
@@ -314,7 +339,7 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
 
 // A flush whose bytes the host can tell in advance: the drain kernel moves them on the producer's
 // own stream, right behind the captures, and says itself when it is over.  Otherwise the host waits
-// for the captures' event, only then starts a copy, and waits for that.  *issued says whether this was done.
+// for the captures' event, only then starts a copy, and waits for that.  *probe: the probe that says when it is over; 0 if this was not done.
 // Measured from a capture's launch to the end of the wait, drain kernel against event and copy engine:
 // 10.0 / 23.4 us for 4 KB, 21.4 / 31.5 for 0.6 MB, 47.5 / 57.5 for 2 MB, 85 / 99.5 for 4.2 MB.  Not above 6 MiB, where the kernel's 64
 // workgroups would be on the GPU for more than 100 us to save a tenth of that.
@@ -326,9 +351,9 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
 // probe behind it already (every sixteenth launch puts one there, and the end of a replayed step) or is known to
 // be captured: those bytes need not wait for what the caller has put on the stream since, which the copy behind
 // it all would.  A launch without a probe gets one now, behind all that, so there the copy waits for nothing more.
-static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *issued)
+static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, uint64_t *probe)
 {
-    *issued = false;
+    *probe = 0;
     if (r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) return DMI_OK;
     if (r->producer.load(std::memory_order_relaxed) != this_thread()) return DMI_OK;
     std::lock_guard<std::mutex> lk(r->mu);
@@ -360,7 +385,7 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
                                 r->hwords_dev + kWordsBehind, note.tick, us));
     // (a probe of its own, even if another thread's drain has just put one there: that one may be in front of the
     // copy; this thread is the producer, whose count of launches starts again behind it)
-    const uint64_t no = probe_by_drain(r, note);
+    const uint64_t no = probe_by_drain(r, note, us);
     r->unprobed_launches = 0;
     r->unprobed_bytes = 0;
     r->direct_probe = no;
@@ -370,7 +395,7 @@ static dmi_status_t flush_behind_captures(dmi_ring *r, uint64_t *moved, bool *is
     r->drain_batches += 1;
     atomic_max(r->host_high, target - r->released);
     *moved = n;
-    *issued = true;
+    *probe = no;
     return DMI_OK;
 }
 
@@ -1513,7 +1538,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     const uint64_t want_seq = r->next_seq.load(std::memory_order_acquire);
     const uint64_t t0 = now_ns();
     uint64_t total = 0, target = UINT64_MAX;
-    bool direct = false;
+    uint64_t direct = 0;
     if ((st = advance_commits(r, false)) != DMI_OK) return st;
     if ((st = flush_behind_captures(r, &total, &direct)) != DMI_OK) return st;
     if (bytes_moved) *bytes_moved = total;
@@ -1548,7 +1573,12 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
         if (moved) { last_move = now_ns(); continue; }
         if (target != UINT64_MAX && host_full)
             return fail(DMI_ERR_AGAIN, "host ring is full: release records and drain again");
-        if (now_ns() - t0 > (uint64_t)r->block_timeout_ms * 1000000ull)
+        const uint64_t waited = now_ns() - t0;
+        if (direct && waited > kPollNs) {
+            if ((st = event_behind(r, direct)) != DMI_OK) return st;
+            direct = 0;
+        }
+        if (waited > (uint64_t)r->block_timeout_ms * 1000000ull)
             return fail(DMI_ERR_AGAIN, target == UINT64_MAX ? "observes did not finish within %u ms"
                                                             : "the drain did not finish within %u ms",
                         r->block_timeout_ms);

@@ -146,13 +146,15 @@ struct DrainNote {
 };
 
 struct Probe {
-    hipEvent_t ev;          // recorded on the producer's stream behind the launches (and the slot fetch); or NULL:
-    DrainNote note;         // a drain kernel behind the launches, which says itself when it is over
+    hipEvent_t ev;          // recorded on the producer's stream behind the launches (and the slot fetch); NULL as long as
+    DrainNote note;         // a drain kernel behind the launches, which says itself when it is over, is polled (event_behind())
     uint64_t covers;        // every launch with seq < covers was enqueued before ev
     uint64_t launches;      // how many capture launches that is
     bool fetched;           // the commit slot of launch covers-1 was copied to the host mirror
     Delta delta;            // else: what the launches since the previous probe added
     uint64_t no;            // how many probes the ring has made, this one included
+    hipStream_t stream;     // where they all went
+    hipError_t failed;      // what came back in place of an event behind the drain kernel
 };
 
 // Largest span a flush moves with the drain kernel behind the captures (flush_behind_captures()).
@@ -170,6 +172,9 @@ struct ChunkRule {
     bool more;                  // captures of the flush are running
 };
 constexpr uint64_t kChunkPatienceNs = 300000;       // how long a flush waits for that many
+// How long a flush only polls the words of a drain kernel.  They say nothing of a GPU that has failed, and what takes longer than
+// this does not take longer for a call of the runtime.
+constexpr uint64_t kPollNs = 1000000;
 // Where the words of dmi_ring::hwords lie.
 constexpr uint32_t kWordsBehind = 0, kWordsDrain = kDrainGroups, kWordNote = 2u * kDrainGroups,
                    kWordTail = kWordNote + 16u, kWords = kWordTail + 16u;

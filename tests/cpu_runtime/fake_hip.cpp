@@ -30,6 +30,7 @@ struct FakeEvent {
 namespace {
 
 std::atomic<unsigned> g_jitter_us{0};
+std::atomic<bool> g_failed{false};
 std::mutex g_reg_mu;
 std::set<FakeStream *> g_streams;
 FakeStream *g_default = nullptr;
@@ -79,10 +80,16 @@ FakeStream *resolve(hipStream_t s)
     return g_default;
 }
 
-void sync_stream(FakeStream *s)
+// (by the system's clock: ThreadSanitizer does not know the waits by the steady one)
+std::chrono::system_clock::time_point in_a_millisecond() { return std::chrono::system_clock::now() + std::chrono::milliseconds(1); }
+
+hipError_t device_error() { return g_failed.load() ? hipErrorLaunchFailure : hipSuccess; }
+
+hipError_t sync_stream(FakeStream *s)
 {
     std::unique_lock<std::mutex> lk(s->mu);
-    s->cv_idle.wait(lk, [&] { return s->q.empty() && !s->busy; });
+    while (!g_failed.load() && !s->cv_idle.wait_until(lk, in_a_millisecond(), [&] { return s->q.empty() && !s->busy; })) {}
+    return device_error();
 }
 
 }  // namespace
@@ -117,6 +124,7 @@ void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s)
     for (const FakeTask &t : graph) fake_enqueue(s, t);
 }
 
+void fake_fail_device(bool failed) { g_failed.store(failed); }
 void fake_set_jitter_us(unsigned max_us) { g_jitter_us.store(max_us); }
 
 const char *hipGetErrorString(hipError_t e)
@@ -125,6 +133,7 @@ const char *hipGetErrorString(hipError_t e)
     case hipSuccess: return "success";
     case hipErrorNotReady: return "not ready";
     case hipErrorOutOfMemory: return "out of memory";
+    case hipErrorLaunchFailure: return "launch failure";
     default: return "invalid value";
     }
 }
@@ -194,9 +203,10 @@ hipError_t hipStreamDestroy(hipStream_t s)
     delete s;
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t s) { sync_stream(resolve(s)); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { return sync_stream(resolve(s)); }
 hipError_t hipStreamQuery(hipStream_t hs)
 {
+    if (g_failed.load()) return device_error();
     FakeStream *s = resolve(hs);
     std::lock_guard<std::mutex> lk(s->mu);
     return s->q.empty() && !s->busy ? hipSuccess : hipErrorNotReady;
@@ -216,6 +226,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = new FakeEvent
 hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
+    if (g_failed.load()) return device_error();
     uint64_t gen;
     {
         std::lock_guard<std::mutex> lk(e->mu);
@@ -230,12 +241,13 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 }
 hipError_t hipEventQuery(hipEvent_t e)
 {
+    if (g_failed.load()) return device_error();
     std::lock_guard<std::mutex> lk(e->mu);
     return e->done == e->recorded ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipEventSynchronize(hipEvent_t e)
 {
     std::unique_lock<std::mutex> lk(e->mu);
-    e->cv.wait(lk, [&] { return e->done == e->recorded; });
-    return hipSuccess;
+    while (!g_failed.load() && !e->cv.wait_until(lk, in_a_millisecond(), [&] { return e->done == e->recorded; })) {}
+    return device_error();
 }

@@ -347,11 +347,56 @@ void a_batch_in_two_launches()
     }
 }
 
+// An observe that finds all commit slots taken waits for the oldest launches, also where what tells of those is the copy of a
+// flush that gave up, and however long that takes: under best effort no record goes by uncounted.
+void commit_slots_wait_for_a_flush_that_gave_up()
+{
+    Bench b(0, 20, 4 * Bench::record(), 8 * Bench::record());
+    const dmi_policy_t drop = {DMI_POLICY_DROP_NEWEST, 1, 0};
+    CHECK(dmi_set_policy(b.ring, &drop) == DMI_OK);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN);
+    std::thread later([&] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(300));
+        b.open_gate();
+    });
+    CHECK(b.observe(1200) == DMI_OK);
+    later.join();
+    CHECK(fake_drain_launches(b.stream) == 1);
+    CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    dmi_stats_t s;
+    CHECK(dmi_get_stats(b.ring, &s) == DMI_OK && s.captured_records + s.dropped_records == 1201);
+}
+
+// A GPU that fails while a flush waits for its copy behind the captures: the flush says so, and does so at once; neither it nor
+// another thread's drain behind it asks to be called again.
+void a_failing_gpu_is_not_a_flush_that_takes_long()
+{
+    Bench b(0, 10000);
+    b.close_gate();
+    CHECK(b.observe() == DMI_OK);
+    std::thread later([] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(30));
+        fake_fail_device(true);
+    });
+    const auto t0 = std::chrono::steady_clock::now();
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_HIP);
+    CHECK(fake_drain_launches(b.stream) == 1);
+    std::thread([&] { CHECK(dmi_drain(b.ring, 0, nullptr) == DMI_ERR_HIP); }).join();
+    CHECK(std::chrono::steady_clock::now() - t0 < std::chrono::seconds(5));
+    later.join();
+    fake_fail_device(false);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"commit_slots_wait_for_a_flush_that_gave_up", commit_slots_wait_for_a_flush_that_gave_up},
+    {"a_failing_gpu_is_not_a_flush_that_takes_long", a_failing_gpu_is_not_a_flush_that_takes_long},
     {"a_batch_in_two_launches", a_batch_in_two_launches},
     {"noted_records_do_not_wait_for_the_captures_behind_them", noted_records_do_not_wait_for_the_captures_behind_them},
     {"a_small_noted_part_goes_with_the_rest", a_small_noted_part_goes_with_the_rest},

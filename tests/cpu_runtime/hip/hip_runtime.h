@@ -14,7 +14,8 @@
 #include <vector>
 
 typedef int hipError_t;
-enum : int { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600 };
+enum : int { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600,
+             hipErrorLaunchFailure = 719 };
 
 struct FakeStream;
 struct FakeEvent;
@@ -69,5 +70,7 @@ void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s);
 void fake_set_jitter_us(unsigned max_us);
 // the next n capture queries of the calling thread fail (and leave their error behind)
 void fake_fail_capture_queries(unsigned n);
+// while set, what asks for the state of a stream or an event, or waits for one, returns an error
+void fake_fail_device(bool failed);
 // how many drain kernels have been launched on `s` (cpu_kernels.cpp)
 unsigned fake_drain_launches(hipStream_t s);
