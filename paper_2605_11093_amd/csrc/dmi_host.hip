@@ -310,7 +310,7 @@ dmi_status_t drain(dmi_ring *r, bool wait, uint64_t *moved, bool *host_full, con
         if (st != DMI_OK) return st;
         mark = r->drain_issued;
         if (!wait || r->direct_probe || r->drain_done.load(std::memory_order_relaxed) == mark) return DMI_OK;
-        if (flush && (flush->more || r->copy_note.groups)) return DMI_OK;       // (polled)
+        if (flush && (flush->more || (flush->poll && r->copy_note.groups))) return DMI_OK;
         noted = r->copy_note.groups != 0;
     }
     // everything issued up to `mark` was on these streams before this call
@@ -1548,7 +1548,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     // as that is worth one (an eighth of it all; every copy costs the link some 8 us).
     const bool by_chunks = !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) &&
                            r->producer.load(std::memory_order_relaxed) == this_thread();
-    ChunkRule rule = {0, true};
+    ChunkRule rule = {0, true, true};
     uint64_t least = 0, last_move = t0;
     if (by_chunks) {
         const uint64_t all = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
@@ -1563,7 +1563,10 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
             target = read_committed(r);
         // (what is complete waits for more of it while there may soon be more)
         rule.more = target == UINT64_MAX;
-        rule.least = now_ns() - last_move < kChunkPatienceNs ? least : 1u;
+        const uint64_t idle = now_ns() - last_move;
+        rule.least = idle < kChunkPatienceNs ? least : 1u;
+        // (what the last copy that the call has started still waits for is the link: no limit applies to it)
+        rule.poll = by_chunks && idle < kPollNs;
         uint64_t moved = 0;
         bool host_full = false;
         if ((st = drain(r, true, &moved, &host_full, by_chunks ? &rule : nullptr)) != DMI_OK) return st;
@@ -1578,7 +1581,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
             if ((st = event_behind(r, direct)) != DMI_OK) return st;
             direct = 0;
         }
-        if (waited > (uint64_t)r->block_timeout_ms * 1000000ull)
+        if (waited > (uint64_t)r->block_timeout_ms * 1000000ull && (target == UINT64_MAX || !rule.poll))
             return fail(DMI_ERR_AGAIN, target == UINT64_MAX ? "observes did not finish within %u ms"
                                                             : "the drain did not finish within %u ms",
                         r->block_timeout_ms);

@@ -170,6 +170,7 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
         g_drain_launches[s]++;
     }
     fake_enqueue(s, [=] {
+        fake_wait_while_held();
         for (uint64_t i = 0; i < nbytes; i += 64u)
             memcpy(host_ring + (from + i) % host_cap, ring + (from + i) % cap, 64);
         for (uint32_t g = 0; done && g < grid; g++) __atomic_store_n(done + g, tick, __ATOMIC_RELEASE);

@@ -30,7 +30,7 @@ struct FakeEvent {
 namespace {
 
 std::atomic<unsigned> g_jitter_us{0};
-std::atomic<bool> g_failed{false};
+std::atomic<bool> g_failed{false}, g_hold{false};
 std::mutex g_reg_mu;
 std::set<FakeStream *> g_streams;
 FakeStream *g_default = nullptr;
@@ -125,6 +125,11 @@ void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s)
 }
 
 void fake_fail_device(bool failed) { g_failed.store(failed); }
+void fake_hold_copies(bool hold) { g_hold.store(hold); }
+void fake_wait_while_held()
+{
+    while (g_hold.load()) std::this_thread::sleep_for(std::chrono::microseconds(20));
+}
 void fake_set_jitter_us(unsigned max_us) { g_jitter_us.store(max_us); }
 
 const char *hipGetErrorString(hipError_t e)
@@ -176,7 +181,7 @@ hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind)
 }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s)
 {
-    fake_enqueue(s, [=] { std::memcpy(dst, src, n); });
+    fake_enqueue(s, [=] { fake_wait_while_held(); std::memcpy(dst, src, n); });
     return hipSuccess;
 }
 hipError_t hipMemsetAsync(void *dst, int value, size_t n, hipStream_t s)

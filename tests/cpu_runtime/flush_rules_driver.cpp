@@ -390,11 +390,37 @@ void a_failing_gpu_is_not_a_flush_that_takes_long()
     fake_fail_device(false);
 }
 
+// A flush whose captures have ended and that has started its last copy does not give up on it, however long that takes, whichever
+// engine moves it (block_timeout_ms is for what the host ring, the observes or the caller's work hold up); a GPU that fails is told of.
+void a_flush_does_not_give_up_on_its_own_copy()
+{
+    for (const bool fails : {false, true})
+        for (const uint32_t flags : {0u, (uint32_t)DMI_DRAIN_COPY_ENGINE, (uint32_t)DMI_DRAIN_KERNEL}) {
+            Bench b(flags, fails ? 10000 : 1);
+            CHECK(b.observe(16) == DMI_OK);         // (the sixteenth puts a probe behind them)
+            CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+            fake_hold_copies(true);
+            std::thread later([&] {
+                std::this_thread::sleep_for(std::chrono::milliseconds(60));
+                if (fails) fake_fail_device(true);
+                else fake_hold_copies(false);
+            });
+            const auto t0 = std::chrono::steady_clock::now();
+            CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == (fails ? DMI_ERR_HIP : DMI_OK));
+            CHECK(std::chrono::steady_clock::now() - t0 < std::chrono::seconds(5));
+            later.join();
+            if (!fails) CHECK(b.poll() == 16);
+            fake_fail_device(false);
+            fake_hold_copies(false);
+        }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"a_flush_does_not_give_up_on_its_own_copy", a_flush_does_not_give_up_on_its_own_copy},
     {"commit_slots_wait_for_a_flush_that_gave_up", commit_slots_wait_for_a_flush_that_gave_up},
     {"a_failing_gpu_is_not_a_flush_that_takes_long", a_failing_gpu_is_not_a_flush_that_takes_long},
     {"a_batch_in_two_launches", a_batch_in_two_launches},

@@ -72,5 +72,8 @@ void fake_set_jitter_us(unsigned max_us);
 void fake_fail_capture_queries(unsigned n);
 // while set, what asks for the state of a stream or an event, or waits for one, returns an error
 void fake_fail_device(bool failed);
+// while set, asynchronous copies and drain kernels that have reached the front of their stream wait there
+void fake_hold_copies(bool hold);
+void fake_wait_while_held();
 // how many drain kernels have been launched on `s` (cpu_kernels.cpp)
 unsigned fake_drain_launches(hipStream_t s);
