@@ -249,12 +249,27 @@ static dmi_status_t copy_span_noted(dmi_ring *r, uint64_t from, uint64_t n)
     return DMI_OK;
 }
 
+// Has the producer's stream nothing on it?  (Under capture, or if the runtime will not say: taken for no; a query would end the capture.
+// Cheap where an event is the last thing on the stream, as it is when the captures are known to be over and nothing is behind them; behind
+// a kernel the runtime first puts a marker there to ask for: 28 us for a flush that asked behind its drain kernel.)
+static bool producer_is_idle(const dmi_ring *r)
+{
+    hipStream_t us = (hipStream_t)r->last_stream.load(std::memory_order_acquire);
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (r->quiet.load(std::memory_order_acquire) || !capture_status(us, &cs) || cs != hipStreamCaptureStatusNone) return false;
+    if (hipStreamQuery(us) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Issue copies for what is complete and fits the host ring.  Caller holds r->mu.
 // `flush`: for a flush by the producer's own thread, which polls.  While captures are still running, one copy at a time of at
 // least flush->least bytes, by the copy engine: a drain kernel beside them has them wait behind its stores across the link (32
-// captures of 64 x 4096 took ten times as long as long as one ran).  Behind the captures a drain kernel, which starts 5 us
-// sooner than the copy engine (from the captures' end to the host's knowing of the copy's: 4 KB 7.7 / 12.3 us, 2 MB 45.5 / 46.5, 4.2 MB
-// 83 / 88, 16.8 MB 311 / 311), also beside a copy that is under way.
+// captures of 64 x 4096 took ten times as long as long as one ran).  Behind the captures, if the producer's stream has come to its end
+// there, a drain kernel, which starts 5 us sooner than the copy engine (from the captures' end to the host's knowing of the
+// copy's: 4 KB 7.7 / 12.3 us, 2 MB 45.5 / 46.5, 4.2 MB 83 / 88, 16.8 MB 311 / 311), also beside a copy that is under way.  Where the caller's
+// next kernels run there, its workgroups wait for places among theirs: 4.2 MB with 2.4 ms of matrix
+// products behind the captures are there after 305 us by the copy engine, and by a drain kernel after 1040.
 dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, const ChunkRule *flush)
 {
     if (moved) *moved = 0;
@@ -282,7 +297,7 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, c
     if (n > batch) n = batch;
     if (n > 0) {
         const uint64_t from = r->drain_issued;
-        if (flush && !flush->more && n <= kChunkKernelBytes) {
+        if (flush && !flush->more && n <= kChunkKernelBytes && producer_is_idle(r)) {
             if ((st = copy_span_noted(r, from, n)) != DMI_OK) return st;
         } else {
             if ((st = copy_span(r, from, n)) != DMI_OK) return st;

@@ -161,6 +161,7 @@ hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStr
 
 static std::mutex g_drain_mu;
 static std::map<hipStream_t, unsigned> g_drain_launches;
+static unsigned g_all_drain_launches;
 
 hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_ring, uint64_t host_cap,
                                uint64_t from, uint64_t nbytes, uint32_t grid, uint64_t *done, uint64_t tick, hipStream_t s)
@@ -168,6 +169,7 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
     {
         std::lock_guard<std::mutex> lk(g_drain_mu);
         g_drain_launches[s]++;
+        g_all_drain_launches++;
     }
     fake_enqueue(s, [=] {
         fake_wait_while_held();
@@ -184,4 +186,10 @@ unsigned fake_drain_launches(hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(dmi::g_drain_mu);
     return dmi::g_drain_launches[s];
+}
+
+unsigned fake_all_drain_launches()
+{
+    std::lock_guard<std::mutex> lk(dmi::g_drain_mu);
+    return dmi::g_all_drain_launches;
 }

@@ -29,7 +29,7 @@ struct FakeEvent {
 
 namespace {
 
-std::atomic<unsigned> g_jitter_us{0};
+std::atomic<unsigned> g_jitter_us{0}, g_queries_under_capture{0};
 std::atomic<bool> g_failed{false}, g_hold{false};
 std::mutex g_reg_mu;
 std::set<FakeStream *> g_streams;
@@ -125,6 +125,7 @@ void fake_graph_launch(const std::vector<FakeTask> &graph, hipStream_t s)
 }
 
 void fake_fail_device(bool failed) { g_failed.store(failed); }
+unsigned fake_queries_under_capture() { return g_queries_under_capture.load(); }
 void fake_hold_copies(bool hold) { g_hold.store(hold); }
 void fake_wait_while_held()
 {
@@ -214,6 +215,7 @@ hipError_t hipStreamQuery(hipStream_t hs)
     if (g_failed.load()) return device_error();
     FakeStream *s = resolve(hs);
     std::lock_guard<std::mutex> lk(s->mu);
+    if (s->capturing) g_queries_under_capture++;
     return s->q.empty() && !s->busy ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipStreamIsCapturing(hipStream_t hs, hipStreamCaptureStatus *status)

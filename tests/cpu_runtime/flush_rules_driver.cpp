@@ -415,11 +415,52 @@ void a_flush_does_not_give_up_on_its_own_copy()
         }
 }
 
+// What a flush still has to move when the captures are over goes by a drain kernel only if the producer's stream has nothing behind
+// them: a kernel would contend with that for compute units, which the copy engine does not need.
+void the_last_copy_leaves_the_compute_units_to_work_behind_the_captures()
+{
+    for (const bool work : {false, true}) {
+        Bench b(0, 2000);
+        std::atomic<bool> go{false};
+        fake_enqueue(b.stream, [&] { while (!go.load()) std::this_thread::sleep_for(std::chrono::microseconds(20)); });
+        CHECK(b.observe(16) == DMI_OK);         // (the sixteenth puts a probe behind them)
+        if (work) b.close_gate();
+        std::thread later([&] {
+            std::this_thread::sleep_for(std::chrono::milliseconds(20));
+            go.store(true);
+        });
+        const unsigned before = fake_all_drain_launches();
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        later.join();
+        CHECK(b.poll() == 16 && fake_all_drain_launches() - before == (work ? 0u : 1u));
+    }
+}
+
+// Nor while the runtime will not say whether that stream is captured, which leaves no error, or while it is: it is not asked then.
+void a_captured_stream_is_not_asked_for_its_state()
+{
+    for (const bool unanswered : {false, true}) {
+        Bench b(0, 2000);
+        CHECK(b.observe(16) == DMI_OK);
+        CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+        const unsigned before = fake_all_drain_launches();
+        if (unanswered) fake_fail_capture_queries(1);
+        else fake_begin_capture(b.stream);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        if (!unanswered) CHECK(fake_end_capture(b.stream).empty());
+        CHECK(b.poll() == 16 && fake_all_drain_launches() == before && fake_queries_under_capture() == 0);
+        CHECK(b.observe() == DMI_OK);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
+     the_last_copy_leaves_the_compute_units_to_work_behind_the_captures},
+    {"a_captured_stream_is_not_asked_for_its_state", a_captured_stream_is_not_asked_for_its_state},
     {"a_flush_does_not_give_up_on_its_own_copy", a_flush_does_not_give_up_on_its_own_copy},
     {"commit_slots_wait_for_a_flush_that_gave_up", commit_slots_wait_for_a_flush_that_gave_up},
     {"a_failing_gpu_is_not_a_flush_that_takes_long", a_failing_gpu_is_not_a_flush_that_takes_long},

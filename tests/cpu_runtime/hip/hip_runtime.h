@@ -75,5 +75,8 @@ void fake_fail_device(bool failed);
 // while set, asynchronous copies and drain kernels that have reached the front of their stream wait there
 void fake_hold_copies(bool hold);
 void fake_wait_while_held();
+// how many times hipStreamQuery has been asked of a stream under capture (which ends the capture)
+unsigned fake_queries_under_capture();
 // how many drain kernels have been launched on `s` (cpu_kernels.cpp)
 unsigned fake_drain_launches(hipStream_t s);
+unsigned fake_all_drain_launches();      // on whatever stream

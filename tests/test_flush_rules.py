@@ -23,7 +23,9 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "noted_records_do_not_wait_for_the_captures_behind_them",
              "a_small_noted_part_goes_with_the_rest", "a_batch_in_two_launches",
              "commit_slots_wait_for_a_flush_that_gave_up", "a_failing_gpu_is_not_a_flush_that_takes_long",
-             "a_flush_does_not_give_up_on_its_own_copy"]
+             "a_flush_does_not_give_up_on_its_own_copy",
+             "the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
+             "a_captured_stream_is_not_asked_for_its_state"]
 
 
 @pytest.fixture(scope="module")
