@@ -286,8 +286,7 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, c
     const uint64_t complete = std::max(read_complete(r), committed);
     atomic_max(r->dev_high, complete - r->drain_done.load(std::memory_order_relaxed));
     const uint64_t avail = complete - r->drain_issued;
-    const bool by_kernel = (r->cfg.flags & DMI_DRAIN_KERNEL) != 0;
-    if (flush && flush->more && (r->copies || by_kernel || avail < flush->least)) return DMI_OK;
+    if (flush && flush->more && (r->copies || avail < flush->least)) return DMI_OK;
     if (flush && r->copy_note.groups) return DMI_OK;
     const uint64_t host_free = r->host_cap - (r->drain_issued - r->released);
     uint64_t n = avail < host_free ? avail : host_free;
@@ -1558,10 +1557,10 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     if ((st = flush_behind_captures(r, &total, &direct)) != DMI_OK) return st;
     if (bytes_moved) *bytes_moved = total;
     if (!direct && (st = record_probe(r)) != DMI_OK) return st;
-    // The producer's own thread (unless the ring has a drain thread, or was asked for the copy engine by name) does not wait for
+    // The producer's own thread (unless the ring has a drain thread, or was asked for one engine by name) does not wait for
     // all captures before it copies the first: it polls the notes that they leave, and starts a copy of what is complete as soon
     // as that is worth one (an eighth of it all; every copy costs the link some 8 us).
-    const bool by_chunks = !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE)) &&
+    const bool by_chunks = !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL)) &&
                            r->producer.load(std::memory_order_relaxed) == this_thread();
     ChunkRule rule = {0, true, true};
     uint64_t least = 0, last_move = t0;
