@@ -262,9 +262,10 @@ static bool producer_is_idle(const dmi_ring *r)
     return false;
 }
 
-// Issue copies for what is complete and fits the host ring.  Caller holds r->mu.
-// `flush`: for a flush by the producer's own thread, which polls.  While captures are still running, one copy at a time of at
-// least flush->least bytes, by the copy engine: a drain kernel beside them has them wait behind its stores across the link (32
+// Issue copies for what is complete and fits the host ring.  Caller holds r->mu.  Complete is what a probe has confirmed, for
+// `flush` also what a launch has noted: a flush by the producer's own thread, which polls and knows how much is still to come (other
+// drains would copy whatever a note happens to say, and every copy costs the link some 8 us).  While captures are still running, one copy
+// at a time of at least flush->least bytes, by the copy engine: a drain kernel beside them has them wait behind its stores across the link (32
 // captures of 64 x 4096 took ten times as long as long as one ran).  Behind the captures, if the producer's stream has come to its end
 // there, a drain kernel, which starts 5 us sooner than the copy engine (from the captures' end to the host's knowing of the
 // copy's: 4 KB 7.7 / 12.3 us, 2 MB 45.5 / 46.5, 4.2 MB 83 / 88, 16.8 MB 311 / 311), also beside a copy that is under way.  Where the caller's
@@ -283,7 +284,8 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, c
         committed = read_committed(r);
         committed_records = r->snap[0];
     }
-    const uint64_t complete = std::max(read_complete(r), committed);
+    // (a flush by notes that has given up may have gone further than an event has confirmed)
+    const uint64_t complete = std::max(flush ? read_complete(r) : committed, r->drain_issued);
     atomic_max(r->dev_high, complete - r->drain_done.load(std::memory_order_relaxed));
     const uint64_t avail = complete - r->drain_issued;
     if (flush && flush->more && (r->copies || avail < flush->least)) return DMI_OK;

@@ -455,11 +455,57 @@ void a_captured_stream_is_not_asked_for_its_state()
     }
 }
 
+// Notes are for a flush by the producer of a ring that may choose its engine: it knows how much is still to come and copies what is
+// worth a copy.  All other drains move what an event has confirmed, and so does the flush of a ring that was asked for one engine by name.
+void other_drains_do_not_copy_by_notes()
+{
+    constexpr uint64_t bytes = 600u << 10;
+    auto noted = [](Bench &b) {                 // three records of which only notes tell, and two behind them
+        for (int i = 0; i < 4; i++) CHECK(observe_bytes(b, bytes) == DMI_OK);
+        CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+        b.close_gate();
+        CHECK(observe_bytes(b, bytes) == DMI_OK);
+    };
+    auto rest = [](Bench &b) {
+        b.open_gate();
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(b.poll() == 5);
+    };
+    {
+        Bench b(0, 200, 64u << 20, 64u << 20);
+        noted(b);
+        uint64_t moved = 1;
+        for (const uint32_t how : {(uint32_t)DMI_DRAIN_NONBLOCK, 0u})
+            CHECK(dmi_drain(b.ring, how, &moved) == DMI_OK && moved == 0);
+        std::thread([&] { CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_ERR_AGAIN && moved == 0); }).join();
+        dmi_stats_t s;
+        CHECK(dmi_get_stats(b.ring, &s) == DMI_OK && s.drained_bytes == s.captured_bytes);
+        rest(b);
+    }
+    for (const uint32_t flags : {(uint32_t)DMI_DRAIN_COPY_ENGINE, (uint32_t)DMI_DRAIN_KERNEL}) {
+        Bench b(flags, 200, 64u << 20, 64u << 20);
+        noted(b);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN && b.poll() == 0);
+        rest(b);
+    }
+    {   // a drain behind a flush that has copied by notes and given up: nothing of that again, and then the rest
+        Bench b(0, 200, 64u << 20, 64u << 20);
+        noted(b);
+        uint64_t moved = 1;
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_ERR_AGAIN && b.poll() == 3);
+        CHECK(dmi_drain(b.ring, 0, &moved) == DMI_OK && moved == 0 && b.poll() == 0);
+        b.open_gate();
+        CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+        CHECK(dmi_drain(b.ring, 0, &moved) == DMI_OK && moved == 2 * bytes && b.poll() == 2);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"other_drains_do_not_copy_by_notes", other_drains_do_not_copy_by_notes},
     {"the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
      the_last_copy_leaves_the_compute_units_to_work_behind_the_captures},
     {"a_captured_stream_is_not_asked_for_its_state", a_captured_stream_is_not_asked_for_its_state},

@@ -25,7 +25,8 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "commit_slots_wait_for_a_flush_that_gave_up", "a_failing_gpu_is_not_a_flush_that_takes_long",
              "a_flush_does_not_give_up_on_its_own_copy",
              "the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
-             "a_captured_stream_is_not_asked_for_its_state"]
+             "a_captured_stream_is_not_asked_for_its_state",
+             "other_drains_do_not_copy_by_notes"]
 
 
 @pytest.fixture(scope="module")
