@@ -172,9 +172,12 @@ dmi_status_t advance_commits(dmi_ring *r, bool block)
 
 uint64_t read_committed(const dmi_ring *r) { return r->committed.load(std::memory_order_acquire); }
 
-// Up to where the device ring is complete: the head as the last probe has confirmed it or as a launch has noted it since.
+// Up to where the device ring is complete: the head as the last probe has confirmed it or as a launch has noted it since.  Not by
+// notes between dmi_step_begin and dmi_step_end: the captures of a replay belong to the drain, and to the counters, from the latter on.
+// Producer thread only.
 static uint64_t read_complete(const dmi_ring *r)
 {
+    if (r->step_open) return read_committed(r);
     const uint64_t noted = __atomic_load_n(r->hwords + kWordNote, __ATOMIC_ACQUIRE);
     return std::max(read_committed(r), noted);
 }
@@ -448,10 +451,6 @@ uint64_t head_upper_bound(dmi_ring *r)
     return committed + r->inflight_sum;
 }
 
-// Bytes that the ring holds at most, of an upper bound of the head.  (The captures of a replay count in that from dmi_step_end
-// on, and by their notes may have been drained before.)
-static uint64_t held(uint64_t head_ub, uint64_t tail) { return head_ub > tail ? head_ub - tail : 0u; }
-
 // Completeness policy: wait on the host until a record of `ub` bytes is sure to fit
 // (the paper's flush before the forward step, section 4.4).  Never a device-side wait.
 dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub)
@@ -463,11 +462,11 @@ dmi_status_t wait_for_room(dmi_ring *r, uint64_t ub)
         // (an older view only makes the bound more cautious)
         uint64_t head_ub = head_upper_bound(r);
         uint64_t tail = r->drain_done.load(std::memory_order_acquire);
-        if (held(head_ub, tail) + ub <= r->dev_cap) break;
+        if (head_ub - tail + ub <= r->dev_cap) break;
         if ((st = advance_commits(r, false)) != DMI_OK) return st;
         head_ub = head_upper_bound(r);
         tail = r->drain_done.load(std::memory_order_acquire);
-        if (held(head_ub, tail) + ub <= r->dev_cap) break;
+        if (head_ub - tail + ub <= r->dev_cap) break;
         if (!t0) t0 = now_ns();
         uint64_t moved = 0;
         if ((st = drain(r, true, &moved)) != DMI_OK) return st;
@@ -1567,7 +1566,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     ChunkRule rule = {0, true, true};
     uint64_t least = 0, last_move = t0;
     if (by_chunks) {
-        const uint64_t all = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
+        const uint64_t all = head_upper_bound(r) - r->drain_done.load(std::memory_order_acquire);
         least = least_chunk(all);
     }
     for (;;) {
@@ -1727,7 +1726,7 @@ dmi_status_t dmi_ring_free_bytes(dmi_ring_t *r, uint64_t *free_bytes)
     (void)hipSetDevice(r->dev);
     dmi_status_t st = advance_commits(r, false);
     if (st != DMI_OK) return st;
-    const uint64_t used = held(head_upper_bound(r), r->drain_done.load(std::memory_order_acquire));
+    const uint64_t used = head_upper_bound(r) - r->drain_done.load(std::memory_order_acquire);
     *free_bytes = used < r->dev_cap ? r->dev_cap - used : 0;
     return DMI_OK;
 }

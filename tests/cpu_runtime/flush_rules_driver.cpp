@@ -500,11 +500,46 @@ void other_drains_do_not_copy_by_notes()
     }
 }
 
+// The captures of a replayed step belong to the drain from dmi_step_end on: a flush while the step is open neither delivers what their
+// notes already say nor counts it.
+void a_flush_leaves_an_open_step_alone()
+{
+    constexpr uint64_t bytes = 600u << 10;
+    Bench b(0, 2000, 64u << 20, 64u << 20);
+    dmi_step_t *step = nullptr;
+    CHECK(dmi_step_create(b.ring, 8, &step) == DMI_OK && dmi_step_capture_begin(step) == DMI_OK);
+    fake_begin_capture(b.stream);
+    const uint32_t rows = (uint32_t)((bytes - 128u) / 64u);
+    dmi_tensor_t t = {b.data.data(), DMI_DTYPE_BF16, {rows, 32}, {32, 1}};
+    const dmi_req_sel_t all = {1, 0, 0, rows, 1};
+    const dmi_selection_t sel = {1, &all, nullptr, nullptr};
+    const dmi_transform_t raw = {DMI_DTYPE_BF16, 0};
+    for (uint32_t i = 0; i < 6; i++) CHECK(dmi_step_observe(step, i, &t, &sel, &raw, b.stream, nullptr) == DMI_OK);
+    const std::vector<FakeTask> graph = fake_end_capture(b.stream);
+    CHECK(dmi_step_seal(step) == DMI_OK);
+    for (uint64_t id = 0; id < 3; id++) {
+        CHECK(b.observe() == DMI_OK);           // (what is in front of the step is delivered)
+        CHECK(dmi_step_begin(step, id, b.stream) == DMI_OK);
+        fake_graph_launch(graph, b.stream);
+        CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+        uint64_t moved = 0;
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK && moved == Bench::record() && b.poll() == 1);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK && moved == 0 && b.poll() == 0);
+        CHECK(dmi_step_end(step, b.stream) == DMI_OK);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK && moved == 6 * bytes && b.poll() == 6);
+        dmi_stats_t s;
+        CHECK(dmi_get_stats(b.ring, &s) == DMI_OK && s.drained_bytes == s.captured_bytes);
+        CHECK(dmi_release_host(b.ring, 7 * (id + 1)) == DMI_OK);
+    }
+    CHECK(dmi_step_destroy(step) == DMI_OK);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"a_flush_leaves_an_open_step_alone", a_flush_leaves_an_open_step_alone},
     {"other_drains_do_not_copy_by_notes", other_drains_do_not_copy_by_notes},
     {"the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
      the_last_copy_leaves_the_compute_units_to_work_behind_the_captures},
