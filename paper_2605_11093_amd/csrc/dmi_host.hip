@@ -356,6 +356,12 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
     else std::this_thread::sleep_for(std::chrono::microseconds(10));
 }
 
+// Whether the flushes of this ring by its producer's thread copy by notes: not if it has a drain thread, or was asked for one engine by name.
+static bool copies_by_notes(const dmi_ring *r)
+{
+    return r->notes && !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL));
+}
+
 // A flush whose bytes the host can tell in advance: the drain kernel moves them on the producer's
 // own stream, right behind the captures, and says itself when it is over.  Otherwise the host waits
 // for the captures' event, only then starts a copy, and waits for that.  *probe: the probe that says when it is over; 0 if this was not done.
@@ -860,6 +866,8 @@ static uint64_t least_chunk(uint64_t all) { return std::min(std::max(all / 8u, k
 // Tensors of a batch's first launch where two launches reach the host sooner than one: the flush behind them copies what
 // the first has captured (the second's note says so) while the second runs.  A batch of which both the capture and the way over
 // the link take long is cut where the first part is across as the second has been captured, at the earliest where a flush takes notice.
+// (Only where the ring's last dmi_drain was such a flush, or there has been none: to a drain by another thread, which follows the events, two
+// launches are no use, and they cost a launch and the end and the start of a kernel, 10 us of 58 on the producer's stream.)
 // That saves capture * link / (capture + link); it costs some 4 us for the launch and 8 for the copy, and has to be a sixteenth of
 // both together (of a batch that is mostly link, one launch is as well).
 // (One launch / two, delivered, us: statistics of 8 caches, 298 MB read, 4.7 MB stored, 0.4 of them first, 157 / 142 after four and 145.5 after three; more parts: three 148,
@@ -900,8 +908,8 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
     // completeness policy they must fit the ring together (the kernels rely on it), so a batch
     // that does not is issued in pieces, each waiting for its room as single observes would
     const uint64_t fit = r->dev_cap / ub < kMaxBatch ? r->dev_cap / ub : kMaxBatch;
-    // (for a flush that copies by notes)
-    const bool by_notes = r->notes && !(r->cfg.flags & (DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL));
+    // (for a flush that copies by notes, if the ring is flushed like that)
+    const bool by_notes = copies_by_notes(r) && r->flushed_by_notes.load(std::memory_order_relaxed);
     const uint32_t n_first = by_notes && mode == DMI_POLICY_BLOCK ? first_launch(a, ub, n) : n;
     uint32_t slot = 0;
     bool staged = false, host_decides = false;
@@ -1537,6 +1545,9 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     (void)hipSetDevice(r->dev);
     if (bytes_moved) *bytes_moved = 0;
     const bool wait = !(flags & DMI_DRAIN_NONBLOCK);
+    const bool by_chunks = (flags & DMI_DRAIN_FLUSH) && copies_by_notes(r) &&
+                           r->producer.load(std::memory_order_relaxed) == this_thread();
+    r->flushed_by_notes.store(by_chunks, std::memory_order_relaxed);
     dmi_status_t st;
     if (!(flags & DMI_DRAIN_FLUSH)) {
         bool idle_probes;
@@ -1558,11 +1569,8 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     if ((st = flush_behind_captures(r, &total, &direct)) != DMI_OK) return st;
     if (bytes_moved) *bytes_moved = total;
     if (!direct && (st = record_probe(r)) != DMI_OK) return st;
-    // The producer's own thread (unless the ring has a drain thread, or was asked for one engine by name) does not wait for
-    // all captures before it copies the first: it polls the notes that they leave, and starts a copy of what is complete as soon
-    // as that is worth one (an eighth of it all; every copy costs the link some 8 us).
-    const bool by_chunks = !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL)) &&
-                           r->producer.load(std::memory_order_relaxed) == this_thread();
+    // The producer's own thread does not wait for all captures before it copies the first: it polls the notes that they leave, and starts
+    // a copy of what is complete as soon as that is worth one (an eighth of it all; every copy costs the link some 8 us).
     ChunkRule rule = {0, true, true};
     uint64_t least = 0, last_move = t0;
     if (by_chunks) {

@@ -267,6 +267,7 @@ struct dmi_ring {
     DrainNote copy_note;                                   // a drain kernel of a flush on ctl_stream (under mu); groups = 0: none
     bool copies = false;                                   // the drain stream has not been seen idle since the last copy (under mu)
     bool notes = false;                                    // whether captures leave notes
+    std::atomic<bool> flushed_by_notes{true};              // the last dmi_drain was a flush that copies by them (or there has been none)
     uint64_t unnoted_bytes = 0;                            // producer: launched since, and by, the last launch with a note
     // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over
     // once probe number `direct_probe` is.  0: none; no other copy is issued while there is one.

@@ -8,6 +8,7 @@
 // summarised here (this shares nothing with the oracle, and proves nothing about the kernels).
 #include "dmi_ring.h"
 
+#include <atomic>
 #include <map>
 #include <mutex>
 
@@ -114,9 +115,12 @@ void model_capture(const CaptureArgs &a, const BatchArgs &b)
 
 }  // namespace
 
+static std::atomic<unsigned> g_captures{0};
+
 hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool, hipStream_t s)
 {
     if (grid == 0 || grid > kMaxGrid || a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
+    g_captures++;
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
@@ -126,6 +130,7 @@ hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t gri
 hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s)
 {
     if (a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
+    g_captures++;
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
@@ -193,3 +198,5 @@ unsigned fake_all_drain_launches()
     std::lock_guard<std::mutex> lk(dmi::g_drain_mu);
     return dmi::g_all_drain_launches;
 }
+
+unsigned fake_capture_launches() { return dmi::g_captures.load(); }

@@ -534,11 +534,45 @@ void a_flush_leaves_an_open_step_alone()
     CHECK(dmi_step_destroy(step) == DMI_OK);
 }
 
+// The second launch is for a flush that copies by notes: not where the ring's last drain was none, or one by another thread.
+void a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes()
+{
+    constexpr uint32_t rows = 65536, width = 1024;
+    const dmi_req_sel_t all = {1, 0, 0, rows, 1};
+    const dmi_selection_t sel = {1, &all, nullptr, nullptr};
+    const dmi_transform_t sums = {DMI_DTYPE_NONE, 7};
+    const uint32_t points[8] = {0, 1, 2, 3, 4, 5, 6, 7};
+    auto launches = [&](Bench &b) {
+        const dmi_tensor_t t = {b.data.data(), DMI_DTYPE_BF16, {rows, width}, {width, 1}};
+        const void *data[8];
+        for (const void *&d : data) d = b.data.data();
+        const unsigned before = fake_capture_launches();
+        CHECK(dmi_observe_batch(b.ring, 8, points, data, &t, &sel, &sums, 0, b.stream, nullptr) == DMI_OK);
+        return fake_capture_launches() - before;
+    };
+    Bench b(0, 2000, 64u << 20, 64u << 20);
+    CHECK(launches(b) == 2);
+    std::thread([&] { CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK); }).join();
+    CHECK(launches(b) == 1);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    CHECK(launches(b) == 2);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_NONBLOCK, nullptr) == DMI_OK);
+    CHECK(launches(b) == 1);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK && b.poll() == 32);
+    for (const uint32_t flags : {(uint32_t)DMI_DRAIN_COPY_ENGINE, (uint32_t)DMI_DRAIN_KERNEL, (uint32_t)DMI_BG_THREAD}) {
+        Bench other(flags, 2000, 64u << 20, 64u << 20);
+        for (int i = 0; i < 2; i++)
+            CHECK(launches(other) == 1 && dmi_drain(other.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
+     a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes},
     {"a_flush_leaves_an_open_step_alone", a_flush_leaves_an_open_step_alone},
     {"other_drains_do_not_copy_by_notes", other_drains_do_not_copy_by_notes},
     {"the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
