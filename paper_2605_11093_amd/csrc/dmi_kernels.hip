@@ -39,7 +39,6 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 
-#include <atomic>
 #include <cstddef>
 #include <cstring>
 #include <type_traits>
@@ -2234,51 +2233,13 @@ extern "C" dmi_status_t dmi_debug_time_next_launch(void *start_event, void *stop
     return DMI_OK;
 }
 
-// A kernel's handle on each device.  A launch through it spares the runtime the way from the kernel's host symbol to the
-// device's code: eight launches with 1.7 KB of arguments take the host 23.5 us by symbol and 18.0 by handle, one with 4 KB 2.56 and 2.38.
-struct KernelHandle {
-    std::atomic<hipFunction_t> on[16];
-    // NULL where it is not to be had that way (a stream of another device than the calling thread's): launch by symbol
-    hipFunction_t get(const void *kernel, hipStream_t s)
-    {
-        int dev = -1, current = -1;
-        if ((s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-        if (dev < 0 || dev >= 16) return nullptr;
-        hipFunction_t f = on[dev].load(std::memory_order_relaxed);
-        if (f) return f;
-        if (hipGetDevice(&current) != hipSuccess || current != dev || hipGetFuncBySymbol(&f, kernel) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        on[dev].store(f, std::memory_order_relaxed);
-        return f;
-    }
-};
-
-// (args: of the kernel's own parameter types, in its order)
-template <typename... ARGS>
-static void launch(KernelHandle &h, const void *kernel, dim3 grid, dim3 block, uint32_t lds, hipStream_t s, const ARGS &...args)
-{
-    void *p[] = {const_cast<void *>(static_cast<const void *>(&args))...};
-    if (hipFunction_t f = h.get(kernel, s))
-        (void)hipModuleLaunchKernel(f, grid.x, grid.y, grid.z, block.x, block.y, block.z, lds, s, p, nullptr);
-    else
-        (void)hipLaunchKernel(kernel, grid, block, p, lds, s);
-}
-// (the errors of either are the thread's last one, which the launchers here return)
-#define DMI_LAUNCH(kernel, grid, block, lds, stream, ...)                                                             \
-    do {                                                                                                              \
-        static KernelHandle handle_;                                                                                  \
-        launch(handle_, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, __VA_ARGS__);               \
-    } while (0)
-
 #define DMI_LAUNCH_CAPTURE(in_step, kernel, grid, lds, stream, ...)                                                   \
     do {                                                                                                              \
         if (t_time_start && t_time_stop && !(in_step)) {                                                              \
             hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, stream, t_time_start, t_time_stop, 0, __VA_ARGS__); \
             t_time_start = t_time_stop = nullptr;                                                                     \
         } else {                                                                                                      \
-            DMI_LAUNCH(kernel, grid, dim3(kThreads), lds, stream, __VA_ARGS__);                                       \
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, stream, __VA_ARGS__);                                \
         }                                                                                                             \
     } while (0)
 
@@ -2501,7 +2462,7 @@ static hipError_t launch_upload_chunk(uint32_t *dst, const uint32_t *words, uint
 {
     UploadChunk<N> c;
     std::memcpy(c.w, words, n * 4u);
-    DMI_LAUNCH((upload_kernel<N>), dim3(1), dim3(kThreads), 0, s, dst, c, n);
+    hipLaunchKernelGGL((upload_kernel<N>), dim3(1), dim3(kThreads), 0, s, dst, c, n);
     return hipGetLastError();
 }
 
@@ -2519,14 +2480,14 @@ hipError_t launch_upload(uint32_t *dst, const uint32_t *words, uint32_t n_words,
 
 hipError_t launch_fetch_slot(const CommitSlot *src, CommitSlot *dst_host, hipStream_t s)
 {
-    DMI_LAUNCH(fetch_slot_kernel, dim3(1), dim3(64), 0, s, src, dst_host);
+    hipLaunchKernelGGL(fetch_slot_kernel, dim3(1), dim3(64), 0, s, src, dst_host);
     return hipGetLastError();
 }
 
 hipError_t launch_step_begin(DevCtrl *ctrl, StepParams *step, StepParams v, uint32_t par_from, uint32_t par_to,
                              const uint64_t *host_tail, hipStream_t s)
 {
-    DMI_LAUNCH(step_begin_kernel, dim3(1), dim3(64), 0, s, ctrl, step, v, par_from, par_to, host_tail);
+    hipLaunchKernelGGL(step_begin_kernel, dim3(1), dim3(64), 0, s, ctrl, step, v, par_from, par_to, host_tail);
     return hipGetLastError();
 }
 
@@ -2540,8 +2501,7 @@ hipError_t launch_drain_kernel(const uint8_t *ring, uint64_t cap, uint8_t *host_
         const uint64_t n = drain_spans(ring, cap, host_ring, host_cap, from, nbytes, d);
         from += n;
         nbytes -= n;
-        uint64_t *const words = nbytes ? nullptr : done;
-        DMI_LAUNCH(drain_kernel, dim3(grid), dim3(kThreads), 0, s, d, words, tick);
+        hipLaunchKernelGGL(drain_kernel, dim3(grid), dim3(kThreads), 0, s, d, nbytes ? nullptr : done, tick);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     } while (nbytes);
