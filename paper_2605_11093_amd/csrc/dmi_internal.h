@@ -80,20 +80,20 @@ struct BatchArgs {
 // In place of the batch block: a launch that writes one record at the start of the caller's memory
 // (dmi_observe_into).  It has no chain of launches, no control words, no policy and no counters, and its
 // request table travels here if it fits: as selection_words() lays it out, or, if only that fits, column by column without the
-// columns whose values are evenly spaced (InlineColumns).  n_words = 0: the table is in device memory, where the other arguments say.
+// columns whose values are evenly spaced (kByColumn).  n_words = 0: the table is in device memory, where the other arguments say.
 constexpr uint32_t kIntoWords = 832;        // 166 requests as they are, or fewer with a word per listed row; 416 with ids and rows
                                             // alone, 832 with ids alone.  Both argument blocks stay below 4 KiB
 constexpr uint32_t kTableColumns = 5;       // req_id, tok_start, tok_step, tok_count, first source row
+constexpr uint32_t kByColumn = 1u << 31;    // in n_words: entry r has base[k] + r * stride[k] in column k if bit k of `even` is set, and
+                                            // else the r-th word of one of the listed columns, which lie in `words` one behind the
+                                            // other (the rows from word rows_at on).  Otherwise entries as they are, first rows behind them
 struct alignas(16) IntoArgs {
     const uint8_t *src[1];
     uint32_t point[1];
     uint32_t n_words;
-    // by_column: entry r has base[k] + r * stride[k] in column k if bit k of `even` is set, and else the r-th word of one of the
-    // listed columns, which lie in `words` one behind the other (the rows from word rows_at on).  Otherwise entries as they are, first rows behind them.
-    uint32_t by_column, even, rows_at;
-    uint32_t base[kTableColumns], stride[kTableColumns];
-    uint32_t spare[3];
     uint32_t words[kIntoWords];
+    uint32_t even, rows_at;
+    uint32_t base[kTableColumns], stride[kTableColumns];
 };
 
 // A table by columns; false if its listed columns do not fit.  rows: whether first source rows are looked up at all, and
@@ -116,8 +116,7 @@ inline bool table_by_columns(const uint32_t *words, uint32_t n, TableRows rows, 
         for (uint32_t r = 0; r < n; r++) b.words[used + r] = value(k, r);
         used += n;
     }
-    b.by_column = 1u;
-    b.n_words = used ? used : 1u;
+    b.n_words = kByColumn | used;
     return true;
 }
 

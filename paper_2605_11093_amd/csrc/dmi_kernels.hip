@@ -609,17 +609,19 @@ __device__ __forceinline__ constant_u32 *inline_table_uniform(uint32_t first)
 }
 static_assert(offsetof(IntoArgs, words) % 16u == 0 && sizeof(CaptureKernelArgs) % 16u == 0, "read as 16-byte entries");
 
-// Entry r of such a table of n, and its first source row.  (What says how the table lies is read where it is, through the scalar
-// cache: the block's arrays by name would be copied out of it first.)
+// Entry r of such a table of n, and its first source row.  (Whether it lies by columns is a bit of a word that the launch's first trip to its
+// arguments has brought along, and what else says how lies behind the words, read where it is, through the scalar cache: the block's arrays by
+// name would be copied out of it first.  With a word of its own to ask for, and the words moved for it, the general kernel took 4.72 us for 64
+// short rows with statistics, and not 4.38; like this 4.38, and no kernel needs a variant for such tables.)
 __device__ __forceinline__ constant_u32 *inline_block(uint32_t first)
 {
     return (constant_u32 *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + first);
 }
-__device__ __forceinline__ u32x4 inline_entry(uint32_t first, uint32_t n, uint32_t r)
+__device__ __forceinline__ u32x4 inline_entry(uint32_t first, uint32_t n_words, uint32_t n, uint32_t r)
 {
     global_u32 *const w = inline_table(first);
+    if (!(n_words & kByColumn)) return *(__attribute__((address_space(1))) const u32x4 *)(w + 4u * r);
     constant_u32 *const b = inline_block(first);
-    if (!b[offsetof(IntoArgs, by_column) / 4u]) return *(__attribute__((address_space(1))) const u32x4 *)(w + 4u * r);
     const uint32_t even = b[offsetof(IntoArgs, even) / 4u];
     u32x4 e;
     uint32_t at = 0;
@@ -631,15 +633,17 @@ __device__ __forceinline__ u32x4 inline_entry(uint32_t first, uint32_t n, uint32
             e[k] = w[at + r];
             at += n;
         }
+        asm volatile("" : "+v"(e[k]) : : "memory");     // one after the other: all their scalar registers at once are more than there are
     }
     return e;
 }
-__device__ __forceinline__ uint32_t inline_row(uint32_t first, uint32_t n, uint32_t r)
+__device__ __forceinline__ uint32_t inline_row(uint32_t first, uint32_t n_words, uint32_t n, uint32_t r)
 {
+    if (!(n_words & kByColumn)) return inline_table(first)[4u * n + r];
     constant_u32 *const b = inline_block(first);
     if (b[offsetof(IntoArgs, even) / 4u] & 16u)
         return b[offsetof(IntoArgs, base) / 4u + 4u] + r * b[offsetof(IntoArgs, stride) / 4u + 4u];
-    return inline_table(first)[(b[offsetof(IntoArgs, by_column) / 4u] ? b[offsetof(IntoArgs, rows_at) / 4u] : 4u * n) + r];
+    return inline_table(first)[b[offsetof(IntoArgs, rows_at) / 4u] + r];
 }
 
 // LOOSE: rows of at least 16 bytes that do not sit on a 16-byte grid.  They are moved in 16-byte units too,
@@ -660,14 +664,14 @@ __global__ void __launch_bounds__(kThreads) capture_kernel(const CaptureKernelAr
     auto table_entry = [&](uint32_t r) -> uint4 {
         if constexpr (INTO)
             if (b.n_words) {
-                const u32x4 e = inline_entry(sizeof(CaptureKernelArgs), a.n_reqs, r);
+                const u32x4 e = inline_entry(sizeof(CaptureKernelArgs), b.n_words, a.n_reqs, r);
                 return make_uint4(e.x, e.y, e.z, e.w);
             }
         return a.req_table[r];
     };
     auto row_first = [&](uint32_t r) -> uint32_t {
         if constexpr (INTO)
-            if (b.n_words) return inline_row(sizeof(CaptureKernelArgs), a.n_reqs, r);
+            if (b.n_words) return inline_row(sizeof(CaptureKernelArgs), b.n_words, a.n_reqs, r);
         return a.row0[r];
     };
     constexpr uint32_t NB_IN = ES_IN * VEC;
@@ -1703,7 +1707,7 @@ __global__ void __launch_bounds__(kThreads, 8) capture_decode_kernel(const Decod
                 bool have = false;
                 if constexpr (INTO)
                     if (b.n_words) {
-                        tv = inline_entry(sizeof(DecodeArgs), a.n_reqs, r);
+                        tv = inline_entry(sizeof(DecodeArgs), b.n_words, a.n_reqs, r);
                         have = true;
                     }
                 if (!have) {
@@ -1811,15 +1815,11 @@ constexpr uint32_t kRowsSimple = 1u;        // no keep vector, one row per reque
 constexpr uint32_t kRowsConsecutive = 2u;   // and request i's row is row_first + i
 constexpr uint32_t kRowsDropNewest = 4u, kRowsParIn = 8u;
 
-// A table by columns has variants of its own: asked for at run time it cost the others, which run through the code around it, 0.6 % (9.3 k
-// x 4096 to fp8 20.4 -> 20.55 us, statistics of 6.4 k kept rows 18.0 -> 18.15).
-struct IntoColumns : IntoArgs {};
-
 // SUMM: 0 no summaries, 1 a wavefront per row, 2 a workgroup per row.
 template <int ES_IN, int OUT, int SUMM, typename SRC, bool LOOSE, bool ONCE>
 __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a, const SRC b)
 {
-    constexpr bool INTO = std::is_base_of<IntoArgs, SRC>::value, BY_COLUMN = std::is_same<SRC, IntoColumns>::value;
+    constexpr bool INTO = std::is_same<SRC, IntoArgs>::value;
     constexpr int VEC = 16 / ES_IN;
     constexpr uint32_t U = 4, SU = U * 64u;                 // units of a step
     constexpr uint32_t NB_IN = 16u, NB_OUT = out_unit_bytes<ES_IN, VEC, OUT>(), ES_OUT = NB_OUT / VEC;
@@ -1919,7 +1919,7 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         struct Step { uint32_t g, part; const uint8_t *base; bool ok; };
         auto listed_row = [&](uint32_t i) -> int64_t {      // a row that is listed somewhere
             if constexpr (INTO)
-                if (b.n_words && !index_mode) return (int64_t)inline_table_uniform(sizeof(RowsArgs))[(BY_COLUMN ? a.rows_at : 4u * n_reqs) + i];
+                if (b.n_words && !index_mode) return (int64_t)inline_table_uniform(sizeof(RowsArgs))[a.rows_at + i];
             const int32_t v = ((constant_i32 *)(index_mode ? a.row_index : reinterpret_cast<const int32_t *>(a.row0)))[i];
             return index_mode ? (int64_t)v : (int64_t)(uint32_t)v;
         };
@@ -2125,14 +2125,17 @@ __global__ void __launch_bounds__(kThreads) capture_rows_kernel(const RowsArgs a
         global_entry *table = (global_entry *)a.req_table;
         if constexpr (INTO)
             if (b.n_words) table = (global_entry *)inline_table(sizeof(RowsArgs));
-        if constexpr (BY_COLUMN) {
-            for (uint32_t r = tid; r < tab_slots; r += kThreads) {
-                const u32x4 tv = inline_entry(sizeof(RowsArgs), n_reqs, r < n_reqs ? r : n_reqs - 1u);
-                ring_store<u32x4>(w, 64u + 16ull * r, r < n_reqs ? tv : u32x4{0u, 0u, 0u, 0u});
+        uint32_t slots = tab_slots;
+        if constexpr (INTO)
+            if (b.n_words & kByColumn) {
+                for (uint32_t r = tid; r < tab_slots; r += kThreads) {
+                    const u32x4 tv = inline_entry(sizeof(RowsArgs), b.n_words, n_reqs, r < n_reqs ? r : n_reqs - 1u);
+                    ring_store<u32x4>(w, 64u + 16ull * r, r < n_reqs ? tv : u32x4{0u, 0u, 0u, 0u});
+                }
+                slots = 0;
             }
-        }
         // (up to 4096 of them: four trips in flight)
-        for (uint32_t r0 = tid; !BY_COLUMN && r0 < tab_slots; r0 += 4u * kThreads) {
+        for (uint32_t r0 = tid; r0 < slots; r0 += 4u * kThreads) {
             u32x4 tv[4];
 #pragma unroll
             for (uint32_t k = 0; k < 4; k++) {
@@ -2247,10 +2250,8 @@ template <int ES_IN, int OUT, int SUMM, bool LOOSE, typename SRC>
 static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid, hipStream_t s)
 {
     if (a.paged || (!a.simple && a.n_reqs > 64u)) return hipErrorInvalidValue;
-    if constexpr (std::is_same<SRC, IntoArgs>::value) {
-        if (b.by_column && !a.simple) return hipErrorInvalidValue;
-        if (b.by_column) return launch_rows<ES_IN, OUT, SUMM, LOOSE>(a, static_cast<const IntoColumns &>(b), grid, s);
-    }
+    if constexpr (std::is_same<SRC, IntoArgs>::value)
+        if ((b.n_words & kByColumn) && !a.simple) return hipErrorInvalidValue;
     RowsArgs d;
     std::memset(&d, 0, sizeof d);
     d.row_stride_b = a.row_stride_b;
@@ -2279,7 +2280,7 @@ static hipError_t launch_rows(const CaptureArgs &a, const SRC &b, uint32_t grid,
         d.parts_magic = (uint32_t)(((1ull << (32u + d.parts_shift)) + d.parts - 1u) / d.parts);
     }
     d.row_groups = grid;
-    if constexpr (std::is_same<SRC, IntoColumns>::value) d.rows_at = b.rows_at;
+    if constexpr (std::is_same<SRC, IntoArgs>::value) d.rows_at = b.n_words & kByColumn ? b.rows_at : 4u * a.n_reqs;
     d.row_first = a.row_first;
     d.seq = a.seq;
     d.step_id = a.step_id;
@@ -2421,7 +2422,7 @@ static hipError_t launch_decode_any(const CaptureArgs &a, const SRC &b, hipStrea
     d.flags = (a.drop_newest ? kDecDropNewest : 0u) | (a.rows_consecutive ? kDecConsecutive : 0u) |
               (a.row_index ? kDecIndexed : 0u) | (a.par_in ? kDecParIn : 0u) | (a.row_map ? kDecRowMap : 0u);
     d.node = a.node;
-    if constexpr (std::is_same<SRC, IntoArgs>::value) d.rows_at = b.by_column ? b.rows_at : (a.row_map ? 5u : 4u) * a.n_reqs;
+    if constexpr (std::is_same<SRC, IntoArgs>::value) d.rows_at = b.n_words & kByColumn ? b.rows_at : (a.row_map ? 5u : 4u) * a.n_reqs;
     d.summary_mask = a.summary_mask;
     d.row_elems = a.row_elems;
     d.seq = a.seq;

@@ -113,7 +113,6 @@ extern "C" dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *
     b.src[0] = a.src;
     b.point[0] = point_id;
     b.n_words = words.size() <= kIntoWords ? (uint32_t)words.size() : 0u;
-    b.by_column = b.even = 0;
     if (b.n_words) memcpy(b.words, words.data(), words.size() * 4u);
     // A longer one mostly does too without what is regular in it: a decode batch's is ids and rows (221 requests x 4032 to fp8 with
     // statistics: 11.8 us a call with the table staged by launches of its own, 7.1 like this).
