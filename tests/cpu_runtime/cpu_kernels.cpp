@@ -8,7 +8,6 @@
 // summarised here (this shares nothing with the oracle, and proves nothing about the kernels).
 #include "dmi_ring.h"
 
-#include <atomic>
 #include <map>
 #include <mutex>
 
@@ -115,12 +114,18 @@ void model_capture(const CaptureArgs &a, const BatchArgs &b)
 
 }  // namespace
 
-static std::atomic<unsigned> g_captures{0};
+static std::mutex g_captures_mu;
+static std::vector<unsigned> g_captures;
+static void note_capture(const CaptureArgs &a)
+{
+    std::lock_guard<std::mutex> lk(g_captures_mu);
+    g_captures.push_back(a.n_batch);
+}
 
 hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t grid, bool, hipStream_t s)
 {
     if (grid == 0 || grid > kMaxGrid || a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
-    g_captures++;
+    note_capture(a);
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
@@ -130,7 +135,7 @@ hipError_t launch_capture(const CaptureArgs &a, const BatchArgs &b, uint32_t gri
 hipError_t launch_capture_decode(const CaptureArgs &a, const BatchArgs &b, hipStream_t s)
 {
     if (a.n_batch == 0 || a.n_batch > kMaxBatch) return hipErrorInvalidValue;
-    g_captures++;
+    note_capture(a);
     const CaptureArgs ac = a;
     const BatchArgs bc = b;
     fake_enqueue(s, [ac, bc] { model_capture(ac, bc); });
@@ -199,4 +204,8 @@ unsigned fake_all_drain_launches()
     return dmi::g_all_drain_launches;
 }
 
-unsigned fake_capture_launches() { return dmi::g_captures.load(); }
+std::vector<unsigned> fake_capture_launches()
+{
+    std::lock_guard<std::mutex> lk(dmi::g_captures_mu);
+    return dmi::g_captures;
+}

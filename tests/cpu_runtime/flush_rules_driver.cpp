@@ -41,7 +41,7 @@ struct Bench {
         cfg.device_ring_bytes = dev;
         cfg.host_ring_bytes = host;
         cfg.flags = flags;
-        cfg.max_reqs_per_observe = 64;
+        cfg.max_reqs_per_observe = 128;
         cfg.block_timeout_ms = timeout_ms;
         CHECK(dmi_ring_create(&cfg, &ring) == DMI_OK);
         CHECK(hipStreamCreate(&stream) == hipSuccess);
@@ -546,9 +546,9 @@ void a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes()
         const dmi_tensor_t t = {b.data.data(), DMI_DTYPE_BF16, {rows, width}, {width, 1}};
         const void *data[8];
         for (const void *&d : data) d = b.data.data();
-        const unsigned before = fake_capture_launches();
+        const size_t before = fake_capture_launches().size();
         CHECK(dmi_observe_batch(b.ring, 8, points, data, &t, &sel, &sums, 0, b.stream, nullptr) == DMI_OK);
-        return fake_capture_launches() - before;
+        return fake_capture_launches().size() - before;
     };
     Bench b(0, 2000, 64u << 20, 64u << 20);
     CHECK(launches(b) == 2);
@@ -566,11 +566,50 @@ void a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes()
     }
 }
 
+// The batches of tests/test_gpu_batch_in_two.py do go by two launches: how many of their tensors the first captures.
+void where_the_batches_of_the_gpu_test_are_cut()
+{
+    struct Shape { uint32_t n, n_reqs, each, width, dtype, sums, paged, first; };
+    const Shape shapes[] = {{4, 32, 2048, 1024, DMI_DTYPE_FP32, 7, 0, 3},
+                            {4, 65, 3001, 128, DMI_DTYPE_BF16, 7, 0, 1},
+                            {4, 70, 930, 1024, DMI_DTYPE_FP32, 7, 0, 3},
+                            {8, 20, 4001, 256, DMI_DTYPE_BF16, 5, 1, 4}};
+    for (const Shape &q : shapes) {
+        Bench b(0, 500, 64u << 20, 64u << 20);
+        std::vector<dmi_req_sel_t> reqs(q.n_reqs);
+        for (uint32_t i = 0; i < q.n_reqs; i++) reqs[i] = {70 + i, q.paged ? i : i * q.each, 0, q.each, 1};
+        const dmi_selection_t sel = {q.n_reqs, reqs.data(), nullptr, nullptr};
+        const dmi_transform_t sums = {DMI_DTYPE_NONE, q.sums};
+        const uint32_t points[8] = {0, 1, 2, 3, 4, 5, 6, 7};
+        const int32_t table = 0;
+        const void *data[8];
+        for (const void *&d : data) d = b.data.data();
+        const size_t before = fake_capture_launches().size();
+        if (q.paged) {
+            dmi_paged_kv_t kv;
+            memset(&kv, 0, sizeof kv);
+            kv.dtype = q.dtype;
+            kv.n_blocks = q.n_reqs * 256; kv.block_size = 16; kv.n_heads = 4; kv.head_dim = 128;
+            kv.block_stride = 16 * 4 * 128; kv.slot_stride = 4 * 128; kv.head_stride = 128;
+            kv.block_table_dev = &table; kv.block_table_stride = 256; kv.n_seqs = q.n_reqs;
+            kv.n_heads_sel = 2; kv.heads_sel[0] = 1; kv.heads_sel[1] = 2;
+            kv.base = data[0];
+            CHECK(dmi_observe_paged_batch(b.ring, q.n, points, data, &kv, &sel, &sums, 0, b.stream, nullptr) == DMI_OK);
+        } else {
+            const dmi_tensor_t t = {data[0], q.dtype, {q.n_reqs * q.each, q.width}, {q.width, 1}};
+            CHECK(dmi_observe_batch(b.ring, q.n, points, data, &t, &sel, &sums, 0, b.stream, nullptr) == DMI_OK);
+        }
+        const std::vector<unsigned> launches = fake_capture_launches();
+        CHECK(launches.size() - before == 2 && launches[before] == q.first && launches[before + 1] == q.n - q.first);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"where_the_batches_of_the_gpu_test_are_cut", where_the_batches_of_the_gpu_test_are_cut},
     {"a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
      a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes},
     {"a_flush_leaves_an_open_step_alone", a_flush_leaves_an_open_step_alone},

@@ -80,4 +80,4 @@ unsigned fake_queries_under_capture();
 // how many drain kernels have been launched on `s` (cpu_kernels.cpp)
 unsigned fake_drain_launches(hipStream_t s);
 unsigned fake_all_drain_launches();      // on whatever stream
-unsigned fake_capture_launches();        // capture launches so far
+std::vector<unsigned> fake_capture_launches();      // the records of every capture launch so far

@@ -1,6 +1,7 @@
 """Batches that go by two launches so that a flush can copy what the first has captured while the second runs: the stream of
 records that the same tensors give when they are observed one by one (which other tests hold against the oracle), through several
-flushes, and a record behind the cut against the oracle's."""
+flushes, and a record behind the cut against the oracle's.  (That these batches are cut, and where, is asserted on the CPU:
+where_the_batches_of_the_gpu_test_are_cut in cpu_runtime/flush_rules_driver.cpp.)"""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +17,7 @@ DEV = "cuda:0"
 # tensors, requests, rows of each, width, source; statistics alone
 CASES = [(4, 32, 2048, 1024, torch.float32, 7),     # capture_rows_kernel; three tensors, then one
          (4, 65, 3001, 128, torch.bfloat16, 7),     # the general kernel, short rows; one tensor, then three
-         (4, 70, 930, 1024, torch.float32, 7)]      # the general kernel, longer ones
+         (4, 70, 930, 1024, torch.float32, 7)]      # the general kernel, longer ones; three, then one
 
 
 @pytest.mark.parametrize("n,n_reqs,each,width,dtype,sums", CASES)
