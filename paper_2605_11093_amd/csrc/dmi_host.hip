@@ -136,7 +136,7 @@ dmi_status_t advance_commits(dmi_ring *r, bool block)
             e = block ? hipEventSynchronize(p.ev) : hipEventQuery(p.ev);
         } else if (block) {         // (another thread's flush polls it, and will put an event there)
             lk.unlock();
-            std::this_thread::yield();
+            std::this_thread::sleep_for(std::chrono::microseconds(10));
             lk.lock();
             continue;
         } else {
