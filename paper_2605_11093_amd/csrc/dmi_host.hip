@@ -356,12 +356,6 @@ static void pause_since(const dmi_ring *r, uint64_t t0)
     else std::this_thread::sleep_for(std::chrono::microseconds(10));
 }
 
-// Whether the flushes of this ring by its producer's thread copy by notes: not if it has a drain thread, or was asked for one engine by name.
-static bool copies_by_notes(const dmi_ring *r)
-{
-    return r->notes && !(r->cfg.flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL));
-}
-
 // A flush whose bytes the host can tell in advance: the drain kernel moves them on the producer's
 // own stream, right behind the captures, and says itself when it is over.  Otherwise the host waits
 // for the captures' event, only then starts a copy, and waits for that.  *probe: the probe that says when it is over; 0 if this was not done.
@@ -909,7 +903,7 @@ dmi_status_t observe_common(dmi_ring *r, uint32_t n, const uint32_t *points, con
     // that does not is issued in pieces, each waiting for its room as single observes would
     const uint64_t fit = r->dev_cap / ub < kMaxBatch ? r->dev_cap / ub : kMaxBatch;
     // (for a flush that copies by notes, if the ring is flushed like that)
-    const bool by_notes = copies_by_notes(r) && r->flushed_by_notes.load(std::memory_order_relaxed);
+    const bool by_notes = r->notes && r->flushed_by_notes.load(std::memory_order_relaxed);
     const uint32_t n_first = by_notes && mode == DMI_POLICY_BLOCK ? first_launch(a, ub, n) : n;
     uint32_t slot = 0;
     bool staged = false, host_decides = false;
@@ -1297,7 +1291,8 @@ dmi_status_t dmi_ring_create(const dmi_ring_config_t *cfg, dmi_ring_t **out)
     int units = 0;
     if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, r->dev)) != hipSuccess)
         return bail(e, "hipDeviceGetAttribute");
-    r->notes = units > 32 && !(flags & DMI_BG_THREAD);
+    // And they are for rings that choose their engine, and whose copies nobody but a flush starts.
+    r->notes = units > 32 && !(flags & (DMI_BG_THREAD | DMI_DRAIN_COPY_ENGINE | DMI_DRAIN_KERNEL));
     if ((e = hipStreamCreateWithFlags(&r->drain_stream, hipStreamNonBlocking)) != hipSuccess)
         return bail(e, "hipStreamCreate");
     if ((e = hipStreamCreateWithFlags(&r->ctl_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -1545,7 +1540,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     (void)hipSetDevice(r->dev);
     if (bytes_moved) *bytes_moved = 0;
     const bool wait = !(flags & DMI_DRAIN_NONBLOCK);
-    const bool by_chunks = (flags & DMI_DRAIN_FLUSH) && copies_by_notes(r) &&
+    const bool by_chunks = (flags & DMI_DRAIN_FLUSH) && r->notes &&
                            r->producer.load(std::memory_order_relaxed) == this_thread();
     r->flushed_by_notes.store(by_chunks, std::memory_order_relaxed);
     dmi_status_t st;

@@ -159,7 +159,7 @@ struct Probe {
 
 // Largest span a flush moves with the drain kernel behind the captures (flush_behind_captures()).
 constexpr uint64_t kFlushKernelBytes = 6u << 20;
-// A launch in front of which as much has been captured since the last note leaves one (of a ring without a drain thread).
+// A launch in front of which as much has been captured since the last note leaves one (dmi_ring::notes).
 constexpr uint64_t kNoteBytes = 512u << 10;
 // Notes still to come for as many bytes: a flush copies by them, instead of all at once behind the captures.
 constexpr uint64_t kWorthNotes = 1536u << 10;
@@ -266,7 +266,7 @@ struct dmi_ring {
     uint64_t drain_tick = 0;                               // how many such drain kernels there have been (under mu)
     DrainNote copy_note;                                   // a drain kernel of a flush on ctl_stream (under mu); groups = 0: none
     bool copies = false;                                   // the drain stream has not been seen idle since the last copy (under mu)
-    bool notes = false;                                    // whether captures leave notes
+    bool notes = false;                                    // whether captures leave notes, and flushes by the producer's thread go by them
     std::atomic<bool> flushed_by_notes{true};              // the last dmi_drain was a flush that copies by them (or there has been none)
     uint64_t unnoted_bytes = 0;                            // producer: launched since, and by, the last launch with a note
     // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over

@@ -604,11 +604,24 @@ void where_the_batches_of_the_gpu_test_are_cut()
     }
 }
 
+// A ring that was asked for one engine by name leaves no notes, and the rules that go by them do not keep its flush from copying behind
+// the captures.
+void a_ring_that_drains_by_kernel_copies_behind_the_captures()
+{
+    Bench b(DMI_DRAIN_KERNEL, 2000, 64u << 20, 64u << 20);
+    for (unsigned k = 1; k <= 3; k++) {
+        for (int i = 0; i < 8; i++) CHECK(observe_bytes(b, 600u << 10) == DMI_OK);
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK);
+        CHECK(fake_drain_launches(b.stream) == k && b.poll() == 8);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"a_ring_that_drains_by_kernel_copies_behind_the_captures", a_ring_that_drains_by_kernel_copies_behind_the_captures},
     {"where_the_batches_of_the_gpu_test_are_cut", where_the_batches_of_the_gpu_test_are_cut},
     {"a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
      a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes},
