@@ -86,7 +86,7 @@ enum {
 /* dmi_drain flags */
 enum {
     DMI_DRAIN_NONBLOCK = 1,     /* issue the copies and return without waiting for them */
-    DMI_DRAIN_FLUSH = 2         /* first wait until every observe issued so far has committed */
+    DMI_DRAIN_FLUSH = 2         /* also wait until every observe issued so far has committed, and move its records */
 };
 
 #define DMI_MAGIC 0x32494D44u
@@ -297,9 +297,13 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
                               uint64_t seq, uint64_t step_id, uint32_t rank_tag, void *out /*[device]*/,
                               uint64_t out_bytes, uint64_t *record_bytes /*[host]*/, void *hip_stream);
 
-/* Move committed bytes from the device ring to the host ring (section 4.3, drain
- * stage).  Copies what is committed and fits the host ring's free space, then
- * lets the device reuse the drained span.  *bytes_moved [host, optional] = bytes
+/* Move captured bytes from the device ring to the host ring (section 4.3, drain
+ * stage).  Copies what is known to be captured and fits the host ring's free space, then
+ * lets the device reuse the drained span.  Known to be captured is what lies in front of an event of the
+ * library's that has been reached (every sixteenth launch puts one behind it, dmi_step_end does, and a drain that
+ * finds none outstanding), and, for a flush by the thread that observes, also what a later launch has found complete when it
+ * started: on a ring without a drain thread, created with neither DMI_DRAIN_COPY_ENGINE nor DMI_DRAIN_KERNEL, and
+ * not between dmi_step_begin and dmi_step_end.  *bytes_moved [host, optional] = bytes
  * whose copy this call issued.  With DMI_DRAIN_FLUSH: DMI_OK means that every record of
  * every observe issued before the call has arrived in the host ring and can be polled,
  * whoever issued its copy (this call or the library's drain thread); DMI_ERR_AGAIN if
@@ -307,10 +311,12 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
  * or the observes did not commit within block_timeout_ms.  A drain without DMI_DRAIN_FLUSH and
  * DMI_DRAIN_NONBLOCK returns once the copies issued so far have ended, DMI_ERR_AGAIN if one that a
  * flush which gave up had left behind the captures did not within block_timeout_ms.
- * A flush of at most 6 MiB by the thread that observes, on a ring without a drain thread and not created with
- * DMI_DRAIN_COPY_ENGINE, does its copy on the stream last passed to dmi_observe, behind the captures, unless
- * some of the records are captured already or have an event of the library's behind them; a flush by another
- * thread never does. */
+ * Where a flush by the thread that observes copies, on a ring without a drain thread and not created with
+ * DMI_DRAIN_COPY_ENGINE: at most 6 MiB by a copy kernel on the stream last passed to dmi_observe, behind the captures, unless
+ * some of the records have an event of the library's behind them or are captured already, or 1 MiB or more is or will be known to
+ * be captured while later captures run.  Then with the copy engine, what is captured while later captures run and the rest behind
+ * them; up to 8 MiB of that rest by a copy kernel on a stream of the library's if that stream has come to its end.  A
+ * flush by another thread puts no copy on the stream of the observes. */
 dmi_status_t dmi_drain(dmi_ring_t *ring, uint32_t flags, uint64_t *bytes_moved);
 
 /* A whole record in the host ring: [p0, p0+n0) then, iff it straddles the end of
@@ -513,7 +519,8 @@ typedef struct {
     uint64_t captured_records, captured_rows, captured_bytes;   /* committed on the device */
     uint64_t dropped_records, dropped_rows, dropped_bytes;      /* discarded by drop-newest */
     uint64_t sampled_out_calls, sampled_out_rows, disabled_calls;
-    uint64_t drained_bytes, released_bytes, drain_batches;
+    uint64_t drained_bytes, released_bytes, drain_batches;      /* drained: copies issued; may be ahead of
+                                   captured_bytes until a flush has returned DMI_OK */
     uint64_t block_wait_ns;
     uint64_t dev_ring_high_water, host_ring_high_water;
     uint64_t bad_rows;          /* rows whose row_index_dev / block-table entry left the source:

@@ -862,10 +862,14 @@ static uint64_t least_chunk(uint64_t all) { return std::min(std::max(all / 8u, k
 // the link take long is cut where the first part is across as the second has been captured, at the earliest where a flush takes notice.
 // (Only where the ring's last dmi_drain was such a flush, or there has been none: to a drain by another thread, which follows the events, two
 // launches are no use, and they cost a launch and the end and the start of a kernel, 10 us of 58 on the producer's stream.)
-// That saves capture * link / (capture + link); it costs some 4 us for the launch and 8 for the copy, and has to be a sixteenth of
-// both together (of a batch that is mostly link, one launch is as well).
-// (One launch / two, delivered, us: statistics of 8 caches, 298 MB read, 4.7 MB stored, 0.4 of them first, 157 / 142 after four and 145.5 after three; more parts: three 148,
-// four 148, eight 163.  Not worth it: 80 x 256 x 8192, statistics, 0.6 MB, in two 83.2 / 85.4; 32 x 64 x 4096 raw 341.6 / 347.5; 8 caches raw, 298 MB 5390 / 5300.)
+// That saves capture * link / (capture + link) at best; it costs the launch, and the end and the start of a kernel, and has to be worth 25 us and
+// a sixteenth of both together.
+// (Saved at best, then one launch / two, delivered, with the tensors in front in brackets, us.  Worth it: 8 caches, 298 MB, norm and largest magnitude
+// 33, 155 / 138 (3: 142, 4: 138, 5: 146, 6: 156; in launches of four, three, two, one each 138, 142, 144, 154); 16 such caches 65, 305 / 243; 8 of 514 MB,
+// three statistics 65, 339 / 284.  Not worth 25 us: 8 caches, 298 MB, norms alone 23, 112 / 114 (6) to 121 (2); 4 caches, 149 MB 16, 88 / 92 (3) to 94 (2);
+// 32 x 256 x 4096 raw 12, 1247 / 1231 (8) to 1240 (24), to fp8 644 / 642 (8) to 649 (24); 80 x 256 x 8192, statistics 9, 79 / 82 (40); 32 x 64 x 4096 raw 3,
+// 336 / 334 (24) to 343 (16).  Not a sixteenth: 8 caches raw, 298 MB 53, 5364 / 5302 (2) to 5341 (6), in eight launches 5290: what is
+// to be had of a flush that is nearly all link is 1 %.)
 static uint32_t first_launch(const CaptureArgs &a, uint64_t ub, uint32_t n)
 {
     constexpr uint64_t kReadRate = 5500, kLinkRate = 57;        // bytes per ns

@@ -260,7 +260,7 @@ struct dmi_ring {
     uint64_t *htail = nullptr;                             // in hwords
     const uint64_t *htail_dev = nullptr;                   // its device address
     // Words that kernels write and the host polls (pinned, coherent): kDrainGroups of the drain kernel that a flush puts
-    // behind the captures (one at a time: direct_probe), as many of the one it starts on the drain stream (copy_note),
+    // behind the captures (one at a time: direct_probe), as many of the one it starts on ctl_stream (copy_note),
     // and the note that captures leave (CaptureKernelArgs::note).  In the last line the word that goes the other way, htail.
     uint64_t *hwords = nullptr, *hwords_dev = nullptr;
     uint64_t drain_tick = 0;                               // how many such drain kernels there have been (under mu)
@@ -268,7 +268,8 @@ struct dmi_ring {
     bool copies = false;                                   // the drain stream has not been seen idle since the last copy (under mu)
     bool notes = false;                                    // whether captures leave notes, and flushes by the producer's thread go by them
     std::atomic<bool> flushed_by_notes{true};              // the last dmi_drain was a flush that copies by them (or there has been none)
-    uint64_t unnoted_bytes = 0;                            // producer: launched since, and by, the last launch with a note
+    // producer: launched since the last launch with a note, and by it; or since the last dmi_step_end, which puts a probe behind its step
+    uint64_t unnoted_bytes = 0;
     // A span that a flush moves on the producer's stream (under mu): bytes up to drain_issued, over
     // once probe number `direct_probe` is.  0: none; no other copy is issued while there is one.
     uint64_t direct_probe = 0;
