@@ -278,10 +278,11 @@ dmi_status_t dmi_observe_paged_batch(dmi_ring_t *ring, uint32_t n, const uint32_
  * life of the process.
  * Runs on the calling thread's current HIP device.  Launches, on hip_stream, the capture kernel
  * dmi_observe would launch, with the request table among its arguments, and returns.  (A table of more
- * than 832 words is staged by small launches in front of it.  It has 5 words per request; where
- * requests list several rows each, at most 1024 in all, and no keep vector is given, it may have one more per
- * listed row: 40 requests of 16 rows make 840 words.)  The record, byte for byte the one dmi_observe would
- * produce with sequence number `seq` and this rank_tag, is written at out[0 ..) [device,
+ * than 832 words travels without the columns whose values are evenly spaced; if that is still more, it is
+ * staged by small launches in front of it.  It has 5 words per request; where requests list several rows
+ * each, at most 1024 in all, and no keep vector is given, it may have one more per listed row, and is then
+ * staged if it is longer: 40 requests of 16 rows make 840 words.)  The record, byte for byte the one
+ * dmi_observe would produce with sequence number `seq` and this rank_tag, is written at out[0 ..) [device,
  * 64-byte aligned]; its size is in its header (bytes 48..55) and, when the selection has no
  * keep vector, in *record_bytes [host, optional] (with one: an upper bound).  Bytes of `out`
  * behind the record are not touched.  No policy applies: nothing is sampled, dropped or waited for.
