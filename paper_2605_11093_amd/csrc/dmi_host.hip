@@ -174,12 +174,13 @@ uint64_t read_committed(const dmi_ring *r) { return r->committed.load(std::memor
 
 // Up to where the device ring is complete: the head as the last probe has confirmed it or as a launch has noted it since.  Not by
 // notes between dmi_step_begin and dmi_step_end: the captures of a replay belong to the drain, and to the counters, from the latter on.
+// And never past what the host counts on as the head: the captures of a step that is destroyed before its end have noted more.
 // Producer thread only.
-static uint64_t read_complete(const dmi_ring *r)
+static uint64_t read_complete(dmi_ring *r)
 {
     if (r->step_open) return read_committed(r);
     const uint64_t noted = __atomic_load_n(r->hwords + kWordNote, __ATOMIC_ACQUIRE);
-    return std::max(read_committed(r), noted);
+    return std::max(read_committed(r), std::min(noted, head_upper_bound(r)));
 }
 
 // The drained-up-to mark, where the kernels read it: one pinned word, written here and read by a

@@ -534,6 +534,35 @@ void a_flush_leaves_an_open_step_alone()
     CHECK(dmi_step_destroy(step) == DMI_OK);
 }
 
+// What the captures of a step have noted that was destroyed before its dmi_step_end the counters never hear of: the drain stays behind
+// the head that the host counts on, and the producer has the room that this says.
+void a_step_destroyed_while_open_is_not_drained_by_its_notes()
+{
+    constexpr uint64_t bytes = 600u << 10;
+    Bench b(0, 50, 64u << 20, 64u << 20);
+    dmi_step_t *step = nullptr;
+    CHECK(dmi_step_create(b.ring, 8, &step) == DMI_OK && dmi_step_capture_begin(step) == DMI_OK);
+    fake_begin_capture(b.stream);
+    const uint32_t rows = (uint32_t)((bytes - 128u) / 64u);
+    dmi_tensor_t t = {b.data.data(), DMI_DTYPE_BF16, {rows, 32}, {32, 1}};
+    const dmi_req_sel_t all = {1, 0, 0, rows, 1};
+    const dmi_selection_t sel = {1, &all, nullptr, nullptr};
+    const dmi_transform_t raw = {DMI_DTYPE_BF16, 0};
+    for (uint32_t i = 0; i < 6; i++) CHECK(dmi_step_observe(step, i, &t, &sel, &raw, b.stream, nullptr) == DMI_OK);
+    const std::vector<FakeTask> graph = fake_end_capture(b.stream);
+    CHECK(dmi_step_seal(step) == DMI_OK);
+    CHECK(dmi_step_begin(step, 0, b.stream) == DMI_OK);
+    fake_graph_launch(graph, b.stream);
+    CHECK(hipStreamSynchronize(b.stream) == hipSuccess);
+    CHECK(dmi_step_destroy(step) == DMI_OK);
+    for (int i = 0; i < 4; i++) {
+        uint64_t moved = 0, room = 0;
+        CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, &moved) == DMI_OK && moved == (i ? Bench::record() : 0u));
+        CHECK(dmi_ring_free_bytes(b.ring, &room) == DMI_OK && room == 64u << 20);
+        CHECK(b.observe() == DMI_OK);
+    }
+}
+
 // The second launch is for a flush that copies by notes: not where the ring's last drain was none, or one by another thread.
 void a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes()
 {
@@ -625,6 +654,7 @@ const Scenario kScenarios[] = {
     {"where_the_batches_of_the_gpu_test_are_cut", where_the_batches_of_the_gpu_test_are_cut},
     {"a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
      a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes},
+    {"a_step_destroyed_while_open_is_not_drained_by_its_notes", a_step_destroyed_while_open_is_not_drained_by_its_notes},
     {"a_flush_leaves_an_open_step_alone", a_flush_leaves_an_open_step_alone},
     {"other_drains_do_not_copy_by_notes", other_drains_do_not_copy_by_notes},
     {"the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",

@@ -27,6 +27,7 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "the_last_copy_leaves_the_compute_units_to_work_behind_the_captures",
              "a_captured_stream_is_not_asked_for_its_state",
              "other_drains_do_not_copy_by_notes", "a_flush_leaves_an_open_step_alone",
+             "a_step_destroyed_while_open_is_not_drained_by_its_notes",
              "a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
              "where_the_batches_of_the_gpu_test_are_cut",
              "a_ring_that_drains_by_kernel_copies_behind_the_captures"]
