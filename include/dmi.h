@@ -316,8 +316,8 @@ dmi_status_t dmi_observe_into(uint32_t point_id, const dmi_tensor_t *tensor /*[h
  * DMI_DRAIN_COPY_ENGINE: at most 6 MiB by a copy kernel on the stream last passed to dmi_observe, behind the captures, unless
  * some of the records have an event of the library's behind them or are captured already, or 1 MiB or more is or will be known to
  * be captured while later captures run.  Then with the copy engine, what is captured while later captures run and the rest behind
- * them; up to 8 MiB of that rest by a copy kernel on a stream of the library's if that stream has come to its end.  A
- * flush by another thread puts no copy on the stream of the observes. */
+ * them; a rest of at most 8 MiB by a copy kernel on a stream of the library's if the stream of the observes has come to its end.
+ * A flush by another thread puts no copy on the stream of the observes. */
 dmi_status_t dmi_drain(dmi_ring_t *ring, uint32_t flags, uint64_t *bytes_moved);
 
 /* A whole record in the host ring: [p0, p0+n0) then, iff it straddles the end of

@@ -274,7 +274,9 @@ static bool producer_is_idle(const dmi_ring *r)
 // there, a drain kernel, which starts 5 us sooner than the copy engine (from the captures' end to the host's knowing of the
 // copy's: 4 KB 7.7 / 12.3 us, 2 MB 45.5 / 46.5, 4.2 MB 83 / 88, 16.8 MB 311 / 311), also beside a copy that is under way.  Where the caller's
 // next kernels run there, its workgroups wait for places among theirs: 4.2 MB with 2.4 ms of matrix
-// products behind the captures are there after 305 us by the copy engine, and by a drain kernel after 1040.
+// products behind the captures are there after 305 us by the copy engine, and by a drain kernel after 1040.  And what is
+// left of a span that went in several copies stays with the copy engine, which has just been at it (64 MiB and 2.4 MB behind them: 1299 us, with
+// a drain kernel for those 1306).
 dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, const ChunkRule *flush)
 {
     if (moved) *moved = 0;
@@ -302,7 +304,7 @@ dmi_status_t drain_issue_locked(dmi_ring *r, uint64_t *moved, bool *host_full, c
     if (n > batch) n = batch;
     if (n > 0) {
         const uint64_t from = r->drain_issued;
-        if (flush && !flush->more && n <= kChunkKernelBytes && producer_is_idle(r)) {
+        if (flush && !flush->more && !flush->engine && n <= kChunkKernelBytes && producer_is_idle(r)) {
             if ((st = copy_span_noted(r, from, n)) != DMI_OK) return st;
         } else {
             if ((st = copy_span(r, from, n)) != DMI_OK) return st;
@@ -1571,7 +1573,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
     if (!direct && (st = record_probe(r)) != DMI_OK) return st;
     // The producer's own thread does not wait for all captures before it copies the first: it polls the notes that they leave, and starts
     // a copy of what is complete as soon as that is worth one (an eighth of it all; every copy costs the link some 8 us).
-    ChunkRule rule = {0, true, true};
+    ChunkRule rule = {0, true, true, false};
     uint64_t least = 0, last_move = t0;
     if (by_chunks) {
         const uint64_t all = head_upper_bound(r) - r->drain_done.load(std::memory_order_acquire);
@@ -1596,7 +1598,7 @@ dmi_status_t dmi_drain(dmi_ring_t *r, uint32_t flags, uint64_t *bytes_moved)
         total += moved;
         if (bytes_moved) *bytes_moved = total;
         if (target != UINT64_MAX && r->drain_done.load(std::memory_order_acquire) >= target) return DMI_OK;
-        if (moved) { last_move = now_ns(); continue; }
+        if (moved) { rule.engine = !rule.more; last_move = now_ns(); continue; }
         if (target != UINT64_MAX && host_full)
             return fail(DMI_ERR_AGAIN, "host ring is full: release records and drain again");
         const uint64_t waited = now_ns() - t0;

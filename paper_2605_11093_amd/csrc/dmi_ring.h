@@ -171,6 +171,7 @@ struct ChunkRule {
     uint64_t least;             // while captures are running, no copy of fewer bytes
     bool more;                  // captures of the flush are running
     bool poll;                  // return with a drain kernel under way, and look at its words again soon
+    bool engine;                // the flush has copied behind the captures before: the copy engine is at it
 };
 constexpr uint64_t kChunkPatienceNs = 300000;       // how long a flush waits for that many
 // How long a flush only polls the words of a drain kernel.  They say nothing of a GPU that has failed, and what takes longer than

@@ -645,11 +645,24 @@ void a_ring_that_drains_by_kernel_copies_behind_the_captures()
     }
 }
 
+// A span that goes in several copies (of at most 64 MiB) goes by the copy engine to its end, also where what is left for the last of
+// them is little.
+void the_rest_of_a_long_copy_stays_with_its_engine()
+{
+    Bench b(0, 2000, 72u << 20, 72u << 20);
+    CHECK(observe_bytes(b, 66ull << 20) == DMI_OK);
+    CHECK(dmi_drain(b.ring, DMI_DRAIN_FLUSH, nullptr) == DMI_OK && b.poll() == 1);
+    dmi_stats_t s;
+    CHECK(dmi_get_stats(b.ring, &s) == DMI_OK && s.drain_batches == 2);
+    CHECK(fake_all_drain_launches() == 0);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
+    {"the_rest_of_a_long_copy_stays_with_its_engine", the_rest_of_a_long_copy_stays_with_its_engine},
     {"a_ring_that_drains_by_kernel_copies_behind_the_captures", a_ring_that_drains_by_kernel_copies_behind_the_captures},
     {"where_the_batches_of_the_gpu_test_are_cut", where_the_batches_of_the_gpu_test_are_cut},
     {"a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",

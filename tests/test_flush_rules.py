@@ -30,7 +30,8 @@ SCENARIOS = ["waiting_drain_after_a_flush_that_gave_up", "polling_alone_sees_a_f
              "a_step_destroyed_while_open_is_not_drained_by_its_notes",
              "a_batch_goes_by_two_launches_only_for_flushes_that_copy_by_notes",
              "where_the_batches_of_the_gpu_test_are_cut",
-             "a_ring_that_drains_by_kernel_copies_behind_the_captures"]
+             "a_ring_that_drains_by_kernel_copies_behind_the_captures",
+             "the_rest_of_a_long_copy_stays_with_its_engine"]
 
 
 @pytest.fixture(scope="module")
